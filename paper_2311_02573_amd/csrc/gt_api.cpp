@@ -479,7 +479,7 @@ gt_status enqueue_walk(Index* ix, Batch* b) {
       a.out_node = b->fr_node[L & 1];
       a.out_mask = b->fr_mask[L & 1];
       a.out_count = b->lvl_count + (size_t)L * gt::kMaxSlots;
-      a.stat_pairs = &b->ctr->pairs[L];
+      a.stat_pairs = gt::stat_levels(b->lvl_count) + L;
       a.bitmap = bitmap;
       a.bit_base = level_row(L);
       a.out_rec = (use_rec && L == dl) ? b->fr_rec[L & 1] : nullptr;
@@ -511,7 +511,7 @@ gt_status enqueue_walk(Index* ix, Batch* b) {
     a.thr = b->thr;
     a.qexp = b->qexp;
     a.lexp = ix->lexp[l + 1];
-    a.stat_pairs = &b->ctr->pairs[l + 1];
+    a.stat_pairs = gt::stat_levels(b->lvl_count) + l + 1;
     a.bitmap = bitmap;
     a.bit_base = level_row(l + 1);
     a.over = &b->ctr->fr_over;
@@ -558,6 +558,7 @@ gt_status enqueue_leaf(Index* ix, Batch* b) {
   la.hit_cap = (unsigned long long)b->hit_cap;
   la.qcount = b->qcount;
   la.ctr = b->ctr;
+  la.stat_pairs = gt::stat_leaf(b->lvl_count);
   la.bitmap = b->counted ? b->bitmap : nullptr;
   la.bit_base = level_row(D);
   // two workgroups (eight waves) per CU: measured faster than one, three,
@@ -584,7 +585,7 @@ gt_status enqueue_pair_check(Index* ix, Batch* b) {
   HIPCHK(gt::launch_pair_check(b->cand, &b->ctr->ncand, (unsigned long long)b->cand_cap, b->qf,
                                ix->leaves, b->invn_q, ix->invn, b->rho, ix->dp, b->hits,
                                (unsigned long long)b->hit_cap, b->band_idx, b->qcount, b->ctr,
-                               ix->n_cu * 4, b->stream));
+                               gt::stat_leaf(b->lvl_count), ix->n_cu * 4, b->stream));
   return GT_OK;
 }
 
@@ -609,7 +610,8 @@ gt_status enqueue_tail(Index* ix, Batch* b) {
                             b->qf, ix->leaves, ix->d, ix->dp, ix->ff, b->rho, b->qcount,
                             b->ctr, s));
   ev_mark(b, 4);
-  HIPCHK(gt::launch_scan_offsets(b->qcount, b->nq, b->offs, nullptr, b->ctr, s));
+  HIPCHK(gt::launch_scan_offsets(b->qcount, b->nq, b->offs,
+                                     gt::stat_levels(b->lvl_count), b->ctr, s));
   TRY(ensure_out(b, 1));
   b->spec_direct = b->tgt_ids != nullptr;
   // (a fixed batch has no staging of its own for the sorted results: without
@@ -634,7 +636,7 @@ gt_status redo_candidates(Index* ix, Batch* b) {
   hipStream_t s = b->stream;
   TRY(zero_dev(b->qcount, (size_t)b->nq_pad * 4, s));
   TRY(zero_dev(&b->ctr->nhits, 8, s));
-  TRY(zero_dev(&b->ctr->leaf_pairs, 8, s));
+  TRY(zero_dev(gt::stat_leaf(b->lvl_count), (size_t)gt::kStatStripes * gt::kLeafStride * 8, s));
   TRY(zero_dev(&b->ctr->rechecked, 8, s));
   TRY(zero_dev(&b->ctr->nband, 8, s));
   if (b->kind == 1) {
@@ -904,7 +906,10 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
   TRY(zero_dev(b->ctr, sizeof(gt::DevCounters), s));
   TRY(zero_dev(b->qcount, (size_t)nq_pad * 4, s));
   TRY(zero_dev(b->tile_mask, (size_t)gt::kMaxTiles * 8, s));
-  if (kind == 1) TRY(zero_dev(b->lvl_count, (size_t)GT_MAX_LEVELS * gt::kMaxSlots * 4, s));
+  if (kind == 1)
+    TRY(zero_dev(b->lvl_count, (size_t)GT_MAX_LEVELS * gt::kMaxSlots * 4, s));
+  else
+    TRY(zero_dev(gt::stat_levels(b->lvl_count), gt::kStatWords * 8, s));
   b->counted = ix->count_unique && kind == 1 && !b->fixed;
   if (b->counted) {
     const int64_t words = (int64_t(2) << ix->depth) / 32 + 1;

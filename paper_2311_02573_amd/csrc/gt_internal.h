@@ -30,6 +30,24 @@ constexpr int kMaxSlots = 8192;       // nt << nb
 constexpr int kMaxSlotsPerXcd = kMaxSlots / kXcds;
 constexpr int kMaxBucketsPerXcd = (1 << kMaxBucketBits) / kXcds;
 
+// Statistics of a call: tests per level and leaf tests, counted on
+// kStatStripes counters each (their lines apart) that the offsets kernel sums.
+// They lie behind the level counters, in the rows of levels that no tree has
+// (a tree's capacity is at most 2^31 leaves).
+constexpr int kStatStripes = 64;
+constexpr int kStatRow = 36;            // first unused row of the level counters
+constexpr int kLeafStride = 16;         // 128 bytes
+constexpr size_t kStatWords = (size_t)kStatStripes * (GT_MAX_LEVELS + kLeafStride);
+static_assert(kStatRow > 32 &&
+                  kStatWords * 8 <= (size_t)(GT_MAX_LEVELS - kStatRow) * kMaxSlots * 4,
+              "the statistics fit behind the deepest level");
+inline unsigned long long* stat_levels(uint32_t* lvl_count) {
+  return reinterpret_cast<unsigned long long*>(lvl_count + (size_t)kStatRow * kMaxSlots);
+}
+inline unsigned long long* stat_leaf(uint32_t* lvl_count) {
+  return stat_levels(lvl_count) + (size_t)kStatStripes * GT_MAX_LEVELS;
+}
+
 // Largest row length (padded columns) whose whole query tile each walk
 // format keeps in LDS; wider rows (up to kMaxWalkWidth: d <= 4096, or the
 // 2 d_pad rows of a signed index) pass the tile through LDS in windows.
@@ -92,7 +110,7 @@ struct WalkLevelArgs {
   const float* thr;         // [nt * TQ] lowered thresholds tau'
   const int* qexp;          // [nt * TQ] float8 query scale exponents
   int lexp;                 // float8 scale exponent of level+1
-  unsigned long long* stat_pairs;
+  unsigned long long* stat_pairs;  // stripe 0 of the level's test counters
   uint32_t* bitmap;         // optional: one bit per tree row read
   int64_t bit_base;         // tree row of node 0 of level+1
   // subtraction step (bfloat16 pools): per entry, 64 bfloat16 upper bounds of
@@ -148,6 +166,7 @@ struct LeafArgs {
   uint32_t* band_idx;       // [hit_cap] indices of band candidates in hits
   unsigned int* qcount;     // [nt * tq] accepted results per query
   DevCounters* ctr;
+  unsigned long long* stat_pairs;  // stripe 0 of the leaf-test counters
   uint32_t* bitmap;         // optional: one bit per tree row read
   int64_t bit_base;         // tree row of leaf 0
 };
@@ -341,8 +360,8 @@ hipError_t launch_recheck(Hit* hits, const uint32_t* band_idx, const unsigned lo
                           unsigned long long cap, const float* qf, const float* leaves, int d,
                           int dp, const double* ff, const double* rho,
                           unsigned int* qcount, DevCounters* ctr, hipStream_t s);
-hipError_t launch_scan_offsets(const unsigned int* qcount, int nq, int64_t* offs_internal,
-                               int64_t* offs_out, DevCounters* ctr, hipStream_t s);
+hipError_t launch_scan_offsets(const unsigned int* qcount, int nq, int64_t* offs,
+                               const unsigned long long* stat, DevCounters* ctr, hipStream_t s);
 hipError_t launch_scatter(const Hit* hits, const DevCounters* ctr, unsigned long long hit_cap,
                           unsigned long long lim, const int64_t* offs, uint32_t* out_id,
                           float* out_sim, hipStream_t s);
@@ -359,7 +378,8 @@ hipError_t launch_pair_check(const uint2* cand, const unsigned long long* ncand,
                              unsigned long long cap, const float* qf, const float* leaves,
                              const float* invn_q, const float* invn_f, const double* rho, int dp,
                              Hit* hits, unsigned long long hit_cap, uint32_t* band_idx,
-                             unsigned int* qcount, DevCounters* ctr, int grid, hipStream_t s);
+                             unsigned int* qcount, DevCounters* ctr,
+                             unsigned long long* stat_pairs, int grid, hipStream_t s);
 // Scratch of the allocation-free entry point (gt_noalloc.hip): taken once per
 // device at set-up (index build), with that device current.
 hipError_t scratch_setup(int device);

@@ -155,7 +155,8 @@ __global__ __launch_bounds__(256) void k_pair_check(const uint2* cand, const uns
                                                     const float* invn_f, const double* rho, int dp,
                                                     Hit* hits, unsigned long long hit_cap,
                                                     uint32_t* band_idx, unsigned int* qcount,
-                                                    DevCounters* ctr) {
+                                                    DevCounters* ctr,
+                                                    unsigned long long* stat_pairs) {
   __shared__ Hit hstage[4][kHitStage];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const unsigned long long n = *ncand < cap ? *ncand : cap;
@@ -190,15 +191,15 @@ __global__ __launch_bounds__(256) void k_pair_check(const uint2* cand, const uns
       h.q = x.x;
       h.id = x.y;
       h.sim = cs;
-      h.flag = flag == HIT_ACCEPT ? flag | accept_slot(&qcount[x.x], ctr) : flag;
+      h.flag = flag;
       ++npairs;
     }
-    stage_hits(buf, cnt, flag != 0u, h, false, ctr, hits, hit_cap, band_idx, lane);
+    stage_hits(buf, cnt, flag != 0u, h, qcount, ctr, hits, hit_cap, band_idx, lane);
   }
-  Hit none;
-  stage_hits(buf, cnt, false, none, true, ctr, hits, hit_cap, band_idx, lane);
+  flush_hits(buf, cnt, qcount, ctr, hits, hit_cap, band_idx, lane, w);
   for (int o = 32; o >= 1; o >>= 1) npairs += __shfl_xor(npairs, o, 64);
-  if (lane == 0 && npairs) atomicAdd(&ctr->leaf_pairs, npairs);
+  if (lane == 0 && npairs)
+    stat_add(stat_pairs, kLeafStride, (uint32_t)(blockIdx.x * nw + w), npairs);
 }
 
 }  // namespace
@@ -219,9 +220,10 @@ hipError_t launch_pair_check(const uint2* cand, const unsigned long long* ncand,
                              unsigned long long cap, const float* qf, const float* leaves,
                              const float* invn_q, const float* invn_f, const double* rho, int dp,
                              Hit* hits, unsigned long long hit_cap, uint32_t* band_idx,
-                             unsigned int* qcount, DevCounters* ctr, int grid, hipStream_t s) {
+                             unsigned int* qcount, DevCounters* ctr,
+                             unsigned long long* stat_pairs, int grid, hipStream_t s) {
   hipLaunchKernelGGL(k_pair_check, dim3(grid), dim3(256), 0, s, cand, ncand, cap, qf, leaves, invn_q,
-                     invn_f, rho, dp, hits, hit_cap, band_idx, qcount, ctr);
+                     invn_f, rho, dp, hits, hit_cap, band_idx, qcount, ctr, stat_pairs);
   return hipGetLastError();
 }
 

@@ -532,7 +532,8 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_level(WalkLevelArgs a)
   }
   if (a.stat_pairs) {
     for (int o = 32; o >= 1; o >>= 1) pairs += __shfl_xor(pairs, o, 64);
-    if (lane == 0 && pairs) atomicAdd(a.stat_pairs, pairs);
+    if (lane == 0 && pairs)
+      stat_add(a.stat_pairs, GT_MAX_LEVELS, blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), pairs);
   }
 }
 
@@ -788,7 +789,8 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_wide(WalkLevelArgs a) 
   }
   if (a.stat_pairs) {
     for (int o = 32; o >= 1; o >>= 1) pairs += __shfl_xor(pairs, o, 64);
-    if (lane == 0 && pairs) atomicAdd(a.stat_pairs, pairs);
+    if (lane == 0 && pairs)
+      stat_add(a.stat_pairs, GT_MAX_LEVELS, blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), pairs);
   }
 }
 
@@ -1130,7 +1132,8 @@ __global__ __launch_bounds__(kSubThreads, 1) void k_walk_sub(WalkLevelArgs a) {
   }
   if (a.stat_pairs) {
     for (int o = 32; o >= 1; o >>= 1) pairs += __shfl_xor(pairs, o, 64);
-    if (lane == 0 && pairs) atomicAdd(a.stat_pairs, pairs);
+    if (lane == 0 && pairs)
+      stat_add(a.stat_pairs, GT_MAX_LEVELS, blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), pairs);
   }
 }
 
@@ -1574,7 +1577,8 @@ __global__ __launch_bounds__(kDThreads, 1) void k_dense_level(DenseLevelArgs a) 
   }
   if (a.stat_pairs) {
     for (int o = 32; o >= 1; o >>= 1) pairs += __shfl_xor(pairs, o, 64);
-    if (lane == 0 && pairs) atomicAdd(a.stat_pairs, pairs);
+    if (lane == 0 && pairs)
+      stat_add(a.stat_pairs, GT_MAX_LEVELS, blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), pairs);
   }
 }
 
@@ -1776,16 +1780,15 @@ __global__ __launch_bounds__(256) void k_leaf(LeafArgs a) {
         h.q = (uint32_t)qg;
         h.id = id;
         h.sim = cs;
-        h.flag = flag == HIT_ACCEPT ? flag | accept_slot(&a.qcount[qg], a.ctr) : flag;
+        h.flag = flag;
         ++npairs;
       }
-      stage_hits(buf, cnt, flag != 0u, h, false, a.ctr, a.hits, a.hit_cap, a.band_idx, lane);
+      stage_hits(buf, cnt, flag != 0u, h, a.qcount, a.ctr, a.hits, a.hit_cap, a.band_idx, lane);
     }
   }
-  Hit none;
-  stage_hits(buf, cnt, false, none, true, a.ctr, a.hits, a.hit_cap, a.band_idx, lane);
+  flush_hits(buf, cnt, a.qcount, a.ctr, a.hits, a.hit_cap, a.band_idx, lane, w);
   for (int o = 32; o >= 1; o >>= 1) npairs += __shfl_xor(npairs, o, 64);
-  if (lane == 0 && npairs) atomicAdd(&a.ctr->leaf_pairs, npairs);
+  if (lane == 0 && npairs) stat_add(a.stat_pairs, kLeafStride, blockIdx.x * nw + w, npairs);
 }
 
 // Candidates within 1e-5 of rho are re-decided with the canonical float64
@@ -1848,12 +1851,23 @@ __global__ __launch_bounds__(256) void k_recheck(Hit* hits, const uint32_t* band
   }
 }
 
-// Exclusive scan of per-query counts -> offsets (one workgroup of 1024).
+// Exclusive scan of per-query counts -> offsets (one workgroup of 1024), and
+// the sums of the striped statistics counters.
 __global__ __launch_bounds__(1024) void k_scan_offsets(const unsigned int* qcount, int nq,
-                                                       int64_t* offs, int64_t* offs_out,
+                                                       int64_t* offs,
+                                                       const unsigned long long* stat,
                                                        DevCounters* ctr) {
   __shared__ int64_t part[1024];
   const int t = threadIdx.x;
+  if (t <= GT_MAX_LEVELS) {  // thread l: tests of level l; the last: leaf tests
+    const unsigned long long* p =
+        t < GT_MAX_LEVELS ? stat + t : stat + (size_t)kStatStripes * GT_MAX_LEVELS;
+    const int stride = t < GT_MAX_LEVELS ? GT_MAX_LEVELS : kLeafStride;
+    unsigned long long sum = 0;
+#pragma unroll 16
+    for (int k = 0; k < kStatStripes; ++k) sum += p[(size_t)k * stride];
+    if (t < GT_MAX_LEVELS) ctr->pairs[t] = sum; else ctr->leaf_pairs = sum;
+  }
   const int per = (nq + 1023) / 1024;
   const int lo = t * per, hi = min(nq, lo + per);
   int64_t s = 0;
@@ -1869,12 +1883,10 @@ __global__ __launch_bounds__(1024) void k_scan_offsets(const unsigned int* qcoun
   int64_t run = part[t] - s;
   for (int i = lo; i < hi; ++i) {
     offs[i] = run;
-    if (offs_out) offs_out[i] = run;
     run += qcount[i];
   }
   if (t == 1023) {
     offs[nq] = part[1023];
-    if (offs_out) offs_out[nq] = part[1023];
     ctr->total = (unsigned long long)part[1023];
   }
 }
@@ -2153,10 +2165,9 @@ hipError_t launch_recheck(Hit* hits, const uint32_t* band_idx, const unsigned lo
   return hipGetLastError();
 }
 
-hipError_t launch_scan_offsets(const unsigned int* qcount, int nq, int64_t* offs_internal,
-                               int64_t* offs_out, DevCounters* ctr, hipStream_t s) {
-  hipLaunchKernelGGL(k_scan_offsets, dim3(1), dim3(1024), 0, s, qcount, nq, offs_internal, offs_out,
-                     ctr);
+hipError_t launch_scan_offsets(const unsigned int* qcount, int nq, int64_t* offs,
+                               const unsigned long long* stat, DevCounters* ctr, hipStream_t s) {
+  hipLaunchKernelGGL(k_scan_offsets, dim3(1), dim3(1024), 0, s, qcount, nq, offs, stat, ctr);
   return hipGetLastError();
 }
 
