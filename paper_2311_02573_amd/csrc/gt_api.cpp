@@ -11,6 +11,7 @@
 
 #include "gt.h"
 #include "gt_internal.h"
+#include "gt_numerics.h"
 
 using gt::Batch;
 using gt::Index;
@@ -143,30 +144,60 @@ gt_status zero_dev(void* p, size_t bytes, hipStream_t s) {
   return GT_OK;
 }
 
-// float8 scale exponent of a level: 2^e with (level max * 2) / 2^e <= 448, so
-// a pool can grow to twice its build-time maximum through inserts before the
-// level has to be rescaled.
-int fp8_exp_for(float mx) {
-  if (!(mx > 0.0f)) return 0;
-  int ex;
-  const double m = frexp((double)mx * 2.0 / 448.0, &ex);
-  return m == 0.5 ? ex - 1 : ex;
+// A float8 level that an insert outgrew: new scale from the level's maximum,
+// every code rewritten.
+gt_status rescale_fp8_level(Index* ix, int level, int64_t n, hipStream_t s) {
+  TRY(zero_dev(ix->d_levelmax + level, 4, s));
+  HIPCHK(gt::launch_level_max(ix->master + level_row(level) * ix->dp, int64_t(1) << level, ix->dp,
+                              ix->d_levelmax + level, s));
+  float mx = 0.0f;
+  HIPCHK(hipMemcpyAsync(&mx, ix->d_levelmax + level, 4, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  ix->lexp[level] = gt::fp8_exp_for(mx);
+  HIPCHK(hipMemcpyAsync(ix->d_lexp + level, &ix->lexp[level], 4, hipMemcpyHostToDevice, s));
+  HIPCHK(gt::launch_quant_fp8(ix->master, ix->pfp8, ix->dp, level, level, ix->depth, n, ix->d_lexp,
+                              ix->d_ing->over, s));
+  return GT_OK;
 }
 
-gt_status quantize_fp8_level(Index* ix, int level, hipStream_t s, bool recompute_scale) {
-  const int64_t nodes = int64_t(1) << level;
-  float* rows = ix->master + level_row(level) * ix->dp;
-  if (recompute_scale) {
-    TRY(zero_dev(ix->d_levelmax + level, 4, s));
-    HIPCHK(gt::launch_level_max(rows, nodes, ix->dp, ix->d_levelmax + level, s));
-    float mx = 0.0f;
-    HIPCHK(hipMemcpyAsync(&mx, ix->d_levelmax + level, 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    ix->lexp[level] = fp8_exp_for(mx);
-    HIPCHK(hipMemcpyAsync(ix->d_lexp + level, &ix->lexp[level], 4, hipMemcpyHostToDevice, s));
+// The pools that cover the rows [lo, hi), bottom-up in every stored format.
+// with_fp8: float8 copies too, with the levels' present exponents; else the
+// sum tree's level maxima are gathered where float8 pools exist.
+gt_status update_pools(Index* ix, int64_t lo, int64_t hi, bool with_fp8, bool gated, hipStream_t s) {
+  gt::TreeArgs a{};
+  a.leaves = ix->leaves;
+  a.depth = ix->depth;
+  a.lo = lo;
+  a.hi = hi;
+  a.gate = gated ? ix->d_ing : nullptr;
+  a.bound = ix->signed_mode ? ix->sbound : 0.0f;
+  if (ix->master) {
+    a.tree = ix->master;
+    a.w = ix->dp;
+    a.p16 = ix->pbf16;
+    a.p8 = with_fp8 ? ix->pfp8 : nullptr;
+    a.lexp = ix->d_lexp;
+    a.over = ix->d_ing->over;
+    a.level_max = ix->pfp8 && !with_fp8 ? ix->d_levelmax : nullptr;
+    HIPCHK(gt::launch_tree_update(a, false, ix->depth, s));
   }
-  HIPCHK(gt::launch_quant_fp8(rows, ix->pfp8 + level_row(level) * ix->dp, nodes * ix->dp,
-                              ix->lexp[level], ix->d_flags + level, s));
+  if (ix->mmax) {
+    a.tree = ix->mmax;
+    a.w = ix->pw;
+    a.p16 = ix->pmax16;
+    a.p8 = nullptr;
+    a.level_max = nullptr;
+    int child = ix->depth;
+    if (ix->signed_mode) {
+      const int l = ix->depth - 1;
+      const int64_t first = lo >> 1, last = (hi - 1) >> 1, off = level_row(l) * ix->pw;
+      HIPCHK(gt::launch_signed_bottom(ix->leaves, ix->mmax + off, first, last - first + 1, ix->dp,
+                                      ix->d, hi, ix->sbound, ix->pmax16 ? ix->pmax16 + off : nullptr,
+                                      a.gate, s));
+      child = l;
+    }
+    HIPCHK(gt::launch_tree_update(a, true, child, s));
+  }
   return GT_OK;
 }
 
@@ -247,17 +278,18 @@ void free_tree(Index* ix) {
   dfree(ix, &ix->invn, cap);
   dfree(ix, &ix->ff, cap);
   dfree(ix, &ix->nf, cap);
-  dfree(ix, &ix->d_mmin, 2);
+  dfree(ix, &ix->d_mmin, 1);
   dfree(ix, &ix->master, tree);
   dfree(ix, &ix->pbf16, tree);
   dfree(ix, &ix->pfp8, tree);
   const size_t mtree = (cap - 1) * (size_t)ix->pw;
   dfree(ix, &ix->mmax, mtree);
   dfree(ix, &ix->pmax16, mtree);
-  dfree(ix, &ix->d_absmax, 1);
   dfree(ix, &ix->d_lexp, GT_MAX_LEVELS);
   dfree(ix, &ix->d_levelmax, GT_MAX_LEVELS);
-  dfree(ix, &ix->d_flags, GT_MAX_LEVELS);
+  dfree(ix, &ix->d_ing, 1);
+  if (ix->h_ing) (void)hipHostFree(ix->h_ing);
+  ix->h_ing = nullptr;
 }
 
 gt_status batch_init(Batch* b) {
@@ -1208,9 +1240,9 @@ gt_status gt_build_tree(const void* feats_dev, int64_t n, int32_t d, gt_dtype dt
   // the device scratch of gt_query_batch_noalloc, once per device
   ix->scratch_err = gt::scratch_setup(ix->device);
   if (ix->scratch_err != hipSuccess) (void)hipGetLastError();
-  hipDeviceProp_t prop;
-  BHIP(hipGetDeviceProperties(&prop, ix->device));
-  ix->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+  int cus = 0;
+  BHIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ix->device));
+  ix->n_cu = cus > 0 ? cus : 256;
   ix->d = d;
   ix->dp = (d + 127) / 128 * 128;
   ix->cap = capacity;
@@ -1230,8 +1262,7 @@ gt_status gt_build_tree(const void* feats_dev, int64_t n, int32_t d, gt_dtype dt
   BTRY(dalloc(ix, &ix->invn, cap));
   BTRY(dalloc(ix, &ix->ff, cap));
   BTRY(dalloc(ix, &ix->nf, cap));
-  BTRY(dalloc(ix, &ix->d_mmin, 2));
-  BTRY(dalloc(ix, &ix->d_absmax, 1));
+  BTRY(dalloc(ix, &ix->d_mmin, 1));
   if (ix->formats & GT_POOL_F32) BTRY(dalloc(ix, &ix->master, tree));
   if (ix->formats & GT_POOL_BF16) BTRY(dalloc(ix, &ix->pbf16, tree));
   if (ix->formats & GT_POOL_FP8E4M3) BTRY(dalloc(ix, &ix->pfp8, tree));
@@ -1239,72 +1270,47 @@ gt_status gt_build_tree(const void* feats_dev, int64_t n, int32_t d, gt_dtype dt
   if (ix->formats & GT_POOL_MAX_BF16) BTRY(dalloc(ix, &ix->pmax16, mtree));
   BTRY(dalloc(ix, &ix->d_lexp, GT_MAX_LEVELS));
   BTRY(dalloc(ix, &ix->d_levelmax, GT_MAX_LEVELS));
-  BTRY(dalloc(ix, &ix->d_flags, GT_MAX_LEVELS));
-  BHIP(hipMemsetAsync(ix->leaves, 0, cap * dp * 4, s));
-  BHIP(hipMemsetAsync(ix->invn, 0, cap * 4, s));
-  BHIP(hipMemsetAsync(ix->ff, 0, cap * 8, s));
-  BHIP(hipMemsetAsync(ix->nf, 0, cap * 4, s));
-  if (ix->master) BHIP(hipMemsetAsync(ix->master, 0, tree * 4, s));
-  if (ix->mmax) BHIP(hipMemsetAsync(ix->mmax, 0, mtree * 4, s));
-  BHIP(hipMemsetAsync(ix->d_absmax, 0, 4, s));
-  BHIP(hipMemsetAsync(ix->d_flags, 0, GT_MAX_LEVELS * 4, s));
+  BTRY(dalloc(ix, &ix->d_ing, 1));
+  BHIP(hipHostMalloc((void**)&ix->h_ing, sizeof(gt::IngestOut), hipHostMallocDefault));
+  // what holds no row is zero: the leaves past n and, per level, the pools
+  // past the last one that covers a row
+  const size_t un = cap - (size_t)n;
+  if (un) BHIP(hipMemsetAsync(ix->leaves + (size_t)n * dp, 0, un * dp * 4, s));
+  if (un) BHIP(hipMemsetAsync(ix->invn + n, 0, un * 4, s));
+  if (un) BHIP(hipMemsetAsync(ix->ff + n, 0, un * 8, s));
+  if (un) BHIP(hipMemsetAsync(ix->nf + n, 0, un * 4, s));
+  if (ix->master) BHIP(gt::launch_zero_tails(ix->master, ix->dp * 4, ix->depth, n, s));
+  if (ix->pbf16) BHIP(gt::launch_zero_tails(ix->pbf16, ix->dp * 2, ix->depth, n, s));
+  if (ix->mmax) BHIP(gt::launch_zero_tails(ix->mmax, ix->pw * 4, ix->depth, n, s));
+  if (ix->pmax16) BHIP(gt::launch_zero_tails(ix->pmax16, ix->pw * 2, ix->depth, n, s));
   BHIP(hipMemsetAsync(ix->d_lexp, 0, GT_MAX_LEVELS * 4, s));
-  const double inf = INFINITY;
-  BHIP(hipMemcpyAsync(ix->d_mmin, &inf, 8, hipMemcpyHostToDevice, s));
-  unsigned int* derr = ix->d_flags + (GT_MAX_LEVELS - 1);
+  BHIP(hipMemsetAsync(ix->d_levelmax, 0, GT_MAX_LEVELS * 4, s));
+  BHIP(gt::launch_ingest_reset(ix->d_ing, s));
   BHIP(gt::launch_ingest(feats_dev, dtype, n, d, ix->dp, ix->leaves, ix->ff, ix->invn, ix->nf,
-                         ix->d_mmin, derr, sgn, sgn ? ix->d_absmax : nullptr, s));
-  unsigned int herr = 0, habs = 0;
-  BHIP(hipMemcpyAsync(&herr, derr, 4, hipMemcpyDeviceToHost, s));
-  BHIP(hipMemcpyAsync(&habs, ix->d_absmax, 4, hipMemcpyDeviceToHost, s));
+                         ix->d_ing, sgn, s));
+  BHIP(hipMemcpyAsync(ix->d_mmin, &ix->d_ing->mmin, 8, hipMemcpyDeviceToDevice, s));
+  BHIP(hipMemcpyAsync(ix->h_ing, ix->d_ing, sizeof(gt::IngestOut), hipMemcpyDeviceToHost, s));
   BHIP(hipStreamSynchronize(s));
-  if (herr)
+  if (ix->h_ing->err)
     return bail(fail(GT_ERR_INVALID_INPUT, sgn ? "features contain a NaN or infinite value"
                                                : "features contain a NaN, infinite or negative value"));
   ix->n = n;
+  ix->m_min = ix->h_ing->mmin;
   if (sgn) {
     // B: the smallest power of two >= the largest |value| (1 if all are zero)
     float amax;
-    memcpy(&amax, &habs, 4);
+    memcpy(&amax, &ix->h_ing->absmax, 4);
     int ex = 0;
     const double m = amax > 0.0f ? frexp((double)amax, &ex) : 0.5;
     ix->sbound = amax > 0.0f ? (float)ldexp(1.0, m == 0.5 ? ex - 1 : ex) : 1.0f;
   }
-
-  // pools, bottom-up; only pools covering some of the first n leaves are non-zero
-  for (int l = ix->depth - 1; l >= 0; --l) {
-    const int64_t span = int64_t(1) << (ix->depth - l);
-    const int64_t nodes = (n + span - 1) / span;
-    if (ix->master) {
-      const float* child = (l == ix->depth - 1) ? ix->leaves : ix->master + level_row(l + 1) * dp;
-      BHIP(gt::launch_build_level(child, ix->master + level_row(l) * dp, nodes, ix->dp, 0, s,
-                                  false));
-    }
-    if (ix->mmax) {
-      float* mpar = ix->mmax + level_row(l) * pw;
-      if (sgn && l == ix->depth - 1) {
-        BHIP(gt::launch_signed_bottom(ix->leaves, mpar, 0, nodes, ix->dp, ix->d, n, ix->sbound, s));
-      } else {
-        const float* mchild = (l == ix->depth - 1) ? ix->leaves : ix->mmax + level_row(l + 1) * pw;
-        BHIP(gt::launch_build_level(mchild, mpar, nodes, ix->pw, 0, s, true));
-      }
-    }
-  }
-  if (ix->pbf16) BHIP(gt::launch_quant_bf16(ix->master, ix->pbf16, (int64_t)tree, s));
-  if (ix->pmax16) BHIP(gt::launch_quant_bf16(ix->mmax, ix->pmax16, (int64_t)mtree, s));
+  if (n > 0) BTRY(update_pools(ix, 0, n, false, false, s));
   if (ix->pfp8) {
-    BHIP(hipMemsetAsync(ix->d_levelmax, 0, GT_MAX_LEVELS * 4, s));
-    for (int l = 0; l < ix->depth; ++l)
-      BHIP(gt::launch_level_max(ix->master + level_row(l) * dp, int64_t(1) << l, ix->dp,
-                                ix->d_levelmax + l, s));
-    float mx[GT_MAX_LEVELS] = {0};
-    BHIP(hipMemcpyAsync(mx, ix->d_levelmax, GT_MAX_LEVELS * 4, hipMemcpyDeviceToHost, s));
-    BHIP(hipStreamSynchronize(s));
-    for (int l = 0; l < ix->depth; ++l) ix->lexp[l] = fp8_exp_for(mx[l]);
-    BHIP(hipMemcpyAsync(ix->d_lexp, ix->lexp, GT_MAX_LEVELS * 4, hipMemcpyHostToDevice, s));
-    for (int l = 0; l < ix->depth; ++l) BTRY(quantize_fp8_level(ix, l, s, false));
+    BHIP(gt::launch_fp8_exps(ix->d_levelmax, ix->depth, ix->d_lexp, s));
+    BHIP(gt::launch_quant_fp8(ix->master, ix->pfp8, ix->dp, 0, ix->depth - 1, ix->depth, n,
+                              ix->d_lexp, ix->d_ing->over, s));
+    BHIP(hipMemcpyAsync(ix->lexp, ix->d_lexp, GT_MAX_LEVELS * 4, hipMemcpyDeviceToHost, s));
   }
-  BHIP(hipMemcpyAsync(&ix->m_min, ix->d_mmin, 8, hipMemcpyDeviceToHost, s));
   BHIP(hipStreamSynchronize(s));
   gt_batch* def = new gt_batch();
   def->ix = ix;
@@ -1328,90 +1334,54 @@ gt_status gt_insert(gt_index* ix, const void* feats_dev, int64_t n_new, void* st
     return fail(GT_ERR_CAPACITY, "insert of " + std::to_string(n_new) + " rows exceeds capacity " +
                                      std::to_string(ix->cap));
   hipStream_t s = (hipStream_t)stream;
-  const size_t dp = (size_t)ix->dp, pw = (size_t)ix->pw;
+  const size_t dp = (size_t)ix->dp;
   const int64_t lo = ix->n, hi = ix->n + n_new;
-  unsigned int* derr = ix->d_flags + (GT_MAX_LEVELS - 1);
-  double* tmp_mmin = ix->d_mmin + 1;
-  const double inf = INFINITY;
   const bool sgn = ix->signed_mode;
-  HIPCHK(hipMemsetAsync(derr, 0, 4, s));
-  HIPCHK(hipMemsetAsync(ix->d_absmax, 0, 4, s));
-  HIPCHK(hipMemcpyAsync(tmp_mmin, &inf, 8, hipMemcpyHostToDevice, s));
+  // A float8 level that must be rescaled is rewritten whole; calls in flight
+  // on other streams must not read it meanwhile, so the device is drained
+  // first when float8 pools exist.  Float32 and bfloat16 pools only grow
+  // (upward-rounded sums of non-negative rows), which in-flight calls tolerate.
+  if (ix->pfp8) HIPCHK(hipDeviceSynchronize());
+  HIPCHK(gt::launch_ingest_reset(ix->d_ing, s));
   HIPCHK(gt::launch_ingest(feats_dev, ix->dtype, n_new, ix->d, ix->dp, ix->leaves + lo * dp,
-                           ix->ff + lo, ix->invn + lo, ix->nf + lo, tmp_mmin, derr, sgn,
-                           sgn ? ix->d_absmax : nullptr, s));
-  unsigned int herr = 0, habs = 0;
-  double mnew = inf;
-  HIPCHK(hipMemcpyAsync(&herr, derr, 4, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(&habs, ix->d_absmax, 4, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(&mnew, tmp_mmin, 8, hipMemcpyDeviceToHost, s));
+                           ix->ff + lo, ix->invn + lo, ix->nf + lo, ix->d_ing, sgn, s));
+  // pools on the root-to-leaf paths of the new rows, re-derived bottom-up; the
+  // kernels do nothing if the ingest refused the rows, so that one wait
+  // serves the whole insert
+  TRY(update_pools(ix, lo, hi, true, true, s));
+  HIPCHK(hipMemcpyAsync(ix->h_ing, ix->d_ing, sizeof(gt::IngestOut), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  const gt::IngestOut got = *ix->h_ing;
   float amax = 0.0f;
-  memcpy(&amax, &habs, 4);
+  memcpy(&amax, &got.absmax, 4);
   // a signed index's shifted rows need every |value| <= B
   const bool beyond = sgn && amax > ix->sbound;
-  if (herr || beyond) {
+  if (got.err || beyond) {
     // leave the unused leaf slots zero, as they were
     HIPCHK(hipMemsetAsync(ix->leaves + lo * dp, 0, (size_t)n_new * dp * 4, s));
     HIPCHK(hipMemsetAsync(ix->ff + lo, 0, (size_t)n_new * 8, s));
     HIPCHK(hipMemsetAsync(ix->invn + lo, 0, (size_t)n_new * 4, s));
     HIPCHK(hipMemsetAsync(ix->nf + lo, 0, (size_t)n_new * 4, s));
     HIPCHK(hipStreamSynchronize(s));
-    if (herr)
+    if (got.err)
       return fail(GT_ERR_INVALID_INPUT, sgn ? "inserted rows contain a NaN or infinite value"
                                             : "inserted rows contain a NaN, infinite or negative value");
     return fail(GT_ERR_INVALID_INPUT, "an inserted value exceeds the index's shift bound " +
                                           std::to_string(ix->sbound) + " in absolute value");
   }
-  // A float8 level that must be rescaled is rewritten whole; calls in flight
-  // on other streams must not read it meanwhile, so the device is drained
-  // first when float8 pools exist.  Float32 and bfloat16 pools only grow
-  // (upward-rounded sums of non-negative rows), which in-flight calls tolerate.
-  if (ix->pfp8) HIPCHK(hipDeviceSynchronize());
-  // pools on the root-to-leaf paths of the new rows, re-derived bottom-up
-  for (int l = ix->depth - 1; l >= 0; --l) {
-    const int sh = ix->depth - l;
-    const int64_t a = lo >> sh, b = (hi - 1) >> sh;
-    float* par = ix->master ? ix->master + level_row(l) * dp : nullptr;
-    if (par) {
-      const float* child = (l == ix->depth - 1) ? ix->leaves : ix->master + level_row(l + 1) * dp;
-      HIPCHK(gt::launch_build_level(child, par, b - a + 1, ix->dp, a, s, false));
-    }
-    if (ix->mmax) {
-      float* mpar = ix->mmax + level_row(l) * pw;
-      if (sgn && l == ix->depth - 1) {
-        HIPCHK(gt::launch_signed_bottom(ix->leaves, mpar, a, b - a + 1, ix->dp, ix->d, hi,
-                                        ix->sbound, s));
-      } else {
-        const float* mchild = (l == ix->depth - 1) ? ix->leaves : ix->mmax + level_row(l + 1) * pw;
-        HIPCHK(gt::launch_build_level(mchild, mpar, b - a + 1, ix->pw, a, s, true));
-      }
-      if (ix->pmax16)
-        HIPCHK(gt::launch_quant_bf16(mpar + a * pw, ix->pmax16 + (level_row(l) + a) * pw,
-                                     (b - a + 1) * ix->pw, s));
-    }
-    if (ix->pbf16)
-      HIPCHK(gt::launch_quant_bf16(par + a * dp, ix->pbf16 + (level_row(l) + a) * dp,
-                                   (b - a + 1) * ix->dp, s));
-    if (ix->pfp8)
-      HIPCHK(gt::launch_quant_fp8(par + a * dp, ix->pfp8 + (level_row(l) + a) * dp,
-                                  (b - a + 1) * ix->dp, ix->lexp[l], ix->d_flags + l, s));
-  }
-  if (ix->pfp8) {
-    unsigned int fl[GT_MAX_LEVELS] = {0};
-    HIPCHK(hipMemcpyAsync(fl, ix->d_flags, GT_MAX_LEVELS * 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+  bool wait = false;
+  if (ix->pfp8)
     for (int l = 0; l < ix->depth; ++l)
-      if (fl[l]) {  // a pool outgrew the level's float8 range: new scale for the level
-        HIPCHK(hipMemsetAsync(ix->d_flags + l, 0, 4, s));
-        TRY(quantize_fp8_level(ix, l, s, true));
+      if (got.over[l]) {  // a pool outgrew the level's float8 range: new scale for the level
+        TRY(rescale_fp8_level(ix, l, hi, s));
+        wait = true;
       }
-  }
-  if (mnew < ix->m_min) {
-    ix->m_min = mnew;
+  if (got.mmin < ix->m_min) {
+    ix->m_min = got.mmin;
     HIPCHK(hipMemcpyAsync(ix->d_mmin, &ix->m_min, 8, hipMemcpyHostToDevice, s));
+    wait = true;
   }
-  HIPCHK(hipStreamSynchronize(s));
+  if (wait) HIPCHK(hipStreamSynchronize(s));
   ix->n = hi;
   ix->epoch++;
   return GT_OK;

@@ -92,6 +92,32 @@ struct DevCounters {
   unsigned long long entries[GT_MAX_LEVELS];  // frontier (pool, tile) entries per level
 };
 
+// What an ingest and the pool updates behind it report (device memory; reset
+// before each).
+struct IngestOut {
+  double mmin;                        // smallest norm of a non-zero new row
+  unsigned int absmax;                // largest |value| as float bits (signed index)
+  unsigned int err;                   // an invalid value was seen
+  unsigned int over[GT_MAX_LEVELS];   // a pool outgrew its level's float8 range
+};
+
+// Bottom-up update of the pools that cover the rows [lo, hi) (sum or max tree).
+constexpr int kPathNodes = 64;  // most pools of a level that one workgroup holds
+struct TreeArgs {
+  const float* leaves;     // [cap x w] rows of level `depth` (unused from child < depth)
+  float* tree;             // levels 0 .. depth-1
+  int w;                   // row length
+  int depth;
+  int64_t lo, hi;
+  uint16_t* p16;           // bfloat16 copies, or NULL
+  uint8_t* p8;             // float8 copies with the levels' exponents, or NULL
+  const int* lexp;         // [levels] (device)
+  unsigned int* over;      // [levels]
+  float* level_max;        // [levels] largest values, or NULL
+  const IngestOut* gate;   // do nothing after a refused ingest, or NULL
+  float bound;             // a signed index's bound (0: none)
+};
+
 // Arguments of one level step of the frontier walk (parents at `level`,
 // children at `level + 1`).
 struct WalkLevelArgs {
@@ -309,7 +335,7 @@ struct Index {
   float* invn = nullptr;     // [cap]
   double* ff = nullptr;      // [cap] canonical squared norms
   float* nf = nullptr;       // [cap] float32 norms rounded down (GEMM epilogue)
-  double* d_mmin = nullptr;  // device copy of m_min, and a scratch slot
+  double* d_mmin = nullptr;  // device copy of m_min
   float* master = nullptr;   // levels 0..depth-1, level l at row (2^l - 1)
   uint16_t* pbf16 = nullptr;
   uint8_t* pfp8 = nullptr;
@@ -321,11 +347,11 @@ struct Index {
   bool signed_mode = false;
   int pw = 0;                // row length of mmax / pmax16 (dp, or 2 dp when signed)
   float sbound = 0.0f;       // B (power of two >= every |value|), signed only
-  unsigned int* d_absmax = nullptr;  // float bits of the largest |value| of an ingest
   int* d_lexp = nullptr;     // float8 scale exponents per level
   int lexp[GT_MAX_LEVELS] = {0};
   float* d_levelmax = nullptr;
-  unsigned int* d_flags = nullptr;  // float8 overflow flags per level; last: input error
+  IngestOut* d_ing = nullptr;       // the last ingest's report, and its pinned host copy
+  IngestOut* h_ing = nullptr;
 
   Batch* def = nullptr;      // workspace of gt_query_batch / gt_exhaustive
   hipError_t scratch_err = hipSuccess;  // set-up of the device scratch at build
@@ -333,19 +359,22 @@ struct Index {
 
 // ---- launch wrappers (kernels in k_build.hip, k_walk.hip, k_exhaustive.hip) ----
 hipError_t launch_zero_u32(uint32_t* p, int64_t n, hipStream_t s);
+hipError_t launch_ingest_reset(IngestOut* o, hipStream_t s);
 hipError_t launch_ingest(const void* src, int dtype, int64_t rows, int d, int dp, float* leaves,
-                         double* ff, float* invn, float* nf, double* mmin, unsigned int* err,
-                         bool allow_negative, unsigned int* absmax, hipStream_t s);
+                         double* ff, float* invn, float* nf, IngestOut* o, bool allow_negative,
+                         hipStream_t s);
 hipError_t launch_signed_bottom(const float* leaves, float* parent, int64_t first, int64_t nodes,
-                                int dp, int d, int64_t n, float bound, hipStream_t s);
-hipError_t launch_build_level(const float* child, float* parent, int64_t nodes, int dp,
-                              int64_t first, hipStream_t s, bool max_pool);
+                                int dp, int d, int64_t n, float bound, uint16_t* parent16,
+                                const IngestOut* gate, hipStream_t s);
+hipError_t launch_tree_update(const TreeArgs& a, bool max_pool, int child, hipStream_t s);
+hipError_t launch_zero_tails(void* tree, int row_bytes, int depth, int64_t n, hipStream_t s);
 hipError_t launch_level_entries(const uint32_t* lvl_count, int first, int levels,
                                 DevCounters* ctr, hipStream_t s);
 hipError_t launch_level_max(const float* rows, int64_t nrows, int dp, float* out_max, hipStream_t s);
-hipError_t launch_quant_bf16(const float* src, uint16_t* dst, int64_t count, hipStream_t s);
-hipError_t launch_quant_fp8(const float* src, uint8_t* dst, int64_t count, int lexp,
-                            unsigned int* overflow, hipStream_t s);
+hipError_t launch_fp8_exps(const float* level_max, int depth, int* lexp, hipStream_t s);
+// float8 copies of levels first .. last (rows past the last populated pool: zero)
+hipError_t launch_quant_fp8(const float* tree, uint8_t* p8, int w, int first, int last, int depth,
+                            int64_t n, const int* lexp, unsigned int* over, hipStream_t s);
 hipError_t launch_query_prep(const float* q, int nq, int d, int dp, int tq, const double* rho,
                              const double* mmin, float* qf, uint16_t* qbf, uint8_t* q8, int* qexp,
                              float* invn_q, double* qq, float* thr, float* thr_gemm,
@@ -384,9 +413,5 @@ hipError_t launch_pair_check(const uint2* cand, const unsigned long long* ncand,
 // device at set-up (index build), with that device current.
 hipError_t scratch_setup(int device);
 void* scratch_of(int device);  // NULL until scratch_setup succeeded on the device
-
-hipError_t launch_insert_paths(float* master, const float* leaves, int depth, int dp, int64_t lo,
-                               int64_t hi, uint16_t* pbf16, uint8_t* pfp8, const int* lexp,
-                               unsigned int* flags, hipStream_t s);
 
 }  // namespace gt

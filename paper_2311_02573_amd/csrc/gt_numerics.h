@@ -58,6 +58,41 @@ __device__ __forceinline__ uint32_t e4m3_up(double x) {
   return code > 0x7Eu ? 0xFFu : code;
 }
 
+// e4m3_up(x / 2^lexp) of a finite float32 x >= 0 on its bits: the float64
+// path's conversions and scalings took a float8 pass over a tree 3x as long as
+// its bytes need.
+__device__ __forceinline__ uint32_t e4m3_up_f32(float x, int lexp) {
+  const uint32_t u = __float_as_uint(x);
+  if (u == 0u) return 0u;
+  int E = (int)(u >> 23) - 127;
+  uint32_t m = u & 0x7FFFFFu;
+  if (E == -127) {  // float32 subnormal: normalise
+    const int s = __clz((int)m) - 8;
+    m = (m << s) & 0x7FFFFFu;
+    E = -126 - s;
+  }
+  E -= lexp;
+  if (E > 8) return 0xFFu;
+  if (E < -6) {  // multiples of 2^-9, rounded up (8 is code 8, the least normal)
+    const int s = 14 - E;  // x = (2^23 + m) 2^(E - 23), in units of 2^-9
+    if (s >= 25) return 1u;
+    return ((m | 0x800000u) + ((1u << s) - 1u)) >> s;
+  }
+  const uint32_t mm = (m + 0xFFFFFu) >> 20;  // 8 carries into the exponent
+  const uint32_t code = ((uint32_t)(E + 7) << 3) + mm;
+  return code > 0x7Eu ? 0xFFu : code;
+}
+
+// float8 scale exponent of a level: 2^e with (level max * 2) / 2^e <= 448, so
+// a pool can grow to twice its build-time maximum through inserts before the
+// level has to be rescaled.
+__host__ __device__ inline int fp8_exp_for(float mx) {
+  if (!(mx > 0.0f)) return 0;
+  int ex;
+  const double m = frexp((double)mx * 2.0 / 448.0, &ex);
+  return m == 0.5 ? ex - 1 : ex;
+}
+
 // float64 -> float32 rounded toward -infinity (thresholds are lowered, never
 // raised).
 __device__ __forceinline__ float f64_to_f32_down(double x) {

@@ -9,6 +9,8 @@
 #include <hip/hip_fp16.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "gt_internal.h"
 #include "gt_numerics.h"
 
@@ -29,95 +31,324 @@ __device__ __forceinline__ float load_feature(const void* src, int dtype, int64_
   return reinterpret_cast<const float*>(src)[idx];
 }
 
-// One workgroup of 64 threads per 64 rows.  Column tiles of 64 are staged
-// through LDS so that loads and stores are coalesced while each thread still
-// sums its own row sequentially in float64 (the canonical squared norm).
-// Values must be finite and >= 0, or only finite with allow_negative (then
-// the largest |value| is folded into *absmax as float bits).
-__global__ __launch_bounds__(64) void k_ingest(const void* src, int dtype, int64_t rows, int d,
-                                               int dp, float* leaves, double* ff, float* invn,
-                                               float* nf, double* mmin, unsigned int* err,
-                                               int allow_negative, unsigned int* absmax) {
-  __shared__ float tile[64][65];
+// Four consecutive features of a row (VEC: one aligned load; else one by one,
+// zero past the row's d columns).
+template <bool VEC>
+__device__ __forceinline__ float4 load_feature4(const void* src, int dtype, int64_t row, int d,
+                                                int c) {
+  float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (VEC) {
+    if (c < d) {
+      const int64_t i = row * d + c;
+      if (dtype == GT_F32) return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(src) + i);
+      const uint2 h = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(src) + i);
+      const uint16_t u[4] = {(uint16_t)h.x, (uint16_t)(h.x >> 16), (uint16_t)h.y, (uint16_t)(h.y >> 16)};
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        v[e] = dtype == GT_F16 ? __half2float(__ushort_as_half(u[e]))
+                               : __uint_as_float((uint32_t)u[e] << 16);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c + e < d) v[e] = load_feature(src, dtype, row * d + c + e);
+  }
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
+__global__ void k_ingest_reset(IngestOut* o) {
   const int t = threadIdx.x;
-  const int64_t r0 = (int64_t)blockIdx.x * 64;
-  double acc = 0.0;
-  bool bad = false;
-  float amax = 0.0f;
-  for (int c0 = 0; c0 < dp; c0 += 64) {
-    const int c = c0 + t;
-    for (int r = 0; r < 64; ++r) {
-      const int64_t row = r0 + r;
-      if (row >= rows) break;
-      float v = 0.0f;
-      if (c < d) {
-        v = load_feature(src, dtype, row * d + c);
-        if (allow_negative) {
-          if (!isfinite(v)) bad = true;
-          amax = fmaxf(amax, fabsf(v));
-        } else if (!(v >= 0.0f) || isinf(v)) {
-          bad = true;
-        }
-      }
-      if (c < dp) leaves[row * dp + c] = v;
-      tile[r][t] = v;
-    }
-    __syncthreads();
-    if (r0 + t < rows) {
-      const int lim = min(64, d - c0);
-      for (int k = 0; k < lim; ++k) {
-        const double x = (double)tile[t][k];
-        acc = __dadd_rn(acc, __dmul_rn(x, x));
-      }
-    }
-    __syncthreads();
-  }
-  if (bad) atomicOr(err, 1u);
-  if (absmax) {
-    for (int o = 32; o >= 1; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
-    if (t == 0 && amax > 0.0f) atomicMax(absmax, __float_as_uint(amax));
-  }
-  const int64_t row = r0 + t;
-  if (row < rows) {
-    ff[row] = acc;
-    const double nrm = __dsqrt_rn(acc);
-    invn[row] = acc > 0.0 ? (float)__ddiv_rn(1.0, nrm) : 0.0f;
-    nf[row] = acc > 0.0 ? f64_to_f32_down(nrm) : 0.0f;
-    if (acc > 0.0 && !bad)
-      atomicMin(reinterpret_cast<unsigned long long*>(mmin),
-                (unsigned long long)__double_as_longlong(nrm));
+  if (t < GT_MAX_LEVELS) o->over[t] = 0u;
+  if (t == 0) {
+    o->mmin = INFINITY;
+    o->absmax = 0u;
+    o->err = 0u;
   }
 }
 
-// parent = children summed with upward rounding, 4 columns per thread.
-// Parent pools of `nodes` nodes from their two children: the element-wise sum
-// rounded up (sum pooling, paper Sec. 2) or the element-wise maximum, which is
-// exact (Our-Max pooling, Sec. 2).
-template <bool MAXP>
-__global__ void k_build_level(const float* __restrict__ child, float* __restrict__ parent,
-                              int64_t first, int64_t nodes, int dp) {
-  const int q = dp / 4;
-  const int64_t total = nodes * q;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t j = first + i / q;
-    const int k = (int)(i % q) * 4;
-    const float4 a = *reinterpret_cast<const float4*>(child + (2 * j) * dp + k);
-    const float4 b = *reinterpret_cast<const float4*>(child + (2 * j + 1) * dp + k);
-    float4 s;
-    if (MAXP) {
-      s.x = fmaxf(a.x, b.x);
-      s.y = fmaxf(a.y, b.y);
-      s.z = fmaxf(a.z, b.z);
-      s.w = fmaxf(a.w, b.w);
-    } else {
-      s.x = add_up(a.x, b.x);
-      s.y = add_up(a.y, b.y);
-      s.z = add_up(a.z, b.z);
-      s.w = add_up(a.w, b.w);
+// Feature rows to float32 leaves, with their canonical squared norm (float64,
+// summed sequentially over the columns), inverse norm and lowered norm.
+// Values must be finite and >= 0, or only finite with allow_negative (then
+// the largest |value| is folded into o->absmax as float bits).
+//
+// Bound by memory (rows in, leaves out) as long as the sequential sums, one
+// lane per row, hide behind it: a workgroup of four waves moves tiles of R
+// rows x 4096 / R columns through registers into one of two LDS buffers while
+// its first R lanes add up the tile before.  64-row tiles for large inputs
+// (200,000 x 1000 float32: 1.66 ms with single-wave workgroups and 4-byte
+// loads, now 0.44); 4-row tiles for small ones, whose time is the chain of one
+// row (100 x 512: 346 us, now 11).
+template <int R, bool VEC>
+__global__ __launch_bounds__(256) void k_ingest(const void* src, int dtype, int64_t rows, int d,
+                                                int dp, float* leaves, double* ff, float* invn,
+                                                float* nf, IngestOut* o, int allow_negative) {
+  constexpr int C = 4096 / R, G = C / 4, S = C + 4;  // S: row stride in LDS (16-byte bank spread)
+  __shared__ __attribute__((aligned(16))) float tile[2][R * S];
+  __shared__ float amax_w[4];
+  const int t = threadIdx.x;
+  const int64_t r0 = (int64_t)blockIdx.x * R;
+  bool bad = false;
+  float amax = 0.0f;
+  const int ntiles = (dp + C - 1) / C;
+  float4 v[4];
+  auto load = [&](int k) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int i = t + 256 * p, c = k * C + 4 * (i % G);
+      const int64_t row = r0 + i / G;
+      v[p] = row < rows && c < dp ? load_feature4<VEC>(src, dtype, row, d, c)
+                                  : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
-    *reinterpret_cast<float4*>(parent + j * dp + k) = s;
+  };
+  auto store = [&](int k) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int i = t + 256 * p, r = i / G, c4 = 4 * (i % G), c = k * C + c4;
+      const float x[4] = {v[p].x, v[p].y, v[p].z, v[p].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (allow_negative) {
+          if (!isfinite(x[e])) bad = true;
+          amax = fmaxf(amax, fabsf(x[e]));
+        } else if (!(x[e] >= 0.0f) || isinf(x[e])) {
+          bad = true;
+        }
+      }
+      if (r0 + r < rows && c < dp) *reinterpret_cast<float4*>(leaves + (r0 + r) * dp + c) = v[p];
+      *reinterpret_cast<float4*>(&tile[k & 1][r * S + c4]) = v[p];
+    }
+  };
+  load(0);
+  store(0);
+  __syncthreads();
+  double acc = 0.0;
+  for (int k = 0; k < ntiles; ++k) {
+    if (k + 1 < ntiles) load(k + 1);
+    if (t < R) {
+      const float* x = &tile[k & 1][t * S];
+      const int lim = min(C, d - k * C);
+      int c = 0;
+      for (; c + 16 <= lim; c += 16) {
+        float4 y[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = *reinterpret_cast<const float4*>(x + c + 4 * j);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {  // (squares of float32 values are exact in float64)
+          acc = __fma_rn((double)y[j].x, (double)y[j].x, acc);
+          acc = __fma_rn((double)y[j].y, (double)y[j].y, acc);
+          acc = __fma_rn((double)y[j].z, (double)y[j].z, acc);
+          acc = __fma_rn((double)y[j].w, (double)y[j].w, acc);
+        }
+      }
+      for (; c < lim; ++c) acc = __fma_rn((double)x[c], (double)x[c], acc);
+    }
+    if (k + 1 < ntiles) store(k + 1);
+    __syncthreads();
   }
+  if (bad) atomicOr(&o->err, 1u);
+  if (allow_negative) {
+    for (int s = 32; s >= 1; s >>= 1) amax = fmaxf(amax, __shfl_xor(amax, s, 64));
+    if ((t & 63) == 0) amax_w[t >> 6] = amax;
+    __syncthreads();
+    if (t == 0) {
+      const uint32_t m = __float_as_uint(fmaxf(fmaxf(amax_w[0], amax_w[1]), fmaxf(amax_w[2], amax_w[3])));
+      if (m > o->absmax) atomicMax(&o->absmax, m);  // (a stale read only adds an atomic)
+    }
+  }
+  if (t < 64) {
+    double mn = INFINITY;
+    const int64_t row = r0 + t;
+    if (t < R && row < rows) {
+      ff[row] = acc;
+      const double nrm = __dsqrt_rn(acc);
+      invn[row] = acc > 0.0 ? (float)__ddiv_rn(1.0, nrm) : 0.0f;
+      nf[row] = acc > 0.0 ? f64_to_f32_down(nrm) : 0.0f;
+      if (acc > 0.0) mn = nrm;
+    }
+    for (int s = R / 2; s >= 1; s >>= 1) mn = fmin(mn, __shfl_xor(mn, s, 64));
+    if (t == 0 && mn < o->mmin)
+      atomicMin(reinterpret_cast<unsigned long long*>(&o->mmin),
+                (unsigned long long)__double_as_longlong(mn));
+  }
+}
+
+// A refused ingest (invalid values, or beyond a signed index's bound) leaves
+// the pools as they are: the kernels enqueued behind it do nothing.
+__device__ __forceinline__ bool refused(const IngestOut* o, float bound) {
+  return o && (o->err != 0u || (bound > 0.0f && __uint_as_float(o->absmax) > bound));
+}
+
+// One pool of two children: the element-wise sum rounded up (sum pooling,
+// paper Sec. 2) or the element-wise maximum, which is exact (Our-Max pooling).
+template <bool MAXP>
+__device__ __forceinline__ float4 pool4(const float4& a, const float4& b) {
+  if constexpr (MAXP)
+    return make_float4(fmaxf(a.x, b.x), fmaxf(a.y, b.y), fmaxf(a.z, b.z), fmaxf(a.w, b.w));
+  else
+    return make_float4(add_up(a.x, b.x), add_up(a.y, b.y), add_up(a.z, b.z), add_up(a.w, b.w));
+}
+
+// Four columns of pool j of level l in every stored format.
+__device__ __forceinline__ void store_pool4(const TreeArgs& a, int l, int64_t j, int c,
+                                            const float4& v) {
+  const size_t at = (size_t)(((int64_t(1) << l) - 1 + j)) * a.w + c;
+  *reinterpret_cast<float4*>(a.tree + at) = v;
+  if (a.p16) {
+    const uint32_t lo = (uint32_t)bf16_up(v.x) | ((uint32_t)bf16_up(v.y) << 16);
+    const uint32_t hi = (uint32_t)bf16_up(v.z) | ((uint32_t)bf16_up(v.w) << 16);
+    *reinterpret_cast<uint2*>(a.p16 + at) = make_uint2(lo, hi);
+  }
+  if (a.p8) {
+    const int e = a.lexp[l];
+    uint32_t q[4] = {e4m3_up_f32(v.x, e), e4m3_up_f32(v.y, e), e4m3_up_f32(v.z, e), e4m3_up_f32(v.w, e)};
+    bool over = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (q[k] == 0xFFu) {
+        over = true;
+        q[k] = 0x7Eu;
+      }
+    *reinterpret_cast<uint32_t*>(a.p8 + at) = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
+    if (over) atomicOr(&a.over[l], 1u);
+  }
+}
+
+// Folds four values into their level's maximum (few threads; a stale read only
+// adds an atomic).
+__device__ __forceinline__ void raise_level_max(const TreeArgs& a, int l, const float4& v) {
+  const float m = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));
+  if (m > a.level_max[l])
+    atomicMax(reinterpret_cast<unsigned int*>(a.level_max + l), __float_as_uint(m));
+}
+
+// Pools of K levels above level `child`: each thread reads four columns of the
+// 2^K rows below one pool of level child - K and writes every pool of that
+// subtree that covers one of the rows [lo, hi), in every stored format, so a
+// level is read once for K levels and never again for its reduced copies.
+// Bound by memory.  200,000 x 1000, sum pools with a bfloat16 copy: one launch
+// per level and a conversion pass took 0.86 ms, now 0.43.
+// With `level_max`, the largest value of each written level as float bits (one
+// atomic per workgroup, and only where it raises the value): a launch per
+// level with one atomic per wave took 6.0 ms.
+template <bool MAXP, int K>
+__global__ __launch_bounds__(256) void k_tree(TreeArgs a, int child) {
+  if (refused(a.gate, a.bound)) return;
+  __shared__ float mx[K][4];
+  const int top = child - K, g = a.w / 4;
+  const int sh = a.depth - top;
+  const int64_t first = a.lo >> sh, count = ((a.hi - 1) >> sh) - first + 1;
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  float m[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) m[k] = 0.0f;
+  if (i < count * g) {
+    const int64_t j = first + i / g;
+    const int c = (int)(i % g) * 4;
+    const float* rows = child == a.depth ? a.leaves : a.tree + (size_t)((int64_t(1) << child) - 1) * a.w;
+    const float* p = rows + (size_t)(j << K) * a.w + c;
+    float4 v[1 << K];
+#pragma unroll
+    for (int r = 0; r < (1 << K); ++r) v[r] = *reinterpret_cast<const float4*>(p + (size_t)r * a.w);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int l = child - 1 - k;
+      const int64_t lo = a.lo >> (a.depth - l), hi = (a.hi - 1) >> (a.depth - l);
+#pragma unroll
+      for (int r = 0; r < (1 << (K - 1 - k)); ++r) {
+        v[r] = pool4<MAXP>(v[2 * r], v[2 * r + 1]);
+        const int64_t node = (j << (K - 1 - k)) + r;
+        if (node >= lo && node <= hi) {
+          store_pool4(a, l, node, c, v[r]);
+          m[k] = fmaxf(m[k], fmaxf(fmaxf(v[r].x, v[r].y), fmaxf(v[r].z, v[r].w)));
+        }
+      }
+    }
+  }
+  if (!a.level_max) return;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    for (int o = 32; o >= 1; o >>= 1) m[k] = fmaxf(m[k], __shfl_xor(m[k], o, 64));
+    if ((threadIdx.x & 63) == 0) mx[k][threadIdx.x >> 6] = m[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < K) {
+    const int k = threadIdx.x;
+    const float v = fmaxf(fmaxf(mx[k][0], mx[k][1]), fmaxf(mx[k][2], mx[k][3]));
+    float* out = a.level_max + (child - 1 - k);
+    if (v > *out) atomicMax(reinterpret_cast<unsigned int*>(out), __float_as_uint(v));
+  }
+}
+
+// Every level above `child` of the pools that cover the rows [lo, hi), where
+// level child - 1 has at most kPathNodes of them.  Columns do not meet, so a
+// workgroup takes 16 columns through all levels by itself: thread (r, q) holds
+// columns 4 q .. 4 q + 3 of the level's r-th pool, the levels pass through LDS,
+// and the siblings outside the range (at most one at each end of a level,
+// which nothing here writes) are read up front.  The time is the chain of
+// levels: an insert of 100 rows (21 levels, d = 512, bfloat16 copies) took 42
+// launches, about 180 us of the call, now one of 12 us.
+template <bool MAXP>
+__global__ __launch_bounds__(4 * kPathNodes) void k_tree_path(TreeArgs a, int child) {
+  if (refused(a.gate, a.bound)) return;
+  __shared__ float4 buf[2][kPathNodes][4];
+  __shared__ float4 edge[GT_MAX_LEVELS][2][4];
+  const int t = threadIdx.x, q = t & 3, r = t >> 2;
+  const int c = blockIdx.x * 16 + 4 * q;
+  auto range = [&](int l, int64_t& x, int64_t& y) {
+    x = a.lo >> (a.depth - l);
+    y = (a.hi - 1) >> (a.depth - l);
+  };
+  for (int i = t; i < (child - 1) * 8; i += blockDim.x) {
+    // siblings of level l = 1 .. child - 1: left (of an odd first pool), right
+    // (of an even last one)
+    const int l = 1 + (i >> 3), side = (i >> 2) & 1, e = i & 3;
+    int64_t x, y;
+    range(l, x, y);
+    const bool has = side == 0 ? (x & 1) : !(y & 1);
+    const int64_t row = (int64_t(1) << l) - 1 + (side == 0 ? x - 1 : y + 1);
+    if (has)
+      edge[l][side][e] = *reinterpret_cast<const float4*>(a.tree + (size_t)row * a.w + blockIdx.x * 16 + 4 * e);
+  }
+  int64_t lo, hi;
+  range(child - 1, lo, hi);
+  if (lo + r <= hi) {
+    const float* rows = child == a.depth ? a.leaves : a.tree + (size_t)((int64_t(1) << child) - 1) * a.w;
+    const float* p = rows + (size_t)(2 * (lo + r)) * a.w + c;
+    const float4 v = pool4<MAXP>(*reinterpret_cast<const float4*>(p),
+                                 *reinterpret_cast<const float4*>(p + a.w));
+    buf[0][r][q] = v;
+    store_pool4(a, child - 1, lo + r, c, v);
+    if (a.level_max) raise_level_max(a, child - 1, v);
+  }
+  for (int l = child - 2, k = 0; l >= 0; --l, k ^= 1) {
+    __syncthreads();
+    const int64_t clo = lo, chi = hi;  // the children's range
+    range(l, lo, hi);
+    if (lo + r <= hi) {
+      float4 v[2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int64_t ch = 2 * (lo + r) + s;
+        v[s] = ch < clo ? edge[l + 1][0][q] : ch > chi ? edge[l + 1][1][q] : buf[k][ch - clo][q];
+      }
+      const float4 x = pool4<MAXP>(v[0], v[1]);
+      buf[k ^ 1][r][q] = x;
+      store_pool4(a, l, lo + r, c, x);
+      if (a.level_max) raise_level_max(a, l, x);
+    }
+  }
+}
+
+// Rows of a tree that cover none of its first n leaves are zero: one grid row
+// per level clears the pools past the level's last populated one.
+__global__ void k_zero_tails(uint4* tree, int row16, int depth, int64_t n) {
+  const int l = blockIdx.y;
+  const int64_t first = n > 0 ? ((n - 1) >> (depth - l)) + 1 : 0;
+  const int64_t base = ((int64_t(1) << l) - 1 + first) * row16;
+  const int64_t count = ((int64_t(1) << l) - first) * row16;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count;
+       i += (int64_t)gridDim.x * blockDim.x)
+    tree[base + i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // Bottom level of the max/min tree of a signed index (paper Sec. 2, negative
@@ -128,7 +359,8 @@ __global__ void k_build_level(const float* __restrict__ child, float* __restrict
 // the shifted rows is taken term by term, which is the shifted max and min.
 __global__ void k_signed_bottom(const float* __restrict__ leaves, float* __restrict__ parent,
                                 int64_t first, int64_t nodes, int dp, int d, int64_t n,
-                                float bound) {
+                                float bound, uint16_t* parent16, const IngestOut* gate) {
+  if (refused(gate, bound)) return;
   const int pw = 2 * dp, qd = pw / 4;
   const int64_t total = nodes * qd;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
@@ -152,6 +384,10 @@ __global__ void k_signed_bottom(const float* __restrict__ leaves, float* __restr
       }
     }
     *reinterpret_cast<float4*>(parent + j * pw + k) = make_float4(o[0], o[1], o[2], o[3]);
+    if (parent16)
+      *reinterpret_cast<uint2*>(parent16 + j * pw + k) =
+          make_uint2((uint32_t)bf16_up(o[0]) | ((uint32_t)bf16_up(o[1]) << 16),
+                     (uint32_t)bf16_up(o[2]) | ((uint32_t)bf16_up(o[3]) << 16));
   }
 }
 
@@ -177,35 +413,61 @@ __global__ __launch_bounds__(1024) void k_level_entries(const uint32_t* __restri
   }
 }
 
-__global__ void k_level_max(const float* __restrict__ rows, int64_t count, float* out) {
+// Largest value of a level (a float8 level that an insert outgrew).
+__global__ __launch_bounds__(256) void k_level_max(const float4* __restrict__ rows, int64_t count4,
+                                                   float* out) {
+  __shared__ float mx[4];
   float m = 0.0f;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count;
-       i += (int64_t)gridDim.x * blockDim.x)
-    m = fmaxf(m, rows[i]);
-  for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-  if ((threadIdx.x & 63) == 0) atomicMax(reinterpret_cast<unsigned int*>(out), __float_as_uint(m));
-}
-
-__global__ void k_quant_bf16(const float* __restrict__ src, uint16_t* __restrict__ dst,
-                             int64_t count) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count;
-       i += (int64_t)gridDim.x * blockDim.x)
-    dst[i] = bf16_up(src[i]);
-}
-
-__global__ void k_quant_fp8(const float* __restrict__ src, uint8_t* __restrict__ dst,
-                            int64_t count, int lexp, unsigned int* overflow) {
-  bool over = false;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count4;
        i += (int64_t)gridDim.x * blockDim.x) {
-    uint32_t c = e4m3_up(ldexp((double)src[i], -lexp));
-    if (c == 0xFFu) {
-      over = true;
-      c = 0x7Eu;
-    }
-    dst[i] = (uint8_t)c;
+    const float4 v = rows[i];
+    m = fmaxf(m, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
   }
-  if (over) atomicOr(overflow, 1u);
+  for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  if ((threadIdx.x & 63) == 0) mx[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    m = fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]));
+    if (m > *out) atomicMax(reinterpret_cast<unsigned int*>(out), __float_as_uint(m));
+  }
+}
+
+// float8 scale exponents of all levels from their largest values.
+__global__ void k_fp8_exps(const float* level_max, int depth, int* lexp) {
+  if ((int)threadIdx.x < depth) lexp[threadIdx.x] = fp8_exp_for(level_max[threadIdx.x]);
+}
+
+// float8 copies of the levels first .. last in one pass over their rows; the
+// rows past a level's last populated pool are zero.
+__global__ void k_quant_fp8(const float* __restrict__ tree, uint8_t* __restrict__ p8, int w,
+                            int first, int last, int depth, int64_t n, const int* lexp,
+                            unsigned int* over) {
+  const int g = w / 4;
+  const int64_t row0 = (int64_t(1) << first) - 1;
+  const int64_t total = ((int64_t(2) << last) - 1 - row0) * g;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t row = row0 + i / g;
+    const int l = 63 - __clzll((unsigned long long)(row + 1));
+    const int64_t j = row + 1 - (int64_t(1) << l);
+    const size_t at = (size_t)row * w + (size_t)(i % g) * 4;
+    uint32_t q[4] = {0u, 0u, 0u, 0u};
+    if (n > 0 && j <= (n - 1) >> (depth - l)) {
+      const float4 v = *reinterpret_cast<const float4*>(tree + at);
+      const int e = lexp[l];
+      q[0] = e4m3_up_f32(v.x, e);
+      q[1] = e4m3_up_f32(v.y, e);
+      q[2] = e4m3_up_f32(v.z, e);
+      q[3] = e4m3_up_f32(v.w, e);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (q[k] == 0xFFu) {
+          atomicOr(&over[l], 1u);
+          q[k] = 0x7Eu;
+        }
+    }
+    *reinterpret_cast<uint32_t*>(p8 + at) = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
+  }
 }
 
 // One workgroup of 256 threads per (padded) query.
@@ -348,33 +610,82 @@ hipError_t launch_zero_u32(uint32_t* p, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_ingest(const void* src, int dtype, int64_t rows, int d, int dp, float* leaves,
-                         double* ff, float* invn, float* nf, double* mmin, unsigned int* err,
-                         bool allow_negative, unsigned int* absmax, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_ingest, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, s, src, dtype, rows,
-                     d, dp, leaves, ff, invn, nf, mmin, err, allow_negative ? 1 : 0, absmax);
+hipError_t launch_ingest_reset(IngestOut* o, hipStream_t s) {
+  hipLaunchKernelGGL(k_ingest_reset, dim3(1), dim3(64), 0, s, o);
   return hipGetLastError();
+}
+
+template <int R>
+hipError_t launch_ingest_rows(const void* src, int dtype, int64_t rows, int d, int dp,
+                              float* leaves, double* ff, float* invn, float* nf, IngestOut* o,
+                              int allow_negative, hipStream_t s) {
+  // wide loads: rows whose starts are all aligned to four features
+  const bool vec = d % 4 == 0 && reinterpret_cast<uintptr_t>(src) % (dtype == GT_F32 ? 16 : 8) == 0;
+  const dim3 grid((unsigned)((rows + R - 1) / R));
+  if (vec)
+    hipLaunchKernelGGL((k_ingest<R, true>), grid, dim3(256), 0, s, src, dtype, rows, d, dp, leaves,
+                       ff, invn, nf, o, allow_negative);
+  else
+    hipLaunchKernelGGL((k_ingest<R, false>), grid, dim3(256), 0, s, src, dtype, rows, d, dp, leaves,
+                       ff, invn, nf, o, allow_negative);
+  return hipGetLastError();
+}
+
+hipError_t launch_ingest(const void* src, int dtype, int64_t rows, int d, int dp, float* leaves,
+                         double* ff, float* invn, float* nf, IngestOut* o, bool allow_negative,
+                         hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  // 64-row tiles once they fill the chip, 4-row tiles below
+  if (rows >= 8192)
+    return launch_ingest_rows<64>(src, dtype, rows, d, dp, leaves, ff, invn, nf, o, allow_negative, s);
+  return launch_ingest_rows<4>(src, dtype, rows, d, dp, leaves, ff, invn, nf, o, allow_negative, s);
 }
 
 hipError_t launch_signed_bottom(const float* leaves, float* parent, int64_t first, int64_t nodes,
-                                int dp, int d, int64_t n, float bound, hipStream_t s) {
+                                int dp, int d, int64_t n, float bound, uint16_t* parent16,
+                                const IngestOut* gate, hipStream_t s) {
   if (nodes <= 0) return hipSuccess;
   if (dp % 4 || d > dp || first < 0 || n < 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_signed_bottom, dim3(grid_for(nodes * (2 * dp / 4), 256)), dim3(256), 0, s,
-                     leaves, parent, first, nodes, dp, d, n, bound);
+                     leaves, parent, first, nodes, dp, d, n, bound, parent16, gate);
   return hipGetLastError();
 }
 
-hipError_t launch_build_level(const float* child, float* parent, int64_t nodes, int dp,
-                              int64_t first, hipStream_t s, bool max_pool) {
-  if (nodes <= 0) return hipSuccess;
-  if (max_pool)
-    hipLaunchKernelGGL(k_build_level<true>, dim3(grid_for(nodes * (dp / 4), 256)), dim3(256), 0, s,
-                       child, parent, first, nodes, dp);
-  else
-    hipLaunchKernelGGL(k_build_level<false>, dim3(grid_for(nodes * (dp / 4), 256)), dim3(256), 0, s,
-                       child, parent, first, nodes, dp);
+// The pools above level `child` that cover the rows [lo, hi), bottom-up: four
+// levels a launch while a level has more pools than the path kernel holds.
+template <bool MAXP>
+hipError_t launch_tree_levels(const TreeArgs& a, int child, hipStream_t s) {
+  while (child > 0) {
+    const int sh = a.depth - (child - 1);
+    if (((a.hi - 1) >> sh) - (a.lo >> sh) + 1 <= kPathNodes) {
+      hipLaunchKernelGGL(k_tree_path<MAXP>, dim3(a.w / 16), dim3(4 * kPathNodes), 0, s, a, child);
+      return hipGetLastError();
+    }
+    // (more than kPathNodes pools: at least seven levels are left)
+    const int st = a.depth - (child - 4);
+    const int64_t threads = (((a.hi - 1) >> st) - (a.lo >> st) + 1) * (a.w / 4);
+    hipLaunchKernelGGL((k_tree<MAXP, 4>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
+                       a, child);
+    if (hipError_t e = hipGetLastError()) return e;
+    child -= 4;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_tree_update(const TreeArgs& a, bool max_pool, int child, hipStream_t s) {
+  if (a.hi <= a.lo || child <= 0) return hipSuccess;
+  if (a.lo < 0 || child > a.depth || a.depth > 31 || a.hi > (int64_t(1) << a.depth) || a.w % 16 ||
+      (a.p8 && (!a.lexp || !a.over)))
+    return hipErrorInvalidValue;
+  return max_pool ? launch_tree_levels<true>(a, child, s) : launch_tree_levels<false>(a, child, s);
+}
+
+hipError_t launch_zero_tails(void* tree, int row_bytes, int depth, int64_t n, hipStream_t s) {
+  if (depth <= 0 || row_bytes % 16) return depth <= 0 ? hipSuccess : hipErrorInvalidValue;
+  const int64_t most = ((int64_t(1) << (depth - 1)) - (n > 0 ? ((n - 1) >> 1) + 1 : 0)) * (row_bytes / 16);
+  const unsigned gx = (unsigned)std::min<int64_t>(4096, std::max<int64_t>(1, (most + 1023) / 1024));
+  hipLaunchKernelGGL(k_zero_tails, dim3(gx, (unsigned)depth), dim3(256), 0, s,
+                     static_cast<uint4*>(tree), row_bytes / 16, depth, n);
   return hipGetLastError();
 }
 
@@ -389,24 +700,24 @@ hipError_t launch_level_entries(const uint32_t* lvl_count, int first, int levels
 
 hipError_t launch_level_max(const float* rows, int64_t nrows, int dp, float* out_max,
                             hipStream_t s) {
-  const int64_t count = nrows * dp;
+  const int64_t count = nrows * dp / 4;
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_level_max, dim3(grid_for(count, 256 * 8)), dim3(256), 0, s, rows, count,
-                     out_max);
+  hipLaunchKernelGGL(k_level_max, dim3((unsigned)std::min<int64_t>(2048, (count + 1023) / 1024)),
+                     dim3(256), 0, s, reinterpret_cast<const float4*>(rows), count, out_max);
   return hipGetLastError();
 }
 
-hipError_t launch_quant_bf16(const float* src, uint16_t* dst, int64_t count, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_quant_bf16, dim3(grid_for(count, 256 * 4)), dim3(256), 0, s, src, dst, count);
+hipError_t launch_fp8_exps(const float* level_max, int depth, int* lexp, hipStream_t s) {
+  hipLaunchKernelGGL(k_fp8_exps, dim3(1), dim3(64), 0, s, level_max, depth, lexp);
   return hipGetLastError();
 }
 
-hipError_t launch_quant_fp8(const float* src, uint8_t* dst, int64_t count, int lexp,
-                            unsigned int* overflow, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_quant_fp8, dim3(grid_for(count, 256 * 4)), dim3(256), 0, s, src, dst, count,
-                     lexp, overflow);
+hipError_t launch_quant_fp8(const float* tree, uint8_t* p8, int w, int first, int last, int depth,
+                            int64_t n, const int* lexp, unsigned int* over, hipStream_t s) {
+  if (first < 0 || last >= depth || first > last || w % 4) return hipErrorInvalidValue;
+  const int64_t total = ((int64_t(2) << last) - (int64_t(1) << first)) * (w / 4);
+  hipLaunchKernelGGL(k_quant_fp8, dim3(grid_for(total, 256 * 4)), dim3(256), 0, s, tree, p8, w,
+                     first, last, depth, n, lexp, over);
   return hipGetLastError();
 }
 
