@@ -81,6 +81,17 @@ int head_of(const Index* ix) {
   return default_head(ix->depth);
 }
 
+// The first tested level where none is given: a level chosen by the caller (a
+// cost model's choice), else the level whose pools hold about 16 of the
+// populated rows; -1 if the head is not above it.
+int dense_rule(const Index* ix, int h) {
+  int lg = 0;
+  while ((int64_t(1) << lg) < ix->n) ++lg;
+  int dl = ix->dense_last >= 0 ? ix->dense_last : ix->dense_start >= 0 ? ix->dense_start : lg - 4;
+  dl = std::min(dl, ix->depth - 1);
+  return dl > h ? dl : -1;
+}
+
 // Last level walked with dense steps (every pool against every query).  Near
 // the root nearly every pool is live for every query tile, so a dense matrix
 // product reads each pool row once per workgroup column instead of once per
@@ -89,13 +100,7 @@ int head_of(const Index* ix) {
 // matrix cores are 16x slower than bfloat16 ones).
 int dense_last_of(const Index* ix, int fmt, int h) {
   if (fmt == GT_POOL_F32 || ix->dense_last == -1) return -1;
-  // automatic: a level given by the caller (a cost model's choice), else
-  // the level whose pools hold about 16 of the populated rows
-  int lg = 0;
-  while ((int64_t(1) << lg) < ix->n) ++lg;
-  int dl = ix->dense_last >= 0 ? ix->dense_last : ix->dense_start >= 0 ? ix->dense_start : lg - 4;
-  dl = std::min(dl, ix->depth - 1);
-  return dl > h ? dl : -1;
+  return dense_rule(ix, h);
 }
 
 // Automatic dense level, per workspace, from its last walk (same format): a
@@ -135,6 +140,53 @@ int bucket_bits_of(int sparse_from, int nt) {
   int nb = std::min(gt::kMaxBucketBits, std::max(0, sparse_from));
   while (nb > 0 && ((int64_t)nt << nb) > gt::kMaxSlots) --nb;
   return nb;
+}
+
+// Calls of few query tiles take the subtree walk (k_subtree.hip).  It saves
+// the level kernels' fixed time per level, but each tile reads the first
+// tested level for itself and both children of every entry, so the line lies
+// at tiles x bytes of that level.  Crossings measured (us per call, subtree
+// walk / level by level):
+//   bfloat16 2^20 x 1000 (134 MB): 128 queries 319 / 366, 192 404 / 398
+//            2^17 x 1000 (17 MB): 1024 queries 314 / 344
+//            2^18 x 256 (8 MB): 1024 queries 460 / 539
+//            2^17 x 2048 (17 MB): 256 queries 243 / 509, 1024 556 / 667
+//   float8   2^20 x 1000 (67 MB): 128 queries 285 / 292, 192 362 / 349
+//            300,007 x 777 (17 MB): 257 queries 283 / 299, 512 394 / 384
+//   float32  2^20 x 1000 (134 MB, 32-query tiles): 256 queries 1157 / 1269,
+//            512 2168 / 1911
+// and 90 against 201 - 327 us for one query.  Larger calls of more than 16
+// tiles were not measured below those sizes and go level by level, as do
+// calls with options that ask for the level kernels (an explicit head or
+// grid, row counting).
+constexpr int kSubtreeTiles = 16;
+
+void choose_subtree(const Index* ix, Batch* b, int width) {
+  b->sub_top = -1;
+  if (b->kind != 1 || b->nt < 1 || b->nt > kSubtreeTiles || b->n_epoch < 1 || b->counted ||
+      ix->grid > 0 || ix->head_level >= 0)
+    return;
+  int first = b->dense_last >= 0 ? b->dense_last : b->head + 1;
+  if (b->fmt == GT_POOL_F32 && ix->dense_last == -2) {
+    // float32 pools have no dense step, but start where the others do
+    const int dl = adapt_dense_last(ix, b, b->fmt, b->maxpool, dense_rule(ix, b->head), b->head);
+    if (dl >= 0) first = dl;
+  }
+  const int rows = b->nt > 1 ? b->tq : std::min(b->tq, b->nq <= 16 ? 16 : b->nq <= 32 ? 32 : 64);
+  // (a first level above the subtrees' roots: the tests start at the roots)
+  int top = -1, window = 0;
+  if (!gt::subtree_shape(b->fmt, width, b->nt, rows, ix->depth, first, top, window)) return;
+  first = std::max(first, top);
+  const int64_t pools = ((b->n_epoch - 1) >> (ix->depth - first)) + 1;
+  const int64_t bytes = pools * width * (b->fmt == GT_POOL_F32 ? 4 : b->fmt == GT_POOL_BF16 ? 2 : 1);
+  const int64_t most = int64_t(b->fmt == GT_POOL_F32 ? 1200 : b->fmt == GT_POOL_BF16 ? 360 : 136) * 1000000;
+  if (bytes * b->nt > most) return;
+  b->sub_top = top;
+  b->sub_window = window;
+  b->sub_first = first;
+  b->sub_rows = rows;
+  if (b->dense_last >= 0) b->dense_last = b->sub_first;
+  b->head = b->sub_first - 1;
 }
 
 int tq_of(int fmt) { return fmt == GT_POOL_F32 ? gt::kQueriesPerTileF32 : gt::kQueriesPerTile16; }
@@ -441,6 +493,35 @@ gt_status enqueue_walk(Index* ix, Batch* b) {
   uint32_t* bitmap = b->counted ? b->bitmap : nullptr;
   b->frontier_launches = 0;
   b->dense_launches = 0;
+  if (b->sub_top >= 0) {
+    gt::SubtreeArgs a{};
+    a.nt = nt;
+    a.dp = (int)dp;
+    a.qrows = b->sub_rows;
+    a.window = b->sub_window;
+    a.top = b->sub_top;
+    a.first = b->sub_first;
+    a.depth = D;
+    a.nb = b->nb;
+    a.bcap = b->fr_cap >> b->nb;
+    a.n_epoch = b->n_epoch;
+    a.pools = pool_base;
+    a.qtile = qtile;
+    a.thr = b->thr;
+    a.qexp = b->qexp;
+    a.lexp = ix->d_lexp;
+    a.tile_mask = b->tile_mask;
+    a.out_node = b->fr_node[(D - 1) & 1];
+    a.out_mask = b->fr_mask[(D - 1) & 1];
+    a.lvl_count = b->lvl_count;
+    a.stat = gt::stat_levels(b->lvl_count);
+    a.over = &b->ctr->fr_over;
+    ev_launch_begin(b);
+    HIPCHK(gt::launch_walk_subtree(f, a, s));
+    ev_launch_end(b, false);
+    b->frontier_launches = 1;
+    return GT_OK;
+  }
   // Subtraction step (bfloat16 pools, score records from a dense step):
   // sparse levels sub_from .. sub_to read only the right children.
   const int ws = ix->walk_subtract < 0 ? 1 : ix->walk_subtract;
@@ -569,7 +650,7 @@ gt_status enqueue_leaf(Index* ix, Batch* b) {
   const int sparse_from = b->dense_last >= 0 ? b->dense_last : b->head;
   gt::LeafArgs la{};
   la.level = D - 1;
-  la.dense = (sparse_from == D - 1) && b->dense_last < 0;
+  la.dense = (sparse_from == D - 1) && b->dense_last < 0 && b->sub_top < 0;
   la.nt = b->nt;
   la.dp = ix->dp;
   la.nb = b->nb;
@@ -926,7 +1007,10 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
   // as its last step alone, up to rounding, which only keeps more.  With an
   // automatic head only the last dense level is tested.
   if (b->dense_last >= 0 && ix->head_level < 0) b->head = b->dense_last - 1;
+  b->counted = ix->count_unique && kind == 1 && !b->fixed;
+  choose_subtree(ix, b, maxp ? ix->pw : ix->dp);
   b->nb = bucket_bits_of(b->dense_last >= 0 ? b->dense_last : b->head, nt);
+  if (b->sub_top >= 0) b->nb = std::min(b->nb, b->sub_top);  // a subtree's entries share a bucket
   b->profile = ix->profile && !b->fixed;
   b->nw = 0;
   if (b->profile && !b->events) {
@@ -942,7 +1026,6 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
     TRY(zero_dev(b->lvl_count, (size_t)GT_MAX_LEVELS * gt::kMaxSlots * 4, s));
   else
     TRY(zero_dev(gt::stat_levels(b->lvl_count), gt::kStatWords * 8, s));
-  b->counted = ix->count_unique && kind == 1 && !b->fixed;
   if (b->counted) {
     const int64_t words = (int64_t(2) << ix->depth) / 32 + 1;
     if (!b->bitmap) {
@@ -1051,7 +1134,7 @@ gt_status finish(Index* ix, Batch* b, int64_t max_results, int64_t* offsets, int
   if (b->kind == 1) {
     // state for the next call's automatic dense level
     b->have_last = true;
-    b->last_dl = b->dense_last;
+    b->last_dl = b->sub_top >= 0 ? b->sub_first : b->dense_last;
     b->last_walk_fmt = b->fmt;
     b->last_maxpool = b->maxpool;
     b->last_walk_nt = b->nt;

@@ -173,6 +173,34 @@ struct DenseLevelArgs {
   unsigned int* over;       // set when an output slot is full (its entry is dropped)
 };
 
+// Arguments of the subtree walk of calls of few query tiles: every level from
+// `first` down to the last pools in one launch.
+struct SubtreeArgs {
+  int nt, dp;
+  int qrows;                // query rows of a tile that are read: 16, 32 or 64
+  int window;               // query bytes per row held at once, 0: whole rows
+  int top;                  // level of the subtrees' roots, one workgroup per (subtree, tile)
+  int first;                // first tested level (>= top)
+  int depth;
+  int nb;                   // bucket bits of the output
+  int64_t bcap;
+  int64_t n_epoch;          // rows visible to the call
+  const void* pools;        // row 0 of the tree in the pool format
+  const void* qtile;
+  const float* thr;
+  const int* qexp;
+  const int* lexp;          // [levels] float8 scale exponents (device)
+  const uint64_t* tile_mask;
+  uint32_t* out_node;       // entries of level depth - 1
+  uint64_t* out_mask;
+  uint32_t* lvl_count;      // [levels x kMaxSlots]
+  unsigned long long* stat; // stripe 0, level 0 of the test counters
+  unsigned int* over;
+};
+// The subtree walk's shape for a call whose first tested level is `first`
+// (false: it does not take the call).
+bool subtree_shape(int fmt, int dp, int nt, int qrows, int depth, int first, int& top, int& window);
+
 struct LeafArgs {
   int level, dense, nt, dp, tq;
   int nb;
@@ -303,6 +331,7 @@ struct Batch {
   hipStream_t stream = nullptr;
   int fmt = 0, nq = 0, nq_pad = 0, nt = 0, tq = 0, head = 0, dense_last = -1, nb = 0;
   int64_t n_epoch = 0;       // vectors visible to the call (ids below this)
+  int sub_top = -1, sub_first = 0, sub_rows = 0, sub_window = 0;  // subtree walk (sub_top < 0: none)
   bool profile = false;
 
   // counters of the last finished call
@@ -383,6 +412,7 @@ hipError_t launch_query_prep(const float* q, int nq, int d, int dp, int tq, cons
                              unsigned int* err, int nq_pad, hipStream_t s);
 hipError_t launch_walk_level(int fmt, const WalkLevelArgs& a, int grid, hipStream_t s);
 hipError_t launch_walk_sub(const WalkLevelArgs& a, int grid, hipStream_t s);
+hipError_t launch_walk_subtree(int fmt, const SubtreeArgs& a, hipStream_t s);
 hipError_t launch_leaf(const LeafArgs& a, int grid, hipStream_t s);
 hipError_t launch_dense_level(int fmt, const DenseLevelArgs& a, hipStream_t s);
 hipError_t launch_recheck(Hit* hits, const uint32_t* band_idx, const unsigned long long* nband,

@@ -14,29 +14,14 @@
 
 #include "gt_internal.h"
 #include "gt_device.h"
+#include "gt_mma.h"
 #include "gt_numerics.h"
 
 namespace gt {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-
-template <int FMT>
-struct WalkFmt;
-template <>
-struct WalkFmt<GT_POOL_F32> {
-  static constexpr int TQ = kQueriesPerTileF32, ESZ = 4, MAXDP = kMaxDpF32;
-};
-template <>
-struct WalkFmt<GT_POOL_BF16> {
-  static constexpr int TQ = kQueriesPerTile16, ESZ = 2, MAXDP = kMaxDpBf16;
-};
-template <>
-struct WalkFmt<GT_POOL_FP8E4M3> {
-  static constexpr int TQ = kQueriesPerTile16, ESZ = 1, MAXDP = kMaxDpFp8;
-};
 
 // One 16-byte slice of a row (per lane) against the same slice of a query:
 // bf16: one 32x32x16 step; float8: two 32x32x16 steps; float32: four 32x32x2
@@ -107,43 +92,6 @@ __device__ __forceinline__ void slot_prefix(uint32_t* pre, int n, int slot0, int
     if (lane == 63) pre[n] = incl;
   }
   __syncthreads();
-}
-
-__device__ __forceinline__ uint4 ld_global16(const unsigned char* p) {
-  return *reinterpret_cast<const uint4*>(p);
-}
-__device__ __forceinline__ uint4 ld_lds16(const unsigned char* p) {
-  return *reinterpret_cast<const uint4*>(p);
-}
-
-// 16x16 forms: one 16-byte slice per lane, 64 bytes of each of 16 rows per
-// wave instruction.  Lane l holds row (l % 16) and slice (l / 16) of a 64-byte
-// step; the A and B lanes of the same index hold the same dimensions.
-// Accumulator: register i of lane l is row 4 (l / 16) + i, column l % 16.
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-template <int FMT>
-__device__ __forceinline__ void mma16x16(const uint4& a, const uint4& b, f32x4& acc);
-template <>
-__device__ __forceinline__ void mma16x16<GT_POOL_BF16>(const uint4& a, const uint4& b, f32x4& acc) {
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-}
-template <>
-__device__ __forceinline__ void mma16x16<GT_POOL_FP8E4M3>(const uint4& a, const uint4& b,
-                                                          f32x4& acc) {
-  const long a0 = (long)(((unsigned long)a.y << 32) | a.x);
-  const long a1 = (long)(((unsigned long)a.w << 32) | a.z);
-  const long b0 = (long)(((unsigned long)b.y << 32) | b.x);
-  const long b1 = (long)(((unsigned long)b.w << 32) | b.z);
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(a0, b0, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(a1, b1, acc, 0, 0, 0);
-}
-template <>
-__device__ __forceinline__ void mma16x16<GT_POOL_F32>(const uint4& a, const uint4& b, f32x4& acc) {
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
 }
 
 // gfx950 f8f6f4 forms for float8 (e4m3: format 0 for both operands, no

@@ -1,0 +1,112 @@
+"""The subtree walk of calls of few query tiles against the float64 oracle and
+against the level-by-level kernels (option grid), at its edges: one query to
+several tiles, the query blocks of 16 / 32 / 64 rows, trees from two levels
+up, ragged and part-filled trees, rows that fit in LDS and rows that pass in
+windows, thresholds that keep everything, zero rows, and rows inserted after
+a call was submitted."""
+import numpy as np
+import pytest
+import torch
+
+import oracle.brute as ob
+from paper_2311_02573_amd import synth
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-6  # the leaf similarity's bound
+
+POOLS = ("f32", "bf16", "fp8", "max_f32", "max_bf16")
+
+
+@pytest.fixture(scope="module")
+def gt():
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    from paper_2311_02573_amd import gt as g
+
+    return g
+
+
+def _same(got, want):
+    for (gi, gs), (oi, os_) in zip(got, want):
+        assert np.array_equal(gi, oi)
+        assert len(gs) == 0 or np.max(np.abs(gs - os_)) <= TOL
+
+
+def _levels(idx, q, rho, pool):
+    """The same call by the level kernels."""
+    idx.set_option("grid", 256)
+    out = idx.query(q, rho, pool=pool).to_lists()
+    idx.set_option("grid", 0)
+    return out
+
+
+@pytest.mark.parametrize("n,d,cap", [(3, 7, 4), (5, 40, 64), (33, 130, 64), (1000, 96, 1024),
+                                     (5000, 1000, 8192), (5000, 200, 1 << 15), (2500, 1300, 4096),
+                                     (900, 2100, 1024), (300, 4096, 512)])
+def test_against_oracle_and_level_kernels(gt, n, d, cap):
+    w = synth.workload_small(n, d, 129, seed_offset=n % 17)
+    feats = w.feats.copy()
+    feats[n // 2] = 0.0  # a zero row never matches
+    idx = gt.GTIndex(torch.from_numpy(feats).cuda(), capacity=cap, pools=POOLS)
+    q = torch.from_numpy(w.queries).cuda()
+    rho = np.full(129, 0.9)
+    rho[::7] = 0.5
+    rho[3::40] = -1.0  # keeps every row
+    want = ob.range_search(feats, w.queries, rho)
+    for pool in POOLS:
+        for nq in (1, 16, 17, 33, 64, 65, 129):
+            # twice: the second call's first level follows the first's frontier
+            for _ in range(2):
+                _same(idx.query(q[:nq], rho[:nq], pool=pool).to_lists(), want[:nq])
+        _same(_levels(idx, q, rho, pool), want)
+        assert idx.stats()["leaf_pairs"] >= sum(len(i) for i, _ in want)
+    idx.close()
+
+
+@pytest.mark.parametrize("d", [48, 700, 1100])
+def test_signed_rows(gt, d):
+    w = synth.workload_signed(1500, d, 40)
+    idx = gt.GTIndex(torch.from_numpy(w.feats).cuda(), pools=("signed", "max_bf16"))
+    q = torch.from_numpy(w.queries).cuda()
+    want = ob.range_search(w.feats, w.queries, 0.9)
+    for pool in ("max_bf16", "max_f32"):
+        for nq in (1, 20, 40):
+            _same(idx.query(q[:nq], 0.9, pool=pool).to_lists(), want[:nq])
+        _same(_levels(idx, q, 0.9, pool), want)
+    idx.close()
+
+
+@pytest.mark.parametrize("pool", ["bf16", "f32"])
+def test_rows_inserted_behind_a_call(gt, pool):
+    """A call sees the rows of its submit; the next one sees the rest."""
+    w = synth.workload_small(3000, 64, 20, seed_offset=3)
+    F = torch.from_numpy(w.feats).cuda()
+    q = torch.from_numpy(w.queries).cuda()
+    idx = gt.GTIndex(F[:1111], capacity=4096, pools=("f32", "bf16"))
+    ws = gt.Workspace(idx, 64)
+    at = 1111
+    for step in (1, 100, 1788):
+        ws.submit(q, 0.8, pool=pool)
+        idx.insert(F[at:at + step])
+        _same(ws.finish().to_lists(), ob.range_search(w.feats[:at], w.queries, 0.8))
+        at += step
+        _same(idx.query(q, 0.8, pool=pool).to_lists(), ob.range_search(w.feats[:at], w.queries, 0.8))
+    ws.close()
+    idx.close()
+
+
+@pytest.mark.parametrize("pool", POOLS)
+def test_level_counts(gt, pool):
+    """Per-level tests: the first level's are all its populated pools for all
+    queries, and a level tests twice the pairs that the level above kept."""
+    w = synth.workload_small(6000, 100, 30, seed_offset=5)
+    idx = gt.GTIndex(torch.from_numpy(w.feats).cuda(), pools=POOLS)
+    idx.query(torch.from_numpy(w.queries).cuda(), 0.9, pool=pool)
+    st = idx.stats()
+    first, D = st["head_level"] + 1, st["depth"]
+    assert st["pairs"][first] == 30 * -(-6000 // (1 << (D - first)))
+    for l in range(first, D - 1):
+        assert st["entries"][l] * 2 >= st["entries"][l + 1] > 0
+        assert st["entries"][l] <= st["pairs"][l] and st["pairs"][l + 1] >= 2 * st["entries"][l] - 1
+    assert st["leaf_pairs"] >= 2 * st["entries"][D - 1] - 1
+    idx.close()
