@@ -474,6 +474,20 @@ float ev_walk(Batch* b, bool dense) {
 }
 
 // ------------------------------------------------------------- launch stages
+// The call's result counters: in their rows behind the level counters, spread
+// as far as they have room, or packed in an array of their own.
+gt::QCount qcount_of(const Batch* b) {
+  if (b->nq_pad > gt::kQCountWords) return {b->qcount, 0};
+  int shift = 5;
+  while (((int64_t)b->nq_pad << shift) > gt::kQCountWords) --shift;
+  return {b->lvl_count + (size_t)gt::kQCountRow * gt::kMaxSlots, shift};
+}
+
+gt_status zero_qcount(const Batch* b, hipStream_t s) {
+  const gt::QCount c = qcount_of(b);
+  return zero_dev(c.p, ((size_t)b->nq_pad << c.shift) * 4, s);
+}
+
 gt_status enqueue_walk(Index* ix, Batch* b) {
   hipStream_t s = b->stream;
   const int f = b->fmt, nt = b->nt, D = ix->depth, h = b->head, dl = b->dense_last;
@@ -669,7 +683,7 @@ gt_status enqueue_leaf(Index* ix, Batch* b) {
   la.hits = b->hits;
   la.band_idx = b->band_idx;
   la.hit_cap = (unsigned long long)b->hit_cap;
-  la.qcount = b->qcount;
+  la.qcount = qcount_of(b);
   la.ctr = b->ctr;
   la.stat_pairs = gt::stat_leaf(b->lvl_count);
   la.bitmap = b->counted ? b->bitmap : nullptr;
@@ -697,7 +711,7 @@ gt_status enqueue_exhaustive(Index* ix, Batch* b) {
 gt_status enqueue_pair_check(Index* ix, Batch* b) {
   HIPCHK(gt::launch_pair_check(b->cand, &b->ctr->ncand, (unsigned long long)b->cand_cap, b->qf,
                                ix->leaves, b->invn_q, ix->invn, b->rho, ix->dp, b->hits,
-                               (unsigned long long)b->hit_cap, b->band_idx, b->qcount, b->ctr,
+                               (unsigned long long)b->hit_cap, b->band_idx, qcount_of(b), b->ctr,
                                gt::stat_leaf(b->lvl_count), ix->n_cu * 4, b->stream));
   return GT_OK;
 }
@@ -720,10 +734,10 @@ gt_status enqueue_place(Batch* b, int64_t lim, int64_t* ids, float* sims) {
 gt_status enqueue_tail(Index* ix, Batch* b) {
   hipStream_t s = b->stream;
   HIPCHK(gt::launch_recheck(b->hits, b->band_idx, &b->ctr->nband, (unsigned long long)b->hit_cap,
-                            b->qf, ix->leaves, ix->d, ix->dp, ix->ff, b->rho, b->qcount,
+                            b->qf, ix->leaves, ix->d, ix->dp, ix->ff, b->rho, qcount_of(b),
                             b->ctr, s));
   ev_mark(b, 4);
-  HIPCHK(gt::launch_scan_offsets(b->qcount, b->nq, b->offs,
+  HIPCHK(gt::launch_scan_offsets(qcount_of(b), b->nq, b->offs,
                                      gt::stat_levels(b->lvl_count), b->ctr, s));
   TRY(ensure_out(b, 1));
   b->spec_direct = b->tgt_ids != nullptr;
@@ -747,7 +761,7 @@ void set_targets(Batch* b, int64_t max_results, int64_t* ids, float* sims) {
 
 gt_status redo_candidates(Index* ix, Batch* b) {
   hipStream_t s = b->stream;
-  TRY(zero_dev(b->qcount, (size_t)b->nq_pad * 4, s));
+  TRY(zero_qcount(b, s));
   TRY(zero_dev(&b->ctr->nhits, 8, s));
   TRY(zero_dev(gt::stat_leaf(b->lvl_count), (size_t)gt::kStatStripes * gt::kLeafStride * 8, s));
   TRY(zero_dev(&b->ctr->rechecked, 8, s));
@@ -1020,12 +1034,14 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
   }
   ev_mark(b, 0);
   TRY(zero_dev(b->ctr, sizeof(gt::DevCounters), s));
-  TRY(zero_dev(b->qcount, (size_t)nq_pad * 4, s));
   TRY(zero_dev(b->tile_mask, (size_t)gt::kMaxTiles * 8, s));
-  if (kind == 1)
+  if (kind == 1) {
     TRY(zero_dev(b->lvl_count, (size_t)GT_MAX_LEVELS * gt::kMaxSlots * 4, s));
-  else
+    if (qcount_of(b).p == b->qcount) TRY(zero_qcount(b, s));
+  } else {
+    TRY(zero_qcount(b, s));
     TRY(zero_dev(gt::stat_levels(b->lvl_count), gt::kStatWords * 8, s));
+  }
   if (b->counted) {
     const int64_t words = (int64_t(2) << ix->depth) / 32 + 1;
     if (!b->bitmap) {

@@ -22,7 +22,7 @@ __device__ __forceinline__ void stat_add(unsigned long long* stat, int stride, u
 // the flag.  Lanes of the same query share one add to its counter for the
 // first four queries met (calls of few queries, whose counters would
 // otherwise take every result as an add of its own); other lanes add alone.
-__device__ __forceinline__ uint32_t accept_slots(bool acc, uint32_t q, unsigned int* qcount,
+__device__ __forceinline__ uint32_t accept_slots(bool acc, uint32_t q, QCount qcount,
                                                  DevCounters* ctr, int lane) {
   uint64_t rem = __ballot(acc);
   if (rem == 0ull) return 0u;
@@ -41,7 +41,7 @@ __device__ __forceinline__ uint32_t accept_slots(bool acc, uint32_t q, unsigned 
     rem &= ~same;
   }
   uint32_t r = 0;
-  if (acc && leader == lane) r = atomicAdd(&qcount[q], add);
+  if (acc && leader == lane) r = atomicAdd(&qcount.p[(size_t)q << qcount.shift], add);
   r = (uint32_t)__shfl((int)r, leader, 64) + rank;
   if (acc && r >= kMaxResultsPerQuery) {
     atomicOr(&ctr->slot_over, 1u);
@@ -54,7 +54,7 @@ __device__ __forceinline__ uint32_t accept_slots(bool acc, uint32_t q, unsigned 
 // takes its slot here, for 64 pairs at a time, so that the test rounds do not
 // wait for the counters.
 __device__ __forceinline__ void write_hits(const Hit* buf, int cnt, unsigned long long base,
-                                           unsigned int* qcount, DevCounters* ctr, Hit* hits,
+                                           QCount qcount, DevCounters* ctr, Hit* hits,
                                            unsigned long long hit_cap, uint32_t* band_idx,
                                            int lane) {
   for (int i0 = 0; i0 < cnt; i0 += 64) {
@@ -78,7 +78,7 @@ __device__ __forceinline__ void write_hits(const Hit* buf, int cnt, unsigned lon
 // flushes the buffer to global memory (one reservation per flush) when it is
 // nearly full.  Called by the whole wave.
 __device__ __forceinline__ void stage_hits(Hit* buf, int& cnt, bool have, const Hit& h,
-                                           unsigned int* qcount, DevCounters* ctr, Hit* hits,
+                                           QCount qcount, DevCounters* ctr, Hit* hits,
                                            unsigned long long hit_cap, uint32_t* band_idx,
                                            int lane) {
   const uint64_t bal = __ballot(have);
@@ -97,7 +97,7 @@ __device__ __forceinline__ void stage_hits(Hit* buf, int& cnt, bool have, const 
 
 // Last flush of a workgroup of four waves: one reservation for all of them
 // (every wave of the workgroup calls it once, with whatever it has staged).
-__device__ __forceinline__ void flush_hits(const Hit* buf, int cnt, unsigned int* qcount,
+__device__ __forceinline__ void flush_hits(const Hit* buf, int cnt, QCount qcount,
                                            DevCounters* ctr, Hit* hits,
                                            unsigned long long hit_cap, uint32_t* band_idx,
                                            int lane, int w) {
@@ -116,8 +116,8 @@ __device__ __forceinline__ void flush_hits(const Hit* buf, int cnt, unsigned int
 }
 
 // Slot of one accepted pair among its query's results (the recheck's).
-__device__ __forceinline__ uint32_t accept_slot(unsigned int* qcount, DevCounters* ctr) {
-  const uint32_t r = atomicAdd(qcount, 1u);
+__device__ __forceinline__ uint32_t accept_slot(QCount qcount, uint32_t q, DevCounters* ctr) {
+  const uint32_t r = atomicAdd(&qcount.p[(size_t)q << qcount.shift], 1u);
   if (r >= kMaxResultsPerQuery) {
     atomicOr(&ctr->slot_over, 1u);
     return 0u;

@@ -41,6 +41,16 @@ constexpr size_t kStatWords = (size_t)kStatStripes * (GT_MAX_LEVELS + kLeafStrid
 static_assert(kStatRow > 32 &&
                   kStatWords * 8 <= (size_t)(GT_MAX_LEVELS - kStatRow) * kMaxSlots * 4,
               "the statistics fit behind the deepest level");
+// Accepted results per query: query q's counter is p[q << shift].  Adds to one
+// 128-byte line are served one after another (about 4 ns each, whatever the
+// address), so calls of up to 1024 queries give every counter a line of its
+// own, larger ones as much room as the counters' rows have.
+constexpr int kQCountRow = 32;          // first row, behind the deepest level
+constexpr int kQCountWords = (kStatRow - kQCountRow) * kMaxSlots;
+struct QCount {
+  unsigned int* p;
+  int shift;
+};
 inline unsigned long long* stat_levels(uint32_t* lvl_count) {
   return reinterpret_cast<unsigned long long*>(lvl_count + (size_t)kStatRow * kMaxSlots);
 }
@@ -218,7 +228,7 @@ struct LeafArgs {
   Hit* hits;
   unsigned long long hit_cap;
   uint32_t* band_idx;       // [hit_cap] indices of band candidates in hits
-  unsigned int* qcount;     // [nt * tq] accepted results per query
+  QCount qcount;            // accepted results per query
   DevCounters* ctr;
   unsigned long long* stat_pairs;  // stripe 0 of the leaf-test counters
   uint32_t* bitmap;         // optional: one bit per tree row read
@@ -418,8 +428,8 @@ hipError_t launch_dense_level(int fmt, const DenseLevelArgs& a, hipStream_t s);
 hipError_t launch_recheck(Hit* hits, const uint32_t* band_idx, const unsigned long long* nband,
                           unsigned long long cap, const float* qf, const float* leaves, int d,
                           int dp, const double* ff, const double* rho,
-                          unsigned int* qcount, DevCounters* ctr, hipStream_t s);
-hipError_t launch_scan_offsets(const unsigned int* qcount, int nq, int64_t* offs,
+                          QCount qcount, DevCounters* ctr, hipStream_t s);
+hipError_t launch_scan_offsets(QCount qcount, int nq, int64_t* offs,
                                const unsigned long long* stat, DevCounters* ctr, hipStream_t s);
 hipError_t launch_scatter(const Hit* hits, const DevCounters* ctr, unsigned long long hit_cap,
                           unsigned long long lim, const int64_t* offs, uint32_t* out_id,
@@ -437,7 +447,7 @@ hipError_t launch_pair_check(const uint2* cand, const unsigned long long* ncand,
                              unsigned long long cap, const float* qf, const float* leaves,
                              const float* invn_q, const float* invn_f, const double* rho, int dp,
                              Hit* hits, unsigned long long hit_cap, uint32_t* band_idx,
-                             unsigned int* qcount, DevCounters* ctr,
+                             QCount qcount, DevCounters* ctr,
                              unsigned long long* stat_pairs, int grid, hipStream_t s);
 // Scratch of the allocation-free entry point (gt_noalloc.hip): taken once per
 // device at set-up (index build), with that device current.

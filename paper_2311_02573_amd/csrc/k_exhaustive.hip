@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256) void k_pair_check(const uint2* cand, const uns
                                                     const float* leaves, const float* invn_q,
                                                     const float* invn_f, const double* rho, int dp,
                                                     Hit* hits, unsigned long long hit_cap,
-                                                    uint32_t* band_idx, unsigned int* qcount,
+                                                    uint32_t* band_idx, QCount qcount,
                                                     DevCounters* ctr,
                                                     unsigned long long* stat_pairs) {
   __shared__ Hit hstage[4][kHitStage];
@@ -220,7 +220,7 @@ hipError_t launch_pair_check(const uint2* cand, const unsigned long long* ncand,
                              unsigned long long cap, const float* qf, const float* leaves,
                              const float* invn_q, const float* invn_f, const double* rho, int dp,
                              Hit* hits, unsigned long long hit_cap, uint32_t* band_idx,
-                             unsigned int* qcount, DevCounters* ctr,
+                             QCount qcount, DevCounters* ctr,
                              unsigned long long* stat_pairs, int grid, hipStream_t s) {
   hipLaunchKernelGGL(k_pair_check, dim3(grid), dim3(256), 0, s, cand, ncand, cap, qf, leaves, invn_q,
                      invn_f, rho, dp, hits, hit_cap, band_idx, qcount, ctr, stat_pairs);

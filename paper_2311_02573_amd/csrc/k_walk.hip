@@ -1751,7 +1751,7 @@ __global__ __launch_bounds__(256) void k_recheck(Hit* hits, const uint32_t* band
                                                  const float* __restrict__ leaves, int d, int dp,
                                                  const double* __restrict__ ff,
                                                  const double* __restrict__ rho,
-                                                 unsigned int* qcount, DevCounters* ctr) {
+                                                 QCount qcount, DevCounters* ctr) {
   const int lane = threadIdx.x & 63;
   const unsigned long long n = *nband < cap ? *nband : cap;
   const unsigned long long nw = blockDim.x >> 6;
@@ -1789,7 +1789,7 @@ __global__ __launch_bounds__(256) void k_recheck(Hit* hits, const uint32_t* band
       const double cs = __ddiv_rn(s, __dmul_rn(__dsqrt_rn(sq), __dsqrt_rn(ff[x.id])));
       atomicAdd(&ctr->rechecked, 1ull);
       if (cs >= rho[x.q]) {
-        x.flag = HIT_ACCEPT | accept_slot(&qcount[x.q], ctr);
+        x.flag = HIT_ACCEPT | accept_slot(qcount, x.q, ctr);
         x.sim = (float)cs;
       } else {
         x.flag = HIT_REJECT;
@@ -1801,7 +1801,7 @@ __global__ __launch_bounds__(256) void k_recheck(Hit* hits, const uint32_t* band
 
 // Exclusive scan of per-query counts -> offsets (one workgroup of 1024), and
 // the sums of the striped statistics counters.
-__global__ __launch_bounds__(1024) void k_scan_offsets(const unsigned int* qcount, int nq,
+__global__ __launch_bounds__(1024) void k_scan_offsets(QCount qcount, int nq,
                                                        int64_t* offs,
                                                        const unsigned long long* stat,
                                                        DevCounters* ctr) {
@@ -1819,7 +1819,7 @@ __global__ __launch_bounds__(1024) void k_scan_offsets(const unsigned int* qcoun
   const int per = (nq + 1023) / 1024;
   const int lo = t * per, hi = min(nq, lo + per);
   int64_t s = 0;
-  for (int i = lo; i < hi; ++i) s += qcount[i];
+  for (int i = lo; i < hi; ++i) s += qcount.p[(size_t)i << qcount.shift];
   part[t] = s;
   __syncthreads();
   for (int o = 1; o < 1024; o <<= 1) {
@@ -1831,7 +1831,7 @@ __global__ __launch_bounds__(1024) void k_scan_offsets(const unsigned int* qcoun
   int64_t run = part[t] - s;
   for (int i = lo; i < hi; ++i) {
     offs[i] = run;
-    run += qcount[i];
+    run += qcount.p[(size_t)i << qcount.shift];
   }
   if (t == 1023) {
     offs[nq] = part[1023];
@@ -2107,13 +2107,13 @@ hipError_t launch_leaf(const LeafArgs& a, int grid, hipStream_t s) {
 hipError_t launch_recheck(Hit* hits, const uint32_t* band_idx, const unsigned long long* nband,
                           unsigned long long cap, const float* qf, const float* leaves, int d,
                           int dp, const double* ff, const double* rho,
-                          unsigned int* qcount, DevCounters* ctr, hipStream_t s) {
+                          QCount qcount, DevCounters* ctr, hipStream_t s) {
   hipLaunchKernelGGL(k_recheck, dim3(64), dim3(256), 0, s, hits, band_idx, nband, cap, qf, leaves, d,
                      dp, ff, rho, qcount, ctr);
   return hipGetLastError();
 }
 
-hipError_t launch_scan_offsets(const unsigned int* qcount, int nq, int64_t* offs,
+hipError_t launch_scan_offsets(QCount qcount, int nq, int64_t* offs,
                                const unsigned long long* stat, DevCounters* ctr, hipStream_t s) {
   hipLaunchKernelGGL(k_scan_offsets, dim3(1), dim3(1024), 0, s, qcount, nq, offs, stat, ctr);
   return hipGetLastError();
