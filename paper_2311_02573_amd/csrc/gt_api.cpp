@@ -342,6 +342,8 @@ void free_tree(Index* ix) {
   dfree(ix, &ix->d_ing, 1);
   if (ix->h_ing) (void)hipHostFree(ix->h_ing);
   ix->h_ing = nullptr;
+  if (ix->h_na) (void)hipHostFree(ix->h_na);
+  ix->h_na = nullptr;
 }
 
 gt_status batch_init(Batch* b) {
@@ -716,44 +718,57 @@ gt_status enqueue_pair_check(Index* ix, Batch* b) {
   return GT_OK;
 }
 
-// Placement of the accepted pairs by query and the per-query sort by id.
-// lim: largest result count the outputs can take; the kernels check the
+// Offsets, placement of the accepted pairs by query and the per-query sort by
+// id.  lim: largest result count the outputs can take; the kernels check the
 // count on the device and do nothing when it is larger.
-gt_status enqueue_place(Batch* b, int64_t lim, int64_t* ids, float* sims) {
+// again: the placement alone, after the host has read the counters.
+gt_status enqueue_place(Batch* b, int64_t lim, int64_t* ids, float* sims, bool again) {
   hipStream_t s = b->stream;
-  const unsigned long long hc = (unsigned long long)b->hit_cap, l = (unsigned long long)lim;
-  HIPCHK(gt::launch_scatter(b->hits, b->ctr, hc, l, b->offs, b->out_id, b->out_sim, s));
+  gt::PlaceArgs a{};
+  a.hits = b->hits;
+  a.hit_cap = (unsigned long long)b->hit_cap;
+  a.lim = (unsigned long long)lim;
+  a.qcount = qcount_of(b);
+  a.nq = b->nq;
+  a.offs = b->offs;
+  a.offs_out = again ? nullptr : b->tgt_offs;
+  a.out_id = b->out_id;
+  a.out_sim = b->out_sim;
+  a.stat = gt::stat_levels(b->lvl_count);
+  a.ctr = b->ctr;
+  a.host_ctr = again ? nullptr : b->h_ctr;
+  HIPCHK(gt::launch_place(a, s));
   HIPCHK(gt::launch_sort_segments(b->offs, b->nq, b->out_id, b->out_sim, b->tmp_id, b->tmp_sim,
-                                  ids, sims, b->ctr, hc, l, b->n_epoch, s));
+                                  ids, sims, b->ctr, a.hit_cap, a.lim, b->n_epoch, s));
   return GT_OK;
 }
 
 // recheck, offsets, placement and sort of the results (before the host has
-// seen their count, so that a call needs one wait), and the copy of the
-// counters the host needs
+// seen their count, so that a call needs one wait); the counters the host
+// needs are stored in its pinned copy on the way
 gt_status enqueue_tail(Index* ix, Batch* b) {
   hipStream_t s = b->stream;
+  const bool walked = b->kind == 1 && b->nq > 0 && b->n_epoch > 0;
+  const int first = b->dense_last >= 0 ? b->dense_last : b->head;
   HIPCHK(gt::launch_recheck(b->hits, b->band_idx, &b->ctr->nband, (unsigned long long)b->hit_cap,
                             b->qf, ix->leaves, ix->d, ix->dp, ix->ff, b->rho, qcount_of(b),
-                            b->ctr, s));
+                            b->lvl_count, first, walked ? ix->depth : 0, b->ctr, s));
   ev_mark(b, 4);
-  HIPCHK(gt::launch_scan_offsets(qcount_of(b), b->nq, b->offs,
-                                     gt::stat_levels(b->lvl_count), b->ctr, s));
   TRY(ensure_out(b, 1));
   b->spec_direct = b->tgt_ids != nullptr;
   // (a fixed batch has no staging of its own for the sorted results: without
   // caller buffers nothing is placed)
   b->spec_lim = b->spec_direct ? std::min(b->out_cap, b->tgt_max) : b->fixed ? 0 : b->out_cap;
   TRY(enqueue_place(b, b->spec_lim, b->spec_direct ? b->tgt_ids : b->fin_id,
-                    b->spec_direct ? b->tgt_sims : b->fin_sim));
-  HIPCHK(hipMemcpyAsync(b->h_ctr, b->ctr, sizeof(gt::DevCounters), hipMemcpyDeviceToHost, s));
+                    b->spec_direct ? b->tgt_sims : b->fin_sim, false));
   if (b->done) HIPCHK(hipEventRecord(b->done, s));
   ev_mark(b, 5);
   return GT_OK;
 }
 
 // candidate stage again after the candidate buffers grew
-void set_targets(Batch* b, int64_t max_results, int64_t* ids, float* sims) {
+void set_targets(Batch* b, int64_t max_results, int64_t* offs, int64_t* ids, float* sims) {
+  b->tgt_offs = offs;
   b->tgt_ids = max_results > 0 ? ids : nullptr;
   b->tgt_sims = max_results > 0 ? sims : nullptr;
   b->tgt_max = max_results;
@@ -1033,14 +1048,33 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
     b->events = true;
   }
   ev_mark(b, 0);
-  TRY(zero_dev(b->ctr, sizeof(gt::DevCounters), s));
-  TRY(zero_dev(b->tile_mask, (size_t)gt::kMaxTiles * 8, s));
-  if (kind == 1) {
-    TRY(zero_dev(b->lvl_count, (size_t)GT_MAX_LEVELS * gt::kMaxSlots * 4, s));
-    if (qcount_of(b).p == b->qcount) TRY(zero_qcount(b, s));
-  } else {
-    TRY(zero_qcount(b, s));
-    TRY(zero_dev(gt::stat_levels(b->lvl_count), gt::kStatWords * 8, s));
+  {
+    gt::CallBegin g{};
+    // a walk's level counters with the counters behind them, or only those
+    const size_t row0 = kind == 1 ? 0 : gt::kQCountRow;
+    const gt::QCount qc = qcount_of(b);
+    g.p[0] = reinterpret_cast<uint4*>(b->ctr);
+    g.n16[0] = sizeof(gt::DevCounters) / 16;
+    g.p[1] = reinterpret_cast<uint4*>(b->tile_mask);
+    g.n16[1] = (int64_t)gt::kMaxTiles * 8 / 16;
+    g.p[2] = reinterpret_cast<uint4*>(b->lvl_count + row0 * gt::kMaxSlots);
+    g.n16[2] = (int64_t)(GT_MAX_LEVELS - row0) * gt::kMaxSlots * 4 / 16;
+    g.p[3] = reinterpret_cast<uint4*>(qc.p);
+    g.n16[3] = qc.p == b->qcount ? (int64_t)nq_pad * 4 / 16 : 0;
+    g.rho = b->rho;
+    g.nq = nq;
+    const double* arg = nullptr;
+    if (b->h_rho) {
+      if (nq > 0) memcpy(b->h_rho, rho, (size_t)nq * 8);
+      g.rho_host = b->h_rho;
+    } else if (nq <= gt::kRhoArg) {
+      arg = rho;
+    } else {
+      HIPCHK(hipMemcpyAsync(b->rho, rho, (size_t)nq * 8, hipMemcpyHostToDevice, s));
+      g.nq = 0;
+    }
+    if (nq == 0) arg = nullptr;
+    HIPCHK(gt::launch_call_begin(g, arg, s));
   }
   if (b->counted) {
     const int64_t words = (int64_t(2) << ix->depth) / 32 + 1;
@@ -1051,12 +1085,6 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
     TRY(zero_dev(b->bitmap, (size_t)words * 4, s));
   }
   if (nq > 0) {
-    if (b->h_rho) {
-      memcpy(b->h_rho, rho, (size_t)nq * 8);
-      HIPCHK(hipMemcpyAsync(b->rho, b->h_rho, (size_t)nq * 8, hipMemcpyHostToDevice, s));
-    } else {
-      HIPCHK(hipMemcpyAsync(b->rho, rho, (size_t)nq * 8, hipMemcpyHostToDevice, s));
-    }
     // reduced query copies only for the call's pool format; the absolute
     // terms of the subtraction step only for bfloat16 sum pools
     const bool w16 = kind == 1 && fmt == GT_POOL_BF16, w8 = kind == 1 && fmt == GT_POOL_FP8E4M3;
@@ -1074,10 +1102,6 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
       TRY(enqueue_walk(ix, b));
       ev_mark(b, 2);
       TRY(enqueue_leaf(ix, b));
-      // entries of every walked level (the automatic dense level and the
-      // memory estimates of a server read them)
-      HIPCHK(gt::launch_level_entries(b->lvl_count, b->dense_last >= 0 ? b->dense_last : b->head,
-                                      ix->depth, b->ctr, s));
     } else {
       TRY(enqueue_exhaustive(ix, b));
       ev_mark(b, 2);
@@ -1163,7 +1187,8 @@ gt_status finish(Index* ix, Batch* b, int64_t max_results, int64_t* offsets, int
   }
   const int64_t total = (int64_t)b->h_ctr->total;
   *total_out = total;
-  HIPCHK(hipMemcpyAsync(offsets, b->offs, (size_t)(b->nq + 1) * 8, hipMemcpyDeviceToDevice, s));
+  if (offsets != b->tgt_offs)
+    HIPCHK(hipMemcpyAsync(offsets, b->offs, (size_t)(b->nq + 1) * 8, hipMemcpyDeviceToDevice, s));
   if (total > max_results) {
     b->pending = keep_on_overflow;
     return fail(GT_ERR_RESULT_OVERFLOW, "need max_results >= " + std::to_string(total));
@@ -1172,7 +1197,7 @@ gt_status finish(Index* ix, Batch* b, int64_t max_results, int64_t* offsets, int
     if (total > b->spec_lim) {
       // the enqueued placement did nothing: buffers were too small
       TRY(ensure_out(b, total));
-      TRY(enqueue_place(b, total, ids, sims));
+      TRY(enqueue_place(b, total, ids, sims, true));
     } else if (!(b->spec_direct && ids == b->tgt_ids && sims == b->tgt_sims)) {
       HIPCHK(hipMemcpyAsync(ids, b->fin_id, (size_t)total * 8, hipMemcpyDeviceToDevice, s));
       HIPCHK(hipMemcpyAsync(sims, b->fin_sim, (size_t)total * 4, hipMemcpyDeviceToDevice, s));
@@ -1226,7 +1251,7 @@ gt_status continue_by_tiles(Index* ix, Batch* b, int64_t max_results, int64_t* o
     b->hits_overflowed = false;
     st = carve_budget(ix, b, b->ext_mem, b->ext_bytes, n, b->user_fmt, -1, false);
     if (st == GT_OK) {
-      set_targets(b, room, ids_t, sims_t);
+      set_targets(b, room, offsets + a, ids_t, sims_t);
       st = submit(ix, b, 1, b->q_in + (size_t)a * ix->d, n, rho.data() + a, b->user_fmt, s);
     }
     if (st == GT_OK) st = finish(ix, b, room, offsets + a, ids_t, sims_t, &tot_t, false);
@@ -1371,6 +1396,7 @@ gt_status gt_build_tree(const void* feats_dev, int64_t n, int32_t d, gt_dtype dt
   BTRY(dalloc(ix, &ix->d_levelmax, GT_MAX_LEVELS));
   BTRY(dalloc(ix, &ix->d_ing, 1));
   BHIP(hipHostMalloc((void**)&ix->h_ing, sizeof(gt::IngestOut), hipHostMallocDefault));
+  BHIP(hipHostMalloc((void**)&ix->h_na, sizeof(gt::DevCounters), hipHostMallocDefault));
   // what holds no row is zero: the leaves past n and, per level, the pools
   // past the last one that covers a row
   const size_t un = cap - (size_t)n;
@@ -1495,7 +1521,7 @@ gt_status gt_query_batch(gt_index* ix, const float* q_dev, int32_t nq, const dou
   if (!offsets_dev) return fail(GT_ERR_INVALID_ARG, "offsets is NULL");
   if (max_results < 0) return fail(GT_ERR_INVALID_ARG, "max_results < 0");
   if (max_results > 0 && (!ids_dev || !sims_dev)) return fail(GT_ERR_INVALID_ARG, "NULL output buffer");
-  set_targets(ix->def, max_results, ids_dev, sims_dev);
+  set_targets(ix->def, max_results, offsets_dev, ids_dev, sims_dev);
   TRY(submit(ix, ix->def, 1, q_dev, nq, rho_host, (int)fmt, (hipStream_t)stream));
   return finish(ix, ix->def, max_results, offsets_dev, ids_dev, sims_dev, total_out, false);
 }
@@ -1509,7 +1535,7 @@ gt_status gt_exhaustive(gt_index* ix, const float* q_dev, int32_t nq, const doub
   if (!offsets_dev) return fail(GT_ERR_INVALID_ARG, "offsets is NULL");
   if (max_results < 0) return fail(GT_ERR_INVALID_ARG, "max_results < 0");
   if (max_results > 0 && (!ids_dev || !sims_dev)) return fail(GT_ERR_INVALID_ARG, "NULL output buffer");
-  set_targets(ix->def, max_results, ids_dev, sims_dev);
+  set_targets(ix->def, max_results, offsets_dev, ids_dev, sims_dev);
   TRY(submit(ix, ix->def, 2, q_dev, nq, rho_host, 0, (hipStream_t)stream));
   return finish(ix, ix->def, max_results, offsets_dev, ids_dev, sims_dev, total_out, false);
 }
@@ -1533,12 +1559,11 @@ gt_status gt_query_batch_noalloc(gt_index* ix, const float* q_dev, int32_t nq,
                                    hipGetErrorString(ix->scratch_err));
   if (nq < 0) return fail(GT_ERR_INVALID_ARG, "nq < 0");
   // buffers carved from the device's scratch; the host copy of the counters
-  // lives on this stack frame (pageable)
+  // is the index's (pinned)
   Batch fb;
-  gt::DevCounters host_ctr;
   TRY(carve_fixed(ix, &fb, base, gt::kScratchBytes, nq, (int)fmt));
-  fb.h_ctr = &host_ctr;
-  set_targets(&fb, max_results, ids_dev, sims_dev);
+  fb.h_ctr = ix->h_na;
+  set_targets(&fb, max_results, offsets_dev, ids_dev, sims_dev);
   TRY(submit(ix, &fb, 1, q_dev, nq, rho_host, (int)fmt, (hipStream_t)stream));
   const gt_status st = finish(ix, &fb, max_results, offsets_dev, ids_dev, sims_dev, total_out, false);
   // the copies out of the scratch are done before the next call may reuse it
@@ -1656,7 +1681,7 @@ gt_status gt_batch_submit_external(gt_batch* b, const float* q_dev, int32_t nq,
   b->continued_tiles = 0;
   b->ext_epoch = ix->n;
   TRY(carve_budget(ix, b, mem_dev, (size_t)mem_bytes, nq, (int)fmt, b->ext_pairs, true));
-  set_targets(b, 0, nullptr, nullptr);
+  set_targets(b, 0, nullptr, nullptr, nullptr);
   return submit(ix, b, 1, q_dev, nq, b->rho_in.data(), (int)fmt, (hipStream_t)stream);
 }
 
@@ -1675,7 +1700,7 @@ gt_status gt_batch_submit(gt_batch* b, const float* q_dev, int32_t nq, const dou
   g_err.clear();
   if (!b) return fail(GT_ERR_INVALID_ARG, "batch is NULL");
   if (b->external) return fail(GT_ERR_INVALID_ARG, "an external workspace takes gt_batch_submit_external");
-  if (!b->pending) set_targets(b, 0, nullptr, nullptr);
+  if (!b->pending) set_targets(b, 0, nullptr, nullptr, nullptr);
   return submit(b->ix, b, 1, q_dev, nq, rho_host, (int)fmt, (hipStream_t)stream);
 }
 

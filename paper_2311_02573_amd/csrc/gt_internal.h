@@ -235,6 +235,35 @@ struct LeafArgs {
   int64_t bit_base;         // tree row of leaf 0
 };
 
+// Start of a call: ranges to clear (16-byte pieces) and its thresholds.
+constexpr int kRhoArg = 256;
+struct CallBegin {
+  uint4* p[4];
+  int64_t n16[4];
+  double* rho;
+  const double* rho_host;
+  int nq;
+};
+struct RhoArg {
+  double v[kRhoArg];
+};
+
+// Results of a call, from its candidates to the caller's arrays.
+struct PlaceArgs {
+  const Hit* hits;
+  unsigned long long hit_cap;
+  unsigned long long lim;    // largest result count the outputs can take
+  QCount qcount;
+  int nq;
+  int64_t* offs;             // the workspace's offsets
+  int64_t* offs_out;         // the caller's offsets, or NULL
+  uint32_t* out_id;          // results by query, unsorted
+  float* out_sim;
+  const unsigned long long* stat;  // striped statistics to sum
+  DevCounters* ctr;
+  DevCounters* host_ctr;     // pinned copy of the counters, or NULL
+};
+
 struct Index;
 
 // Device workspace of one query call (query copies, frontiers, counters,
@@ -315,6 +344,7 @@ struct Batch {
   // Placement and sort are enqueued with the call, before the host has seen
   // the result count: into the caller's buffers (tgt_*) when the call passed
   // them, else into fin_*.  They do nothing unless the count fits spec_lim.
+  int64_t* tgt_offs = nullptr;
   int64_t* tgt_ids = nullptr;
   float* tgt_sims = nullptr;
   int64_t tgt_max = 0;
@@ -326,7 +356,7 @@ struct Batch {
   int64_t bitmap_words = 0;
   bool counted = false;
   DevCounters* ctr = nullptr;
-  DevCounters* h_ctr = nullptr;  // pinned
+  DevCounters* h_ctr = nullptr;  // pinned; written by the call's last kernels
   double* h_rho = nullptr;       // pinned staging for thresholds
   hipEvent_t done = nullptr;     // counters copied to h_ctr
   hipEvent_t ev[8] = {};
@@ -391,6 +421,7 @@ struct Index {
   float* d_levelmax = nullptr;
   IngestOut* d_ing = nullptr;       // the last ingest's report, and its pinned host copy
   IngestOut* h_ing = nullptr;
+  DevCounters* h_na = nullptr;      // pinned counters of the allocation-free calls
 
   Batch* def = nullptr;      // workspace of gt_query_batch / gt_exhaustive
   hipError_t scratch_err = hipSuccess;  // set-up of the device scratch at build
@@ -407,8 +438,9 @@ hipError_t launch_signed_bottom(const float* leaves, float* parent, int64_t firs
                                 const IngestOut* gate, hipStream_t s);
 hipError_t launch_tree_update(const TreeArgs& a, bool max_pool, int child, hipStream_t s);
 hipError_t launch_zero_tails(void* tree, int row_bytes, int depth, int64_t n, hipStream_t s);
-hipError_t launch_level_entries(const uint32_t* lvl_count, int first, int levels,
-                                DevCounters* ctr, hipStream_t s);
+// rho: thresholds on the host (at most kRhoArg, passed as arguments), or NULL:
+// a.rho_host, pinned, is read by the device
+hipError_t launch_call_begin(const CallBegin& a, const double* rho, hipStream_t s);
 hipError_t launch_level_max(const float* rows, int64_t nrows, int dp, float* out_max, hipStream_t s);
 hipError_t launch_fp8_exps(const float* level_max, int depth, int* lexp, hipStream_t s);
 // float8 copies of levels first .. last (rows past the last populated pool: zero)
@@ -425,15 +457,15 @@ hipError_t launch_walk_sub(const WalkLevelArgs& a, int grid, hipStream_t s);
 hipError_t launch_walk_subtree(int fmt, const SubtreeArgs& a, hipStream_t s);
 hipError_t launch_leaf(const LeafArgs& a, int grid, hipStream_t s);
 hipError_t launch_dense_level(int fmt, const DenseLevelArgs& a, hipStream_t s);
+// Float64 recheck of the band candidates, and the frontier entries of levels
+// first .. levels - 1 (none where first >= levels).
 hipError_t launch_recheck(Hit* hits, const uint32_t* band_idx, const unsigned long long* nband,
                           unsigned long long cap, const float* qf, const float* leaves, int d,
-                          int dp, const double* ff, const double* rho,
-                          QCount qcount, DevCounters* ctr, hipStream_t s);
-hipError_t launch_scan_offsets(QCount qcount, int nq, int64_t* offs,
-                               const unsigned long long* stat, DevCounters* ctr, hipStream_t s);
-hipError_t launch_scatter(const Hit* hits, const DevCounters* ctr, unsigned long long hit_cap,
-                          unsigned long long lim, const int64_t* offs, uint32_t* out_id,
-                          float* out_sim, hipStream_t s);
+                          int dp, const double* ff, const double* rho, QCount qcount,
+                          const uint32_t* lvl_count, int first, int levels, DevCounters* ctr,
+                          hipStream_t s);
+// Offsets, statistics, and every accepted pair to its query's segment.
+hipError_t launch_place(const PlaceArgs& a, hipStream_t s);
 hipError_t launch_sort_segments(const int64_t* offs, int nq, uint32_t* id, float* sim,
                                 uint32_t* tmp_id, float* tmp_sim, int64_t* ids_out,
                                 float* sims_out, const DevCounters* ctr,

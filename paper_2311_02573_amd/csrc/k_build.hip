@@ -24,6 +24,22 @@ __global__ void k_zero_u32(uint32_t* p, int64_t n) {
     p[i] = 0u;
 }
 
+// Start of a query call in one launch: clears its counters and moves the
+// thresholds to the device, from pinned host memory or (KARG) from the kernel
+// arguments.  As four clearing launches and a copy this was 11 us of the
+// device and most of the calls' launch gaps.
+template <bool KARG>
+__global__ __launch_bounds__(256) void k_call_begin(CallBegin a, RhoArg r) {
+  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  for (int k = 0; k < 4; ++k)
+    for (int64_t i = i0; i < a.n16[k]; i += step) a.p[k][i] = make_uint4(0u, 0u, 0u, 0u);
+  if constexpr (KARG) {
+    if (blockIdx.x == 0 && (int)threadIdx.x < a.nq) a.rho[threadIdx.x] = r.v[threadIdx.x];
+  } else {
+    for (int64_t i = i0; i < a.nq; i += step) a.rho[i] = a.rho_host[i];
+  }
+}
+
 __device__ __forceinline__ float load_feature(const void* src, int dtype, int64_t idx) {
   if (dtype == GT_F16) return __half2float(reinterpret_cast<const __half*>(src)[idx]);
   if (dtype == GT_BF16)
@@ -391,28 +407,6 @@ __global__ void k_signed_bottom(const float* __restrict__ leaves, float* __restr
   }
 }
 
-// Frontier entries per level of a call: the sum of the level's per-slot
-// counters (one workgroup per level, levels first .. levels-1; 16-byte loads).
-__global__ __launch_bounds__(1024) void k_level_entries(const uint32_t* __restrict__ counts,
-                                                        int first, DevCounters* ctr) {
-  __shared__ unsigned long long part[16];
-  const int l = first + blockIdx.x, t = threadIdx.x;
-  const uint4* c4 = reinterpret_cast<const uint4*>(counts + (size_t)l * kMaxSlots);
-  unsigned long long sum = 0;
-  for (int k = t; k < kMaxSlots / 4; k += blockDim.x) {
-    const uint4 v = c4[k];
-    sum += (unsigned long long)v.x + v.y + v.z + v.w;
-  }
-  for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
-  if ((t & 63) == 0) part[t >> 6] = sum;
-  __syncthreads();
-  if (t == 0) {
-    unsigned long long tot = 0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) tot += part[w];
-    ctr->entries[l] = tot;
-  }
-}
-
 // Largest value of a level (a float8 level that an insert outgrew).
 __global__ __launch_bounds__(256) void k_level_max(const float4* __restrict__ rows, int64_t count4,
                                                    float* out) {
@@ -610,6 +604,20 @@ hipError_t launch_zero_u32(uint32_t* p, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
+hipError_t launch_call_begin(const CallBegin& a, const double* rho, hipStream_t s) {
+  RhoArg r;
+  for (int k = 0; k < 4; ++k)
+    if (reinterpret_cast<uintptr_t>(a.p[k]) % 16) return hipErrorInvalidValue;
+  if (rho) {
+    if (a.nq > kRhoArg) return hipErrorInvalidValue;
+    for (int i = 0; i < a.nq; ++i) r.v[i] = rho[i];
+    hipLaunchKernelGGL(k_call_begin<true>, dim3(256), dim3(256), 0, s, a, r);
+  } else {
+    hipLaunchKernelGGL(k_call_begin<false>, dim3(256), dim3(256), 0, s, a, r);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_ingest_reset(IngestOut* o, hipStream_t s) {
   hipLaunchKernelGGL(k_ingest_reset, dim3(1), dim3(64), 0, s, o);
   return hipGetLastError();
@@ -686,15 +694,6 @@ hipError_t launch_zero_tails(void* tree, int row_bytes, int depth, int64_t n, hi
   const unsigned gx = (unsigned)std::min<int64_t>(4096, std::max<int64_t>(1, (most + 1023) / 1024));
   hipLaunchKernelGGL(k_zero_tails, dim3(gx, (unsigned)depth), dim3(256), 0, s,
                      static_cast<uint4*>(tree), row_bytes / 16, depth, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_level_entries(const uint32_t* lvl_count, int first, int levels,
-                                DevCounters* ctr, hipStream_t s) {
-  if (first < 0 || levels > GT_MAX_LEVELS) return hipErrorInvalidValue;
-  if (first >= levels) return hipSuccess;
-  hipLaunchKernelGGL(k_level_entries, dim3(levels - first), dim3(1024), 0, s, lvl_count, first,
-                     ctr);
   return hipGetLastError();
 }
 

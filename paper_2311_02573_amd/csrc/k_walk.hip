@@ -1744,18 +1744,44 @@ __global__ __launch_bounds__(256) void k_leaf(LeafArgs a) {
 // norm run sequentially over k, lane by lane (lane l holds elements
 // [16 l, 16 l + 16) of each 1024-chunk, so lane order is k order), one wave
 // per candidate; the rows' squared norms are the canonical ones of ingest.
+// Workgroups from kRecheckGroups on sum the frontier entries of one level
+// each over its slots' counters (the automatic dense level and a server's
+// memory estimates read them).
+constexpr int kRecheckGroups = 64;
+__device__ __forceinline__ void level_entries(const uint32_t* __restrict__ counts, int l,
+                                              DevCounters* ctr) {
+  __shared__ unsigned long long part[4];
+  const int t = threadIdx.x;
+  const uint4* c4 = reinterpret_cast<const uint4*>(counts + (size_t)l * kMaxSlots);
+  unsigned long long sum = 0;
+#pragma unroll
+  for (int k = 0; k < kMaxSlots / 4 / 256; ++k) {
+    const uint4 v = c4[t + 256 * k];
+    sum += (unsigned long long)v.x + v.y + v.z + v.w;
+  }
+  for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if ((t & 63) == 0) part[t >> 6] = sum;
+  __syncthreads();
+  if (t == 0) ctr->entries[l] = part[0] + part[1] + part[2] + part[3];
+}
+
 __global__ __launch_bounds__(256) void k_recheck(Hit* hits, const uint32_t* band_idx,
                                                  const unsigned long long* nband,
                                                  unsigned long long cap,
                                                  const float* __restrict__ qf,
                                                  const float* __restrict__ leaves, int d, int dp,
                                                  const double* __restrict__ ff,
-                                                 const double* __restrict__ rho,
-                                                 QCount qcount, DevCounters* ctr) {
+                                                 const double* __restrict__ rho, QCount qcount,
+                                                 const uint32_t* lvl_count, int first,
+                                                 DevCounters* ctr) {
+  if (blockIdx.x >= kRecheckGroups) {
+    level_entries(lvl_count, first + (int)blockIdx.x - kRecheckGroups, ctr);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const unsigned long long n = *nband < cap ? *nband : cap;
   const unsigned long long nw = blockDim.x >> 6;
-  for (unsigned long long b = blockIdx.x * nw + (threadIdx.x >> 6); b < n; b += gridDim.x * nw) {
+  for (unsigned long long b = blockIdx.x * nw + (threadIdx.x >> 6); b < n; b += kRecheckGroups * nw) {
     const uint32_t hi = band_idx[b];
     Hit x = hits[hi];
     const float* q = qf + (size_t)x.q * dp;
@@ -1799,67 +1825,117 @@ __global__ __launch_bounds__(256) void k_recheck(Hit* hits, const uint32_t* band
   }
 }
 
-// Exclusive scan of per-query counts -> offsets (one workgroup of 1024), and
-// the sums of the striped statistics counters.
-__global__ __launch_bounds__(1024) void k_scan_offsets(QCount qcount, int nq,
-                                                       int64_t* offs,
-                                                       const unsigned long long* stat,
-                                                       DevCounters* ctr) {
-  __shared__ int64_t part[1024];
+// True where every candidate was kept and the results fit the output; the
+// placement and the sort are enqueued before the host has seen the counts and
+// do nothing otherwise.
+__device__ __forceinline__ bool results_fit(const DevCounters* ctr, unsigned long long total,
+                                            unsigned long long hit_cap, unsigned long long lim) {
+  return ctr->nhits <= hit_cap && total <= lim && ctr->slot_over == 0u && ctr->err == 0u;
+}
+
+// Exclusive scan of the per-query counts by a workgroup of 1024: thread t gets
+// the offset of its first query (per consecutive queries each); returns the
+// total.
+__device__ __forceinline__ int64_t scan_counts(QCount qcount, int nq, int per, int64_t& first) {
+  __shared__ int64_t wsum[16];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int lo = min(nq, t * per), hi = min(nq, lo + per);
+  int64_t s = 0;
+  for (int i = lo; i < hi; ++i) s += qcount.p[(size_t)i << qcount.shift];
+  int64_t incl = s;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int64_t v = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += v;
+  }
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  int64_t before = 0, total = 0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    if (k < w) before += wsum[k];
+    total += wsum[k];
+  }
+  first = before + incl - s;
+  return total;
+}
+
+// Offsets and statistics of a call (one workgroup of 1024), and the host's copy
+// of the counters: a store to pinned memory instead of a copy of its own.
+// Offsets go to the caller's array too unless the call has to be repeated or
+// refused.
+__device__ __forceinline__ void write_call(const PlaceArgs& a, int per, int64_t first,
+                                           int64_t total) {
   const int t = threadIdx.x;
+  const DevCounters* c = a.ctr;
+  int64_t* out = c->nhits <= a.hit_cap && c->slot_over == 0u && c->err == 0u && c->fr_over == 0u
+                     ? a.offs_out : nullptr;
+  int64_t run = first;
+  for (int i = min(a.nq, t * per); i < min(a.nq, t * per + per); ++i) {
+    a.offs[i] = run;
+    if (out) out[i] = run;
+    run += a.qcount.p[(size_t)i << a.qcount.shift];
+  }
   if (t <= GT_MAX_LEVELS) {  // thread l: tests of level l; the last: leaf tests
     const unsigned long long* p =
-        t < GT_MAX_LEVELS ? stat + t : stat + (size_t)kStatStripes * GT_MAX_LEVELS;
+        t < GT_MAX_LEVELS ? a.stat + t : a.stat + (size_t)kStatStripes * GT_MAX_LEVELS;
     const int stride = t < GT_MAX_LEVELS ? GT_MAX_LEVELS : kLeafStride;
     unsigned long long sum = 0;
 #pragma unroll 16
     for (int k = 0; k < kStatStripes; ++k) sum += p[(size_t)k * stride];
-    if (t < GT_MAX_LEVELS) ctr->pairs[t] = sum; else ctr->leaf_pairs = sum;
-  }
-  const int per = (nq + 1023) / 1024;
-  const int lo = t * per, hi = min(nq, lo + per);
-  int64_t s = 0;
-  for (int i = lo; i < hi; ++i) s += qcount.p[(size_t)i << qcount.shift];
-  part[t] = s;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    int64_t v = t >= o ? part[t - o] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  int64_t run = part[t] - s;
-  for (int i = lo; i < hi; ++i) {
-    offs[i] = run;
-    run += qcount.p[(size_t)i << qcount.shift];
+    if (t < GT_MAX_LEVELS) a.ctr->pairs[t] = sum; else a.ctr->leaf_pairs = sum;
   }
   if (t == 1023) {
-    offs[nq] = part[1023];
-    ctr->total = (unsigned long long)part[1023];
+    a.offs[a.nq] = total;
+    if (out) out[a.nq] = total;
+    a.ctr->total = (unsigned long long)total;
+  }
+  __syncthreads();
+  if (a.host_ctr) {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(a.ctr);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(a.host_ctr);
+    for (int i = t; i < (int)(sizeof(DevCounters) / 4); i += 1024) dst[i] = src[i];
   }
 }
 
 // Accepted pairs to their query's segment: slot = offset of the query + the
-// pair's slot among the query's results.  Enqueued before the host has seen
-// the counts; does nothing unless every candidate was kept (hit_cap) and the
-// results fit the output (lim).
-__device__ __forceinline__ bool results_fit(const DevCounters* ctr, unsigned long long hit_cap,
-                                            unsigned long long lim) {
-  return ctr->nhits <= hit_cap && ctr->total <= lim && ctr->slot_over == 0u && ctr->err == 0u;
+// pair's slot among the query's results.  Up to kPlaceQueries queries every
+// workgroup scans the counts for itself (the offsets in LDS; the first one
+// writes them out), which saves a launch; above, k_scan_offsets ran before.
+constexpr int kPlaceQueries = 4096;
+__global__ __launch_bounds__(1024) void k_scan_offsets(PlaceArgs a) {
+  const int per = (a.nq + 1023) / 1024;
+  int64_t first;
+  const int64_t total = scan_counts(a.qcount, a.nq, per, first);
+  write_call(a, per, first, total);
 }
 
-__global__ void k_scatter(const Hit* hits, const DevCounters* ctr, unsigned long long hit_cap,
-                          unsigned long long lim, const int64_t* offs, uint32_t* out_id,
-                          float* out_sim) {
-  if (!results_fit(ctr, hit_cap, lim)) return;
-  const unsigned long long n = ctr->nhits;
-  for (unsigned long long h = blockIdx.x * (unsigned long long)blockDim.x + threadIdx.x; h < n;
-       h += (unsigned long long)gridDim.x * blockDim.x) {
-    const Hit x = hits[h];
+template <bool SCAN>
+__global__ __launch_bounds__(1024) void k_place(PlaceArgs a) {
+  __shared__ int64_t loffs[SCAN ? kPlaceQueries : 1];
+  int64_t total;
+  if constexpr (SCAN) {
+    const int per = (a.nq + 1023) / 1024, t = threadIdx.x;
+    int64_t first;
+    total = scan_counts(a.qcount, a.nq, per, first);
+    int64_t run = first;
+    for (int i = min(a.nq, t * per); i < min(a.nq, t * per + per); ++i) {
+      loffs[i] = run;
+      run += a.qcount.p[(size_t)i << a.qcount.shift];
+    }
+    if (blockIdx.x == 0) write_call(a, per, first, total);
+    __syncthreads();
+  } else {
+    total = (int64_t)a.ctr->total;
+  }
+  if (!results_fit(a.ctr, (unsigned long long)total, a.hit_cap, a.lim)) return;
+  const unsigned long long n = a.ctr->nhits;
+  for (unsigned long long h = blockIdx.x * 1024ull + threadIdx.x; h < n; h += gridDim.x * 1024ull) {
+    const Hit x = a.hits[h];
     if (hit_kind(x.flag) != HIT_ACCEPT) continue;
-    const int64_t pos = offs[x.q] + (int64_t)hit_slot(x.flag);
-    out_id[pos] = x.id;
-    out_sim[pos] = x.sim;
+    const int64_t pos = (SCAN ? loffs[x.q] : a.offs[x.q]) + (int64_t)hit_slot(x.flag);
+    a.out_id[pos] = x.id;
+    a.out_sim[pos] = x.sim;
   }
 }
 
@@ -1880,7 +1956,7 @@ __global__ __launch_bounds__(256) void k_sort_segments(const int64_t* offs, uint
   __shared__ float val[4096];
   __shared__ uint32_t hist[16 * 256];
   __shared__ uint32_t tot[257];
-  if (!results_fit(ctr, hit_cap, lim)) return;
+  if (!results_fit(ctr, ctr->total, hit_cap, lim)) return;
   const int q = blockIdx.x, t = threadIdx.x;
   const int64_t lo = offs[q], n = offs[q + 1] - lo;
   if (n <= 0) return;
@@ -2106,24 +2182,24 @@ hipError_t launch_leaf(const LeafArgs& a, int grid, hipStream_t s) {
 
 hipError_t launch_recheck(Hit* hits, const uint32_t* band_idx, const unsigned long long* nband,
                           unsigned long long cap, const float* qf, const float* leaves, int d,
-                          int dp, const double* ff, const double* rho,
-                          QCount qcount, DevCounters* ctr, hipStream_t s) {
-  hipLaunchKernelGGL(k_recheck, dim3(64), dim3(256), 0, s, hits, band_idx, nband, cap, qf, leaves, d,
-                     dp, ff, rho, qcount, ctr);
+                          int dp, const double* ff, const double* rho, QCount qcount,
+                          const uint32_t* lvl_count, int first, int levels, DevCounters* ctr,
+                          hipStream_t s) {
+  if (first < 0 || levels > GT_MAX_LEVELS) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_recheck, dim3(kRecheckGroups + (levels > first ? levels - first : 0)),
+                     dim3(256), 0, s, hits, band_idx, nband, cap, qf, leaves, d, dp, ff, rho,
+                     qcount, lvl_count, first, ctr);
   return hipGetLastError();
 }
 
-hipError_t launch_scan_offsets(QCount qcount, int nq, int64_t* offs,
-                               const unsigned long long* stat, DevCounters* ctr, hipStream_t s) {
-  hipLaunchKernelGGL(k_scan_offsets, dim3(1), dim3(1024), 0, s, qcount, nq, offs, stat, ctr);
-  return hipGetLastError();
-}
-
-hipError_t launch_scatter(const Hit* hits, const DevCounters* ctr, unsigned long long hit_cap,
-                          unsigned long long lim, const int64_t* offs, uint32_t* out_id,
-                          float* out_sim, hipStream_t s) {
-  hipLaunchKernelGGL(k_scatter, dim3(1024), dim3(256), 0, s, hits, ctr, hit_cap, lim, offs, out_id,
-                     out_sim);
+hipError_t launch_place(const PlaceArgs& a, hipStream_t s) {
+  if (a.nq <= kPlaceQueries) {
+    hipLaunchKernelGGL(k_place<true>, dim3(128), dim3(1024), 0, s, a);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(k_scan_offsets, dim3(1), dim3(1024), 0, s, a);
+  if (hipError_t e = hipGetLastError()) return e;
+  hipLaunchKernelGGL(k_place<false>, dim3(256), dim3(1024), 0, s, a);
   return hipGetLastError();
 }
 
