@@ -303,6 +303,8 @@ void free_batch(Batch* b) {
   dfree(ix, &b->hits, (size_t)b->hit_cap);
   dfree(ix, &b->band_idx, (size_t)b->hit_cap);
   dfree(ix, &b->cand, (size_t)b->cand_cap);
+  dfree(ix, &b->qsplit, b->qsplit_rows * (size_t)ix->dp * 4);
+  dfree(ix, &b->qsplit_thr, b->qsplit_rows);
   dfree(ix, &b->out_id, (size_t)b->out_cap);
   dfree(ix, &b->out_sim, (size_t)b->out_cap);
   dfree(ix, &b->tmp_id, (size_t)b->out_cap);
@@ -702,10 +704,19 @@ gt_status enqueue_exhaustive(Index* ix, Batch* b) {
     b->cand_cap = int64_t(1) << 20;
     TRY(dalloc(ix, &b->cand, (size_t)b->cand_cap));
   }
+  const size_t need = gt::split_rows(b->nq_pad);
+  if (need > b->qsplit_rows) {
+    dfree(ix, &b->qsplit, b->qsplit_rows * (size_t)ix->dp * 4);
+    dfree(ix, &b->qsplit_thr, b->qsplit_rows);
+    b->qsplit_rows = 0;
+    TRY(dalloc(ix, &b->qsplit, need * (size_t)ix->dp * 4));
+    TRY(dalloc(ix, &b->qsplit_thr, need));
+    b->qsplit_rows = need;
+  }
   ev_launch_begin(b);
   HIPCHK(gt::launch_exhaustive_gemm(b->qf, b->nq_pad, ix->leaves, b->n_epoch, ix->dp, b->thr_gemm,
-                                    ix->nf, b->cand, (unsigned long long)b->cand_cap, b->ctr,
-                                    b->nq, b->stream));
+                                    ix->nf, b->qsplit, b->qsplit_thr, b->cand,
+                                    (unsigned long long)b->cand_cap, b->ctr, b->nq, b->stream));
   ev_launch_end(b, true);
   return GT_OK;
 }

@@ -332,6 +332,9 @@ struct Batch {
   Hit* hits = nullptr;
   uint32_t* band_idx = nullptr;
   int64_t hit_cap = 0;
+  unsigned char* qsplit = nullptr;  // split query rows of the exhaustive path
+  float* qsplit_thr = nullptr;
+  size_t qsplit_rows = 0;
   uint2* cand = nullptr;     // exhaustive candidates
   int64_t cand_cap = 0;
   uint32_t* out_id = nullptr;    // results placed by query, unsorted
@@ -471,8 +474,11 @@ hipError_t launch_sort_segments(const int64_t* offs, int nq, uint32_t* id, float
                                 float* sims_out, const DevCounters* ctr,
                                 unsigned long long hit_cap, unsigned long long lim,
                                 int64_t id_bound, hipStream_t s);
+// qsplit: [split_rows(nq_pad) x dp] words and qsplit_thr [split_rows(nq_pad)] of scratch
+inline size_t split_rows(int nq_pad) { return (size_t)(nq_pad + 255) / 256 * 256; }
 hipError_t launch_exhaustive_gemm(const float* qf, int nq_pad, const float* leaves, int64_t n,
-                                  int dp, const float* thr_gemm, const float* nf, uint2* cand,
+                                  int dp, const float* thr_gemm, const float* nf,
+                                  unsigned char* qsplit, float* qsplit_thr, uint2* cand,
                                   unsigned long long cand_cap, DevCounters* ctr, int nq,
                                   hipStream_t s);
 hipError_t launch_pair_check(const uint2* cand, const unsigned long long* ncand,
