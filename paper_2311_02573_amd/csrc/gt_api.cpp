@@ -585,6 +585,11 @@ float ev_walk(Batch* b, bool dense) {
 }
 
 // ------------------------------------------------------------- launch stages
+// Buckets that hold rows the call sees.
+int buckets_used(const Index* ix, const Batch* b) {
+  return b->n_epoch > 0 ? (int)((b->n_epoch - 1) >> (ix->depth - b->nb)) + 1 : 1;
+}
+
 // The call's result counters: in their rows behind the level counters, spread
 // as far as they have room, or packed in an array of their own.
 gt::QCount qcount_of(const Batch* b) {
@@ -736,6 +741,7 @@ gt_status enqueue_walk(Index* ix, Batch* b) {
     a.nt = nt;
     a.dp = (int)dp;
     a.nb = b->nb;
+    a.nbu = buckets_used(ix, b);
     a.bcap = b->fr_cap >> b->nb;
     a.child_rows = pool_base + (size_t)level_row(l + 1) * dp * esz;
     a.in_node = b->fr_node[l & 1];
@@ -779,6 +785,7 @@ gt_status enqueue_leaf(Index* ix, Batch* b) {
   la.nt = b->nt;
   la.dp = ix->dp;
   la.nb = b->nb;
+  la.nbu = buckets_used(ix, b);
   la.bcap = b->fr_cap >> b->nb;
   la.tq = b->tq;
   la.in_node = b->fr_node[(D - 1) & 1];

@@ -20,10 +20,11 @@ constexpr int kHitStage = 192;        // per-wave LDS staging of candidate hits
 // Frontier buckets.  A sparse frontier entry (pool p of level l, mask) lives
 // in bucket p >> (l - nb): the subtree of node p's ancestor at level nb, so a
 // child stays in its parent's bucket.  Bucket b of tile t is the slot
-// b * nt + t; its entries are stored at slot * (fr_cap >> nb).  Buckets are
-// dealt to the chip's 8 XCDs in contiguous ranges, so each subtree's pool
-// rows are only read through one XCD's L2, where the copies needed by the
-// different query tiles meet.
+// b * nt + t; its entries are stored at slot * (fr_cap >> nb).  The buckets
+// that hold rows (rows fill the tree from the left) are dealt to the chip's 8
+// XCDs in even contiguous ranges, so each subtree's pool rows are only read
+// through one XCD's L2, where the copies needed by the different query tiles
+// meet.
 constexpr int kXcds = 8;
 constexpr int kMaxBucketBits = 7;
 constexpr int kMaxSlots = 8192;       // nt << nb
@@ -133,6 +134,7 @@ struct TreeArgs {
 struct WalkLevelArgs {
   int level, dense, nt, dp;
   int nb;                   // bucket bits
+  int nbu;                  // buckets that hold rows; dealt to the XCDs in even ranges
   int64_t bcap;             // entries per bucket slot
   const void* child_rows;   // first row of level+1 in the pool format
   const uint32_t* in_node;
@@ -213,7 +215,7 @@ bool subtree_shape(int fmt, int dp, int nt, int qrows, int depth, int first, int
 
 struct LeafArgs {
   int level, dense, nt, dp, tq;
-  int nb;
+  int nb, nbu;
   int64_t bcap;
   const uint32_t* in_node;
   const uint64_t* in_mask;

@@ -130,8 +130,10 @@ __device__ __forceinline__ int find_slot(const uint32_t* pre, int n, uint32_t g)
 constexpr int kPipe = 8;  // 64-byte steps of a lane's two rows fetched ahead
 
 // One level step of the sparse walk.  Workgroup -> XCD x = blockIdx % 8 (the
-// hardware deals workgroups to XCDs round robin), which owns the buckets
-// [x R, x R + R).  Within an XCD the workgroups split the query tiles; when
+// hardware deals workgroups to XCDs round robin), which owns an even
+// contiguous range of the buckets that hold rows (with ranges of all buckets,
+// a tree filled to 57% left three XCDs idle: the leaf of 257 queries, n =
+// 300,007 of 2^19, took 143 us, now 96).  Within an XCD the workgroups split the query tiles; when
 // there are fewer tiles than workgroups, the c workgroups of a tile each take
 // part m of every bucket.  Every workgroup goes through its buckets in
 // order, so at any moment the XCD's workgroups read the same subtrees for
@@ -159,10 +161,9 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_level(WalkLevelArgs a)
   const int nsteps = NSTEPS > 0 ? NSTEPS : rowbytes / 64;
   const int c16 = lane & 15, g4 = lane >> 4;
 
-  const int nbk = 1 << a.nb;
-  const int xs = nbk < kXcds ? nbk : kXcds;
-  const int R = nbk / xs;
+  const int xs = a.nbu < kXcds ? a.nbu : kXcds;
   const int x = blockIdx.x % kXcds;
+  const int b0 = x * a.nbu / xs, R = (x + 1) * a.nbu / xs - b0;  // this XCD's buckets
   const int W = gridDim.x / kXcds, j = blockIdx.x / kXcds;
   if (x >= xs) return;
   int t0, tstep, m, c;
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_level(WalkLevelArgs a)
       uint32_t ng = 0, lo = 0, hi = 0;
       if (lane < R && tmask) {
         const uint32_t n = a.dense ? (1u << bshift)
-                                   : min(a.in_count[(size_t)(x * R + lane) * a.nt + t], (uint32_t)a.bcap);
+                                   : min(a.in_count[(size_t)(b0 + lane) * a.nt + t], (uint32_t)a.bcap);
         lo = (uint32_t)(((uint64_t)n * m) / c);
         hi = (uint32_t)(((uint64_t)n * (m + 1)) / c);
         ng = (hi - lo + kGroupEntries - 1) / kGroupEntries;
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_level(WalkLevelArgs a)
       const uint32_t e0 = glo[r] + (gg - gpre[r]) * kGroupEntries + (c16 >> 1);
       const uint32_t e1 = e0 + 8;
       const uint32_t hi = ghi[r];
-      const uint32_t bk = (uint32_t)(x * R + r);
+      const uint32_t bk = (uint32_t)(b0 + r);
       slot = bk * (uint32_t)a.nt + (uint32_t)t;
       // Loads are issued in both input modes and for padding lanes (at the
       // group's first entry, always valid) so that no branch separates them
@@ -513,10 +514,9 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_wide(WalkLevelArgs a) 
   const int nwin = (rowbytes + kWideWindow - 1) / kWideWindow;
   const int c16 = lane & 15, g4 = lane >> 4;
 
-  const int nbk = 1 << a.nb;
-  const int xs = nbk < kXcds ? nbk : kXcds;
-  const int R = nbk / xs;
+  const int xs = a.nbu < kXcds ? a.nbu : kXcds;
   const int x = blockIdx.x % kXcds;
+  const int b0 = x * a.nbu / xs, R = (x + 1) * a.nbu / xs - b0;  // this XCD's buckets
   const int W = gridDim.x / kXcds, j = blockIdx.x / kXcds;
   if (x >= xs) return;
   int t0, tstep, m, c;
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_wide(WalkLevelArgs a) 
       uint32_t ng = 0, lo = 0, hi = 0;
       if (lane < R && tmask) {
         const uint32_t n = a.dense ? (1u << bshift)
-                                   : min(a.in_count[(size_t)(x * R + lane) * a.nt + t], (uint32_t)a.bcap);
+                                   : min(a.in_count[(size_t)(b0 + lane) * a.nt + t], (uint32_t)a.bcap);
         lo = (uint32_t)(((uint64_t)n * m) / c);
         hi = (uint32_t)(((uint64_t)n * (m + 1)) / c);
         ng = (hi - lo + kGroupEntries - 1) / kGroupEntries;
@@ -581,7 +581,7 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_wide(WalkLevelArgs a) 
       const uint32_t e0 = glo[r] + (ge - gpre[r]) * kGroupEntries + (c16 >> 1);
       const uint32_t e1 = e0 + 8;
       const uint32_t ehi = ghi[r];
-      const uint32_t bk = (uint32_t)(x * R + r);
+      const uint32_t bk = (uint32_t)(b0 + r);
       const uint32_t slot = bk * (uint32_t)a.nt + (uint32_t)t;
       const size_t ebase = (size_t)slot * a.bcap;
       const uint32_t ef = e0 - (c16 >> 1);
@@ -782,10 +782,9 @@ __global__ __launch_bounds__(kSubThreads, 1) void k_walk_sub(WalkLevelArgs a) {
   const int c16 = lane & 15, g4 = lane >> 4;
   const int e32 = lane & 31;  // the entry this lane fetches (lanes 32-63 repeat 0-31)
 
-  const int nbk = 1 << a.nb;
-  const int xs = nbk < kXcds ? nbk : kXcds;
-  const int R = nbk / xs;
+  const int xs = a.nbu < kXcds ? a.nbu : kXcds;
   const int x = blockIdx.x % kXcds;
+  const int b0 = x * a.nbu / xs, R = (x + 1) * a.nbu / xs - b0;  // this XCD's buckets
   const int W = gridDim.x / kXcds, j = blockIdx.x / kXcds;
   if (x >= xs) return;
   int t0, tstep, m, c;
@@ -824,7 +823,7 @@ __global__ __launch_bounds__(kSubThreads, 1) void k_walk_sub(WalkLevelArgs a) {
     if (wave == 0) {
       uint32_t ng = 0, lo = 0, hi = 0;
       if (lane < R && tmask) {
-        const uint32_t n = min(a.in_count[(size_t)(x * R + lane) * a.nt + t], (uint32_t)a.bcap);
+        const uint32_t n = min(a.in_count[(size_t)(b0 + lane) * a.nt + t], (uint32_t)a.bcap);
         lo = (uint32_t)(((uint64_t)n * m) / c);
         hi = (uint32_t)(((uint64_t)n * (m + 1)) / c);
         ng = (hi - lo + kSubGroup - 1) / kSubGroup;
@@ -882,7 +881,7 @@ __global__ __launch_bounds__(kSubThreads, 1) void k_walk_sub(WalkLevelArgs a) {
       const uint32_t ef = glo[r] + (gg - gpre[r]) * kSubGroup;
       const uint32_t e = ef + (uint32_t)e32;
       const uint32_t hi = ghi[r];
-      slot = (uint32_t)(x * R + r) * (uint32_t)a.nt + (uint32_t)t;
+      slot = (uint32_t)(b0 + r) * (uint32_t)a.nt + (uint32_t)t;
       const uint32_t ie = e < hi ? e : ef;
       pos = (uint32_t)((size_t)slot * a.bcap + ie);
       p = a.in_node[pos];
@@ -1572,8 +1571,9 @@ __device__ __forceinline__ void leaf_norms(const LeafArgs& a, LeafEntry& x) {
   x.inv1 = i0 + 1 < a.n_epoch ? a.invn_f[i0 + 1] : 0.0f;
 }
 
-// Workgroup -> XCD x = blockIdx % 8, which owns the bucket slots of buckets
-// [x R, x R + R) (slots are bucket-major, so they are contiguous); the XCD's
+// Workgroup -> XCD x = blockIdx % 8, which owns an even contiguous range of
+// the buckets that hold rows (slots are bucket-major, so theirs are contiguous
+// too); the XCD's
 // workgroups sweep its entries in slot order, so the tiles' copies of a leaf
 // pair are tested close together in time and share the XCD's L2.
 // NV: 16-byte slices per lane and 1024-column chunk that can be non-zero, 4
@@ -1586,12 +1586,12 @@ __global__ __launch_bounds__(256) void k_leaf(LeafArgs a) {
   __shared__ uint32_t epre[kMaxSlotsPerXcd + 1];
   __shared__ Hit hstage[4][kHitStage];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int nbk = 1 << a.nb;
-  const int xs = nbk < kXcds ? nbk : kXcds;
+  const int xs = a.nbu < kXcds ? a.nbu : kXcds;
   const int x = blockIdx.x % kXcds;
   if (x >= xs) return;
-  const int nsl = (nbk / xs) * a.nt;
-  const int slot0 = x * nsl;
+  const int b0 = x * a.nbu / xs;
+  const int nsl = ((x + 1) * a.nbu / xs - b0) * a.nt;
+  const int slot0 = b0 * a.nt;
   slot_prefix(epre, nsl, slot0, a.nt, a.dense, a.level - a.nb, a.tile_mask, a.in_count,
               (uint32_t)a.bcap);
   const uint32_t etot = epre[nsl];
@@ -2099,7 +2099,7 @@ hipError_t launch_walk_level(int fmt, const WalkLevelArgs& a, int grid, hipStrea
   grid = kXcds * ((grid + kXcds - 1) / kXcds);
   if (a.nb < 0 || a.nb > kMaxBucketBits || ((int64_t)a.nt << a.nb) > kMaxSlots ||
       a.level < a.nb || a.nt < 1 || a.nt > kMaxTiles || a.dp < 128 || a.dp % 128 != 0 ||
-      a.dp > kMaxWalkWidth)
+      a.dp > kMaxWalkWidth || a.nbu < 1 || a.nbu > (1 << a.nb))
     return hipErrorInvalidValue;
   // rows wider than the LDS query tile: windows of the tile through LDS
   if (a.dp > maxdp_walk(fmt)) {
@@ -2131,7 +2131,8 @@ hipError_t launch_walk_sub(const WalkLevelArgs& a, int grid, hipStream_t s) {
   grid = kXcds * ((grid + kXcds - 1) / kXcds);
   if (a.dp > kMaxDpBf16 || a.dp < 128 || a.dp % 128 != 0 ||
       a.nb < 0 || a.nb > kMaxBucketBits || ((int64_t)a.nt << a.nb) > kMaxSlots ||
-      a.level < a.nb || a.nt < 1 || a.nt > kMaxTiles || a.dense || !a.in_rec || !a.sabs ||
+      a.level < a.nb || a.nt < 1 || a.nt > kMaxTiles || a.nbu < 1 || a.nbu > (1 << a.nb) ||
+      a.dense || !a.in_rec || !a.sabs ||
       a.level + 1 >= a.depth || a.depth > 32)
     return hipErrorInvalidValue;
   if (a.dp * 2 / 64 == 32)
@@ -2166,7 +2167,7 @@ hipError_t launch_dense_level(int fmt, const DenseLevelArgs& a, hipStream_t s) {
 hipError_t launch_leaf(const LeafArgs& a, int grid, hipStream_t s) {
   grid = kXcds * ((grid + kXcds - 1) / kXcds);
   if (a.nb < 0 || a.nb > kMaxBucketBits || ((int64_t)a.nt << a.nb) > kMaxSlots ||
-      a.level < a.nb || a.nt < 1 || a.nt > kMaxTiles)
+      a.level < a.nb || a.nt < 1 || a.nt > kMaxTiles || a.nbu < 1 || a.nbu > (1 << a.nb))
     return hipErrorInvalidValue;
   // rows of at most 512 columns: two slices per lane, fewer registers
   // (three waves per SIMD instead of two), so three workgroups per CU
