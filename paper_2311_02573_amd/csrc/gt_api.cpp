@@ -776,6 +776,12 @@ gt_status enqueue_walk(Index* ix, Batch* b) {
   return GT_OK;
 }
 
+// Query tiles from which the leaf sweep's entries are sorted by pool first: the
+// tiles have to share pools for it to pay.  Leaf with sort / without, us: 16
+// tiles 339 / 384 (2^20 x 1000), 358 / 410 (2^20 x 512, any sign), 8 tiles
+// 189 / 194 and 209 / 179 (clustered rows, 256 columns), 5 tiles 90 / 90.
+constexpr int kSortTiles = 16;
+
 gt_status enqueue_leaf(Index* ix, Batch* b) {
   const int D = ix->depth;
   const int sparse_from = b->dense_last >= 0 ? b->dense_last : b->head;
@@ -806,10 +812,18 @@ gt_status enqueue_leaf(Index* ix, Batch* b) {
   la.stat_pairs = gt::stat_leaf(b->lvl_count);
   la.bitmap = b->counted ? b->bitmap : nullptr;
   la.bit_base = level_row(D);
-  // two workgroups (eight waves) per CU: measured faster than one, three,
-  // four or eight per CU on this kernel, whose loads already fill the CU's
-  // outstanding-request budget
-  HIPCHK(gt::launch_leaf(la, ix->n_cu * 2, b->stream));
+  la.tile_bits = -1;
+  int tb = 0;
+  while ((1 << tb) < la.nt) ++tb;
+  if (la.nt >= kSortTiles && !la.dense && la.level - la.nb + tb <= 32) {
+    // into the frontier buffers of the level above, whose entries are spent
+    la.tile_bits = tb;
+    la.sort_node = b->fr_node[D & 1];
+    la.sort_mask = b->fr_mask[D & 1];
+    la.sort_count = b->lvl_count + (size_t)gt::kSortRow * gt::kMaxSlots;
+    HIPCHK(gt::launch_leaf_sort(la, b->stream));
+  }
+  HIPCHK(gt::launch_leaf(la, ix->n_cu, b->stream));
   return GT_OK;
 }
 

@@ -35,6 +35,7 @@ constexpr int kMaxBucketsPerXcd = (1 << kMaxBucketBits) / kXcds;
 // kStatStripes counters each (their lines apart) that the offsets kernel sums.
 // They lie behind the level counters, in the rows of levels that no tree has
 // (a tree's capacity is at most 2^31 leaves).
+constexpr int kSortRow = 31;            // entries per bucket of a sorted leaf sweep
 constexpr int kStatStripes = 64;
 constexpr int kStatRow = 36;            // first unused row of the level counters
 constexpr int kLeafStride = 16;         // 128 bytes
@@ -233,6 +234,13 @@ struct LeafArgs {
   QCount qcount;            // accepted results per query
   DevCounters* ctr;
   unsigned long long* stat_pairs;  // stripe 0 of the leaf-test counters
+  // entries sorted by pool within their bucket (tile_bits >= 0; k_leaf_sort):
+  // bucket b's are sort_count[b] entries from slot b * nt on, node =
+  // (pool - first pool of the bucket) << tile_bits | tile
+  int tile_bits;
+  const uint32_t* sort_node;
+  const uint64_t* sort_mask;
+  const uint32_t* sort_count;
   uint32_t* bitmap;         // optional: one bit per tree row read
   int64_t bit_base;         // tree row of leaf 0
 };
@@ -460,7 +468,9 @@ hipError_t launch_query_prep(const float* q, int nq, int d, int dp, int tq, cons
 hipError_t launch_walk_level(int fmt, const WalkLevelArgs& a, int grid, hipStream_t s);
 hipError_t launch_walk_sub(const WalkLevelArgs& a, int grid, hipStream_t s);
 hipError_t launch_walk_subtree(int fmt, const SubtreeArgs& a, hipStream_t s);
-hipError_t launch_leaf(const LeafArgs& a, int grid, hipStream_t s);
+// Sorts the entries a leaf launch takes by pool (a.sort_* are its outputs).
+hipError_t launch_leaf_sort(const LeafArgs& a, hipStream_t s);
+hipError_t launch_leaf(const LeafArgs& a, int n_cu, hipStream_t s);
 hipError_t launch_dense_level(int fmt, const DenseLevelArgs& a, hipStream_t s);
 // Float64 recheck of the band candidates, and the frontier entries of levels
 // first .. levels - 1 (none where first >= levels).

@@ -186,7 +186,7 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 //   slice v:  fma(x0, y0, x1 y1) + fma(x2, y2, x3 y3)
 //   chunk:    (slice 0 + slice 1) + (slice 2 + slice 3)
 // Callers add the chunks in order and then sum over the lanes with
-// wave_reduce8; the result depends only on the two rows.  Slices past dp
+// wave_reduce4; the result depends only on the two rows.  Slices past dp
 // count as zero; their loads are redirected to the last slice of the row so
 // that every load stays in bounds and no branch is needed.
 // Each product meets at most three roundings within its slice (as with
@@ -220,25 +220,20 @@ __device__ __forceinline__ float lane_partial16(const float* __restrict__ a,
   return chunk_sum4(sv[0], sv[1], sv[2], sv[3]);
 }
 
-// Sums eight per-lane values over the 64 lanes, each by the same tree
-// (partners at lane distance 32, 16, 8, 4, 2, 1), using 10 shuffles instead
-// of 6 per value.  Lanes 8v .. 8v+7 receive the sum of value v.
-__device__ __forceinline__ float wave_reduce8(const float (&a)[8], int lane) {
-  const bool h = (lane >> 5) & 1, g = (lane >> 4) & 1, f = (lane >> 3) & 1;
-  float b[4], c[2];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float send = h ? a[j] : a[j + 4];
-    const float keep = h ? a[j + 4] : a[j];
-    b[j] = __fadd_rn(keep, __shfl_xor(send, 32, 64));
-  }
+// Sums four per-lane values over the 64 lanes, each by the same tree (partners
+// at lane distance 32, 16, 8, 4, 2, 1), with 7 shuffles instead of 6 per
+// value.  Lanes 16v .. 16v+15 receive the sum of value v.
+__device__ __forceinline__ float wave_reduce4(const float (&a)[4], int lane) {
+  const bool h = (lane >> 5) & 1, g = (lane >> 4) & 1;
+  float b[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const float send = g ? b[j] : b[j + 2];
-    const float keep = g ? b[j + 2] : b[j];
-    c[j] = __fadd_rn(keep, __shfl_xor(send, 16, 64));
+    const float send = h ? a[j] : a[j + 2];
+    const float keep = h ? a[j + 2] : a[j];
+    b[j] = __fadd_rn(keep, __shfl_xor(send, 32, 64));
   }
-  float dsum = __fadd_rn(f ? c[1] : c[0], __shfl_xor(f ? c[0] : c[1], 8, 64));
+  float dsum = __fadd_rn(g ? b[1] : b[0], __shfl_xor(g ? b[0] : b[1], 16, 64));
+  dsum = __fadd_rn(dsum, __shfl_xor(dsum, 8, 64));
   dsum = __fadd_rn(dsum, __shfl_xor(dsum, 4, 64));
   dsum = __fadd_rn(dsum, __shfl_xor(dsum, 2, 64));
   dsum = __fadd_rn(dsum, __shfl_xor(dsum, 1, 64));

@@ -347,19 +347,18 @@ __global__ __launch_bounds__(256) void k_pair_check(const uint2* cand, const uns
     uint2 pr[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) pr[k] = cand[b0 + k < n ? b0 + k : b0];
-    float acc[8];
+    float acc[4];
     for (int c = 0; c * 1024 < dp; ++c) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float v = lane_partial16(qf + (size_t)pr[k].x * dp, leaves + (size_t)pr[k].y * dp,
                                        c, dp, lane);
         acc[k] = c == 0 ? v : __fadd_rn(acc[k], v);
-        acc[k + 4] = 0.0f;
       }
     }
-    const float dot = wave_reduce8(acc, lane);
-    const int v = lane >> 3;
-    const bool mine = (lane & 7) == 0 && v < 4 && b0 + v < n;
+    const float dot = wave_reduce4(acc, lane);
+    const int v = lane >> 4;
+    const bool mine = (lane & 15) == 0 && b0 + v < n;
     Hit h;
     uint32_t flag = 0;
     if (mine) {

@@ -1531,9 +1531,18 @@ __global__ __launch_bounds__(kDThreads, 1) void k_dense_level(DenseLevelArgs a) 
 
 // Exact leaf test: entries (pool p at level depth-1, mask) -> vectors 2p and
 // 2p+1 for every query of the mask.  A wave takes two entries at a time and,
-// per round, up to two mask bits of each: 2 entries x 2 queries x 2 vectors =
-// eight dot products whose rows are all fetched together and reduced at once.
-// The next pair of entries is fetched while the current one is computed.
+// per step, one mask bit of each: 2 entries x 2 vectors = four dot products of
+// six rows (an entry has 1.0 to 1.6 live queries here, so two bits per step
+// left half of the products unused).  The steps form one pipeline: a slice of
+// the next step's rows is requested as soon as the present one's is used up, so
+// that row loads are in flight through the reduction and the classification;
+// the next entries and their norms are requested two and one pairs ahead.  Row
+// addresses are scalar bases with a 32-bit lane offset, which leaves registers
+// for three waves per SIMD (four for narrow rows).  Bound by the memory beyond
+// L2: 1024 queries on 2^20 x 1000 (0.27 M entries, 12 KB each) 0.39 ms with
+// eight products per unpipelined step, now 0.33 + 0.01 for the sort; on
+// 2^20 x 512 of any sign (0.66 M entries) 0.49 ms, now 0.34 + 0.01; 4096
+// queries (1.3 M entries) 1.88 ms, now 1.35 + 0.04.
 struct LeafEntry {
   int t;
   uint32_t p;
@@ -1541,17 +1550,34 @@ struct LeafEntry {
   float inv0, inv1;  // inverse norms of vectors 2p and 2p+1 (0: beyond the epoch or zero)
 };
 
+// SORTED: slots are the XCD's buckets, entries sorted by pool.
+template <bool SORTED>
 __device__ __forceinline__ LeafEntry leaf_entry(const LeafArgs& a, const uint32_t* epre, int nsl,
-                                                int slot0, uint32_t idx, uint32_t etot) {
+                                                int slot0, uint32_t idx, uint32_t etot,
+                                                int& cursor) {
   LeafEntry x;
   x.t = 0;
   x.p = 0;
   x.m = 0ull;
   x.inv0 = x.inv1 = 0.0f;
   if (idx >= etot) return x;
-  const int sl = find_slot(epre, nsl, idx);
-  const int gs = slot0 + sl;
+  // a wave's indices only grow: few, large sorted slots are walked by a cursor,
+  // the many small ones of the unsorted sweep searched
+  if constexpr (SORTED) {
+    while ((uint32_t)__builtin_amdgcn_readfirstlane((int)epre[cursor + 1]) <= idx) ++cursor;
+  } else {
+    cursor = __builtin_amdgcn_readfirstlane(find_slot(epre, nsl, idx));
+  }
+  const int sl = cursor;
   const uint32_t e = idx - epre[sl];
+  const int gs = slot0 + sl;
+  if constexpr (SORTED) {
+    const size_t o = (size_t)gs * a.nt * a.bcap + e;
+    x.t = gs;
+    x.p = a.sort_node[o];
+    x.m = a.sort_mask[o];
+    return x;
+  }
   x.t = gs % a.nt;
   if (a.dense) {
     x.p = ((uint32_t)(gs / a.nt) << (a.level - a.nb)) + e;
@@ -1562,14 +1588,123 @@ __device__ __forceinline__ LeafEntry leaf_entry(const LeafArgs& a, const uint32_
   }
   return x;
 }
+// Pool and tile of a requested entry (SORTED: t is its bucket and p the sorted
+// value until here, which takes no registers while the request is on its way).
+template <bool SORTED>
+__device__ __forceinline__ uint32_t entry_pool(const LeafArgs& a, const LeafEntry& x) {
+  return SORTED ? ((uint32_t)x.t << (a.level - a.nb)) + (x.p >> a.tile_bits) : x.p;
+}
+
+// Entries of a bucket sorted by pool (a counting sort in LDS, one workgroup per
+// bucket; pools share a bin where a bucket has more than kSortBins).  Unsorted,
+// a leaf pair is read again for every tile that kept it, far apart in time:
+// 4096 queries on 2^20 x 1000 fetched 13.4 GB for 3.3 GB of distinct rows.
+// Sorted, the tiles' entries of a pool are neighbours, mostly of the same wave.
+// Bound by the latency of its reads and LDS adds: 8 us for 0.27 M entries of
+// 16 tiles, 42 us for 1.3 M of 64.
+constexpr int kSortBins = 4096;
+__global__ __launch_bounds__(1024) void k_leaf_sort(LeafArgs a, uint32_t* out_node,
+                                                    uint64_t* out_mask, uint32_t* out_count) {
+  __shared__ uint32_t bin[kSortBins];
+  __shared__ uint32_t wsum[16];
+  const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int bits = a.level - a.nb;  // pools per bucket (log2)
+  const int shift = bits > 12 ? bits - 12 : 0;
+  const uint32_t first = (uint32_t)b << bits;
+  static_assert(kSortBins == 1 << 12, "bins of the top 12 bits");
+  for (int i = t; i < kSortBins; i += 1024) bin[i] = 0u;
+  __syncthreads();
+  // 16 waves, one tile's slot at a time
+  for (int tl = w; tl < a.nt; tl += 16) {
+    const size_t gs = (size_t)b * a.nt + tl;
+    const uint32_t n = min(a.in_count[gs], (uint32_t)a.bcap);
+    const uint32_t* node = a.in_node + gs * a.bcap;
+    for (uint32_t i = lane; i < n; i += 256) {  // four loads in flight
+      uint32_t v[4];
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) v[k] = node[i + 64 * k < n ? i + 64 * k : i];
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k)
+        if (i + 64 * k < n) atomicAdd(&bin[(v[k] - first) >> shift], 1u);
+    }
+  }
+  __syncthreads();
+  // exclusive prefix over the bins, four per thread
+  uint32_t c[4], sum = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    c[k] = sum;
+    sum += bin[4 * t + k];
+  }
+  uint32_t incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t v = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += v;
+  }
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  uint32_t before = incl - sum;
+  for (int k = 0; k < w; ++k) before += wsum[k];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) bin[4 * t + k] = before + c[k];
+  if (t == 1023) out_count[b] = before + sum;
+  __syncthreads();
+  const size_t base = (size_t)b * a.nt * a.bcap;
+  for (int tl = w; tl < a.nt; tl += 16) {
+    const size_t gs = (size_t)b * a.nt + tl;
+    const uint32_t n = min(a.in_count[gs], (uint32_t)a.bcap);
+    const uint32_t* node = a.in_node + gs * a.bcap;
+    const uint64_t* mask = a.in_mask + gs * a.bcap;
+    for (uint32_t i = lane; i < n; i += 256) {
+      uint32_t v[4];
+      uint64_t m[4];
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t j = i + 64 * k < n ? i + 64 * k : i;
+        v[k] = node[j];
+        m[k] = mask[j];
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k)
+        if (i + 64 * k < n) {
+          const uint32_t rel = v[k] - first;
+          const uint32_t pos = atomicAdd(&bin[rel >> shift], 1u);
+          out_node[base + pos] = (rel << a.tile_bits) | (uint32_t)tl;
+          out_mask[base + pos] = m[k];
+        }
+    }
+  }
+}
 
 // Inverse norms of an entry's two vectors, fetched one round before its use
 // (the entry itself is fetched two rounds before).
+template <bool SORTED>
 __device__ __forceinline__ void leaf_norms(const LeafArgs& a, LeafEntry& x) {
-  const int64_t i0 = 2 * (int64_t)x.p;
+  const int64_t i0 = 2 * (int64_t)entry_pool<SORTED>(a, x);
   x.inv0 = i0 < a.n_epoch ? a.invn_f[i0] : 0.0f;
   x.inv1 = i0 + 1 < a.n_epoch ? a.invn_f[i0 + 1] : 0.0f;
 }
+
+// The entry's values (the same in every lane) in scalar registers, so that its
+// rows are read at scalar bases and take no vector registers for addresses.
+template <bool SORTED>
+__device__ __forceinline__ LeafEntry leaf_uniform(const LeafArgs& a, const LeafEntry& v) {
+  auto u = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+  LeafEntry x;
+  x.t = (int)u(SORTED ? v.p & ((1u << a.tile_bits) - 1u) : (uint32_t)v.t);
+  x.p = u(entry_pool<SORTED>(a, v));
+  x.m = ((uint64_t)u((uint32_t)(v.m >> 32)) << 32) | u((uint32_t)v.m);
+  x.inv0 = __uint_as_float(u(__float_as_uint(v.inv0)));
+  x.inv1 = __uint_as_float(u(__float_as_uint(v.inv1)));
+  return x;
+}
+struct LeafStep {
+  uint32_t q0, q1, p0, p1;
+  float i00, i01, i10, i11;  // inverse norms of the entries' vectors (0: not tested)
+  float invq;                // of the lane's query
+  double rho;
+};
 
 // Workgroup -> XCD x = blockIdx % 8, which owns an even contiguous range of
 // the buckets that hold rows (slots are bucket-major, so theirs are contiguous
@@ -1581,158 +1716,181 @@ __device__ __forceinline__ void leaf_norms(const LeafArgs& a, LeafEntry& x) {
 // would only reload the row's last slice).  Each dot product is summed in the
 // same order either way: a slice past dp is zero and adds nothing to
 // chunk_sum4.
-template <int NV>
+template <int NV, bool SORTED>
 __global__ __launch_bounds__(256) void k_leaf(LeafArgs a) {
   __shared__ uint32_t epre[kMaxSlotsPerXcd + 1];
   __shared__ Hit hstage[4][kHitStage];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int xs = a.nbu < kXcds ? a.nbu : kXcds;
   const int x = blockIdx.x % kXcds;
   if (x >= xs) return;
   const int b0 = x * a.nbu / xs;
-  const int nsl = ((x + 1) * a.nbu / xs - b0) * a.nt;
-  const int slot0 = b0 * a.nt;
-  slot_prefix(epre, nsl, slot0, a.nt, a.dense, a.level - a.nb, a.tile_mask, a.in_count,
-              (uint32_t)a.bcap);
-  const uint32_t etot = epre[nsl];
+  const int R = (x + 1) * a.nbu / xs - b0;
+  const int nsl = SORTED ? R : R * a.nt;
+  const int slot0 = SORTED ? b0 : b0 * a.nt;
+  if constexpr (SORTED)
+    slot_prefix(epre, nsl, slot0, a.nt, 0, 0, a.tile_mask, a.sort_count, 0xFFFFFFFFu);
+  else
+    slot_prefix(epre, nsl, slot0, a.nt, a.dense, a.level - a.nb, a.tile_mask, a.in_count,
+                (uint32_t)a.bcap);
+  const uint32_t etot = (uint32_t)__builtin_amdgcn_readfirstlane((int)epre[nsl]);
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t wgs = gridDim.x / kXcds;
   const uint32_t stride = 2u * wgs * nw;
   Hit* buf = hstage[w];
   int cnt = 0;
   unsigned long long npairs = 0;
-  const int v = lane >> 3;              // value owned after the reduction
-  const int vs = v >> 2, vk = (v >> 1) & 1, vl = v & 1;
-  uint32_t idx = 2u * ((blockIdx.x / kXcds) * nw + w);
-  LeafEntry nx0 = leaf_entry(a, epre, nsl, slot0, idx, etot);
-  LeafEntry nx1 = leaf_entry(a, epre, nsl, slot0, idx + 1, etot);
-  leaf_norms(a, nx0);
-  leaf_norms(a, nx1);
-  LeafEntry nn0 = leaf_entry(a, epre, nsl, slot0, idx + stride, etot);
-  LeafEntry nn1 = leaf_entry(a, epre, nsl, slot0, idx + stride + 1, etot);
-  for (; idx < etot; idx += stride) {
-    LeafEntry en[2] = {nx0, nx1};
-    nx0 = nn0;
-    nx1 = nn1;
-    leaf_norms(a, nx0);
-    leaf_norms(a, nx1);
-    nn0 = leaf_entry(a, epre, nsl, slot0, idx + 2 * stride, etot);
-    nn1 = leaf_entry(a, epre, nsl, slot0, idx + 2 * stride + 1, etot);
-    float inv[2][2];
-    const float* frow[2][2];
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const int64_t i = 2 * (int64_t)en[s2].p + c;
-        inv[s2][c] = en[s2].m ? (c == 0 ? en[s2].inv0 : en[s2].inv1) : 0.0f;
-        frow[s2][c] = a.leaves + i * a.dp;
-        if (a.bitmap && lane == 0 && inv[s2][c] != 0.0f)
-          atomicOr(&a.bitmap[(a.bit_base + i) >> 5], 1u << ((a.bit_base + i) & 31));
-      }
-      // a zero vector has no cosine and is never a member
-      if (inv[s2][0] == 0.0f && inv[s2][1] == 0.0f) en[s2].m = 0ull;
+  const int vs = lane >> 5, vl = (lane >> 4) & 1;  // value owned after the reduction
+  const int nchunks = (a.dp + 1023) / 1024;
+
+  // The wave's entries: en (uniform, in scalar registers) is worked on, nx has
+  // its norms requested, nn itself is requested.
+  uint32_t idx = 2u * ((blockIdx.x / kXcds) * nw + (uint32_t)w);  // of nx
+  int cursor = 0;
+  LeafEntry nx0 = leaf_entry<SORTED>(a, epre, nsl, slot0, idx, etot, cursor);
+  LeafEntry nx1 = leaf_entry<SORTED>(a, epre, nsl, slot0, idx + 1, etot, cursor);
+  leaf_norms<SORTED>(a, nx0);
+  leaf_norms<SORTED>(a, nx1);
+  LeafEntry nn0 = leaf_entry<SORTED>(a, epre, nsl, slot0, idx + stride, etot, cursor);
+  LeafEntry nn1 = leaf_entry<SORTED>(a, epre, nsl, slot0, idx + stride + 1, etot, cursor);
+  LeafEntry e0, e1;
+  e0.t = e1.t = 0;
+  e0.p = e1.p = 0u;
+  e0.m = e1.m = 0ull;
+  e0.inv0 = e0.inv1 = e1.inv0 = e1.inv1 = 0.0f;
+
+  // A step tests one query against both vectors of each of two entries.
+  LeafStep cur, nxt;
+  auto start = [&](LeafEntry& e) {
+    if (a.bitmap && lane == 0 && e.m) {
+      const int64_t i = a.bit_base + 2 * (int64_t)e.p;
+      if (e.inv0 != 0.0f) atomicOr(&a.bitmap[i >> 5], 1u << (i & 31));
+      if (e.inv1 != 0.0f) atomicOr(&a.bitmap[(i + 1) >> 5], 1u << ((i + 1) & 31));
     }
-    while (en[0].m | en[1].m) {
-      int qs[2][2];
-      bool qv[2][2];
+    // a zero vector has no cosine and is never a member
+    if (e.inv0 == 0.0f && e.inv1 == 0.0f) e.m = 0ull;
+  };
+  // (an entry whose bits are done: valid rows, sums dropped)
+  auto take = [&](LeafEntry& e, uint32_t& q, uint32_t& p, float& i0, float& i1) {
+    const bool live = e.m != 0ull;
+    q = live ? (uint32_t)(e.t * a.tq + (__ffsll((unsigned long long)e.m) - 1)) : 0u;
+    p = e.p;
+    i0 = live ? e.inv0 : 0.0f;
+    i1 = live ? e.inv1 : 0.0f;
+    e.m &= e.m - 1ull;
+  };
+  auto next_step = [&](LeafStep& st) {
+    while (!(e0.m | e1.m)) {
+      if (idx >= etot) return false;
+      e0 = leaf_uniform<SORTED>(a, nx0);
+      e1 = leaf_uniform<SORTED>(a, nx1);
+      nx0 = nn0;
+      nx1 = nn1;
+      leaf_norms<SORTED>(a, nx0);
+      leaf_norms<SORTED>(a, nx1);
+      idx += stride;
+      nn0 = leaf_entry<SORTED>(a, epre, nsl, slot0, idx + stride, etot, cursor);
+      nn1 = leaf_entry<SORTED>(a, epre, nsl, slot0, idx + stride + 1, etot, cursor);
+      start(e0);
+      start(e1);
+    }
+    take(e0, st.q0, st.p0, st.i00, st.i01);
+    take(e1, st.q1, st.p1, st.i10, st.i11);
+    const uint32_t qg = vs ? st.q1 : st.q0;
+    st.invq = a.invn_q[qg];
+    st.rho = a.rho[qg];
+    return true;
+  };
+  // Slice v of chunk c of the step's six rows.
+  float4 qx[NV][2], fx[NV][2][2];
+  auto load_slice = [&](const LeafStep& st, int c, int v) {
+    bool ok;
+    // (a 32-bit byte offset from a scalar base: no address registers)
+    const uint32_t off = 16u * (uint32_t)slice_index(c, v, lane, a.dp, ok);
+    auto ld = [&](const float* row) {
+      return *reinterpret_cast<const float4*>(reinterpret_cast<const unsigned char*>(row) + off);
+    };
+    const float* f0 = a.leaves + 2 * (size_t)st.p0 * a.dp;
+    const float* f1 = a.leaves + 2 * (size_t)st.p1 * a.dp;
+    qx[v][0] = ld(a.qf + (size_t)st.q0 * a.dp);
+    fx[v][0][0] = ld(f0);
+    fx[v][0][1] = ld(f0 + a.dp);
+    qx[v][1] = ld(a.qf + (size_t)st.q1 * a.dp);
+    fx[v][1][0] = ld(f1);
+    fx[v][1][1] = ld(f1 + a.dp);
+  };
+  float acc[4];
+  int c = 0;
+  bool go = next_step(cur);
+  if (go) {
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2)
+    for (int v = 0; v < NV; ++v) load_slice(cur, 0, v);
+  }
+  while (go) {
+    // what follows: the next chunk of the same rows, or the next step; its
+    // slices are requested as this one's are used up (at the end of the
+    // wave's work the last rows again)
+    const bool last = c + 1 == nchunks;
+    bool more = true;
+    int nc = c + 1;
+    if (last) {
+      more = next_step(nxt);
+      nc = more ? 0 : c;
+    }
+    if (!last || !more) nxt = cur;
+    float sv[4][4];
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          qv[s2][k] = en[s2].m != 0ull;
-          qs[s2][k] = qv[s2][k] ? en[s2].t * a.tq + (__ffsll((unsigned long long)en[s2].m) - 1) : 0;
-          en[s2].m &= en[s2].m - 1ull;
-        }
-      // all eight rows' slices are loaded before any arithmetic (rows of
-      // unused combinations are valid rows; their sums are dropped below)
-      const float4* q4[2][2];
-      const float4* f4[2][2];
+    for (int v = 0; v < 4; ++v) {
+      if (v >= NV) {
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          q4[s2][k] = reinterpret_cast<const float4*>(a.qf + (size_t)qs[s2][k] * a.dp);
-          f4[s2][k] = reinterpret_cast<const float4*>(frow[s2][k]);
-        }
-      float acc[8];
-      for (int c = 0; c * 1024 < a.dp; ++c) {
-        float sv[8][4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          if (v >= NV) {
-#pragma unroll
-            for (int vi = 0; vi < 8; ++vi) sv[vi][v] = 0.0f;
-            continue;
-          }
-          bool ok;
-          const int ec = slice_index(c, v, lane, a.dp, ok);
-          float4 qx[2][2], fx[2][2];
-#pragma unroll
-          for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-              qx[s2][k] = q4[s2][k][ec];
-              fx[s2][k] = f4[s2][k][ec];
-            }
-#pragma unroll
-          for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-#pragma unroll
-              for (int l = 0; l < 2; ++l)
-              {
-                // computed for every slice (a redirected slice holds valid
-                // data), then selected: no branch per slice
-                const float dv = slice_dot4(qx[s2][k], fx[s2][l]);
-                sv[4 * s2 + 2 * k + l][v] = ok ? dv : 0.0f;
-              }
-        }
-#pragma unroll
-        for (int vi = 0; vi < 8; ++vi) {
-          const float part = chunk_sum4(sv[vi][0], sv[vi][1], sv[vi][2], sv[vi][3]);
-          acc[vi] = c == 0 ? part : __fadd_rn(acc[vi], part);
-        }
+        for (int vi = 0; vi < 4; ++vi) sv[vi][v] = 0.0f;
+        continue;
       }
+      bool ok;
+      (void)slice_index(c, v, lane, a.dp, ok);
 #pragma unroll
       for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
+        for (int l = 0; l < 2; ++l) {
+          // computed for every slice (a redirected slice holds valid data),
+          // then selected: no branch per slice
+          const float dv = slice_dot4(qx[v][s2], fx[v][s2][l]);
+          sv[2 * s2 + l][v] = ok ? dv : 0.0f;
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      load_slice(nxt, nc, v);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-          for (int l = 0; l < 2; ++l)
-            if (!(qv[s2][k] && inv[s2][l] != 0.0f)) acc[4 * s2 + 2 * k + l] = 0.0f;
-      const float dot = wave_reduce8(acc, lane);
-      // lane 8v classifies value v = (entry vs, query vk, vector vl)
-      int qg = 0;
-      bool ok = false;
-      float invf = 0.0f;
-      uint32_t id = 0;
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-          for (int l = 0; l < 2; ++l)
-            if (vs == s2 && vk == k && vl == l) {
-              qg = qs[s2][k];
-              ok = qv[s2][k] && inv[s2][l] != 0.0f;
-              invf = inv[s2][l];
-              id = 2u * en[s2].p + (uint32_t)l;
-            }
-      const bool mine = (lane & 7) == 0 && ok;
+    for (int vi = 0; vi < 4; ++vi) {
+      const float part = chunk_sum4(sv[vi][0], sv[vi][1], sv[vi][2], sv[vi][3]);
+      acc[vi] = c == 0 ? part : __fadd_rn(acc[vi], part);
+    }
+    if (last) {
+      if (cur.i00 == 0.0f) acc[0] = 0.0f;
+      if (cur.i01 == 0.0f) acc[1] = 0.0f;
+      if (cur.i10 == 0.0f) acc[2] = 0.0f;
+      if (cur.i11 == 0.0f) acc[3] = 0.0f;
+      const float dot = wave_reduce4(acc, lane);
+      // lane 16 v classifies value v = (entry vs, vector vl)
+      const float invf = vs ? (vl ? cur.i11 : cur.i10) : (vl ? cur.i01 : cur.i00);
       Hit h;
       uint32_t flag = 0;
-      if (mine) {
-        const float cs = __fmul_rn(__fmul_rn(dot, a.invn_q[qg]), invf);
-        flag = classify(cs, a.rho[qg]);
-        h.q = (uint32_t)qg;
-        h.id = id;
+      if ((lane & 15) == 0 && invf != 0.0f) {
+        const float cs = __fmul_rn(__fmul_rn(dot, cur.invq), invf);
+        flag = classify(cs, cur.rho);
+        h.q = vs ? cur.q1 : cur.q0;
+        h.id = 2u * (vs ? cur.p1 : cur.p0) + (uint32_t)vl;
         h.sim = cs;
         h.flag = flag;
         ++npairs;
       }
       stage_hits(buf, cnt, flag != 0u, h, a.qcount, a.ctr, a.hits, a.hit_cap, a.band_idx, lane);
     }
+    cur = nxt;
+    c = nc;
+    go = more;
   }
   flush_hits(buf, cnt, a.qcount, a.ctr, a.hits, a.hit_cap, a.band_idx, lane, w);
   for (int o = 32; o >= 1; o >>= 1) npairs += __shfl_xor(npairs, o, 64);
@@ -2164,20 +2322,38 @@ hipError_t launch_dense_level(int fmt, const DenseLevelArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_leaf(const LeafArgs& a, int grid, hipStream_t s) {
-  grid = kXcds * ((grid + kXcds - 1) / kXcds);
+hipError_t launch_leaf(const LeafArgs& a, int n_cu, hipStream_t s) {
   if (a.nb < 0 || a.nb > kMaxBucketBits || ((int64_t)a.nt << a.nb) > kMaxSlots ||
-      a.level < a.nb || a.nt < 1 || a.nt > kMaxTiles || a.nbu < 1 || a.nbu > (1 << a.nb))
+      a.level < a.nb || a.nt < 1 || a.nt > kMaxTiles || a.nbu < 1 || a.nbu > (1 << a.nb) || n_cu < 1)
     return hipErrorInvalidValue;
-  // rows of at most 512 columns: two slices per lane, fewer registers
-  // (three waves per SIMD instead of two), so three workgroups per CU
-  // (the grid stays a multiple of the XCD count: every XCD's workgroups
-  // split its entries by blockIdx / 8)
-  if (a.dp <= 512)
-    hipLaunchKernelGGL(k_leaf<2>, dim3(kXcds * ((grid / 2 * 3 + kXcds - 1) / kXcds)), dim3(256),
-                       0, s, a);
+  // As many workgroups of four waves per CU as its registers hold at once:
+  // three, or four for rows of at most 512 columns (two slices per lane); with
+  // fewer the loads in flight do not cover their latency (two and three:
+  // 0.41 ms against 0.38, 0.44 against 0.41), with one more the rows spill.
+  // The grid is a multiple of the XCD count: every XCD's workgroups split its
+  // entries by blockIdx / 8.
+  const bool sorted = a.tile_bits >= 0, narrow = a.dp <= 512;
+  const dim3 g(kXcds * ((n_cu * (narrow ? 4 : 3) + kXcds - 1) / kXcds));
+  if (narrow && sorted)
+    hipLaunchKernelGGL((k_leaf<2, true>), g, dim3(256), 0, s, a);
+  else if (narrow)
+    hipLaunchKernelGGL((k_leaf<2, false>), g, dim3(256), 0, s, a);
+  else if (sorted)
+    hipLaunchKernelGGL((k_leaf<4, true>), g, dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL(k_leaf<4>, dim3(grid), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_leaf<4, false>), g, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_leaf_sort(const LeafArgs& a, hipStream_t s) {
+  if (a.nb < 0 || a.nb > kMaxBucketBits || ((int64_t)a.nt << a.nb) > kMaxSlots ||
+      a.level < a.nb || a.nt < 1 || a.nbu < 1 || a.nbu > (1 << a.nb) || a.dense ||
+      (1 << a.tile_bits) < a.nt || a.level - a.nb + a.tile_bits > 32 || !a.sort_node ||
+      !a.sort_mask || !a.sort_count || a.sort_node == a.in_node || a.sort_mask == a.in_mask)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_leaf_sort, dim3(a.nbu), dim3(1024), 0, s, a,
+                     const_cast<uint32_t*>(a.sort_node), const_cast<uint64_t*>(a.sort_mask),
+                     const_cast<uint32_t*>(a.sort_count));
   return hipGetLastError();
 }
 
