@@ -211,9 +211,9 @@ __device__ __forceinline__ float lane_partial16(const float* __restrict__ a,
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     bool ok;
-    const int ec = slice_index(chunk, v, lane, dp, ok);
-    const float4 x = reinterpret_cast<const float4*>(a)[ec];
-    const float4 y = reinterpret_cast<const float4*>(b)[ec];
+    const uint32_t off = 16u * (uint32_t)slice_index(chunk, v, lane, dp, ok);
+    const float4 x = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a) + off);
+    const float4 y = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(b) + off);
     const float dv = slice_dot4(x, y);
     sv[v] = ok ? dv : 0.0f;
   }

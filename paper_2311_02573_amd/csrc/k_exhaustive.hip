@@ -337,35 +337,46 @@ __global__ __launch_bounds__(256) void k_pair_check(const uint2* cand, const uns
                                                     DevCounters* ctr,
                                                     unsigned long long* stat_pairs) {
   __shared__ Hit hstage[4][kHitStage];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const unsigned long long n = *ncand < cap ? *ncand : cap;
   const unsigned long long nw = blockDim.x >> 6;
   Hit* buf = hstage[w];
   int cnt = 0;
   unsigned long long npairs = 0;
-  for (unsigned long long b0 = (blockIdx.x * nw + w) * 4ull; b0 < n; b0 += gridDim.x * nw * 4ull) {
-    uint2 pr[4];
+  // Lane 16 v .. 16 v + 15 hold pair v of the step; a step's pairs are requested
+  // a step ahead.
+  const int v = lane >> 4;
+  const unsigned long long step = gridDim.x * nw * 4ull;
+  unsigned long long b0 = (blockIdx.x * nw + w) * 4ull;
+  auto pair_at = [&](unsigned long long b) { return cand[b + v < n ? b + v : n - 1]; };
+  uint2 nx = make_uint2(0u, 0u);
+  if (b0 < n) nx = pair_at(b0);
+  for (; b0 < n; b0 += step) {
+    const uint2 x = nx;
+    if (b0 + step < n) nx = pair_at(b0 + step);
+    const float invf = invn_f[x.y], invq = invn_q[x.x];
+    const double rh = rho[x.x];
+    const float *q[4], *f[4];  // (at scalar bases)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) pr[k] = cand[b0 + k < n ? b0 + k : b0];
+    for (int k = 0; k < 4; ++k) {
+      q[k] = qf + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)x.x, 16 * k) * dp;
+      f[k] = leaves + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)x.y, 16 * k) * dp;
+    }
     float acc[4];
     for (int c = 0; c * 1024 < dp; ++c) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const float v = lane_partial16(qf + (size_t)pr[k].x * dp, leaves + (size_t)pr[k].y * dp,
-                                       c, dp, lane);
-        acc[k] = c == 0 ? v : __fadd_rn(acc[k], v);
+        const float part = lane_partial16(q[k], f[k], c, dp, lane);
+        acc[k] = c == 0 ? part : __fadd_rn(acc[k], part);
       }
     }
     const float dot = wave_reduce4(acc, lane);
-    const int v = lane >> 4;
-    const bool mine = (lane & 15) == 0 && b0 + v < n;
     Hit h;
     uint32_t flag = 0;
-    if (mine) {
-      const uint2 x = pr[v];
-      const float invf = invn_f[x.y];
-      const float cs = __fmul_rn(__fmul_rn(dot, invn_q[x.x]), invf);
-      flag = invf != 0.0f ? classify(cs, rho[x.x]) : 0u;
+    if ((lane & 15) == 0 && b0 + v < n) {
+      const float cs = __fmul_rn(__fmul_rn(dot, invq), invf);
+      flag = invf != 0.0f ? classify(cs, rh) : 0u;
       h.q = x.x;
       h.id = x.y;
       h.sim = cs;

@@ -1899,9 +1899,13 @@ __global__ __launch_bounds__(256) void k_leaf(LeafArgs a) {
 
 // Candidates within 1e-5 of rho are re-decided with the canonical float64
 // cosine, bit-identical to the oracle: the dot product and the query's squared
-// norm run sequentially over k, lane by lane (lane l holds elements
-// [16 l, 16 l + 16) of each 1024-chunk, so lane order is k order), one wave
-// per candidate; the rows' squared norms are the canonical ones of ingest.
+// norm run sequentially over k, one wave per candidate; the rows' squared norms
+// are the canonical ones of ingest.  The time is the chain of one row, so the
+// wave forms the products q_k f_k and q_k^2 of 1024 columns first (exact in
+// float64, so adding them is the same as a fused multiply-add), into LDS, and
+// lane 0 adds up the ones while lane 1 adds up the others (the launch at d =
+// 1000 with few candidates: 10 us; with the sums passed from lane to lane 13;
+// with operands read and converted in the chain 22).
 // Workgroups from kRecheckGroups on sum the frontier entries of one level
 // each over its slots' counters (the automatic dense level and a server's
 // memory estimates read them).
@@ -1936,39 +1940,52 @@ __global__ __launch_bounds__(256) void k_recheck(Hit* hits, const uint32_t* band
     level_entries(lvl_count, first + (int)blockIdx.x - kRecheckGroups, ctr);
     return;
   }
-  const int lane = threadIdx.x & 63;
+  __shared__ __attribute__((aligned(16))) double prod[4][2][1024];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const unsigned long long n = *nband < cap ? *nband : cap;
   const unsigned long long nw = blockDim.x >> 6;
-  for (unsigned long long b = blockIdx.x * nw + (threadIdx.x >> 6); b < n; b += kRecheckGroups * nw) {
+  const double2* mine = reinterpret_cast<const double2*>(prod[w][lane & 1]);
+  for (unsigned long long b = blockIdx.x * nw + w; b < n; b += kRecheckGroups * nw) {
     const uint32_t hi = band_idx[b];
     Hit x = hits[hi];
     const float* q = qf + (size_t)x.q * dp;
     const float* f = leaves + (size_t)x.id * dp;
-    // dot = sum q_k f_k and qq = sum q_k^2, both sequential over k (two
-    // independent chains in step)
-    double s = 0.0, sq = 0.0;
-    for (int c = 0; c * 1024 < dp; ++c) {
-      const int base = c * 1024 + 16 * lane;
-      float qv[16], fv[16];
+    double acc = 0.0;
+    for (int c = 0; c < d; c += 1024) {
+      const int cols = min(1024, dp - c);  // (a multiple of 128; zero past d: acc + 0 = acc)
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        qv[j] = base + j < d ? q[base + j] : 0.0f;
-        fv[j] = base + j < d ? f[base + j] : 0.0f;
-      }
-      // (values past d are zero: fma(0, 0, s) = s, so no branch splits the
-      // two chains)
-      for (int L = 0; L < 64; ++L) {
-        if (lane == L) {
-#pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            s = __fma_rn((double)qv[j], (double)fv[j], s);
-            sq = __fma_rn((double)qv[j], (double)qv[j], sq);
-          }
+      for (int j = 0; j < 4; ++j) {
+        const int k = 4 * lane + 256 * j;
+        if (k < cols) {
+          const float4 u = *reinterpret_cast<const float4*>(q + c + k);
+          const float4 v = *reinterpret_cast<const float4*>(f + c + k);
+          double2* p = reinterpret_cast<double2*>(&prod[w][0][k]);
+          double2* r = reinterpret_cast<double2*>(&prod[w][1][k]);
+          p[0] = make_double2(__dmul_rn((double)u.x, (double)v.x), __dmul_rn((double)u.y, (double)v.y));
+          p[1] = make_double2(__dmul_rn((double)u.z, (double)v.z), __dmul_rn((double)u.w, (double)v.w));
+          r[0] = make_double2(__dmul_rn((double)u.x, (double)u.x), __dmul_rn((double)u.y, (double)u.y));
+          r[1] = make_double2(__dmul_rn((double)u.z, (double)u.z), __dmul_rn((double)u.w, (double)u.w));
         }
-        s = __shfl(s, L, 64);
-        sq = __shfl(sq, L, 64);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      // 16 columns at a time, the next 16 read while these are added (every
+      // lane does it: no branch around the reads)
+      double2 v[8], nx[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = mine[j];
+      for (int k = 8; k <= cols / 2; k += 8) {
+        const int kn = k < cols / 2 ? k : 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) nx[j] = mine[kn + j];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc = __dadd_rn(__dadd_rn(acc, v[j].x), v[j].y);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = nx[j];
       }
     }
+    const double s = __shfl(acc, 0, 64), sq = __shfl(acc, 1, 64);
     if (lane == 0) {
       const double cs = __ddiv_rn(s, __dmul_rn(__dsqrt_rn(sq), __dsqrt_rn(ff[x.id])));
       atomicAdd(&ctr->rechecked, 1ull);
