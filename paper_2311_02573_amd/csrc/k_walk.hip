@@ -127,6 +127,22 @@ __device__ __forceinline__ int find_slot(const uint32_t* pre, int n, uint32_t g)
   return lo;
 }
 
+// Entries [lo, hi) of a bucket's n that part m of c takes: whole groups (a part
+// that ends inside one costs a wave step for each side of it), dealt by
+// buckets in rotation so that the parts' totals stay even.  Level kernel on
+// 2^20 x 1000 float32 pools, 256 queries, nine levels: 845 us, 1050 with equal
+// shares; even at 1024 queries, and worse for the smaller groups of k_walk_sub
+// (256 queries 173 / 160), which keeps equal shares.
+__device__ __forceinline__ void bucket_share(uint32_t n, int m, int c, int bucket, uint32_t group,
+                                             uint32_t& lo, uint32_t& hi) {
+  const uint32_t g = (n + group - 1) / group, rot = (uint32_t)(bucket % c);
+  auto cut = [&](int k) {
+    return k <= 0 ? 0u : k >= c ? g : (uint32_t)(((uint64_t)g * (uint32_t)k + rot) / (uint32_t)c);
+  };
+  lo = min(n, cut(m) * group);
+  hi = min(n, cut(m + 1) * group);
+}
+
 constexpr int kPipe = 8;  // 64-byte steps of a lane's two rows fetched ahead
 
 // One level step of the sparse walk.  Workgroup -> XCD x = blockIdx % 8 (the
@@ -189,8 +205,7 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_level(WalkLevelArgs a)
       if (lane < R && tmask) {
         const uint32_t n = a.dense ? (1u << bshift)
                                    : min(a.in_count[(size_t)(b0 + lane) * a.nt + t], (uint32_t)a.bcap);
-        lo = (uint32_t)(((uint64_t)n * m) / c);
-        hi = (uint32_t)(((uint64_t)n * (m + 1)) / c);
+        bucket_share(n, m, c, b0 + lane, kGroupEntries, lo, hi);
         ng = (hi - lo + kGroupEntries - 1) / kGroupEntries;
       }
       uint32_t incl = ng;
@@ -542,8 +557,7 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_wide(WalkLevelArgs a) 
       if (lane < R && tmask) {
         const uint32_t n = a.dense ? (1u << bshift)
                                    : min(a.in_count[(size_t)(b0 + lane) * a.nt + t], (uint32_t)a.bcap);
-        lo = (uint32_t)(((uint64_t)n * m) / c);
-        hi = (uint32_t)(((uint64_t)n * (m + 1)) / c);
+        bucket_share(n, m, c, b0 + lane, kGroupEntries, lo, hi);
         ng = (hi - lo + kGroupEntries - 1) / kGroupEntries;
       }
       uint32_t incl = ng;
