@@ -60,10 +60,20 @@ __device__ __forceinline__ void stage_queries(unsigned char* lds, const unsigned
 }
 
 // Products of one 16-row group with the staged query columns: nsteps 64-byte
-// steps from `row` (this lane's row and slice) against `brow`.
+// steps from `row` against `brow`.  The matrix-core operand of lane 16 g + i is
+// row i, 16-byte chunk g; loads in that order touch four lines with each four
+// lanes.  kQuads: four lanes take 64 contiguous bytes of a row (lanes 4 R ..
+// 4 R + 3: row R), and the operand comes from lane 4 i + g (bp).  Kernel with /
+// without (us): float8 of 300,007 x 777, 257 queries 124 / 134; float32 of
+// 100,003 x 300, 65 queries 55 / 60.  Not where the passing between lanes costs
+// more: one block of queries (float32, 524,288 x 500, 1 query 40 / 33), or
+// bfloat16 (4 blocks 88 / 86).
+template <int FMT, int NQB>
+constexpr bool kQuads = FMT != GT_POOL_BF16 && NQB >= 2;
+
 template <int FMT, int NQB>
 __device__ __forceinline__ void group_products(const unsigned char* row, const unsigned char* brow,
-                                               int rs, int nsteps, f32x4 (&acc)[NQB]) {
+                                               int rs, int nsteps, int bp, f32x4 (&acc)[NQB]) {
   for (int s0 = 0; s0 < nsteps; s0 += kSteps) {
     uint4 x[kSteps];
 #pragma unroll
@@ -79,17 +89,23 @@ __device__ __forceinline__ void group_products(const unsigned char* row, const u
 #pragma unroll
     for (int c = 0; c < kSteps; ++c)
       if (s0 + c < nsteps) {
+        uint4 v = x[c];
+        if constexpr (kQuads<FMT, NQB>) {
+          v.x = (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)v.x);
+          v.y = (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)v.y);
+          v.z = (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)v.z);
+          v.w = (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)v.w);
+        }
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb)
-          mma16x16<FMT>(x[c], ld_lds16(brow + qb * 16 * rs + 64 * (s0 + c)), acc[qb]);
+          mma16x16<FMT>(v, ld_lds16(brow + qb * 16 * rs + 64 * (s0 + c)), acc[qb]);
       }
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
 // A wave takes 16 pool rows at a time (16 pools of the first level, then both
-// children of 8 entries): lane l loads 16 bytes of row l % 16 at 16 (l / 16)
-// of every 64-byte step, the matrix-core operand layout, 32 steps in flight.
+// children of 8 entries), 32 64-byte steps of them in flight.
 // Scores, thresholds and decisions are those of the level kernels' direct
 // test (the sums run over the same products in another order, which the
 // thresholds' slack covers).
@@ -134,6 +150,7 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
   }
   const uint32_t slot = (uint32_t)(sub >> (a.top - a.nb)) * (uint32_t)a.nt + (uint32_t)t;
   const unsigned char* brow = lds + c16 * rs + 16 * g4;
+  const int bp = 4 * (4 * c16 + g4);
 
   for (int l = a.first; l < D; ++l) {
     __syncthreads();  // the query rows, and the entries of the level above
@@ -157,12 +174,13 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
     for (int qb = 0; qb < NQB; ++qb)
       th[qb] = FMT == GT_POOL_FP8E4M3 ? ldexpf(th0[qb] * kFp8ThrFactor, -(qe[qb] + a.lexp[l])) : th0[qb];
     const unsigned char* level = reinterpret_cast<const unsigned char*>(a.pools) +
-                                 (size_t)((int64_t(1) << l) - 1) * rowbytes + 16 * g4;
+                                 (size_t)((int64_t(1) << l) - 1) * rowbytes + 16 * (kQuads<FMT, NQB> ? lane & 3 : g4);
     uint32_t pairs = 0;
     // (every wave takes part in every round of a windowed tile)
     for (uint32_t g0 = WIN ? 0u : (uint32_t)wave; 16u * g0 < n; g0 += G * NW) {
       uint32_t node[G];
       uint64_t pm[G];
+      const unsigned char* row[G];  // of the row this lane loads
       f32x4 acc[G][NQB];
       bool any[G];  // the wave has this group
 #pragma unroll
@@ -177,6 +195,8 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
           node[k] = 2u * in_node[rr >> 1] + (rr & 1u);
           pm[k] = r < n && ((int64_t)node[k] << shift) < a.n_epoch ? in_mask[rr >> 1] : 0ull;
         }
+        const uint32_t rn = kQuads<FMT, NQB> ? (uint32_t)__shfl((int)node[k], lane >> 2, 64) : node[k];
+        row[k] = level + (size_t)rn * rowbytes;
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
@@ -191,10 +211,10 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
 #pragma unroll
           for (int k = 0; k < G; ++k)
             if (any[k])
-              group_products<FMT, NQB>(level + (size_t)node[k] * rowbytes + from, brow, rs, nb / 64, acc[k]);
+              group_products<FMT, NQB>(row[k] + from, brow, rs, nb / 64, bp, acc[k]);
         }
       } else {
-        group_products<FMT, NQB>(level + (size_t)node[0] * rowbytes, brow, rs, rowbytes / 64, acc[0]);
+        group_products<FMT, NQB>(row[0], brow, rs, rowbytes / 64, bp, acc[0]);
       }
 #pragma unroll
       for (int k = 0; k < G; ++k) {
