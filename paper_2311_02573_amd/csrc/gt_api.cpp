@@ -227,7 +227,7 @@ int adapt_dense_last(const Index* ix, const Batch* b, int fmt, bool maxp, int dl
       b->last_walk_fmt != fmt || b->last_maxpool != maxp || b->last_walk_nt <= 0)
     return dl;
   const int D = ix->depth;
-  const double thr = 4.6e-4 * width;
+  const double thr = fmt == GT_POOL_F32 ? 0.5 : 4.6e-4 * width;
   auto density = [&](int L) {
     const int64_t span = int64_t(1) << (D - L);
     const int64_t pop =
@@ -238,6 +238,21 @@ int adapt_dense_last(const Index* ix, const Batch* b, int fmt, bool maxp, int dl
   while (L + 1 <= D - 1 && density(L) > thr) ++L;
   if (L == b->last_dl && L - 1 > h && density(L) < 0.5 * thr) --L;
   return L > h ? L : dl;
+}
+
+// First tested level of float32 pools: the level whose pools hold about 32 of
+// the populated rows, then by the last call's entries.  The first launch tests
+// every pool of its level against every query; entering one level lower drops
+// one launch (a test per pool of level L) for a test of the pools of level
+// L + 1 that have no entry above them, so it pays while the entries of L fill
+// more than half of its (pool, tile) pairs.  Walk of 2^20 x 1000 rows from this
+// level / from the head (us): 1024 queries 2249 / 2770, 512 queries 1200 / 1598.
+// The subtree walk starts one level lower (up = 0): a level more costs it a
+// step, a level less only idle tests (100,003 x 300, 65 queries: 128 / 133).
+int f32_first_of(const Index* ix, const Batch* b, int up) {
+  const int rule = dense_rule(ix, b->head) - up;
+  if (ix->dense_last != -2 || ix->head_level >= 0 || rule <= b->head) return b->head + 1;
+  return adapt_dense_last(ix, b, b->fmt, b->maxpool, rule, b->head);
 }
 
 // Bucket bits of a call's sparse frontier: subtrees of level nb, at most
@@ -260,8 +275,14 @@ int bucket_bits_of(int sparse_from, int nt) {
 //            2^17 x 2048 (17 MB): 256 queries 243 / 509, 1024 556 / 667
 //   float8   2^20 x 1000 (67 MB): 128 queries 285 / 292, 192 362 / 349
 //            300,007 x 777 (17 MB): 257 queries 283 / 299, 512 394 / 384
-//   float32  2^20 x 1000 (134 MB, 32-query tiles): 256 queries 1157 / 1269,
-//            512 2168 / 1911
+// With float32 pools (32-query tiles) the sides cross by tiles x pools of the
+// level kernels' first level instead, whatever the width:
+//   2^20 x 1000 (32,768 pools): 64 queries 343 / 405, 128 578 / 548,
+//            256 1056 / 839
+//   2^20 x 256: 64 queries 273 / 309, 128 441 / 437, 256 769 / 696
+//   2^17 x 1000 (4,096 pools): 256 queries 219 / 299, 512 344 / 397
+//   2^18 x 1000, max pools (8,192): 256 queries 339 / 408, 512 569 / 574
+//   300,007 x 777 (9,376): 257 queries 457 / 500, 512 704 / 641
 // and 90 against 201 - 327 us for one query.  Larger calls of more than 16
 // tiles were not measured below those sizes and go level by level, as do
 // calls with options that ask for the level kernels (an explicit head or
@@ -273,21 +294,21 @@ void choose_subtree(const Index* ix, Batch* b, int width) {
   if (b->kind != 1 || b->nt < 1 || b->nt > kSubtreeTiles || b->n_epoch < 1 || b->counted ||
       ix->grid > 0 || ix->head_level >= 0)
     return;
-  int first = b->dense_last >= 0 ? b->dense_last : b->head + 1;
-  if (b->fmt == GT_POOL_F32 && ix->dense_last == -2) {
-    // float32 pools have no dense step, but start where the others do
-    const int dl = adapt_dense_last(ix, b, b->fmt, b->maxpool, dense_rule(ix, b->head), b->head);
-    if (dl >= 0) first = dl;
-  }
+  const bool f32 = b->fmt == GT_POOL_F32;
+  int first = b->dense_last >= 0 ? b->dense_last : f32 ? f32_first_of(ix, b, 0) : b->head + 1;
   const int rows = b->nt > 1 ? b->tq : std::min(b->tq, b->nq <= 16 ? 16 : b->nq <= 32 ? 32 : 64);
   // (a first level above the subtrees' roots: the tests start at the roots)
   int top = -1, window = 0;
   if (!gt::subtree_shape(b->fmt, width, b->nt, rows, ix->depth, first, top, window)) return;
   first = std::max(first, top);
   const int64_t pools = ((b->n_epoch - 1) >> (ix->depth - first)) + 1;
-  const int64_t bytes = pools * width * (b->fmt == GT_POOL_F32 ? 4 : b->fmt == GT_POOL_BF16 ? 2 : 1);
-  const int64_t most = int64_t(b->fmt == GT_POOL_F32 ? 1200 : b->fmt == GT_POOL_BF16 ? 360 : 136) * 1000000;
-  if (bytes * b->nt > most) return;
+  if (f32) {
+    const int level = std::max(top, f32_first_of(ix, b, 1));
+    if ((((b->n_epoch - 1) >> (ix->depth - level)) + 1) * b->nt > 100000) return;
+  } else {
+    const int64_t bytes = pools * width * (b->fmt == GT_POOL_BF16 ? 2 : 1);
+    if (bytes * b->nt > int64_t(b->fmt == GT_POOL_BF16 ? 360 : 136) * 1000000) return;
+  }
   b->sub_top = top;
   b->sub_window = window;
   b->sub_first = first;
@@ -1177,6 +1198,8 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
   if (b->dense_last >= 0 && ix->head_level < 0) b->head = b->dense_last - 1;
   b->counted = ix->count_unique && kind == 1 && !b->fixed;
   choose_subtree(ix, b, maxp ? ix->pw : ix->dp);
+  if (kind == 1 && fmt == GT_POOL_F32 && b->sub_top < 0 && !b->counted)
+    b->head = f32_first_of(ix, b, 1) - 1;
   b->nb = bucket_bits_of(b->dense_last >= 0 ? b->dense_last : b->head, nt);
   if (b->sub_top >= 0) b->nb = std::min(b->nb, b->sub_top);  // a subtree's entries share a bucket
   b->profile = ix->profile && !b->fixed;
@@ -1313,7 +1336,7 @@ gt_status finish(Index* ix, Batch* b, int64_t max_results, int64_t* offsets, int
   if (b->kind == 1) {
     // state for the next call's automatic dense level
     b->have_last = true;
-    b->last_dl = b->sub_top >= 0 ? b->sub_first : b->dense_last;
+    b->last_dl = b->sub_top >= 0 ? b->sub_first : b->fmt == GT_POOL_F32 ? b->head + 1 : b->dense_last;
     b->last_walk_fmt = b->fmt;
     b->last_maxpool = b->maxpool;
     b->last_walk_nt = b->nt;

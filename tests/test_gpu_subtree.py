@@ -110,3 +110,23 @@ def test_level_counts(gt, pool):
         assert st["entries"][l] <= st["pairs"][l] and st["pairs"][l + 1] >= 2 * st["entries"][l] - 1
     assert st["leaf_pairs"] >= 2 * st["entries"][D - 1] - 1
     idx.close()
+
+
+@pytest.mark.parametrize("n,d,nq,cap", [(40, 24, 600, 64), (3000, 72, 1025, 1 << 16),
+                                        (20000, 520, 640, 1 << 15)])
+@pytest.mark.parametrize("pool", ("f32", "max_f32"))
+def test_float32_first_level(gt, n, d, nq, cap, pool):
+    """Float32 pools of more than 16 tiles start at the level of about 32 rows
+    and move with the frontier from call to call, never the results."""
+    w = synth.workload_small(n, d, nq, seed_offset=5)
+    idx = gt.GTIndex(torch.from_numpy(w.feats).cuda(), capacity=cap, pools=(pool,))
+    q = torch.from_numpy(w.queries).cuda()
+    rho = np.full(nq, 0.9)
+    rho[::50] = -1.0
+    want = ob.range_search(w.feats, w.queries, rho)
+    for keep in (rho, np.full(nq, -1.0 if n < 1000 else 0.6), rho, rho, rho):
+        w_keep = want if keep is rho else ob.range_search(w.feats, w.queries, keep)
+        _same(idx.query(q, keep, pool=pool).to_lists(), w_keep)
+        assert idx.stats()["head_level"] < idx.stats()["depth"]
+    idx.set_option("head_level", 0)
+    _same(idx.query(q, rho, pool=pool).to_lists(), want)
