@@ -299,7 +299,8 @@ void choose_subtree(const Index* ix, Batch* b, int width) {
   const int rows = b->nt > 1 ? b->tq : std::min(b->tq, b->nq <= 16 ? 16 : b->nq <= 32 ? 32 : 64);
   // (a first level above the subtrees' roots: the tests start at the roots)
   int top = -1, window = 0;
-  if (!gt::subtree_shape(b->fmt, width, b->nt, rows, ix->depth, first, top, window)) return;
+  if (!gt::subtree_shape(b->fmt, width, b->nt, rows, ix->depth, first, b->n_epoch, ix->n_cu, top, window))
+    return;
   first = std::max(first, top);
   const int64_t pools = ((b->n_epoch - 1) >> (ix->depth - first)) + 1;
   if (f32) {

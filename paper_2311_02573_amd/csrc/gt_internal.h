@@ -212,7 +212,8 @@ struct SubtreeArgs {
 };
 // The subtree walk's shape for a call whose first tested level is `first`
 // (false: it does not take the call).
-bool subtree_shape(int fmt, int dp, int nt, int qrows, int depth, int first, int& top, int& window);
+bool subtree_shape(int fmt, int dp, int nt, int qrows, int depth, int first, int64_t n_epoch, int n_cu,
+                   int& top, int& window);
 
 struct LeafArgs {
   int level, dense, nt, dp, tq;

@@ -58,4 +58,22 @@ __device__ __forceinline__ void mma16x16<GT_POOL_F32>(const uint4& a, const uint
   acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
 }
 
+// gfx950 f8f6f4 forms for float8 (e4m3: format 0 for both operands, no
+// block scales): 32 bytes per lane, the lane's two 16-byte slices a0, a1 and
+// the matching slices b0, b1 of the other operand, so A and B lanes again
+// carry the same dimensions.  Same numerics as the fp8 forms above (measured
+// equal), twice the products per instruction.
+typedef __attribute__((ext_vector_type(8))) int i32x8;
+__device__ __forceinline__ i32x8 pack32(const uint4& x0, const uint4& x1) {
+  i32x8 v;
+  v[0] = (int)x0.x; v[1] = (int)x0.y; v[2] = (int)x0.z; v[3] = (int)x0.w;
+  v[4] = (int)x1.x; v[5] = (int)x1.y; v[6] = (int)x1.z; v[7] = (int)x1.w;
+  return v;
+}
+__device__ __forceinline__ void mma_f8_16x16x128(const uint4& a0, const uint4& a1, const uint4& b0,
+                                                 const uint4& b1, f32x4& acc) {
+  acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(pack32(a0, a1), pack32(b0, b1), acc, 0, 0,
+                                                        0, 0, 0, 0);
+}
+
 }  // namespace gt

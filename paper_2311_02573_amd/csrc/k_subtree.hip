@@ -10,6 +10,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "gt_internal.h"
 #include "gt_device.h"
@@ -23,8 +24,11 @@ namespace {
 constexpr int kSubtreeThreads = 512;
 constexpr int kSubtreeLevels = 11;        // most levels below a subtree's root pool
 constexpr int kSubtreeLds = 160 * 1024;
-constexpr int kSteps = 32;                // 64-byte row steps in flight per lane
-constexpr int kWindowLds = 128 * 1024;    // query bytes held at once where a tile does not fit
+constexpr int kWaves = kSubtreeThreads / 64;
+constexpr int kChunk = 1024;              // query bytes a wave copies at once
+constexpr int kWindowChunks = 8 * kWaves; // of a window, where a tile's rows do not fit
+
+typedef __attribute__((address_space(3))) void* lds_ptr;
 
 // LDS: the query rows, then the lists of (pool, mask) entries.  A list of level
 // l holds at most 2^(l - top) entries; consecutive levels alternate between
@@ -34,91 +38,188 @@ __host__ __device__ inline int list_entries(int depth, int top, int which) {
   const int m = depth - 2 - top - which;  // which: 0 the larger, 1 the smaller
   return m < 0 ? 1 : 1 << m;
 }
-__host__ __device__ inline int subtree_lds(int qbytes, int qrows, int depth, int top) {
-  return qrows * (qbytes + 16) + (list_entries(depth, top, 0) + list_entries(depth, top, 1)) * 12 + 64;
+__host__ __device__ inline int subtree_lds(int query_lds, int depth, int top) {
+  return query_lds + (list_entries(depth, top, 0) + list_entries(depth, top, 1)) * 12 + 64;
+}
+// The query rows, padded by 16 bytes each (bank spread), or two windows of them.
+__host__ __device__ inline int query_lds_of(int rowbytes, int qrows, int window) {
+  return window > 0 ? 2 * qrows * (window + 16) : qrows * (rowbytes + 16);
 }
 
-// Copies nbytes (a multiple of 16) of each of the tile's query rows, from
-// column byte `from`, to LDS rows of stride rs.
-__device__ __forceinline__ void stage_queries(unsigned char* lds, const unsigned char* src,
-                                              int rowbytes, int from, int nbytes, int rs,
-                                              int qrows) {
-  const int vpr = nbytes / 16, nvec = qrows * vpr;
-  for (int v0 = 0; v0 < nvec; v0 += 8 * kSubtreeThreads) {
-    uint4 buf[8];
+// The tile's query rows to LDS rows of stride rowbytes + 16, by direct loads of
+// 64 lanes x 16 bytes (wave w copies rows w, w + 8, ...).
+template <int NQB>
+__device__ __forceinline__ void stage_rows(unsigned char* lds, const unsigned char* src, int rowbytes,
+                                           int wave, int lane) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int v = v0 + k * kSubtreeThreads + (int)threadIdx.x, vv = v < nvec ? v : nvec - 1;
-      buf[k] = *reinterpret_cast<const uint4*>(src + (size_t)(vv / vpr) * rowbytes + from + (vv % vpr) * 16);
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int v = v0 + k * kSubtreeThreads + (int)threadIdx.x;
-      if (v < nvec) *reinterpret_cast<uint4*>(lds + (v / vpr) * rs + (v % vpr) * 16) = buf[k];
-    }
+  for (int m = 0; m < 16 * NQB / kWaves; ++m) {
+    const int row = wave + m * kWaves;
+    for (int c = 0; c < rowbytes; c += kChunk)
+      if (c + 16 * lane < rowbytes)
+        __builtin_amdgcn_global_load_lds((const void*)(src + (size_t)row * rowbytes + c + 16 * lane),
+                                         (lds_ptr)(lds + row * (rowbytes + 16) + c), 16, 0, 0);
   }
 }
+
+// The same for the columns of one window, from byte `from`, in two parts: 8
+// chunks a wave to registers, and from there to LDS.  (Not direct loads: with
+// one in flight the compiler lets no LDS read go before all of a wave's loads.)
+template <int NQB>
+struct WindowCopy {
+  static constexpr int M = kWindowChunks / kWaves, CPR = kWindowChunks / (16 * NQB);  // chunks of a wave, row
+  uint4 v[M];
+  __device__ __forceinline__ void load(const unsigned char* src, int rowbytes, int from, int wave, int lane) {
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const int row = (wave * M + m) / CPR, c = (wave * M + m) % CPR * kChunk;
+      const int byte = from + c + 16 * lane;
+      v[m] = ld_global16(src + (size_t)row * rowbytes + (byte < rowbytes ? byte : 0));
+    }
+  }
+  __device__ __forceinline__ void store(unsigned char* buf, int wave, int lane) const {
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const int row = (wave * M + m) / CPR, c = (wave * M + m) % CPR * kChunk;
+      *reinterpret_cast<uint4*>(buf + row * (CPR * kChunk + 16) + c + 16 * lane) = v[m];
+    }
+  }
+};
 
 // Products of one 16-row group with the staged query columns: nsteps 64-byte
 // steps from `row` against `brow`.  The matrix-core operand of lane 16 g + i is
 // row i, 16-byte chunk g; loads in that order touch four lines with each four
 // lanes.  kQuads: four lanes take 64 contiguous bytes of a row (lanes 4 R ..
 // 4 R + 3: row R), and the operand comes from lane 4 i + g (bp).  Kernel with /
-// without (us): float8 of 300,007 x 777, 257 queries 124 / 134; float32 of
-// 100,003 x 300, 65 queries 55 / 60.  Not where the passing between lanes costs
-// more: one block of queries (float32, 524,288 x 500, 1 query 40 / 33), or
-// bfloat16 (4 blocks 88 / 86).
-template <int FMT, int NQB>
-constexpr bool kQuads = FMT != GT_POOL_BF16 && NQB >= 2;
+// without (us): float8 of 300,007 x 777, 257 queries 97 / 106; float32 of
+// 100,003 x 300, 65 queries 51 / 55.  Not where the passing between lanes costs
+// as much: one block of queries (bfloat16, 2^20 x 1000, 23 / 22), windows
+// (float8, 65,536 x 3000, 64 / 54), bfloat16 (2^19 x 256, 512 queries 180 / 172,
+// though 2^20 x 1000, 128 queries 130 / 136).
+template <int FMT, int NQB, bool WIN>
+constexpr bool kQuads = FMT != GT_POOL_BF16 && NQB >= 2 && !WIN;
 
-template <int FMT, int NQB>
-__device__ __forceinline__ void group_products(const unsigned char* row, const unsigned char* brow,
-                                               int rs, int nsteps, int bp, f32x4 (&acc)[NQB]) {
-  for (int s0 = 0; s0 < nsteps; s0 += kSteps) {
-    uint4 x[kSteps];
+__device__ __forceinline__ uint4 by_quads(const uint4& x, int bp) {
+  return make_uint4((uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)x.x),
+                    (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)x.y),
+                    (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)x.z),
+                    (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)x.w));
+}
+
+// The first `left` of C steps of G groups against the staged columns at `b`.
+// The operands of a unit (a step, or the two of a float8 product) are read
+// while the one before it is multiplied: its own reads take longer than its
+// products.  Walk with / without (us): bfloat16 2^19 x 256, 512 queries 168 /
+// 208; 2^20 x 1000, 64 queries 77 / 85; float8 300,007 x 777, 257 queries 112 /
+// 126, and 96 with 128 columns to a product.
+template <int FMT, int NQB, bool WIN, int G, int C>
+__device__ __forceinline__ void step_products(const uint4 (&x)[G][C], const unsigned char* b, int rs,
+                                              int left, int bp, f32x4 (&acc)[G][NQB]) {
+  constexpr int S = FMT == GT_POOL_FP8E4M3 ? 2 : 1;  // steps of a unit
+  constexpr int U = FMT == GT_POOL_FP8E4M3 ? 2 : 4;  // steps of 128 columns: rows hold whole ones
+  uint4 p[2][G][S], q[2][NQB][S];
+  auto read = [&](int c, int o) {
 #pragma unroll
-    for (int c = 0; c < kSteps; c += 4)
-      if (s0 + c < nsteps) {
+    for (int u = 0; u < S; ++u) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int st = s0 + c + u < nsteps ? s0 + c + u : nsteps - 1;
-          x[c + u] = ld_global16(row + 64 * st);
+      for (int k = 0; k < G; ++k) p[o][k][u] = kQuads<FMT, NQB, WIN> ? by_quads(x[k][c + u], bp) : x[k][c + u];
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb) q[o][qb][u] = ld_lds16(b + qb * 16 * rs + 64 * (c + u));
+    }
+  };
+  if (left > 0) read(0, 0);
+#pragma unroll
+  for (int c = 0; c < C; c += S)
+    if (c / U * U < left) {
+      const int o = c / S & 1;
+      if (c % U + S < U || (c + S < C && c + S < left)) read(c + S, o ^ 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+          if constexpr (S == 2)
+            mma_f8_16x16x128(p[o][k][0], p[o][k][1], q[o][qb][0], q[o][qb][1], acc[k][qb]);
+          else
+            mma16x16<FMT>(p[o][k][0], q[o][qb][0], acc[k][qb]);
         }
-      }
-    __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// C steps of a row from step s0 (the last one again past the row's end).
+template <int C>
+__device__ __forceinline__ void load_steps(uint4 (&x)[C], const unsigned char* row, int s0, int nsteps) {
 #pragma unroll
-    for (int c = 0; c < kSteps; ++c)
-      if (s0 + c < nsteps) {
-        uint4 v = x[c];
-        if constexpr (kQuads<FMT, NQB>) {
-          v.x = (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)v.x);
-          v.y = (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)v.y);
-          v.z = (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)v.z);
-          v.w = (uint32_t)__builtin_amdgcn_ds_bpermute(bp, (int)v.w);
-        }
+  for (int c = 0; c < C; c += 4)
+    if (c == 0 || s0 + c < nsteps) {
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb)
-          mma16x16<FMT>(v, ld_lds16(brow + qb * 16 * rs + 64 * (s0 + c)), acc[qb]);
+      for (int u = 0; u < 4; ++u) {
+        const int st = s0 + c + u < nsteps ? s0 + c + u : nsteps - 1;
+        x[c + u] = ld_global16(row + 64 * st);
       }
+    }
+}
+
+// Products of G 16-row groups of each wave where the query columns pass
+// through LDS in windows (wg: windows multiplied so far; on entry `copy` holds
+// the first).  The loads of a block of C steps are issued before the products
+// of the one before it, across windows too, and the next window is on its way
+// while one is multiplied: without either, a level of 2048 bfloat16 columns
+// took 21 us, 12 of them for copying 256 KB.  Walk of 2^17 x 2048, 256 queries:
+// 82 us, 152 before.  (Blocks are what the registers hold: a larger one spills,
+// 98 us.)
+template <int FMT, int NQB, int G>
+__device__ __forceinline__ void windowed_products(const unsigned char* const (&row)[G], bool any,
+                                                  unsigned char* lds, const unsigned char* qsrc,
+                                                  int brow, int rowbytes, int bp, int wave, int lane,
+                                                  uint32_t& wg, WindowCopy<NQB>& copy,
+                                                  f32x4 (&acc)[G][NQB]) {
+  constexpr int W = WindowCopy<NQB>::CPR * kChunk, RS = W + 16, BUF = 16 * NQB * RS;
+  constexpr int C = G == 2 ? 4 : NQB == 4 ? 8 : 16;  // steps of a block and group (what the registers hold)
+  constexpr int NB = W / (64 * C);     // blocks of a window
+  const int nsteps = rowbytes / 64, nblk = (nsteps + C - 1) / C;
+  uint4 x0[G][C], x1[G][C];
+  auto load = [&](uint4 (&x)[G][C], int i) {
+#pragma unroll
+    for (int k = 0; k < G; ++k) load_steps<C>(x[k], row[k], i * C, nsteps);
+  };
+  auto block = [&](const uint4 (&cu)[G][C], uint4 (&nx)[G][C], int i) {
+    if (i % NB == 0) {
+      copy.store(lds + wg % 2u * BUF, wave, lane);  // (all are done with the window before the last)
+      __syncthreads();
+      const int next = (i / NB + 1) * W;
+      copy.load(qsrc, rowbytes, next < rowbytes ? next : 0, wave, lane);
+      ++wg;
+    }
+    if (!any) return;
+    if (i + 1 < nblk) load(nx, i + 1);
     __builtin_amdgcn_sched_barrier(0);
+    step_products<FMT, NQB, true, G, C>(cu, lds + (wg - 1u) % 2u * BUF + brow + i % NB * (64 * C), RS,
+                                  nsteps - i * C, bp, acc);
+  };
+  if (any) load(x0, 0);
+  for (int i = 0; i < nblk; i += 2) {
+    block(x0, x1, i);
+    if (i + 1 < nblk) block(x1, x0, i + 1);
   }
 }
 
 // A wave takes 16 pool rows at a time (16 pools of the first level, then both
-// children of 8 entries), 32 64-byte steps of them in flight.
+// children of 8 entries).
 // Scores, thresholds and decisions are those of the level kernels' direct
 // test (the sums run over the same products in another order, which the
 // thresholds' slack covers).
 // WIN: the tile's query rows do not fit beside the lists and pass through LDS
-// in windows; the waves then step through the windows together, two groups
-// each, so that a window serves up to 16 groups.
+// in windows; the waves then step through the windows together, with two
+// groups each where there are more than 8.
 template <int FMT, int NQB, bool WIN>
 __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs a) {
   using F = WalkFmt<FMT>;
-  constexpr int TQ = F::TQ, NW = kSubtreeThreads / 64, G = WIN ? 2 : 1;
+  constexpr int TQ = F::TQ, NW = kWaves;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   __shared__ uint32_t cnt[GT_MAX_LEVELS], prs[GT_MAX_LEVELS];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, g4 = lane >> 4;
   // the tiles of a subtree run on one XCD, which then shares its rows in L2
   const int i = blockIdx.x / kXcds;
@@ -130,17 +231,21 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
   if (tmask == 0ull) return;
 
   const int rowbytes = a.dp * F::ESZ;
-  const int qbytes = WIN ? a.window : rowbytes;  // query columns held at once
-  const int rs = qbytes + 16;                    // LDS row stride (bank spread)
+  const int rs = (WIN ? a.window : rowbytes) + 16;  // LDS row stride (bank spread)
   const int cap0 = list_entries(D, a.top, 0);
-  uint64_t* const mask0 = reinterpret_cast<uint64_t*>(lds + a.qrows * rs);
+  uint64_t* const mask0 = reinterpret_cast<uint64_t*>(lds + query_lds_of(rowbytes, 16 * NQB, WIN ? a.window : 0));
   uint64_t* const mask1 = mask0 + cap0;
   uint32_t* const node0 = reinterpret_cast<uint32_t*>(mask1 + list_entries(D, a.top, 1));
   uint32_t* const node1 = node0 + cap0;
   if (tid < GT_MAX_LEVELS) cnt[tid] = prs[tid] = 0u;
   const unsigned char* qsrc =
       reinterpret_cast<const unsigned char*>(a.qtile) + (size_t)t * TQ * rowbytes;
-  if (!WIN) stage_queries(lds, qsrc, rowbytes, 0, rowbytes, rs, a.qrows);
+  WindowCopy<NQB> copy;
+  if constexpr (WIN)
+    copy.load(qsrc, rowbytes, 0, wave, lane);
+  else
+    stage_rows<NQB>(lds, qsrc, rowbytes, wave, lane);
+  uint32_t windows = 0;  // multiplied so far
   float th0[NQB];
   int qe[NQB];
 #pragma unroll
@@ -151,6 +256,8 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
   const uint32_t slot = (uint32_t)(sub >> (a.top - a.nb)) * (uint32_t)a.nt + (uint32_t)t;
   const unsigned char* brow = lds + c16 * rs + 16 * g4;
   const int bp = 4 * (4 * c16 + g4);
+
+  __builtin_amdgcn_s_waitcnt(0x0070);  // this wave's direct loads (a barrier alone does not wait)
 
   for (int l = a.first; l < D; ++l) {
     __syncthreads();  // the query rows, and the entries of the level above
@@ -174,90 +281,118 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
     for (int qb = 0; qb < NQB; ++qb)
       th[qb] = FMT == GT_POOL_FP8E4M3 ? ldexpf(th0[qb] * kFp8ThrFactor, -(qe[qb] + a.lexp[l])) : th0[qb];
     const unsigned char* level = reinterpret_cast<const unsigned char*>(a.pools) +
-                                 (size_t)((int64_t(1) << l) - 1) * rowbytes + 16 * (kQuads<FMT, NQB> ? lane & 3 : g4);
+                                 (size_t)((int64_t(1) << l) - 1) * rowbytes + 16 * (kQuads<FMT, NQB, WIN> ? lane & 3 : g4);
     uint32_t pairs = 0;
-    // (every wave takes part in every round of a windowed tile)
-    for (uint32_t g0 = WIN ? 0u : (uint32_t)wave; 16u * g0 < n; g0 += G * NW) {
-      uint32_t node[G];
-      uint64_t pm[G];
-      const unsigned char* row[G];  // of the row this lane loads
-      f32x4 acc[G][NQB];
-      bool any[G];  // the wave has this group
-#pragma unroll
-      for (int k = 0; k < G; ++k) {
-        const uint32_t gf = 16u * (g0 + (WIN ? (uint32_t)(wave + k * NW) : 0u));
-        any[k] = gf < n;
-        const uint32_t r = gf + (uint32_t)c16, rr = r < n ? r : any[k] ? gf : 0u;
-        if (head) {
-          node[k] = root + rr;
-          pm[k] = r < n ? tmask : 0ull;
-        } else {
-          node[k] = 2u * in_node[rr >> 1] + (rr & 1u);
-          pm[k] = r < n && ((int64_t)node[k] << shift) < a.n_epoch ? in_mask[rr >> 1] : 0ull;
-        }
-        const uint32_t rn = kQuads<FMT, NQB> ? (uint32_t)__shfl((int)node[k], lane >> 2, 64) : node[k];
-        row[k] = level + (size_t)rn * rowbytes;
-#pragma unroll
-        for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-          for (int x = 0; x < 4; ++x) acc[k][qb][x] = 0.0f;
+    const int nsteps = rowbytes / 64;
+
+    struct Group {
+      uint32_t node;             // of row c16, and its live queries
+      uint64_t pm;
+      const unsigned char* row;  // this lane loads
+    };
+    // The 16 rows from row gf (gf >= n: any row, no queries).
+    auto group = [&](uint32_t gf) {
+      Group g;
+      const uint32_t r = gf + (uint32_t)c16, rr = r < n ? r : gf < n ? gf : 0u;
+      if (head) {
+        g.node = root + rr;
+        g.pm = r < n ? tmask : 0ull;
+      } else {
+        g.node = 2u * in_node[rr >> 1] + (rr & 1u);
+        g.pm = r < n && ((int64_t)g.node << shift) < a.n_epoch ? in_mask[rr >> 1] : 0ull;
       }
-      if constexpr (WIN) {
-        for (int from = 0; from < rowbytes; from += qbytes) {
-          const int nb = min(qbytes, rowbytes - from);
-          __syncthreads();  // every wave is done with the previous window
-          stage_queries(lds, qsrc, rowbytes, from, nb, rs, a.qrows);
-          __syncthreads();
+      const uint32_t rn = kQuads<FMT, NQB, WIN> ? (uint32_t)__shfl((int)g.node, lane >> 2, 64) : g.node;
+      g.row = level + (size_t)rn * rowbytes;
+      return g;
+    };
+    auto clear = [&](f32x4 (&acc)[NQB]) {
 #pragma unroll
-          for (int k = 0; k < G; ++k)
-            if (any[k])
-              group_products<FMT, NQB>(row[k] + from, brow, rs, nb / 64, bp, acc[k]);
+      for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[qb][x] = 0.0f;
+    };
+    // The group's surviving entries, to the next list or the frontier.
+    auto emit = [&](const Group& g, const f32x4 (&acc)[NQB]) {
+      // register x of lane j: row 4 (j / 16) + x, query 16 qb + j % 16; lane
+      // r < 16 ends with row r's mask
+      uint64_t mine = 0ull;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        uint64_t part = 0ull;
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb) {
+          const uint64_t bal = __ballot(acc[qb][x] >= th[qb]);
+          part |= ((bal >> (16 * ((lane & 15) >> 2))) & 0xffffull) << (16 * qb);
+        }
+        if ((lane & 3) == x) mine = part;
+      }
+      mine = lane < 16 ? (mine & g.pm) : 0ull;
+      if (lane < 16) pairs += (uint32_t)__popcll(g.pm);
+      const uint64_t bal = __ballot(mine != 0ull);
+      if (bal == 0ull) return;
+      const uint32_t rank = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+      uint32_t base = 0;
+      if (l < D - 1) {
+        if (lane == 0) base = atomicAdd(&cnt[l], (uint32_t)__popcll(bal));
+        base = __shfl(base, 0, 64);
+        if (mine) {
+          on[base + rank] = g.node;
+          om[base + rank] = mine;
         }
       } else {
-        group_products<FMT, NQB>(row[0], brow, rs, rowbytes / 64, bp, acc[0]);
+        if (lane == 0)
+          base = atomicAdd(&a.lvl_count[(size_t)l * kMaxSlots + slot], (uint32_t)__popcll(bal));
+        base = __shfl(base, 0, 64);
+        if (mine) {
+          if (base + rank < a.bcap) {
+            const size_t o = (size_t)slot * a.bcap + base + rank;
+            a.out_node[o] = g.node;
+            a.out_mask[o] = mine;
+          } else {
+            atomicOr(a.over, 1u);
+          }
+        }
       }
+    };
+
+    if constexpr (WIN) {
+      // every wave takes part in every round, with one or two groups
+      const int b0 = c16 * rs + 16 * g4;
+      auto round = [&](uint32_t g0, auto ng) {
+        constexpr int G = decltype(ng)::value;
+        Group g[G];
+        const unsigned char* row[G];
+        f32x4 acc[G][NQB];
 #pragma unroll
-      for (int k = 0; k < G; ++k) {
-        // register x of lane j: row 4 (j / 16) + x, query 16 qb + j % 16; lane
-        // r < 16 ends with row r's mask
-        uint64_t mine = 0ull;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          uint64_t part = 0ull;
-#pragma unroll
-          for (int qb = 0; qb < NQB; ++qb) {
-            const uint64_t bal = __ballot(acc[k][qb][x] >= th[qb]);
-            part |= ((bal >> (16 * ((lane & 15) >> 2))) & 0xffffull) << (16 * qb);
-          }
-          if ((lane & 3) == x) mine = part;
+        for (int k = 0; k < G; ++k) {
+          g[k] = group(16u * (g0 + (uint32_t)(wave + k * NW)));
+          row[k] = g[k].row;
+          clear(acc[k]);
         }
-        mine = lane < 16 ? (mine & pm[k]) : 0ull;
-        if (lane < 16) pairs += (uint32_t)__popcll(pm[k]);
-        const uint64_t bal = __ballot(mine != 0ull);
-        if (bal == 0ull) continue;
-        const uint32_t rank = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-        uint32_t base = 0;
-        if (l < D - 1) {
-          if (lane == 0) base = atomicAdd(&cnt[l], (uint32_t)__popcll(bal));
-          base = __shfl(base, 0, 64);
-          if (mine) {
-            on[base + rank] = node[k];
-            om[base + rank] = mine;
-          }
-        } else {
-          if (lane == 0)
-            base = atomicAdd(&a.lvl_count[(size_t)l * kMaxSlots + slot], (uint32_t)__popcll(bal));
-          base = __shfl(base, 0, 64);
-          if (mine) {
-            if (base + rank < a.bcap) {
-              const size_t o = (size_t)slot * a.bcap + base + rank;
-              a.out_node[o] = node[k];
-              a.out_mask[o] = mine;
-            } else {
-              atomicOr(a.over, 1u);
-            }
-          }
+        windowed_products<FMT, NQB, G>(row, 16u * (g0 + (uint32_t)wave) < n, lds, qsrc, b0, rowbytes, bp,
+                                       wave, lane, windows, copy, acc);
+#pragma unroll
+        for (int k = 0; k < G; ++k) emit(g[k], acc[k]);
+      };
+      for (uint32_t g0 = 0; 16u * g0 < n; g0 += 2 * NW) {
+        if (16u * (g0 + (uint32_t)NW) < n)
+          round(g0, std::integral_constant<int, 2>());
+        else
+          round(g0, std::integral_constant<int, 1>());
+      }
+    } else {
+      constexpr int C = FMT == GT_POOL_FP8E4M3 ? 16 : 32;  // steps in flight
+      for (uint32_t gw = (uint32_t)wave; 16u * gw < n; gw += NW) {
+        const Group g = group(16u * gw);
+        f32x4 acc[1][NQB];
+        clear(acc[0]);
+        for (int s0 = 0; s0 < nsteps; s0 += C) {
+          uint4 x[1][C];
+          load_steps<C>(x[0], g.row, s0, nsteps);
+          __builtin_amdgcn_sched_barrier(0);
+          step_products<FMT, NQB, false, 1, C>(x, brow + 64 * s0, rs, nsteps - s0, bp, acc);
         }
+        emit(g, acc[0]);
       }
     }
     for (int o = 8; o >= 1; o >>= 1) pairs += __shfl_xor(pairs, o, 64);
@@ -272,7 +407,7 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
 
 template <int FMT, int NQB, bool WIN>
 hipError_t launch_subtree(const SubtreeArgs& a, hipStream_t s) {
-  const int bytes = subtree_lds(WIN ? a.window : a.dp * WalkFmt<FMT>::ESZ, a.qrows, a.depth, a.top);
+  const int bytes = subtree_lds(query_lds_of(a.dp * WalkFmt<FMT>::ESZ, a.qrows, WIN ? a.window : 0), a.depth, a.top);
   const int64_t subs = ((a.n_epoch - 1) >> (a.depth - a.top)) + 1;
   const int64_t grid = kXcds * ((subs + kXcds - 1) / kXcds) * a.nt;
   const void* fn = reinterpret_cast<const void*>(k_walk_subtree<FMT, NQB, WIN>);
@@ -295,32 +430,36 @@ hipError_t launch_subtree_fmt(const SubtreeArgs& a, hipStream_t s) {
 
 int esz_of(int fmt) { return fmt == GT_POOL_F32 ? 4 : fmt == GT_POOL_BF16 ? 2 : 1; }
 
-bool subtree_fits(int qbytes, int qrows, int depth, int top) {
-  return depth - 1 - top <= kSubtreeLevels && subtree_lds(qbytes, qrows, depth, top) + 512 <= kSubtreeLds;
+bool subtree_fits(int query_lds, int depth, int top) {
+  return depth - 1 - top <= kSubtreeLevels && subtree_lds(query_lds, depth, top) + 512 <= kSubtreeLds;
 }
 
 }  // namespace
 
-// About one workgroup per CU over all tiles (2^8 subtrees for one tile), and
-// more, smaller subtrees where the frontier lists would not fit beside the
-// query rows.  Query rows that do not fit with the largest lists are windowed.
-bool subtree_shape(int fmt, int dp, int nt, int qrows, int depth, int first, int& top, int& window) {
-  if (first > depth - 1 || depth > 31) return false;
-  int lg = 0;
-  while ((1 << lg) < nt) ++lg;
+// As many subtrees as give every CU of an XCD at most one workgroup over all
+// tiles (each holds a CU's registers; 2^8 for one tile of a full tree), and
+// more, smaller ones where the frontier lists would not fit beside the query
+// rows.  Query rows that do not fit with the largest lists are windowed.
+bool subtree_shape(int fmt, int dp, int nt, int qrows, int depth, int first, int64_t n_epoch, int n_cu,
+                   int& top, int& window) {
+  if (first > depth - 1 || depth > 31 || n_epoch < 1) return false;
+  auto per_xcd = [&](int t) { return ((((n_epoch - 1) >> (depth - t)) + kXcds) / kXcds) * nt; };
+  int most = 0;
+  while (most < depth - 1 && per_xcd(most + 1) <= n_cu / kXcds) ++most;
   const int rowbytes = dp * esz_of(fmt);
-  window = qrows * (rowbytes + 16) + 12 * 1024 <= kSubtreeLds ? 0 : kWindowLds / qrows;
-  for (top = std::max(std::min(std::max(8 - lg, 0), first), depth - 1 - kSubtreeLevels); top <= depth - 1; ++top)
-    if (subtree_fits(window > 0 ? window : rowbytes, qrows, depth, top)) return true;
+  window = qrows * (rowbytes + 16) + 12 * 1024 <= kSubtreeLds ? 0 : kWindowChunks / qrows * kChunk;
+  for (top = std::max(std::min(most, first), depth - 1 - kSubtreeLevels); top <= depth - 1; ++top)
+    if (subtree_fits(query_lds_of(rowbytes, qrows, window), depth, top)) return true;
   return false;
 }
 
 hipError_t launch_walk_subtree(int fmt, const SubtreeArgs& a, hipStream_t s) {
   if (a.n_epoch < 1 || a.nt < 1 || a.nt > kMaxTiles || a.dp < 128 || a.dp % 128 != 0 || a.nb < 0 ||
       a.nb > kMaxBucketBits || ((int64_t)a.nt << a.nb) > kMaxSlots || a.top < a.nb ||
-      a.first < a.top || a.first > a.depth - 1 || a.depth > 31 || a.window < 0 || a.window % 128 != 0 ||
+      a.first < a.top || a.first > a.depth - 1 || a.depth > 31 || a.qrows < 16 ||
+      (a.window != 0 && a.window != kWindowChunks / a.qrows * kChunk) ||
       a.n_epoch > (int64_t(1) << a.depth) ||
-      !subtree_fits(a.window > 0 ? a.window : a.dp * esz_of(fmt), a.qrows, a.depth, a.top))
+      !subtree_fits(query_lds_of(a.dp * esz_of(fmt), a.qrows, a.window), a.depth, a.top))
     return hipErrorInvalidValue;
   switch (fmt) {
     case GT_POOL_BF16: return launch_subtree_fmt<GT_POOL_BF16>(a, s);

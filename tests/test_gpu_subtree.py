@@ -130,3 +130,20 @@ def test_float32_first_level(gt, n, d, nq, cap, pool):
         assert idx.stats()["head_level"] < idx.stats()["depth"]
     idx.set_option("head_level", 0)
     _same(idx.query(q, rho, pool=pool).to_lists(), want)
+
+
+@pytest.mark.parametrize("n,d,nq,pool", [(5000, 1300, 500, "f32"), (5000, 1300, 1000, "max_bf16"),
+                                         (5000, 1152, 1000, "bf16"), (4000, 2400, 600, "fp8"),
+                                         (6000, 200, 1000, "fp8"), (4000, 900, 500, "max_f32")])
+def test_many_rows_per_workgroup(gt, n, d, nq, pool):
+    """Sixteen tiles leave few subtrees, so a wave takes several groups of rows
+    (two at a time where the queries pass in windows)."""
+    w = synth.workload_small(n, d, nq, seed_offset=9)
+    idx = gt.GTIndex(torch.from_numpy(w.feats).cuda(), pools=(pool,))
+    q = torch.from_numpy(w.queries).cuda()
+    rho = np.full(nq, 0.9)
+    rho[::40] = -1.0  # every tile keeps every row
+    want = ob.range_search(w.feats, w.queries, rho)
+    _same(idx.query(q, rho, pool=pool).to_lists(), want)
+    assert idx.stats()["frontier_launches"] == 1
+    _same(_levels(idx, q, rho, pool), want)
