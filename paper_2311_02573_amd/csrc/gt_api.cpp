@@ -913,7 +913,7 @@ gt_status enqueue_tail(Index* ix, Batch* b) {
   const int first = b->dense_last >= 0 ? b->dense_last : b->head;
   HIPCHK(gt::launch_recheck(b->hits, b->band_idx, &b->ctr->nband, (unsigned long long)b->hit_cap,
                             b->qf, ix->leaves, ix->d, ix->dp, ix->ff, b->rho, qcount_of(b),
-                            b->lvl_count, first, walked ? ix->depth : 0, b->ctr, s));
+                            b->lvl_count, first, walked ? ix->depth : 0, b->qexp, b->nq, b->ctr, s));
   ev_mark(b, 4);
   TRY(ensure_out(b, 1));
   b->spec_direct = b->tgt_ids != nullptr;
@@ -1211,34 +1211,6 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
     b->events = true;
   }
   ev_mark(b, 0);
-  {
-    gt::CallBegin g{};
-    // a walk's level counters with the counters behind them, or only those
-    const size_t row0 = kind == 1 ? 0 : gt::kQCountRow;
-    const gt::QCount qc = qcount_of(b);
-    g.p[0] = reinterpret_cast<uint4*>(b->ctr);
-    g.n16[0] = sizeof(gt::DevCounters) / 16;
-    g.p[1] = reinterpret_cast<uint4*>(b->tile_mask);
-    g.n16[1] = (int64_t)gt::kMaxTiles * 8 / 16;
-    g.p[2] = reinterpret_cast<uint4*>(b->lvl_count + row0 * gt::kMaxSlots);
-    g.n16[2] = (int64_t)(GT_MAX_LEVELS - row0) * gt::kMaxSlots * 4 / 16;
-    g.p[3] = reinterpret_cast<uint4*>(qc.p);
-    g.n16[3] = qc.p == b->qcount ? (int64_t)nq_pad * 4 / 16 : 0;
-    g.rho = b->rho;
-    g.nq = nq;
-    const double* arg = nullptr;
-    if (b->h_rho) {
-      if (nq > 0) memcpy(b->h_rho, rho, (size_t)nq * 8);
-      g.rho_host = b->h_rho;
-    } else if (nq <= gt::kRhoArg) {
-      arg = rho;
-    } else {
-      HIPCHK(hipMemcpyAsync(b->rho, rho, (size_t)nq * 8, hipMemcpyHostToDevice, s));
-      g.nq = 0;
-    }
-    if (nq == 0) arg = nullptr;
-    HIPCHK(gt::launch_call_begin(g, arg, s));
-  }
   if (b->counted) {
     const int64_t words = (int64_t(2) << ix->depth) / 32 + 1;
     if (!b->bitmap) {
@@ -1247,17 +1219,53 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
     }
     TRY(zero_dev(b->bitmap, (size_t)words * 4, s));
   }
-  if (nq > 0) {
+  {
+    gt::QueryPrep g{};
+    // a walk's level counters with the counters behind them, or only those
+    const size_t row0 = kind == 1 ? 0 : gt::kQCountRow;
+    const gt::QCount qc = qcount_of(b);
+    g.p[0] = reinterpret_cast<uint4*>(b->ctr);
+    g.n16[0] = sizeof(gt::DevCounters) / 16;
+    g.p[1] = reinterpret_cast<uint4*>(b->lvl_count + row0 * gt::kMaxSlots);
+    g.n16[1] = (int64_t)(GT_MAX_LEVELS - row0) * gt::kMaxSlots * 4 / 16;
+    g.p[2] = reinterpret_cast<uint4*>(qc.p);
+    g.n16[2] = qc.p == b->qcount ? (int64_t)nq_pad * 4 / 16 : 0;
     // reduced query copies only for the call's pool format; the absolute
     // terms of the subtraction step only for bfloat16 sum pools
     const bool w16 = kind == 1 && fmt == GT_POOL_BF16, w8 = kind == 1 && fmt == GT_POOL_FP8E4M3;
-    const bool w32s = kind == 1 && fmt == GT_POOL_F32 && ix->signed_mode;
-    HIPCHK(gt::launch_query_prep(q, nq, ix->d, ix->dp, tq, b->rho, ix->d_mmin, b->qf,
-                                 w16 ? b->qbf : nullptr, w8 ? b->q8 : nullptr, b->qexp, b->invn_q,
-                                 b->qq, b->thr, b->thr_gemm, b->tile_mask,
-                                 w16 && !maxp ? ix->master + level_row(0) * ix->dp : nullptr,
-                                 w16 && !maxp ? b->sabs : nullptr, w32s ? b->qw : nullptr, ix->pw,
-                                 ix->signed_mode ? ix->sbound : 0.0f, &b->ctr->err, nq_pad, s));
+    g.q = q;
+    g.nq = nq;
+    g.nq_pad = nq_pad;
+    g.d = ix->d;
+    g.dp = ix->dp;
+    g.tq = tq;
+    g.pw = ix->pw;
+    g.rho = b->rho;
+    g.rho_src = b->rho;
+    g.mmin = ix->d_mmin;
+    g.qf = b->qf;
+    g.qbf = w16 ? b->qbf : nullptr;
+    g.q8 = w8 ? b->q8 : nullptr;
+    g.qw = kind == 1 && fmt == GT_POOL_F32 && ix->signed_mode ? b->qw : nullptr;
+    g.qexp = b->qexp;
+    g.invn_q = b->invn_q;
+    g.qq = b->qq;
+    g.thr = b->thr;
+    g.thr_gemm = b->thr_gemm;
+    g.sabs = w16 && !maxp ? b->sabs : nullptr;
+    g.tile_mask = b->tile_mask;
+    g.root = w16 && !maxp ? ix->master + level_row(0) * ix->dp : nullptr;
+    g.sbound = ix->signed_mode ? ix->sbound : 0.0f;
+    const double* arg = nullptr;
+    if (nq <= gt::kRhoArg) {
+      arg = rho;
+    } else if (b->h_rho) {
+      memcpy(b->h_rho, rho, (size_t)nq * 8);
+      g.rho_src = b->h_rho;
+    } else {
+      HIPCHK(hipMemcpyAsync(b->rho, rho, (size_t)nq * 8, hipMemcpyHostToDevice, s));
+    }
+    HIPCHK(gt::launch_query_prep(g, arg, s));
   }
   ev_mark(b, 1);
   if (nq > 0 && b->n_epoch > 0) {

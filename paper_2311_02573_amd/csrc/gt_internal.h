@@ -246,14 +246,28 @@ struct LeafArgs {
   int64_t bit_base;         // tree row of leaf 0
 };
 
-// Start of a call: ranges to clear (16-byte pieces) and its thresholds.
+// Start of a call: ranges to clear (16-byte pieces) and its queries.
 constexpr int kRhoArg = 256;
-struct CallBegin {
-  uint4* p[4];
-  int64_t n16[4];
-  double* rho;
-  const double* rho_host;
-  int nq;
+constexpr int kBadQuery = 1 << 20;  // qexp of a query with a value that is not allowed
+struct QueryPrep {
+  uint4* p[3];
+  int64_t n16[3];
+  const float* q;          // [nq][d]
+  int nq, nq_pad, d, dp, tq, pw;
+  const double* rho_src;   // thresholds (device or pinned host memory)
+  double* rho;             // device copy
+  const double* mmin;
+  float* qf;               // [nq_pad][dp]
+  uint16_t* qbf;           // reduced copies, or null
+  uint8_t* q8;
+  float* qw;
+  int* qexp;
+  float* invn_q;
+  double* qq;
+  float *thr, *thr_gemm, *sabs;
+  uint64_t* tile_mask;
+  const float* root;       // root pool, or null
+  float sbound;
 };
 struct RhoArg {
   double v[kRhoArg];
@@ -452,20 +466,14 @@ hipError_t launch_signed_bottom(const float* leaves, float* parent, int64_t firs
                                 const IngestOut* gate, hipStream_t s);
 hipError_t launch_tree_update(const TreeArgs& a, bool max_pool, int child, hipStream_t s);
 hipError_t launch_zero_tails(void* tree, int row_bytes, int depth, int64_t n, hipStream_t s);
-// rho: thresholds on the host (at most kRhoArg, passed as arguments), or NULL:
-// a.rho_host, pinned, is read by the device
-hipError_t launch_call_begin(const CallBegin& a, const double* rho, hipStream_t s);
 hipError_t launch_level_max(const float* rows, int64_t nrows, int dp, float* out_max, hipStream_t s);
 hipError_t launch_fp8_exps(const float* level_max, int depth, int* lexp, hipStream_t s);
 // float8 copies of levels first .. last (rows past the last populated pool: zero)
 hipError_t launch_quant_fp8(const float* tree, uint8_t* p8, int w, int first, int last, int depth,
                             int64_t n, const int* lexp, unsigned int* over, hipStream_t s);
-hipError_t launch_query_prep(const float* q, int nq, int d, int dp, int tq, const double* rho,
-                             const double* mmin, float* qf, uint16_t* qbf, uint8_t* q8, int* qexp,
-                             float* invn_q, double* qq, float* thr, float* thr_gemm,
-                             uint64_t* tile_mask, const float* root, float* sabs,
-                             float* qw, int pw, float sbound,
-                             unsigned int* err, int nq_pad, hipStream_t s);
+// rho: thresholds on the host (at most kRhoArg, passed as arguments), or NULL:
+// a.rho_src is read by the device
+hipError_t launch_query_prep(QueryPrep a, const double* rho, hipStream_t s);
 hipError_t launch_walk_level(int fmt, const WalkLevelArgs& a, int grid, hipStream_t s);
 hipError_t launch_walk_sub(const WalkLevelArgs& a, int grid, hipStream_t s);
 hipError_t launch_walk_subtree(int fmt, const SubtreeArgs& a, hipStream_t s);
@@ -478,7 +486,7 @@ hipError_t launch_dense_level(int fmt, const DenseLevelArgs& a, hipStream_t s);
 hipError_t launch_recheck(Hit* hits, const uint32_t* band_idx, const unsigned long long* nband,
                           unsigned long long cap, const float* qf, const float* leaves, int d,
                           int dp, const double* ff, const double* rho, QCount qcount,
-                          const uint32_t* lvl_count, int first, int levels, DevCounters* ctr,
+                          const uint32_t* lvl_count, int first, int levels, const int* qexp, int nq, DevCounters* ctr,
                           hipStream_t s);
 // Offsets, statistics, and every accepted pair to its query's segment.
 hipError_t launch_place(const PlaceArgs& a, hipStream_t s);

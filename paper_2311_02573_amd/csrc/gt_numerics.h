@@ -39,28 +39,11 @@ __device__ __forceinline__ uint16_t bf16_up(float x) {
   return (uint16_t)hi;
 }
 
-// Least OCP float8 e4m3 value >= x, for x >= 0 given exactly as a double.
+// Least OCP float8 e4m3 value >= x / 2^lexp, for a finite float32 x >= 0.
 // e4m3: exponent bias 7, 3 mantissa bits, subnormals m * 2^-9, largest finite
-// 448 (code 0x7E); 0x7F is NaN.  Returns 0xFF when x > 448.
-__device__ __forceinline__ uint32_t e4m3_up(double x) {
-  if (!(x > 0.0)) return 0u;
-  if (x > 448.0) return 0xFFu;
-  int e;
-  double m = frexp(x, &e);            // x = m * 2^e, m in [0.5, 1)
-  int E = e - 1;                      // x = (2m) * 2^E
-  if (E < -6) {                       // below the smallest normal 2^-6
-    double k = ceil(ldexp(x, 9));     // multiples of 2^-9; k == 8 is 2^-6 = code 8
-    return (uint32_t)k;
-  }
-  int mm = (int)ceil(ldexp(2.0 * m - 1.0, 3));
-  if (mm == 8) { mm = 0; E += 1; }
-  uint32_t code = (uint32_t)(((E + 7) << 3) | mm);
-  return code > 0x7Eu ? 0xFFu : code;
-}
-
-// e4m3_up(x / 2^lexp) of a finite float32 x >= 0 on its bits: the float64
-// path's conversions and scalings took a float8 pass over a tree 3x as long as
-// its bytes need.
+// 448 (code 0x7E); 0x7F is NaN.  Returns 0xFF past 448.  On the bits of x:
+// float64 conversions and scalings took a float8 pass over a tree 3x as long
+// as its bytes need.
 __device__ __forceinline__ uint32_t e4m3_up_f32(float x, int lexp) {
   const uint32_t u = __float_as_uint(x);
   if (u == 0u) return 0u;

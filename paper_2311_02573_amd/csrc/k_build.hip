@@ -24,22 +24,6 @@ __global__ void k_zero_u32(uint32_t* p, int64_t n) {
     p[i] = 0u;
 }
 
-// Start of a query call in one launch: clears its counters and moves the
-// thresholds to the device, from pinned host memory or (KARG) from the kernel
-// arguments.  As four clearing launches and a copy this was 11 us of the
-// device and most of the calls' launch gaps.
-template <bool KARG>
-__global__ __launch_bounds__(256) void k_call_begin(CallBegin a, RhoArg r) {
-  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
-  for (int k = 0; k < 4; ++k)
-    for (int64_t i = i0; i < a.n16[k]; i += step) a.p[k][i] = make_uint4(0u, 0u, 0u, 0u);
-  if constexpr (KARG) {
-    if (blockIdx.x == 0 && (int)threadIdx.x < a.nq) a.rho[threadIdx.x] = r.v[threadIdx.x];
-  } else {
-    for (int64_t i = i0; i < a.nq; i += step) a.rho[i] = a.rho_host[i];
-  }
-}
-
 __device__ __forceinline__ float load_feature(const void* src, int dtype, int64_t idx) {
   if (dtype == GT_F16) return __half2float(reinterpret_cast<const __half*>(src)[idx]);
   if (dtype == GT_BF16)
@@ -464,95 +448,142 @@ __global__ void k_quant_fp8(const float* __restrict__ tree, uint8_t* __restrict_
   }
 }
 
-// One workgroup of 256 threads per (padded) query.
-__global__ __launch_bounds__(256) void k_query_prep(
-    const float* __restrict__ q, int nq, int d, int dp, int tq, const double* __restrict__ rho,
-    const double* __restrict__ mmin, float* qf, uint16_t* qbf, uint8_t* q8, int* qexp,
-    float* invn_q, double* qq_out, float* thr, float* thr_gemm, uint64_t* tile_mask,
-    const float* __restrict__ root, float* sabs, float* qw, int pw, float sbound,
-    unsigned int* err) {
-  __shared__ float qs[4096];
-  __shared__ float red[4];
-  __shared__ double l1red[4], l2red[4];
-  const int b = blockIdx.x, t = threadIdx.x;
-  const bool real = b < nq;
-  float mx = 0.0f;
-  bool bad = false;
-  const bool sgn = sbound > 0.0f;  // signed index: any finite value
-  for (int k = t; k < d; k += blockDim.x) {
-    const float v = real ? q[(int64_t)b * d + k] : 0.0f;
-    if (sgn ? !isfinite(v) : (!(v >= 0.0f) || isinf(v))) bad = true;
-    qs[k] = v;
-    mx = fmaxf(mx, v);
+// Start of a query call: clears the call's counters and prepares its queries,
+// in one launch (every workgroup clears a share; nothing prepared lies in the
+// cleared ranges).  A wave takes one (padded) query and a workgroup eight, one
+// byte of a tile's mask of live queries, which so needs no atomics and no
+// clearing; a query that is not allowed is marked in qexp.  Bound by its round
+// trips: 1024 queries of 1000 columns 12.5 us (16 and 3 as two launches), 4096
+// 20 (30 and 4), one query 10 (5 and 3, and a launch).
+constexpr int kPrepQueries = 8;
+typedef __attribute__((address_space(3))) void* lds_ptr;
+template <bool KARG>
+__global__ __launch_bounds__(64 * kPrepQueries) void k_query_prep(QueryPrep a, RhoArg r) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  {
+    const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + t, step = (int64_t)gridDim.x * blockDim.x;
+    for (int k = 0; k < 3; ++k)
+      for (int64_t i = i0; i < a.n16[k]; i += step) a.p[k][i] = make_uint4(0u, 0u, 0u, 0u);
   }
-  if (bad) atomicOr(err, 1u);
-  // |q|_1 + |root pool|_1 (any order: only an upper bound is needed); for a
-  // signed index |q|_1 alone, which sets the threshold's shift B |q|_1
-  double l1 = 0.0;
-  for (int k = t; k < d; k += blockDim.x) l1 += (double)fabsf(qs[k]);
-  if (root)
-    for (int k = t; k < dp; k += blockDim.x) l1 += (double)root[k];
-  // |q|^2 by a fixed-order parallel sum (deterministic, relative error below
+  if ((int)blockIdx.x >= a.nq_pad / kPrepQueries) return;
+  __shared__ int live[kPrepQueries];
+  const int b = blockIdx.x * kPrepQueries + wave, d = a.d, dp = a.dp;
+  const bool real = b < a.nq;
+  const bool sgn = a.sbound > 0.0f;  // signed index: any finite value
+  double rho = 0.0;
+  if (real) rho = KARG ? r.v[b] : a.rho_src[b];
+  // The wave's row, and the root pool's, in LDS.  (The loads are all in flight
+  // from a rolled loop; unrolled to hold them in registers the kernel was 18 KB
+  // of code run once, 13 us for one query of 1000 columns, for its fetch.)
+  extern __shared__ float rows[];
+  float* const row = rows + wave * dp;
+  float* const root = rows + kPrepQueries * dp;
+  const float* q = a.q + (int64_t)b * d;
+#pragma unroll 1
+  for (int c = 0; c < dp; c += 64)
+    if (real && c + lane < d)
+      __builtin_amdgcn_global_load_lds((const void*)(q + c + lane), (lds_ptr)(row + c), 4, 0, 0);
+    else
+      row[c + lane] = 0.0f;
+  if (a.root)
+#pragma unroll 1
+    for (int c = 64 * wave; c < dp; c += 64 * kPrepQueries)
+      __builtin_amdgcn_global_load_lds((const void*)(a.root + c + lane), (lds_ptr)(root + c), 4, 0, 0);
+  const double mmin = *a.mmin;
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+  __syncthreads();
+  // Column k belongs to partial sum (k / 64) % 4 of lane k % 64: |q|^2 and
+  // |q|_1 are added in a fixed order (deterministic, relative error below
   // 2^-40 for d <= 4096; the thresholds' slack covers far more).  The
   // canonical sequential sum, which the float64 recheck needs bit for bit,
   // is formed there for the few candidates that reach it.
-  double l2 = 0.0;
-  for (int k = t; k < d; k += blockDim.x) l2 = __fma_rn((double)qs[k], (double)qs[k], l2);
-  for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  for (int o = 32; o >= 1; o >>= 1) l1 += __shfl_xor(l1, o, 64);
-  for (int o = 32; o >= 1; o >>= 1) l2 += __shfl_xor(l2, o, 64);
-  if ((t & 63) == 0) {
-    red[t >> 6] = mx;
-    l1red[t >> 6] = l1;
-    l2red[t >> 6] = l2;
-  }
-  __syncthreads();
-  const double qq = (l2red[0] + l2red[1]) + (l2red[2] + l2red[3]);
-  const float qmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  // float8 query scale 2^e with qmax / 2^e in (224, 448]
-  int e = 0;
-  if (qmax > 0.0f) {
-    int ex;
-    const double m = frexp((double)qmax / 448.0, &ex);
-    e = (m == 0.5) ? ex - 1 : ex;
-  }
-  for (int k = t; k < dp; k += blockDim.x) {
-    const float v = k < d ? qs[k] : 0.0f;
-    qf[(int64_t)b * dp + k] = v;
-    if (sgn) {
-      // walk query [max(q,0) | max(-q,0)] against rows [max + B | B - min]
-      const float vp = fmaxf(v, 0.0f), vn = fmaxf(-v, 0.0f);
-      if (qw) {
-        qw[(int64_t)b * pw + k] = vp;
-        qw[(int64_t)b * pw + dp + k] = vn;
+  float mx = 0.0f;
+  bool bad = false;
+  double l1[4] = {0.0, 0.0, 0.0, 0.0}, l2[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+  for (int c = lane; c < dp; c += 256) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int k = c + 64 * u;
+      if (k >= dp) continue;
+      const float v = row[k];
+      if (sgn ? !isfinite(v) : (!(v >= 0.0f) || isinf(v))) bad = true;
+      mx = fmaxf(mx, v);
+      l1[u] += (double)fabsf(v);
+      l2[u] = __fma_rn((double)v, (double)v, l2[u]);
+      a.qf[(int64_t)b * dp + k] = v;
+      if (sgn) {
+        // walk query [max(q,0) | max(-q,0)] against rows [max + B | B - min]
+        const float vp = fmaxf(v, 0.0f), vn = fmaxf(-v, 0.0f);
+        const int64_t at = (int64_t)b * a.pw + k;
+        if (a.qw) {
+          a.qw[at] = vp;
+          a.qw[at + dp] = vn;
+        }
+        if (a.qbf) {
+          a.qbf[at] = bf16_up(vp);
+          a.qbf[at + dp] = bf16_up(vn);
+        }
+      } else if (a.qbf) {
+        a.qbf[(int64_t)b * dp + k] = bf16_up(v);
       }
-      if (qbf) {
-        qbf[(int64_t)b * pw + k] = bf16_up(vp);
-        qbf[(int64_t)b * pw + dp + k] = bf16_up(vn);
-      }
-    } else {
-      if (qbf) qbf[(int64_t)b * dp + k] = bf16_up(v);
-      if (q8) q8[(int64_t)b * dp + k] = (uint8_t)e4m3_up(ldexp((double)v, -e));
     }
   }
-  if (t == 0) {
-    const bool live = real && qq > 0.0 && !bad;
+  // |q|_1 + |root pool|_1 (only an upper bound is needed); for a signed index
+  // |q|_1 alone, which sets the threshold's shift B |q|_1
+  if (a.root)
+#pragma unroll 1
+    for (int c = lane; c < dp; c += 256) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c + 64 * u < dp) l1[u] += (double)root[c + 64 * u];
+    }
+#pragma unroll 1
+  for (int o = 32; o >= 1; o >>= 1) {
+    mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      l1[u] += __shfl_xor(l1[u], o, 64);
+      l2[u] += __shfl_xor(l2[u], o, 64);
+    }
+  }
+  bad = __any(bad);
+  const double qq = (l2[0] + l2[1]) + (l2[2] + l2[3]);
+  // float8 query scale 2^e with qmax / 2^e in (224, 448]
+  int e = 0;
+  if (mx > 0.0f) {
+    int ex;
+    const double m = frexp((double)mx / 448.0, &ex);
+    e = (m == 0.5) ? ex - 1 : ex;
+  }
+  if (a.q8)
+#pragma unroll 1
+    for (int k = 4 * lane; k < dp; k += 256) {
+      const float4 v = *reinterpret_cast<const float4*>(row + k);
+      *reinterpret_cast<uint32_t*>(a.q8 + (int64_t)b * dp + k) =
+          (e4m3_up_f32(v.x, e) & 0xFFu) | (e4m3_up_f32(v.y, e) & 0xFFu) << 8 |
+          (e4m3_up_f32(v.z, e) & 0xFFu) << 16 | (e4m3_up_f32(v.w, e) & 0xFFu) << 24;
+    }
+  const bool on = real && qq > 0.0 && !bad;
+  if (lane == 0) {
+    live[wave] = on;
     const double nrm = __dsqrt_rn(qq);
-    qq_out[b] = qq;
-    qexp[b] = e;
-    invn_q[b] = qq > 0.0 ? (float)__ddiv_rn(1.0, nrm) : 0.0f;
+    if (real) a.rho[b] = rho;
+    a.qq[b] = qq;
+    a.qexp[b] = bad ? kBadQuery : e;
+    a.invn_q[b] = qq > 0.0 ? (float)__ddiv_rn(1.0, nrm) : 0.0f;
     float th = INFINITY, tg = INFINITY;
-    if (live) {
-      const double r = rho[b];
-      if (r <= 0.0) {
+    const double l1s = (l1[0] + l1[1]) + (l1[2] + l1[3]);
+    if (on) {
+      if (rho <= 0.0) {
         th = -INFINITY;
         tg = -INFINITY;
       } else {
         // cos >= rho with the float64 definition implies the real cosine is
         // at least rho * (1 - 2e-11) for d <= 4096; every member norm is at
         // least m_min, so a pool holding a neighbour scores >= tau (reals).
-        const double reff = r * (1.0 - 4e-11);
-        const double tau = reff * nrm * (*mmin) * (1.0 - 4e-11);
+        const double reff = rho * (1.0 - 4e-11);
+        const double tau = reff * nrm * mmin * (1.0 - 4e-11);
         if (sgn) {
           // A member's q.f is at most the pool's max/min score U, and the
           // walk computes [q+ | q-] . [max + B | B - min] = U + B |q|_1 over
@@ -560,10 +591,9 @@ __global__ __launch_bounds__(256) void k_query_prep(
           // float64 |q|_1 of <= 4096 terms is within 2^-40 of the real one).
           // Products of mixed sign in the leaf GEMM carry an error relative
           // to sum |q_k f_k| <= |q| |f|, hence rho - slack there.
-          const double sl = pool_slack(pw);
-          const double l1s = (l1red[0] + l1red[1]) + (l1red[2] + l1red[3]);
-          const double kappa = (double)sbound * l1s * (1.0 - 1e-12);
-          th = f64_to_f32_down((tau + kappa) * (1.0 - sl) - 2.0 * pw * 0x1p-126);
+          const double sl = pool_slack(a.pw);
+          const double kappa = (double)a.sbound * l1s * (1.0 - 1e-12);
+          th = f64_to_f32_down((tau + kappa) * (1.0 - sl) - 2.0 * a.pw * 0x1p-126);
           const double cg = reff * (1.0 - 4e-11) - pool_slack(dp);
           tg = cg > 0.0 ? f64_to_f32_down(cg * nrm) : -INFINITY;
         } else {
@@ -572,20 +602,27 @@ __global__ __launch_bounds__(256) void k_query_prep(
           tg = f64_to_f32_down(reff * nrm * (1.0 - 4e-11) * (1.0 - sl));
         }
       }
-      atomicOr(reinterpret_cast<unsigned long long*>(&tile_mask[b / tq]),
-               (unsigned long long)(1ull << (b % tq)));
     }
-    thr[b] = th;
-    thr_gemm[b] = tg;
-    if (sabs && !sgn) {
+    a.thr[b] = th;
+    a.thr_gemm[b] = tg;
+    if (a.sabs && !sgn) {
       // absolute term of the subtraction step's lower bound: 2^-125 (|S|_1 +
       // |q|_1 + dp 2^-126) + 2^-126, a normal float32 rounded up
-      const double l1s = (l1red[0] + l1red[1]) + (l1red[2] + l1red[3]);
       const double v = ldexp(1.01 * l1s + (double)dp * 0x1p-126, -125) + 0x1p-126;
       float f = (float)v;
       if ((double)f < v) f = __uint_as_float(__float_as_uint(f) + 1u);
-      sabs[b] = f;
+      a.sabs[b] = f;
     }
+  }
+  __syncthreads();
+  if (t == 0) {
+    uint32_t m = 0u;
+#pragma unroll
+    for (int w = 0; w < kPrepQueries; ++w) m |= (uint32_t)live[w] << w;
+    uint8_t* tile = reinterpret_cast<uint8_t*>(a.tile_mask + blockIdx.x * kPrepQueries / a.tq);
+    const int byte = (int)(blockIdx.x * kPrepQueries % a.tq) / 8;
+    tile[byte] = (uint8_t)m;
+    if (a.tq == 32) tile[byte + 4] = 0u;
   }
 }
 
@@ -601,20 +638,6 @@ inline int grid_for(int64_t work, int block) {
 hipError_t launch_zero_u32(uint32_t* p, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_zero_u32, dim3(grid_for(n, 256)), dim3(256), 0, s, p, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_call_begin(const CallBegin& a, const double* rho, hipStream_t s) {
-  RhoArg r;
-  for (int k = 0; k < 4; ++k)
-    if (reinterpret_cast<uintptr_t>(a.p[k]) % 16) return hipErrorInvalidValue;
-  if (rho) {
-    if (a.nq > kRhoArg) return hipErrorInvalidValue;
-    for (int i = 0; i < a.nq; ++i) r.v[i] = rho[i];
-    hipLaunchKernelGGL(k_call_begin<true>, dim3(256), dim3(256), 0, s, a, r);
-  } else {
-    hipLaunchKernelGGL(k_call_begin<false>, dim3(256), dim3(256), 0, s, a, r);
-  }
   return hipGetLastError();
 }
 
@@ -720,17 +743,27 @@ hipError_t launch_quant_fp8(const float* tree, uint8_t* p8, int w, int first, in
   return hipGetLastError();
 }
 
-hipError_t launch_query_prep(const float* q, int nq, int d, int dp, int tq, const double* rho,
-                             const double* mmin, float* qf, uint16_t* qbf, uint8_t* q8, int* qexp,
-                             float* invn_q, double* qq, float* thr, float* thr_gemm,
-                             uint64_t* tile_mask, const float* root, float* sabs,
-                             float* qw, int pw, float sbound,
-                             unsigned int* err, int nq_pad, hipStream_t s) {
-  if (nq_pad <= 0) return hipSuccess;
-  if (sbound > 0.0f && pw != 2 * dp) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_query_prep, dim3(nq_pad), dim3(256), 0, s, q, nq, d, dp, tq, rho, mmin, qf,
-                     qbf, q8, qexp, invn_q, qq, thr, thr_gemm, tile_mask, root, sabs, qw, pw,
-                     sbound, err);
+hipError_t launch_query_prep(QueryPrep a, const double* rho, hipStream_t s) {
+  if (a.nq < 0 || a.nq > a.nq_pad || a.nq_pad % kPrepQueries || a.nq_pad % a.tq ||
+      (a.tq != 32 && a.tq != 64) || a.d < 1 || a.d > a.dp || a.dp % 128 ||
+      (a.sbound > 0.0f && a.pw != 2 * a.dp))
+    return hipErrorInvalidValue;
+  for (int k = 0; k < 3; ++k)
+    if (reinterpret_cast<uintptr_t>(a.p[k]) % 16) return hipErrorInvalidValue;
+  if (a.nq == 0) a.nq_pad = 0;  // only clear
+  const dim3 grid((unsigned)std::max(128, a.nq_pad / kPrepQueries)), block(64 * kPrepQueries);
+  const int lds = (kPrepQueries + 1) * a.dp * 4;
+  const void* fn = reinterpret_cast<const void*>(rho ? k_query_prep<true> : k_query_prep<false>);
+  if (lds + 1024 > 160 * 1024) return hipErrorInvalidValue;
+  if (hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return err;
+  RhoArg r;
+  if (rho) {
+    if (a.nq > kRhoArg) return hipErrorInvalidValue;
+    for (int i = 0; i < a.nq; ++i) r.v[i] = rho[i];
+    hipLaunchKernelGGL(k_query_prep<true>, grid, block, lds, s, a, r);
+  } else {
+    hipLaunchKernelGGL(k_query_prep<false>, grid, block, lds, s, a, r);
+  }
   return hipGetLastError();
 }
 

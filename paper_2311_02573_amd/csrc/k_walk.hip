@@ -1906,7 +1906,8 @@ __global__ __launch_bounds__(256) void k_leaf(LeafArgs a) {
 // with operands read and converted in the chain 22).
 // Workgroups from kRecheckGroups on sum the frontier entries of one level
 // each over its slots' counters (the automatic dense level and a server's
-// memory estimates read them).
+// memory estimates read them); the last one looks for queries that the
+// preparation marked as not allowed.
 constexpr int kRecheckGroups = 64;
 __device__ __forceinline__ void level_entries(const uint32_t* __restrict__ counts, int l,
                                               DevCounters* ctr) {
@@ -1933,7 +1934,14 @@ __global__ __launch_bounds__(256) void k_recheck(Hit* hits, const uint32_t* band
                                                  const double* __restrict__ ff,
                                                  const double* __restrict__ rho, QCount qcount,
                                                  const uint32_t* lvl_count, int first,
+                                                 const int* __restrict__ qexp, int nq,
                                                  DevCounters* ctr) {
+  if (blockIdx.x == gridDim.x - 1) {
+    bool bad = false;
+    for (int i = threadIdx.x; i < nq; i += blockDim.x) bad = bad || qexp[i] == kBadQuery;
+    if (bad) atomicOr(&ctr->err, 1u);
+    return;
+  }
   if (blockIdx.x >= kRecheckGroups) {
     level_entries(lvl_count, first + (int)blockIdx.x - kRecheckGroups, ctr);
     return;
@@ -2375,12 +2383,12 @@ hipError_t launch_leaf_sort(const LeafArgs& a, hipStream_t s) {
 hipError_t launch_recheck(Hit* hits, const uint32_t* band_idx, const unsigned long long* nband,
                           unsigned long long cap, const float* qf, const float* leaves, int d,
                           int dp, const double* ff, const double* rho, QCount qcount,
-                          const uint32_t* lvl_count, int first, int levels, DevCounters* ctr,
-                          hipStream_t s) {
+                          const uint32_t* lvl_count, int first, int levels, const int* qexp, int nq,
+                          DevCounters* ctr, hipStream_t s) {
   if (first < 0 || levels > GT_MAX_LEVELS) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_recheck, dim3(kRecheckGroups + (levels > first ? levels - first : 0)),
+  hipLaunchKernelGGL(k_recheck, dim3(kRecheckGroups + (levels > first ? levels - first : 0) + 1),
                      dim3(256), 0, s, hits, band_idx, nband, cap, qf, leaves, d, dp, ff, rho,
-                     qcount, lvl_count, first, ctr);
+                     qcount, lvl_count, first, qexp, nq, ctr);
   return hipGetLastError();
 }
 
