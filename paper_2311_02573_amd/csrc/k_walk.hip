@@ -1710,8 +1710,9 @@ struct LeafStep {
 // workgroups sweep its entries in slot order, so the tiles' copies of a leaf
 // pair are tested close together in time and share the XCD's L2.
 // NV: 16-byte slices per lane and 1024-column chunk that can be non-zero, 4
-// in general and 2 for rows of at most 512 columns (whose other two slices
-// would only reload the row's last slice).  Each dot product is summed in the
+// in general, 2 for rows of at most 512 columns and 1 for at most 256 (whose
+// other slices would only reload the row's last slice; 2^20 x 256, 1024
+// queries: 324 us, 379 with two).  Each dot product is summed in the
 // same order either way: a slice past dp is zero and adds nothing to
 // chunk_sum4.
 template <int NV, bool SORTED>
@@ -2350,14 +2351,19 @@ hipError_t launch_leaf(const LeafArgs& a, int n_cu, hipStream_t s) {
       a.level < a.nb || a.nt < 1 || a.nt > kMaxTiles || a.nbu < 1 || a.nbu > (1 << a.nb) || n_cu < 1)
     return hipErrorInvalidValue;
   // As many workgroups of four waves per CU as its registers hold at once:
-  // three, or four for rows of at most 512 columns (two slices per lane); with
-  // fewer the loads in flight do not cover their latency (two and three:
-  // 0.41 ms against 0.38, 0.44 against 0.41), with one more the rows spill.
+  // three, or four for rows of at most 512 columns (two slices per lane) and
+  // five for at most 256; with fewer the loads in flight do not cover their
+  // latency (two, three and four: 0.41 ms against 0.38, 0.44 against 0.41, 0.35
+  // against 0.32), with one more the rows spill or wait (six: 0.40).
   // The grid is a multiple of the XCD count: every XCD's workgroups split its
   // entries by blockIdx / 8.
   const bool sorted = a.tile_bits >= 0, narrow = a.dp <= 512;
-  const dim3 g(kXcds * ((n_cu * (narrow ? 4 : 3) + kXcds - 1) / kXcds));
-  if (narrow && sorted)
+  const dim3 g(kXcds * ((n_cu * (a.dp <= 256 ? 5 : narrow ? 4 : 3) + kXcds - 1) / kXcds));
+  if (a.dp <= 256 && sorted)
+    hipLaunchKernelGGL((k_leaf<1, true>), g, dim3(256), 0, s, a);
+  else if (a.dp <= 256)
+    hipLaunchKernelGGL((k_leaf<1, false>), g, dim3(256), 0, s, a);
+  else if (narrow && sorted)
     hipLaunchKernelGGL((k_leaf<2, true>), g, dim3(256), 0, s, a);
   else if (narrow)
     hipLaunchKernelGGL((k_leaf<2, false>), g, dim3(256), 0, s, a);
