@@ -2084,6 +2084,8 @@ __device__ __forceinline__ void write_call(const PlaceArgs& a, int per, int64_t 
 // pair's slot among the query's results.  Up to kPlaceQueries queries every
 // workgroup scans the counts for itself (the offsets in LDS; the first one
 // writes them out), which saves a launch; above, k_scan_offsets ran before.
+// Four pairs a thread in flight on every CU: 1.0 M pairs of 4096 queries 41 us,
+// 54 with one on half of them.
 constexpr int kPlaceQueries = 4096;
 __global__ __launch_bounds__(1024) void k_scan_offsets(PlaceArgs a) {
   const int per = (a.nq + 1023) / 1024;
@@ -2112,60 +2114,76 @@ __global__ __launch_bounds__(1024) void k_place(PlaceArgs a) {
   }
   if (!results_fit(a.ctr, (unsigned long long)total, a.hit_cap, a.lim)) return;
   const unsigned long long n = a.ctr->nhits;
-  for (unsigned long long h = blockIdx.x * 1024ull + threadIdx.x; h < n; h += gridDim.x * 1024ull) {
-    const Hit x = a.hits[h];
-    if (hit_kind(x.flag) != HIT_ACCEPT) continue;
-    const int64_t pos = (SCAN ? loffs[x.q] : a.offs[x.q]) + (int64_t)hit_slot(x.flag);
-    a.out_id[pos] = x.id;
-    a.out_sim[pos] = x.sim;
+  const unsigned long long step = gridDim.x * 1024ull;
+  for (unsigned long long h = blockIdx.x * 1024ull + threadIdx.x; h < n; h += 4 * step) {
+    Hit x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = a.hits[h + k * step < n ? h + k * step : h];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (h + k * step >= n || hit_kind(x[k].flag) != HIT_ACCEPT) continue;
+      const int64_t pos = (SCAN ? loffs[x[k].q] : a.offs[x[k].q]) + (int64_t)hit_slot(x[k].flag);
+      a.out_id[pos] = x[k].id;
+      a.out_sim[pos] = x[k].sim;
+    }
   }
 }
 
-// Sort each query's results by id (ids of one query are distinct).  Up to
-// 4096 results: a counting sort on the top 8 bits of the id (id >> shift,
-// shift chosen by the host so that every id below the call's epoch has a
-// top part below 256) groups the ids in LDS, then each id is placed at its
-// group's start plus the number of smaller ids in its group.  Larger
-// segments: stable 4-bit LSD radix sort by the same workgroup.
-constexpr int kSortPerThread = 16;  // 4096 / 256
-__global__ __launch_bounds__(256) void k_sort_segments(const int64_t* offs, uint32_t* id,
-                                                       float* sim, uint32_t* tmp_id,
-                                                       float* tmp_sim, int64_t* ids_out,
-                                                       float* sims_out, const DevCounters* ctr,
-                                                       unsigned long long hit_cap,
-                                                       unsigned long long lim, int shift) {
-  __shared__ uint32_t key[4096];
-  __shared__ float val[4096];
-  __shared__ uint32_t hist[16 * 256];
-  __shared__ uint32_t tot[257];
+// Sort each query's results by id (ids of one query are distinct), by their
+// bin: the top 12 bits of the id (id >> shift, shift chosen by the host so that
+// every id below the call's epoch has a bin below 4096; the top 8 for a few
+// results, whose bins cost more than they).  A bin's results are counted, the
+// counts scanned, and a result's place is its bin's start plus the number of
+// smaller ids in its bin, read in LDS.  Up to 4096 results a workgroup holds
+// them in registers; above, it passes over them once per window of about 2048
+// places, and up to kSegSplit workgroups share a segment's windows.  Bins
+// wider than half a window (more than 2^22 rows) and segments whose passes
+// would cost more than a radix sort take stable 4-bit LSD passes by one
+// workgroup.  256 threads, 256 bins and radix passes above 4096 before / now
+// (us): 64 queries of 5,100 results on average 285 / 35, 512 of them 700 / 100,
+// 512 of 2,080 161 / 52, 51 of 2,000 and more 21 / 8, 4096 of 250 18 / 18.
+constexpr int kSegThreads = 512, kSegBins = 4096, kSegKeys = 4096, kSegFew = 512;
+constexpr int kSegWindow = kSegKeys / 2;  // results of a window: a key and a value each
+constexpr int kSegSplit = 16;
+constexpr int64_t kSegWindowed = 1 << 18;
+__global__ __launch_bounds__(kSegThreads) void k_sort_segments(
+    const int64_t* offs, uint32_t* id, float* sim, uint32_t* tmp_id, float* tmp_sim, int64_t* ids_out,
+    float* sims_out, const DevCounters* ctr, unsigned long long hit_cap, unsigned long long lim,
+    int shift) {
+  constexpr int T = kSegThreads, W = T / 64, B = kSegBins / T, kSegPerThread = kSegKeys / T;
+  __shared__ uint32_t bin[kSegBins + 1];
+  __shared__ uint32_t key[kSegKeys];
+  __shared__ uint32_t cur[kSegBins];
+  __shared__ uint32_t wsum[W];
   if (!results_fit(ctr, ctr->total, hit_cap, lim)) return;
-  const int q = blockIdx.x, t = threadIdx.x;
+  const int q = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int64_t lo = offs[q], n = offs[q + 1] - lo;
-  if (n <= 0) return;
-  if (n <= 4096) {
+  const bool radix = n > kSegKeys && (n > kSegWindowed || (2 << shift) > kSegWindow);
+  if (n <= 0 || (blockIdx.y > 0 && (n <= kSegKeys || radix))) return;
+  if (n <= kSegFew) {
     const int ni = (int)n;
-    tot[t] = 0u;
-    if (t == 0) tot[256] = 0u;
-    __syncthreads();
-    uint32_t k[kSortPerThread], g[kSortPerThread], r[kSortPerThread];
-    float v[kSortPerThread];
+    if (t < 256) bin[t] = 0u;
+    uint32_t k[kSegFew / T], g[kSegFew / T], r[kSegFew / T];
+    float v[kSegFew / T];
 #pragma unroll
-    for (int e = 0; e < kSortPerThread; ++e) {
-      const int i = t + 256 * e;
-      if (i < ni) {
-        k[e] = id[lo + i];
-        v[e] = sim[lo + i];
-        const uint32_t gg = k[e] >> shift;
-        g[e] = gg < 255u ? gg : 255u;
-        r[e] = atomicAdd(&tot[g[e]], 1u);
-      }
+    for (int e = 0; e < kSegFew / T; ++e) {
+      const int i = t + T * e < ni ? t + T * e : 0;
+      k[e] = id[lo + i];
+      v[e] = sim[lo + i];
     }
     __syncthreads();
-    if (t < 64) {  // exclusive prefix of the 256 group sizes, four per lane
+#pragma unroll
+    for (int e = 0; e < kSegFew / T; ++e)
+      if (t + T * e < ni) {
+        g[e] = min(k[e] >> (shift + 4), 255u);
+        r[e] = atomicAdd(&bin[g[e]], 1u);
+      }
+    __syncthreads();
+    if (w == 0) {  // exclusive prefix of the 256 bins, four per lane
       uint32_t c[4], sum = 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        c[j] = tot[4 * t + j];
+        c[j] = bin[4 * t + j];
         sum += c[j];
       }
       uint32_t incl = sum;
@@ -2177,51 +2195,180 @@ __global__ __launch_bounds__(256) void k_sort_segments(const int64_t* offs, uint
       uint32_t run = incl - sum;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        hist[4 * t + j] = run;
+        bin[4 * t + j] = run;
         run += c[j];
       }
-      if (t == 63) hist[256] = incl;
+      if (t == 63) bin[256] = incl;
     }
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < kSortPerThread; ++e) {
-      const int i = t + 256 * e;
-      if (i < ni) {
-        key[hist[g[e]] + r[e]] = k[e];
-        val[hist[g[e]] + r[e]] = v[e];
-      }
-    }
+    for (int e = 0; e < kSegFew / T; ++e)
+      if (t + T * e < ni) key[bin[g[e]] + r[e]] = k[e];
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < kSortPerThread; ++e) {
-      const int i = t + 256 * e;
-      if (i < ni) {
-        const uint32_t b0 = hist[g[e]], b1 = hist[g[e] + 1];
+    for (int e = 0; e < kSegFew / T; ++e)
+      if (t + T * e < ni) {
+        const uint32_t b0 = bin[g[e]], b1 = bin[g[e] + 1];
         uint32_t pos = b0;
         for (uint32_t j = b0; j < b1; ++j) pos += key[j] < k[e];
         ids_out[lo + pos] = (int64_t)k[e];
         sims_out[lo + pos] = v[e];
       }
+    return;
+  }
+  // the bins' counts to their starts, in place
+  auto scan_bins = [&]() {
+    uint32_t c[B], sum = 0;
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      c[j] = bin[t * B + j];
+      sum += c[j];
+    }
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    uint32_t run = incl - sum;
+#pragma unroll
+    for (int k = 0; k < W; ++k)
+      if (k < w) run += wsum[k];
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      bin[t * B + j] = run;
+      run += c[j];
+    }
+    if (t == 0) bin[kSegBins] = (uint32_t)n;
+    __syncthreads();
+  };
+  if (n <= kSegKeys) {
+    const int ni = (int)n;
+    for (int i = t; i < kSegBins; i += T) bin[i] = 0u;
+    uint32_t k[kSegPerThread], g[kSegPerThread], r[kSegPerThread];
+    float v[kSegPerThread];
+#pragma unroll
+    for (int e = 0; e < kSegPerThread; ++e) {
+      const int i = t + T * e < ni ? t + T * e : 0;
+      if (T * e < ni) {
+        k[e] = id[lo + i];
+        v[e] = sim[lo + i];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kSegPerThread; ++e)
+      if (t + T * e < ni) {
+        g[e] = min(k[e] >> shift, (uint32_t)kSegBins - 1u);
+        r[e] = atomicAdd(&bin[g[e]], 1u);
+      }
+    __syncthreads();
+    scan_bins();
+#pragma unroll
+    for (int e = 0; e < kSegPerThread; ++e)
+      if (t + T * e < ni) key[bin[g[e]] + r[e]] = k[e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kSegPerThread; ++e)
+      if (t + T * e < ni) {
+        const uint32_t b0 = bin[g[e]], b1 = bin[g[e] + 1];
+        uint32_t pos = b0;
+        for (uint32_t j = b0; j < b1; ++j) pos += key[j] < k[e];
+        ids_out[lo + pos] = (int64_t)k[e];
+        sims_out[lo + pos] = v[e];
+      }
+    return;
+  }
+  if (!radix) {
+    const uint32_t* src = id + lo;
+    for (int i = t; i < kSegBins; i += T) bin[i] = cur[i] = 0u;
+    __syncthreads();
+    for (int64_t i0 = 0; i0 < n; i0 += 8 * T) {
+      uint32_t k[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t i = i0 + T * e + t;
+        k[e] = src[i < n ? i : n - 1];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (i0 + T * e + t < n) atomicAdd(&bin[min(k[e] >> shift, (uint32_t)kSegBins - 1u)], 1u);
+    }
+    __syncthreads();
+    scan_bins();
+    // window: the bins that start in [first, first + step); a bin has at most
+    // 2^shift ids, so at most kSegWindow results
+    const uint32_t step = (uint32_t)(kSegWindow - (1 << shift));
+    for (uint32_t first = blockIdx.y * step; first < n; first += gridDim.y * step) {
+      // (bins of one window follow each other: it holds places base .. end - 1)
+      if (t == 0) wsum[0] = 0xFFFFFFFFu, wsum[1] = 0u;
+      __syncthreads();
+      for (int i = t; i < kSegBins; i += T) {
+        const uint32_t b0 = bin[i], b1 = bin[i + 1];
+        if (b0 < b1 && b0 - first < step) {
+          atomicMin(&wsum[0], b0);
+          atomicMax(&wsum[1], b1);
+        }
+      }
+      __syncthreads();
+      const uint32_t base = wsum[0], end = wsum[1];
+      for (int64_t i0 = 0; i0 < n; i0 += 8 * T) {
+        uint32_t k[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int64_t i = i0 + T * e + t;
+          k[e] = src[i < n ? i : n - 1];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int64_t i = i0 + T * e + t;
+          const uint32_t g = min(k[e] >> shift, (uint32_t)kSegBins - 1u);
+          if (i < n && bin[g] - first < step) {
+            const uint32_t at = bin[g] - base + atomicAdd(&cur[g], 1u);
+            key[at] = k[e];
+            key[kSegWindow + at] = __float_as_uint(sim[lo + i]);
+          }
+        }
+      }
+      __syncthreads();
+      for (uint32_t i = t; base + i < end; i += T) {
+        const uint32_t k = key[i], g = min(k >> shift, (uint32_t)kSegBins - 1u);
+        const uint32_t b0 = bin[g], b1 = bin[g + 1];
+        uint32_t pos = b0;
+        for (uint32_t j = b0; j < b1; ++j) pos += key[j - base] < k;
+        ids_out[lo + pos] = (int64_t)k;
+        sims_out[lo + pos] = __uint_as_float(key[kSegWindow + i]);
+      }
+      __syncthreads();
     }
     return;
   }
+  // (256 threads: hist of (digit, thread) in key, its sums in cur)
+  uint32_t *hist = key, *tot = cur;
   uint32_t *si = id + lo, *di = tmp_id + lo;
   float *sv = sim + lo, *dv = tmp_sim + lo;
+  const bool on = t < 256;
   const int64_t chunk = (n + 255) / 256;
-  const int64_t a0 = min(n, t * chunk), a1 = min(n, a0 + chunk);
+  const int64_t a0 = on ? min(n, t * chunk) : 0, a1 = on ? min(n, a0 + chunk) : 0;
   for (int pass = 0; pass < 8; ++pass) {
     const int sh = 4 * pass;
     uint32_t h[16];
 #pragma unroll
     for (int b = 0; b < 16; ++b) h[b] = 0;
     for (int64_t i = a0; i < a1; ++i) h[(si[i] >> sh) & 15u]++;
+    if (on) {
 #pragma unroll
-    for (int b = 0; b < 16; ++b) hist[b * 256 + t] = h[b];
+      for (int b = 0; b < 16; ++b) hist[b * 256 + t] = h[b];
+    }
     __syncthreads();
     // exclusive scan over hist in (digit, thread) order: thread t owns 16 slots
-    uint32_t s = 0;
-    for (int k = 0; k < 16; ++k) s += hist[t * 16 + k];
-    tot[t] = s;
+    if (on) {
+      uint32_t s = 0;
+      for (int k = 0; k < 16; ++k) s += hist[t * 16 + k];
+      tot[t] = s;
+    }
     __syncthreads();
     if (t == 0) {
       uint32_t run = 0;
@@ -2232,15 +2379,19 @@ __global__ __launch_bounds__(256) void k_sort_segments(const int64_t* offs, uint
       }
     }
     __syncthreads();
-    uint32_t run = tot[t];
-    for (int k = 0; k < 16; ++k) {
-      const uint32_t v = hist[t * 16 + k];
-      hist[t * 16 + k] = run;
-      run += v;
+    if (on) {
+      uint32_t run = tot[t];
+      for (int k = 0; k < 16; ++k) {
+        const uint32_t v = hist[t * 16 + k];
+        hist[t * 16 + k] = run;
+        run += v;
+      }
     }
     __syncthreads();
+    if (on) {
 #pragma unroll
-    for (int b = 0; b < 16; ++b) h[b] = hist[b * 256 + t];
+      for (int b = 0; b < 16; ++b) h[b] = hist[b * 256 + t];
+    }
     for (int64_t i = a0; i < a1; ++i) {
       const uint32_t k = si[i];
       const uint32_t pos = h[(k >> sh) & 15u]++;
@@ -2251,7 +2402,7 @@ __global__ __launch_bounds__(256) void k_sort_segments(const int64_t* offs, uint
     uint32_t* ti = si; si = di; di = ti;
     float* tv = sv; sv = dv; dv = tv;
   }
-  for (int64_t i = t; i < n; i += 256) {
+  for (int64_t i = t; i < n; i += T) {
     ids_out[lo + i] = (int64_t)si[i];
     sims_out[lo + i] = sv[i];
   }
@@ -2400,7 +2551,7 @@ hipError_t launch_recheck(Hit* hits, const uint32_t* band_idx, const unsigned lo
 
 hipError_t launch_place(const PlaceArgs& a, hipStream_t s) {
   if (a.nq <= kPlaceQueries) {
-    hipLaunchKernelGGL(k_place<true>, dim3(128), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL(k_place<true>, dim3(256), dim3(1024), 0, s, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_scan_offsets, dim3(1), dim3(1024), 0, s, a);
@@ -2415,12 +2566,13 @@ hipError_t launch_sort_segments(const int64_t* offs, int nq, uint32_t* id, float
                                 unsigned long long hit_cap, unsigned long long lim,
                                 int64_t id_bound, hipStream_t s) {
   if (nq <= 0) return hipSuccess;
-  // top 8 bits of the ids below id_bound
+  // top 12 bits of the ids below id_bound
   int bits = 0;
   while (bits < 32 && (int64_t(1) << bits) < id_bound) ++bits;
-  const int shift = bits > 8 ? bits - 8 : 0;
-  hipLaunchKernelGGL(k_sort_segments, dim3(nq), dim3(256), 0, s, offs, id, sim, tmp_id, tmp_sim,
-                     ids_out, sims_out, ctr, hit_cap, lim, shift);
+  const int shift = bits > 12 ? bits - 12 : 0;
+  const int split = std::max(1, std::min(kSegSplit, 256 / nq));
+  hipLaunchKernelGGL(k_sort_segments, dim3(nq, split), dim3(kSegThreads), 0, s, offs, id, sim,
+                     tmp_id, tmp_sim, ids_out, sims_out, ctr, hit_cap, lim, shift);
   return hipGetLastError();
 }
 
