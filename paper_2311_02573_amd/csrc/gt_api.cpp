@@ -264,30 +264,29 @@ int bucket_bits_of(int sparse_from, int nt) {
   return nb;
 }
 
-// Calls of few query tiles take the subtree walk (k_subtree.hip).  It saves
-// the level kernels' fixed time per level, but each tile reads the first
-// tested level for itself and both children of every entry, so the line lies
-// at tiles x bytes of that level.  Crossings measured (us per call, subtree
-// walk / level by level):
-//   bfloat16 2^20 x 1000 (134 MB): 128 queries 319 / 366, 192 404 / 398
-//            2^17 x 1000 (17 MB): 1024 queries 314 / 344
-//            2^18 x 256 (8 MB): 1024 queries 460 / 539
-//            2^17 x 2048 (17 MB): 256 queries 243 / 509, 1024 556 / 667
-//   float8   2^20 x 1000 (67 MB): 128 queries 285 / 292, 192 362 / 349
-//            300,007 x 777 (17 MB): 257 queries 283 / 299, 512 394 / 384
-// With float32 pools (32-query tiles) the sides cross by tiles x pools of the
-// level kernels' first level instead, whatever the width:
-//   2^20 x 1000 (32,768 pools): 64 queries 343 / 405, 128 578 / 548,
-//            256 1056 / 839
-//   2^20 x 256: 64 queries 273 / 309, 128 441 / 437, 256 769 / 696
-//   2^17 x 1000 (4,096 pools): 256 queries 219 / 299, 512 344 / 397
-//   2^18 x 1000, max pools (8,192): 256 queries 339 / 408, 512 569 / 574
-//   300,007 x 777 (9,376): 257 queries 457 / 500, 512 704 / 641
-// and 90 against 201 - 327 us for one query.  Larger calls of more than 16
-// tiles were not measured below those sizes and go level by level, as do
-// calls with options that ask for the level kernels (an explicit head or
-// grid, row counting).
-constexpr int kSubtreeTiles = 16;
+// Calls of few query tiles or on small trees take the subtree walk
+// (k_subtree.hip).  It saves the level kernels' fixed time per level, but each
+// tile reads the first tested level for itself and both children of every
+// entry, so the line lies at tiles x bytes of that level, or tiles x pools
+// where the rows are short to begin with.  Calls measured (us, subtree walk /
+// level by level):
+//   bfloat16, up to 384 columns: 2^20 x 300 (50 MB), 512 queries 645 / 711, 1024
+//     1166 / 1250; 2^19 x 200 (17 MB), 2048 1226 / 1469; 2^14 x 256, 4096 184 / 322
+//   bfloat16, wider: 2^20 x 1000 (134 MB), 64 queries 174 / 285, 192 328 / 346,
+//     256 413 / 392; 2^17 x 1000 (17 MB), 1024 269 / 312, 2048 442 / 384;
+//     30,000 x 2000 (2 MB), 4096 464 / 1030; 2^16 x 500, max pools (8 MB), 2048
+//     190 / 195, 4096 316 / 304
+//   float8 (by pools): 2^20 x 1000 (65,536), 192 queries 273 / 298, 256 341 / 347,
+//     512 588 / 540; 2^17 x 1000 (8,192), 1024 214 / 242, 2048 336 / 325; 2^20 x
+//     128, 512 1143 / 1127, 1024 1974 / 1815; 2^14 x 256 (1,024), 4096 184 / 224
+//   float32 (32-query tiles; by pools of the level kernels' first level): 2^20 x
+//     1000 (32,768), 64 queries 343 / 405, 128 578 / 548, 256 1056 / 839; 2^17 x
+//     1000 (4,096), 512 344 / 397; 300,007 x 777 (9,376), 257 457 / 500, 512 704 /
+//     641; 2^14 x 1000 (512), 2048 267 / 858; few pools of few columns: 2^16 x
+//     300 (2,048), 2048 440 / 646, 2^18 x 128 (8,192), 1024 722 / 764
+// and 88 against 201 - 327 us for one query.  Calls with options that ask for
+// the level kernels (an explicit head or grid, row counting) take those.
+constexpr int kSubtreeTiles = 128;
 
 void choose_subtree(const Index* ix, Batch* b, int width) {
   b->sub_top = -1;
@@ -305,10 +304,12 @@ void choose_subtree(const Index* ix, Batch* b, int width) {
   const int64_t pools = ((b->n_epoch - 1) >> (ix->depth - first)) + 1;
   if (f32) {
     const int level = std::max(top, f32_first_of(ix, b, 1));
-    if ((((b->n_epoch - 1) >> (ix->depth - level)) + 1) * b->nt > 100000) return;
-  } else {
-    const int64_t bytes = pools * width * (b->fmt == GT_POOL_BF16 ? 2 : 1);
-    if (bytes * b->nt > int64_t(b->fmt == GT_POOL_BF16 ? 360 : 136) * 1000000) return;
+    const int64_t first_pools = ((b->n_epoch - 1) >> (ix->depth - level)) + 1;
+    if (first_pools * b->nt > (first_pools <= 8192 && width <= 384 ? 270000 : 100000)) return;
+  } else if (b->fmt == GT_POOL_BF16) {
+    if (pools * width * 2 * b->nt > int64_t(width <= 384 ? 900 : 450) * 1000000) return;
+  } else if (pools * b->nt > 262144) {
+    return;
   }
   b->sub_top = top;
   b->sub_window = window;

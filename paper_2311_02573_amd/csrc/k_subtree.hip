@@ -437,7 +437,8 @@ bool subtree_fits(int query_lds, int depth, int top) {
 }  // namespace
 
 // As many subtrees as give every CU of an XCD at most one workgroup over all
-// tiles (each holds a CU's registers; 2^8 for one tile of a full tree), and
+// tiles (each holds a CU's registers; 2^8 for one tile of a full tree), but
+// one for every XCD, and
 // more, smaller ones where the frontier lists would not fit beside the query
 // rows.  Query rows that do not fit with the largest lists are windowed.
 bool subtree_shape(int fmt, int dp, int nt, int qrows, int depth, int first, int64_t n_epoch, int n_cu,
@@ -445,7 +446,7 @@ bool subtree_shape(int fmt, int dp, int nt, int qrows, int depth, int first, int
   if (first > depth - 1 || depth > 31 || n_epoch < 1) return false;
   auto per_xcd = [&](int t) { return ((((n_epoch - 1) >> (depth - t)) + kXcds) / kXcds) * nt; };
   int most = 0;
-  while (most < depth - 1 && per_xcd(most + 1) <= n_cu / kXcds) ++most;
+  while (most < depth - 1 && per_xcd(most + 1) <= std::max(n_cu / kXcds, nt)) ++most;
   const int rowbytes = dp * esz_of(fmt);
   window = qrows * (rowbytes + 16) + 12 * 1024 <= kSubtreeLds ? 0 : kWindowChunks / qrows * kChunk;
   for (top = std::max(std::min(most, first), depth - 1 - kSubtreeLevels); top <= depth - 1; ++top)

@@ -147,3 +147,21 @@ def test_many_rows_per_workgroup(gt, n, d, nq, pool):
     _same(idx.query(q, rho, pool=pool).to_lists(), want)
     assert idx.stats()["frontier_launches"] == 1
     _same(_levels(idx, q, rho, pool), want)
+
+
+@pytest.mark.parametrize("n,d,nq,cap", [(60, 20, 4096, 64), (3000, 130, 4100, 4096), (9000, 72, 4096, 1 << 15),
+                                        (2000, 1200, 2100, 2048)])
+@pytest.mark.parametrize("pool", POOLS)
+def test_many_tiles(gt, n, d, nq, cap, pool):
+    """Up to 128 tiles take the subtree walk on a small tree: several to a CU,
+    and at least one subtree for every XCD.  The level kernels' float32 walk
+    (from its own first level) gives the same."""
+    w = synth.workload_small(n, d, nq, seed_offset=3)
+    idx = gt.GTIndex(torch.from_numpy(w.feats).cuda(), capacity=cap, pools=(pool,))
+    q = torch.from_numpy(w.queries).cuda()
+    rho = np.full(nq, 0.9)
+    rho[::200] = -1.0
+    want = ob.range_search(w.feats, w.queries, rho)
+    for _ in range(2):
+        _same(idx.query(q, rho, pool=pool).to_lists(), want)
+        _same(_levels(idx, q, rho, pool), want)
