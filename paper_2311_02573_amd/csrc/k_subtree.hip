@@ -25,10 +25,8 @@ constexpr int kSubtreeThreads = 512;
 constexpr int kSubtreeLevels = 11;        // most levels below a subtree's root pool
 constexpr int kSubtreeLds = 160 * 1024;
 constexpr int kWaves = kSubtreeThreads / 64;
-constexpr int kChunk = 1024;              // query bytes a wave copies at once
 constexpr int kWindowChunks = 8 * kWaves; // of a window, where a tile's rows do not fit
 
-typedef __attribute__((address_space(3))) void* lds_ptr;
 
 // LDS: the query rows, then the lists of (pool, mask) entries.  A list of level
 // l holds at most 2^(l - top) entries; consecutive levels alternate between
@@ -46,22 +44,7 @@ __host__ __device__ inline int query_lds_of(int rowbytes, int qrows, int window)
   return window > 0 ? 2 * qrows * (window + 16) : qrows * (rowbytes + 16);
 }
 
-// The tile's query rows to LDS rows of stride rowbytes + 16, by direct loads of
-// 64 lanes x 16 bytes (wave w copies rows w, w + 8, ...).
-template <int NQB>
-__device__ __forceinline__ void stage_rows(unsigned char* lds, const unsigned char* src, int rowbytes,
-                                           int wave, int lane) {
-#pragma unroll
-  for (int m = 0; m < 16 * NQB / kWaves; ++m) {
-    const int row = wave + m * kWaves;
-    for (int c = 0; c < rowbytes; c += kChunk)
-      if (c + 16 * lane < rowbytes)
-        __builtin_amdgcn_global_load_lds((const void*)(src + (size_t)row * rowbytes + c + 16 * lane),
-                                         (lds_ptr)(lds + row * (rowbytes + 16) + c), 16, 0, 0);
-  }
-}
-
-// The same for the columns of one window, from byte `from`, in two parts: 8
+// The columns of one window of the query rows, from byte `from`, in two parts: 8
 // chunks a wave to registers, and from there to LDS.  (Not direct loads: with
 // one in flight the compiler lets no LDS read go before all of a wave's loads.)
 template <int NQB>
@@ -71,7 +54,7 @@ struct WindowCopy {
   __device__ __forceinline__ void load(const unsigned char* src, int rowbytes, int from, int wave, int lane) {
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-      const int row = (wave * M + m) / CPR, c = (wave * M + m) % CPR * kChunk;
+      const int row = (wave * M + m) / CPR, c = (wave * M + m) % CPR * kStageChunk;
       const int byte = from + c + 16 * lane;
       v[m] = ld_global16(src + (size_t)row * rowbytes + (byte < rowbytes ? byte : 0));
     }
@@ -79,8 +62,8 @@ struct WindowCopy {
   __device__ __forceinline__ void store(unsigned char* buf, int wave, int lane) const {
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-      const int row = (wave * M + m) / CPR, c = (wave * M + m) % CPR * kChunk;
-      *reinterpret_cast<uint4*>(buf + row * (CPR * kChunk + 16) + c + 16 * lane) = v[m];
+      const int row = (wave * M + m) / CPR, c = (wave * M + m) % CPR * kStageChunk;
+      *reinterpret_cast<uint4*>(buf + row * (CPR * kStageChunk + 16) + c + 16 * lane) = v[m];
     }
   }
 };
@@ -174,7 +157,7 @@ __device__ __forceinline__ void windowed_products(const unsigned char* const (&r
                                                   int brow, int rowbytes, int bp, int wave, int lane,
                                                   uint32_t& wg, WindowCopy<NQB>& copy,
                                                   f32x4 (&acc)[G][NQB]) {
-  constexpr int W = WindowCopy<NQB>::CPR * kChunk, RS = W + 16, BUF = 16 * NQB * RS;
+  constexpr int W = WindowCopy<NQB>::CPR * kStageChunk, RS = W + 16, BUF = 16 * NQB * RS;
   constexpr int C = G == 2 ? 4 : NQB == 4 ? 8 : 16;  // steps of a block and group (what the registers hold)
   constexpr int NB = W / (64 * C);     // blocks of a window
   const int nsteps = rowbytes / 64, nblk = (nsteps + C - 1) / C;
@@ -244,7 +227,7 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
   if constexpr (WIN)
     copy.load(qsrc, rowbytes, 0, wave, lane);
   else
-    stage_rows<NQB>(lds, qsrc, rowbytes, wave, lane);
+    stage_rows<16 * NQB, kWaves>(lds, qsrc, rowbytes, wave, lane);
   uint32_t windows = 0;  // multiplied so far
   float th0[NQB];
   int qe[NQB];
@@ -257,7 +240,7 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
   const unsigned char* brow = lds + c16 * rs + 16 * g4;
   const int bp = 4 * (4 * c16 + g4);
 
-  __builtin_amdgcn_s_waitcnt(0x0070);  // this wave's direct loads (a barrier alone does not wait)
+  wait_loads();
 
   for (int l = a.first; l < D; ++l) {
     __syncthreads();  // the query rows, and the entries of the level above
@@ -448,7 +431,7 @@ bool subtree_shape(int fmt, int dp, int nt, int qrows, int depth, int first, int
   int most = 0;
   while (most < depth - 1 && per_xcd(most + 1) <= std::max(n_cu / kXcds, nt)) ++most;
   const int rowbytes = dp * esz_of(fmt);
-  window = qrows * (rowbytes + 16) + 12 * 1024 <= kSubtreeLds ? 0 : kWindowChunks / qrows * kChunk;
+  window = qrows * (rowbytes + 16) + 12 * 1024 <= kSubtreeLds ? 0 : kWindowChunks / qrows * kStageChunk;
   for (top = std::max(std::min(most, first), depth - 1 - kSubtreeLevels); top <= depth - 1; ++top)
     if (subtree_fits(query_lds_of(rowbytes, qrows, window), depth, top)) return true;
   return false;
@@ -458,7 +441,7 @@ hipError_t launch_walk_subtree(int fmt, const SubtreeArgs& a, hipStream_t s) {
   if (a.n_epoch < 1 || a.nt < 1 || a.nt > kMaxTiles || a.dp < 128 || a.dp % 128 != 0 || a.nb < 0 ||
       a.nb > kMaxBucketBits || ((int64_t)a.nt << a.nb) > kMaxSlots || a.top < a.nb ||
       a.first < a.top || a.first > a.depth - 1 || a.depth > 31 || a.qrows < 16 ||
-      (a.window != 0 && a.window != kWindowChunks / a.qrows * kChunk) ||
+      (a.window != 0 && a.window != kWindowChunks / a.qrows * kStageChunk) ||
       a.n_epoch > (int64_t(1) << a.depth) ||
       !subtree_fits(query_lds_of(a.dp * esz_of(fmt), a.qrows, a.window), a.depth, a.top))
     return hipErrorInvalidValue;

@@ -208,38 +208,16 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_level(WalkLevelArgs a)
     __syncthreads();
     const uint32_t gtot = gpre[R];
     if (gtot == 0) continue;
-    {
-      const unsigned char* src =
-          reinterpret_cast<const unsigned char*>(a.qtile) + (size_t)t * TQ * rowbytes;
-      // 8 loads in flight per thread before their LDS stores (a plain
-      // load-store loop would pay one memory latency per 16 bytes)
-      const int vec_per_row = rowbytes / 16;
-      const int nvec = TQ * vec_per_row;
-      for (int v0 = 0; v0 < nvec; v0 += 8 * kWalkThreads) {
-        uint4 buf[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int v = v0 + k * kWalkThreads + tid;
-          const int vv = v < nvec ? v : nvec - 1;
-          const int row = vv / vec_per_row, col = vv - row * vec_per_row;
-          buf[k] = *reinterpret_cast<const uint4*>(src + (size_t)row * rowbytes + col * 16);
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int v = v0 + k * kWalkThreads + tid;
-          if (v < nvec) {
-            const int row = v / vec_per_row, col = v - row * vec_per_row;
-            *reinterpret_cast<uint4*>(qlds + row * rs + col * 16) = buf[k];
-          }
-        }
-      }
-    }
+    stage_rows<TQ, kWalkThreads / 64>(
+        qlds, reinterpret_cast<const unsigned char*>(a.qtile) + (size_t)t * TQ * rowbytes, rowbytes,
+        __builtin_amdgcn_readfirstlane(wave), lane);
     if (tid < TQ) {
       const int qi = t * TQ + tid;
       float th = a.thr[qi];
       if (FMT == GT_POOL_FP8E4M3) th = ldexpf(th * kFp8ThrFactor, -(a.qexp[qi] + a.lexp));
       thr_lds[tid] = th;
     }
+    wait_loads();
     __syncthreads();
 
     // entries of group gg held by this lane: rows c16 (entry c16 / 2) and
@@ -767,6 +745,7 @@ __global__ __launch_bounds__(kSubThreads, 1) void k_walk_sub(WalkLevelArgs a) {
   constexpr int TQ = F::TQ;
   constexpr int NQB = TQ / 16;
   static_assert(TQ == 64, "records hold 64 queries");
+  static_assert(PIPE == 4, "a row has whole groups of 128 columns, four steps");
   __shared__ __attribute__((aligned(16))) unsigned char qlds[TQ * (F::MAXDP * F::ESZ + 16)];
   __shared__ uint32_t gpre[kMaxBucketsPerXcd + 1];
   __shared__ uint32_t glo[kMaxBucketsPerXcd], ghi[kMaxBucketsPerXcd];
@@ -842,34 +821,14 @@ __global__ __launch_bounds__(kSubThreads, 1) void k_walk_sub(WalkLevelArgs a) {
     __syncthreads();
     const uint32_t gtot = gpre[R];
     if (gtot == 0) continue;
-    {
-      const unsigned char* src =
-          reinterpret_cast<const unsigned char*>(a.qtile) + (size_t)t * TQ * rowbytes;
-      const int vec_per_row = rowbytes / 16;
-      const int nvec = TQ * vec_per_row;
-      for (int v0 = 0; v0 < nvec; v0 += 8 * kSubThreads) {
-        uint4 buf[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int v = v0 + k * kSubThreads + tid;
-          const int vv = v < nvec ? v : nvec - 1;
-          const int row = vv / vec_per_row, col = vv - row * vec_per_row;
-          buf[k] = *reinterpret_cast<const uint4*>(src + (size_t)row * rowbytes + col * 16);
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int v = v0 + k * kSubThreads + tid;
-          if (v < nvec) {
-            const int row = v / vec_per_row, col = v - row * vec_per_row;
-            *reinterpret_cast<uint4*>(qlds + row * rs + col * 16) = buf[k];
-          }
-        }
-      }
-    }
+    stage_rows<TQ, kSubThreads / 64>(
+        qlds, reinterpret_cast<const unsigned char*>(a.qtile) + (size_t)t * TQ * rowbytes, rowbytes,
+        __builtin_amdgcn_readfirstlane(wave), lane);
     if (tid < TQ) {
       thr_lds[tid] = a.thr[t * TQ + tid];
       sabs_lds[tid] = a.sabs[t * TQ + tid];
     }
+    wait_loads();
     __syncthreads();
 
     // entry e32 of group gg: its pool, mask and position (padding lanes take
@@ -970,8 +929,7 @@ __global__ __launch_bounds__(kSubThreads, 1) void k_walk_sub(WalkLevelArgs a) {
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < PIPE; ++u)
-          if (s0 + u < nsteps) step(bA0[u], bA1[u], s0 + u);
+        for (int u = 0; u < PIPE; ++u) step(bA0[u], bA1[u], s0 + u);
         __builtin_amdgcn_sched_barrier(0);
         {
           const bool same = s0 + 2 * PIPE < nsteps;
@@ -986,9 +944,10 @@ __global__ __launch_bounds__(kSubThreads, 1) void k_walk_sub(WalkLevelArgs a) {
           }
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (s0 + PIPE < nsteps) {
 #pragma unroll
-        for (int u = 0; u < PIPE; ++u)
-          if (s0 + PIPE + u < nsteps) step(bB0[u], bB1[u], s0 + PIPE + u);
+          for (int u = 0; u < PIPE; ++u) step(bB0[u], bB1[u], s0 + PIPE + u);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
 
