@@ -28,26 +28,31 @@ __device__ __forceinline__ uint4 ld_lds16(const unsigned char* p) {
   return *reinterpret_cast<const uint4*>(p);
 }
 
-// A tile's query rows to LDS rows of stride rowbytes + 16 (bank spread), by
-// direct loads of 64 lanes x 16 bytes: wave w of WAVES copies rows w, w + WAVES,
-// ...  All of a row's loads are in flight, and no thread divides an index by
-// the row's length (through registers, 32 divisions a thread for 64 x 2 KB: 2^20
-// x 1000, 1024 queries, three subtraction levels 340 us, 351 before; 2^19 x 800
-// 240, 260).
+// A tile's query rows (stage_columns: nbytes of each) to LDS rows of stride
+// rowbytes + 16 (rs), which spreads the banks, by direct loads of 64 lanes x 16
+// bytes: wave w of WAVES copies rows w, w + WAVES, ...  All of a row's loads are
+// in flight, and no thread divides an index by the row's length (through
+// registers, 32 divisions a thread for 64 x 2 KB: 2^20 x 1000, 1024 queries,
+// three subtraction levels 340 us, 351 before; 2^19 x 800 240, 260).
 constexpr int kStageChunk = 1024;
 template <int ROWS, int WAVES>
-__device__ __forceinline__ void stage_rows(unsigned char* lds, const unsigned char* src, int rowbytes,
-                                           int wave, int lane) {
+__device__ __forceinline__ void stage_columns(unsigned char* lds, int rs, const unsigned char* src,
+                                              int rowbytes, int nbytes, int wave, int lane) {
   typedef __attribute__((address_space(3))) void* lds_ptr;
   static_assert(ROWS % WAVES == 0, "whole rows per wave");
 #pragma unroll
   for (int m = 0; m < ROWS / WAVES; ++m) {
     const int row = wave + m * WAVES;
-    for (int c = 0; c < rowbytes; c += kStageChunk)
-      if (c + 16 * lane < rowbytes)
+    for (int c = 0; c < nbytes; c += kStageChunk)
+      if (c + 16 * lane < nbytes)
         __builtin_amdgcn_global_load_lds((const void*)(src + (size_t)row * rowbytes + c + 16 * lane),
-                                         (lds_ptr)(lds + row * (rowbytes + 16) + c), 16, 0, 0);
+                                         (lds_ptr)(lds + row * rs + c), 16, 0, 0);
   }
+}
+template <int ROWS, int WAVES>
+__device__ __forceinline__ void stage_rows(unsigned char* lds, const unsigned char* src, int rowbytes,
+                                           int wave, int lane) {
+  stage_columns<ROWS, WAVES>(lds, rowbytes + 16, src, rowbytes, rowbytes, wave, lane);
 }
 // This wave's loads, direct ones too, which a barrier alone does not wait for.
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0070); }
