@@ -274,8 +274,11 @@ int bucket_bits_of(int sparse_from, int nt) {
 //     1166 / 1250; 2^19 x 200 (17 MB), 2048 1226 / 1469; 2^14 x 256, 4096 184 / 322
 //   bfloat16, wider: 2^20 x 1000 (134 MB), 64 queries 174 / 285, 192 328 / 346,
 //     256 413 / 392; 2^17 x 1000 (17 MB), 1024 269 / 312, 2048 442 / 384;
-//     30,000 x 2000 (2 MB), 4096 464 / 1030; 2^16 x 500, max pools (8 MB), 2048
-//     190 / 195, 4096 316 / 304
+//     2^16 x 500, max pools (8 MB), 2048 190 / 195, 4096 316 / 304
+//   bfloat16, in windows: 30,000 x 2000 (2 MB), 4096 464 / 1030; 2^17 x 2000 (8 MB),
+//     2048 648 / 709; 250,000 x 2000 (16 MB), 1024 619 / 630, 2048 1105 / 989;
+//     400,000 x 1200 (32 MB), 256 285 / 350, 512 460 / 427; any sign, 200,000 x
+//     800 (22 MB), 256 266 / 355, 512 424 / 419
 //   float8 (by pools): 2^20 x 1000 (65,536), 192 queries 273 / 298, 256 341 / 347,
 //     512 588 / 540; 2^17 x 1000 (8,192), 1024 214 / 242, 2048 336 / 325; 2^20 x
 //     128, 512 1143 / 1127, 1024 1974 / 1815; 2^14 x 256 (1,024), 4096 184 / 224
@@ -307,7 +310,8 @@ void choose_subtree(const Index* ix, Batch* b, int width) {
     const int64_t first_pools = ((b->n_epoch - 1) >> (ix->depth - level)) + 1;
     if (first_pools * b->nt > (first_pools <= 8192 && width <= 384 ? 270000 : 100000)) return;
   } else if (b->fmt == GT_POOL_BF16) {
-    if (pools * width * 2 * b->nt > int64_t(width <= 384 ? 900 : 450) * 1000000) return;
+    const int64_t most = window > 0 ? 240 : width <= 384 ? 900 : 450;
+    if (pools * width * 2 * b->nt > most * 1000000) return;
   } else if (pools * b->nt > 262144) {
     return;
   }
