@@ -307,8 +307,11 @@ gt_status gt_read_pools(const gt_index* index, int32_t level, int64_t first, int
  *   "profile"     0/1: time kernel groups with HIP events (gt_stats.ms_*)
  *   "head_level"  level whose pools are all taken as live, 0..depth-1; tests
  *                 start at level head_level + 1 (-1 = automatic: with dense
- *                 steps only the last dense level is tested)
- *   "grid"        workgroups of the persistent walk kernels (0 = one per CU)
+ *                 steps only the last dense level is tested; float32 pools
+ *                 start where pools hold about 32 rows and follow the calls'
+ *                 frontiers, unless dense_last is given)
+ *   "grid"        workgroups of the persistent walk kernels (0 = one per CU; any
+ *                 other value also has every call walked level by level)
  *   "dense_last"  last level tested with dense steps, every pool against every
  *                 query (-2 = automatic, -1 = none; bf16 and fp8 pools only).
  *                 Automatic: the level whose pools hold about 16 populated
