@@ -323,6 +323,25 @@ void choose_subtree(const Index* ix, Batch* b, int width) {
   b->head = b->sub_first - 1;
 }
 
+// The call's levels (head, last dense level or subtree walk) and bucket bits.
+void choose_levels(const Index* ix, Batch* b) {
+  b->head = head_of(ix);
+  b->dense_last = b->kind == 1 ? dense_last_of(ix, b->fmt, b->head) : -1;
+  if (b->kind == 1) b->dense_last = adapt_dense_last(ix, b, b->fmt, b->maxpool, b->dense_last, b->head);
+  // A dense step computes every pool of its level against every query, and
+  // a pool's score never exceeds its parent's (non-negative rows, sums
+  // rounded up), so a chain of dense steps keeps the same (pool, query) pairs
+  // as its last step alone, up to rounding, which only keeps more.  With an
+  // automatic head only the last dense level is tested.
+  if (b->dense_last >= 0 && ix->head_level < 0) b->head = b->dense_last - 1;
+  b->counted = ix->count_unique && b->kind == 1 && !b->fixed;
+  choose_subtree(ix, b, b->maxpool ? ix->pw : ix->dp);
+  if (b->kind == 1 && b->fmt == GT_POOL_F32 && b->sub_top < 0 && !b->counted)
+    b->head = f32_first_of(ix, b, 1) - 1;
+  b->nb = bucket_bits_of(b->dense_last >= 0 ? b->dense_last : b->head, b->nt);
+  if (b->sub_top >= 0) b->nb = std::min(b->nb, b->sub_top);  // a subtree's entries share a bucket
+}
+
 int tq_of(int fmt) { return fmt == GT_POOL_F32 ? gt::kQueriesPerTileF32 : gt::kQueriesPerTile16; }
 
 gt_status zero_dev(void* p, size_t bytes, hipStream_t s) {
@@ -1193,21 +1212,7 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
   b->tq = tq;
   // a continuation tile sees the rows its call saw, whatever was inserted since
   b->n_epoch = b->cont ? b->ext_epoch : ix->n;
-  b->head = head_of(ix);
-  b->dense_last = kind == 1 ? dense_last_of(ix, fmt, b->head) : -1;
-  if (kind == 1) b->dense_last = adapt_dense_last(ix, b, fmt, maxp, b->dense_last, b->head);
-  // A dense step computes every pool of its level against every query, and
-  // a pool's score never exceeds its parent's (non-negative rows, sums
-  // rounded up), so a chain of dense steps keeps the same (pool, query) pairs
-  // as its last step alone, up to rounding, which only keeps more.  With an
-  // automatic head only the last dense level is tested.
-  if (b->dense_last >= 0 && ix->head_level < 0) b->head = b->dense_last - 1;
-  b->counted = ix->count_unique && kind == 1 && !b->fixed;
-  choose_subtree(ix, b, maxp ? ix->pw : ix->dp);
-  if (kind == 1 && fmt == GT_POOL_F32 && b->sub_top < 0 && !b->counted)
-    b->head = f32_first_of(ix, b, 1) - 1;
-  b->nb = bucket_bits_of(b->dense_last >= 0 ? b->dense_last : b->head, nt);
-  if (b->sub_top >= 0) b->nb = std::min(b->nb, b->sub_top);  // a subtree's entries share a bucket
+  choose_levels(ix, b);
   b->profile = ix->profile && !b->fixed;
   b->nw = 0;
   if (b->profile && !b->events) {

@@ -130,6 +130,14 @@ struct TreeArgs {
   float bound;             // a signed index's bound (0: none)
 };
 
+// Where a level step reads entry i of a slot in its input arrays.  Dense input
+// (every pool of every bucket) has no stored entries: i runs over the bucket's
+// pools, of which a slot may have more than its bcap entries, and the loads that
+// the kernels issue all the same go to the arrays' first entry.
+__host__ __device__ inline size_t input_entry(bool dense, uint32_t slot, int64_t bcap, uint32_t i) {
+  return dense ? 0 : (size_t)slot * bcap + i;
+}
+
 // Arguments of one level step of the frontier walk (parents at `level`,
 // children at `level + 1`).
 struct WalkLevelArgs {

@@ -233,11 +233,11 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_level(WalkLevelArgs a)
       // Loads are issued in both input modes and for padding lanes (at the
       // group's first entry, always valid) so that no branch separates them
       // from their use; dense input (every pool of the bucket) ignores them.
-      const size_t base = (size_t)slot * a.bcap;
       const uint32_t ef = e0 - (c16 >> 1);
       const uint32_t i0 = e0 < hi ? e0 : ef, i1 = e1 < hi ? e1 : ef;
-      const uint32_t ld0 = a.in_node[base + i0], ld1 = a.in_node[base + i1];
-      const uint64_t lm0 = a.in_mask[base + i0], lm1 = a.in_mask[base + i1];
+      const size_t at0 = input_entry(a.dense, slot, a.bcap, i0), at1 = input_entry(a.dense, slot, a.bcap, i1);
+      const uint32_t ld0 = a.in_node[at0], ld1 = a.in_node[at1];
+      const uint64_t lm0 = a.in_mask[at0], lm1 = a.in_mask[at1];
       const uint32_t first = bk << bshift;
       p0 = a.dense ? first + i0 : ld0;
       p1 = a.dense ? first + i1 : ld1;
@@ -562,14 +562,14 @@ __global__ __launch_bounds__(kWalkThreads, 1) void k_walk_wide(WalkLevelArgs a) 
       const uint32_t ehi = ghi[r];
       const uint32_t bk = (uint32_t)(b0 + r);
       const uint32_t slot = bk * (uint32_t)a.nt + (uint32_t)t;
-      const size_t ebase = (size_t)slot * a.bcap;
       const uint32_t ef = e0 - (c16 >> 1);
       const uint32_t i0 = e0 < ehi ? e0 : ef, i1 = e1 < ehi ? e1 : ef;
+      const size_t at0 = input_entry(a.dense, slot, a.bcap, i0), at1 = input_entry(a.dense, slot, a.bcap, i1);
       const uint32_t first = bk << bshift;
-      const uint32_t p0 = a.dense ? first + i0 : a.in_node[ebase + i0];
-      const uint32_t p1 = a.dense ? first + i1 : a.in_node[ebase + i1];
-      const uint64_t pm0 = (valid && e0 < ehi) ? (a.dense ? tmask : a.in_mask[ebase + i0]) : 0ull;
-      const uint64_t pm1 = (valid && e1 < ehi) ? (a.dense ? tmask : a.in_mask[ebase + i1]) : 0ull;
+      const uint32_t p0 = a.dense ? first + i0 : a.in_node[at0];
+      const uint32_t p1 = a.dense ? first + i1 : a.in_node[at1];
+      const uint64_t pm0 = (valid && e0 < ehi) ? (a.dense ? tmask : a.in_mask[at0]) : 0ull;
+      const uint64_t pm1 = (valid && e1 < ehi) ? (a.dense ? tmask : a.in_mask[at1]) : 0ull;
       // rows this lane loads: lanes 4R'..4R'+3 take 64 contiguous bytes of
       // row R' (entry R' / 2, child R' % 2) of each block
       const int src = 2 * (lane >> 3);
