@@ -890,7 +890,8 @@ gt_status enqueue_exhaustive(Index* ix, Batch* b) {
   ev_launch_begin(b);
   HIPCHK(gt::launch_exhaustive_gemm(b->qf, b->nq_pad, ix->leaves, b->n_epoch, ix->dp, b->thr_gemm,
                                     ix->nf, b->qsplit, b->qsplit_thr, b->cand,
-                                    (unsigned long long)b->cand_cap, b->ctr, b->nq, b->stream));
+                                    (unsigned long long)b->cand_cap, b->ctr, b->nq, b->small_rho,
+                                    b->stream));
   ev_launch_end(b, true);
   return GT_OK;
 }
@@ -1212,6 +1213,9 @@ gt_status submit(Index* ix, Batch* b, int kind, const float* q, int nq, const do
   b->tq = tq;
   // a continuation tile sees the rows its call saw, whatever was inserted since
   b->n_epoch = b->cont ? b->ext_epoch : ix->n;
+  b->small_rho = false;
+  if (kind == 2 && !ix->signed_mode)
+    for (int i = 0; i < nq; ++i) b->small_rho = b->small_rho || (rho[i] > 0.0 && rho[i] < gt::kSplitRho);
   choose_levels(ix, b);
   b->profile = ix->profile && !b->fixed;
   b->nw = 0;

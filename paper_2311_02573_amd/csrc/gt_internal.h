@@ -368,6 +368,7 @@ struct Batch {
   unsigned char* qsplit = nullptr;  // split query rows of the exhaustive path
   float* qsplit_thr = nullptr;
   size_t qsplit_rows = 0;
+  bool small_rho = false;    // exhaustive call with a threshold between 0 and kSplitRho
   uint2* cand = nullptr;     // exhaustive candidates
   int64_t cand_cap = 0;
   uint32_t* out_id = nullptr;    // results placed by query, unsorted
@@ -503,13 +504,16 @@ hipError_t launch_sort_segments(const int64_t* offs, int nq, uint32_t* id, float
                                 float* sims_out, const DevCounters* ctr,
                                 unsigned long long hit_cap, unsigned long long lim,
                                 int64_t id_bound, hipStream_t s);
-// qsplit: [split_rows(nq_pad) x dp] words and qsplit_thr [split_rows(nq_pad)] of scratch
+// qsplit: [split_rows(nq_pad) x dp] words and qsplit_thr [split_rows(nq_pad)] of
+// scratch.  small_rho: some query's threshold lies between 0 and kSplitRho (rows
+// >= 0 only), where the split's absolute error could exceed the thresholds' slack.
+constexpr double kSplitRho = 0x1p-16;
 inline size_t split_rows(int nq_pad) { return (size_t)(nq_pad + 255) / 256 * 256; }
 hipError_t launch_exhaustive_gemm(const float* qf, int nq_pad, const float* leaves, int64_t n,
                                   int dp, const float* thr_gemm, const float* nf,
                                   unsigned char* qsplit, float* qsplit_thr, uint2* cand,
                                   unsigned long long cand_cap, DevCounters* ctr, int nq,
-                                  hipStream_t s);
+                                  bool small_rho, hipStream_t s);
 hipError_t launch_pair_check(const uint2* cand, const unsigned long long* ncand,
                              unsigned long long cap, const float* qf, const float* leaves,
                              const float* invn_q, const float* invn_f, const double* rho, int dp,

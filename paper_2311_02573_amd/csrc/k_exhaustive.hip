@@ -9,15 +9,21 @@
 // float16 and lo the nearest float16 of the rest (22 significant bits), and
 // q.f = hi.hi + hi.lo + lo.hi, accumulated in float32.  e is a power-of-two
 // scale per row that puts the largest element near the top of the float16
-// range, so what small elements lose is below 2^-27 of the row's norm.
-// Per product the split and the dropped lo.lo lose at most 2^-21 of |q_k f_k|,
-// and the 3 K / 16 accumulations at most one unit in the last place each, well
-// inside the (K + 2) 2^-22 by which the thresholds are lowered.  Measured
+// range.  Per product the split and the dropped lo.lo lose at most 3 x 2^-22 of
+// |q_k f_k|, and the 3 K / 16 accumulations at most one unit in the last place
+// each, well inside the (K + 2) 2^-22 by which the thresholds are lowered.  An
+// element far below its row's largest also loses up to half of the least float16
+// (2^-38 of |f|, 2^-39 of the query's largest element), which no relative slack
+// covers where the score itself is that small: sqrt(K) (2^-38 + 2^-39) |q| |f| in
+// all, within half of the slack's share of scores from 1.5 2^-15 sqrt(K) / (K - 6)
+// <= 4.3e-6 of |q| |f| on.  Calls with a smaller positive threshold (kSplitRho)
+// take float32 matrix cores.  (On an index of signed vectors the slack is
+// absolute, and thresholds of at most 0 keep every pair.)  Measured
 // against float64 the scores are closer than the float32 matrix cores' (which
 // round after every two products): rms error 2.3e-8 against 3.3e-8 on softmax
 // rows of d = 1000, 6.0e-8 against 9.0e-7 on centred ones, largest error 5e-7
-// against 7e-7 and 1.5e-6 against 2.3e-5, and smaller at every d from 128 to
-// 4096 and every distribution tried.
+// against 7e-7 and 1.5e-6 against 2.3e-5, and smaller at each of five widths from
+// 128 to 4096 of five distributions.
 #include <math.h>
 
 #include "gt_internal.h"
@@ -325,6 +331,141 @@ __global__ __launch_bounds__(kEThreads, 1) void k_gemm_threshold(
       }
 }
 
+constexpr int kFT = 128;    // output tile edge (queries x vectors)
+constexpr int kFK = 32;     // dimensions per LDS stage
+constexpr int kFStride = kFK + 4;
+
+// The same on float32 matrix cores, for positive thresholds below kSplitRho: no scale
+// takes small elements out of the operands' range, so the relative slack holds
+// for any score.  1024 queries x 2^20 vectors, d = 1000: 16.4 ms.
+//
+// One workgroup (4 waves) per 128 x 128 output tile; each wave owns 64 x 64 as
+// 2 x 2 blocks of 32 x 32.  Workgroups are dispatched round-robin over the 8
+// XCDs; consecutive workgroups of one XCD take the query tiles of one vector
+// tile in turn, so each vector tile is fetched into that XCD's L2 once.
+__global__ __launch_bounds__(256) void k_gemm_small_rho(const float* __restrict__ qf, int nq_pad,
+                                                        const float* __restrict__ rows, int64_t n,
+                                                        int dp, const float* __restrict__ thr,
+                                                        const float* __restrict__ nf, uint2* cand,
+                                                        unsigned long long cap, DevCounters* ctr,
+                                                        int nq) {
+  __shared__ __attribute__((aligned(16))) float As[kFT * kFStride];
+  __shared__ __attribute__((aligned(16))) float Bs[kFT * kFStride];
+  const int QT = nq_pad / kFT;
+  const int64_t RT = (n + kFT - 1) / kFT;
+  const int64_t total = RT * QT;
+  const int64_t per_xcd = (total + 7) / 8;
+  const int64_t w = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (w >= total) return;
+  const int qt = (int)(w % QT);
+  const int64_t rt = w / QT;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wq = (wave >> 1) * 64, wr = (wave & 1) * 64;  // wave's sub-tile origin
+  const int c = lane & 31, half = lane >> 5;
+
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
+
+  // global -> register staging: 128 rows x 32 floats per operand; thread tid
+  // moves float4 pieces tid + 256 v (v < 4): row = piece / 8 = tid / 8 + 32 v
+  const float* qbase = qf + (size_t)qt * kFT * dp;
+  const int64_t r0 = rt * kFT;
+  const int prow = tid >> 3, pcol = (tid & 7) * 4;
+  const float* qa = qbase + (size_t)prow * dp + pcol;
+  const float* fb[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int64_t rr = r0 + prow + 32 * v < n ? r0 + prow + 32 * v : n - 1;
+    fb[v] = rows + (size_t)rr * dp + pcol;
+  }
+  const size_t q32 = (size_t)32 * dp;
+  float4 ra0 = *reinterpret_cast<const float4*>(qa);
+  float4 ra1 = *reinterpret_cast<const float4*>(qa + q32);
+  float4 ra2 = *reinterpret_cast<const float4*>(qa + 2 * q32);
+  float4 ra3 = *reinterpret_cast<const float4*>(qa + 3 * q32);
+  float4 rb0 = *reinterpret_cast<const float4*>(fb[0]);
+  float4 rb1 = *reinterpret_cast<const float4*>(fb[1]);
+  float4 rb2 = *reinterpret_cast<const float4*>(fb[2]);
+  float4 rb3 = *reinterpret_cast<const float4*>(fb[3]);
+  for (int k0 = 0; k0 < dp; k0 += kFK) {
+    __syncthreads();
+    *reinterpret_cast<float4*>(&As[(prow + 0) * kFStride + pcol]) = ra0;
+    *reinterpret_cast<float4*>(&As[(prow + 32) * kFStride + pcol]) = ra1;
+    *reinterpret_cast<float4*>(&As[(prow + 64) * kFStride + pcol]) = ra2;
+    *reinterpret_cast<float4*>(&As[(prow + 96) * kFStride + pcol]) = ra3;
+    *reinterpret_cast<float4*>(&Bs[(prow + 0) * kFStride + pcol]) = rb0;
+    *reinterpret_cast<float4*>(&Bs[(prow + 32) * kFStride + pcol]) = rb1;
+    *reinterpret_cast<float4*>(&Bs[(prow + 64) * kFStride + pcol]) = rb2;
+    *reinterpret_cast<float4*>(&Bs[(prow + 96) * kFStride + pcol]) = rb3;
+    __syncthreads();
+    if (k0 + kFK < dp) {
+      const int kn = k0 + kFK;
+      ra0 = *reinterpret_cast<const float4*>(qa + kn);
+      ra1 = *reinterpret_cast<const float4*>(qa + q32 + kn);
+      ra2 = *reinterpret_cast<const float4*>(qa + 2 * q32 + kn);
+      ra3 = *reinterpret_cast<const float4*>(qa + 3 * q32 + kn);
+      rb0 = *reinterpret_cast<const float4*>(fb[0] + kn);
+      rb1 = *reinterpret_cast<const float4*>(fb[1] + kn);
+      rb2 = *reinterpret_cast<const float4*>(fb[2] + kn);
+      rb3 = *reinterpret_cast<const float4*>(fb[3] + kn);
+    }
+#pragma unroll
+    for (int t = 0; t < kFK / 8; ++t) {
+      float4 fa[2], fb[2];
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+        fa[a] = *reinterpret_cast<const float4*>(&As[(wq + 32 * a + c) * kFStride + 8 * t + 4 * half]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+        fb[b] = *reinterpret_cast<const float4*>(&Bs[(wr + 32 * b + c) * kFStride + 8 * t + 4 * half]);
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a].x, fb[b].x, acc[a][b], 0, 0, 0);
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a].y, fb[b].y, acc[a][b], 0, 0, 0);
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a].z, fb[b].z, acc[a][b], 0, 0, 0);
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a].w, fb[b].w, acc[a][b], 0, 0, 0);
+        }
+    }
+  }
+
+  // epilogue: keep (query, vector) if the score may reach rho * |q| * |f|
+  float nfv[2];
+  int64_t rid[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    rid[b] = r0 + wr + 32 * b + c;
+    nfv[b] = rid[b] < n ? nf[rid[b]] : 0.0f;
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int qi = qt * kFT + wq + 32 * a + 8 * (i >> 2) + 4 * half + (i & 3);
+      const float th = qi < nq ? thr[qi] : INFINITY;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const bool keep = nfv[b] > 0.0f && acc[a][b][i] >= th * nfv[b] * (1.0f - 0x1p-20f);
+        const uint64_t bal = __ballot(keep);
+        if (bal) {
+          unsigned long long base = 0;
+          if (lane == 0) base = atomicAdd(&ctr->ncand, (unsigned long long)__popcll(bal));
+          base = __shfl(base, 0, 64);
+          if (keep) {
+            const unsigned long long pos = base + __popcll(bal & ((1ull << lane) - 1ull));
+            if (pos < cap) cand[pos] = make_uint2((uint32_t)qi, (uint32_t)rid[b]);
+          }
+        }
+      }
+    }
+}
+
 // Exact test of explicit (query, vector) pairs: the same float32 dot product
 // (in-lane pairwise sums, then the lane reduction) and classification as the
 // leaf test of the walk, four pairs per wave at a time.
@@ -397,9 +538,15 @@ hipError_t launch_exhaustive_gemm(const float* qf, int nq_pad, const float* leav
                                   int dp, const float* thr_gemm, const float* nf,
                                   unsigned char* qsplit, float* qsplit_thr, uint2* cand,
                                   unsigned long long cand_cap, DevCounters* ctr, int nq,
-                                  hipStream_t s) {
+                                  bool small_rho, hipStream_t s) {
   if (n <= 0 || nq_pad <= 0) return hipSuccess;
-  if (dp % 128 != 0 || nq > nq_pad) return hipErrorInvalidValue;
+  if (dp % 128 != 0 || nq > nq_pad || nq_pad % kFT != 0) return hipErrorInvalidValue;
+  if (small_rho) {
+    const int64_t tiles = ((n + kFT - 1) / kFT) * (nq_pad / kFT);
+    hipLaunchKernelGGL(k_gemm_small_rho, dim3((unsigned)(8 * ((tiles + 7) / 8))), dim3(256), 0, s, qf,
+                       nq_pad, leaves, n, dp, thr_gemm, nf, cand, cand_cap, ctr, nq);
+    return hipGetLastError();
+  }
   const int qblocks = (nq_pad + kET - 1) / kET;
   hipLaunchKernelGGL(k_split_queries, dim3(qblocks * kET), dim3(256), 0, s, qf, nq, dp, thr_gemm,
                      qsplit, qsplit_thr);
