@@ -269,7 +269,11 @@ void gt_batch_destroy(gt_batch* batch);
  *                INVALID_ARG, DEVICE.
  *   gt_batch_poll / gt_batch_finish / gt_batch_destroy as for any workspace;
  *   after a result overflow of a continued call, the next finish runs its
- *   tiles again.  A tile whose candidates outgrow `pairs` fails with CAPACITY.
+ *   tiles again.  A tile whose candidates outgrow the memory runs query by
+ *   query; a query whose candidates alone do fails the call with CAPACITY.
+ * gt_batch_needed_pairs  after that failure: the candidates of the query that
+ *                did not fit (0 after any other end of a call).  Submitted again
+ *                with at least as many `pairs`, the call gets past that query.
  * gt_batch_info  of the workspace's last finished call: the largest number
  *                of frontier entries at any level, the results, and how many
  *                tiles ran one by one (0: the call fitted its memory).  Any
@@ -282,6 +286,7 @@ gt_status gt_batch_submit_external(gt_batch* batch, const float* q_dev, int32_t 
                                    int64_t mem_bytes, int64_t pairs, void* stream);
 gt_status gt_batch_info(const gt_batch* batch, int64_t* max_level_entries, int64_t* results,
                         int32_t* continued_tiles);
+gt_status gt_batch_needed_pairs(const gt_batch* batch, int64_t* pairs);
 
 /* Counters of the index and of its last query call.  Synchronises the device
  * stream of the last call.  Errors: INVALID_ARG. */

@@ -558,7 +558,7 @@ gt_status batch_reserve(Batch* b, int nq_pad, int nt) {
 gt_status grow_hits(Batch* b, int64_t need) {
   Index* ix = b->ix;
   if (b->fixed) {
-    b->hits_overflowed = true;
+    b->hits_needed = need;
     return fail(GT_ERR_CAPACITY, "the call's " + std::to_string(need) +
                                      " leaf candidates exceed the fixed scratch (room for " +
                                      std::to_string(b->hit_cap) + "); use fewer queries per call");
@@ -1433,14 +1433,14 @@ gt_status continue_by_tiles(Index* ix, Batch* b, int64_t max_results, int64_t* o
     int64_t* ids_t = room > 0 ? ids + total : nullptr;
     float* sims_t = room > 0 ? sims + total : nullptr;
     int64_t tot_t = 0;
-    b->hits_overflowed = false;
+    b->hits_needed = 0;
     st = carve_budget(ix, b, b->ext_mem, b->ext_bytes, n, b->user_fmt, -1, false);
     if (st == GT_OK) {
       set_targets(b, room, offsets + a, ids_t, sims_t);
       st = submit(ix, b, 1, b->q_in + (size_t)a * ix->d, n, rho.data() + a, b->user_fmt, s);
     }
     if (st == GT_OK) st = finish(ix, b, room, offsets + a, ids_t, sims_t, &tot_t, false);
-    if (st == GT_ERR_CAPACITY && b->hits_overflowed && n > 1) {
+    if (st == GT_ERR_CAPACITY && b->hits_needed > 0 && n > 1) {
       // too many candidates for one tile: its queries one by one
       std::vector<std::pair<int, int>> singles;
       for (int k = 0; k < n; ++k) singles.emplace_back(a + k, 1);
@@ -1865,6 +1865,7 @@ gt_status gt_batch_submit_external(gt_batch* b, const float* q_dev, int32_t nq,
   b->cont_again = false;
   b->continued_tiles = 0;
   b->ext_epoch = ix->n;
+  b->hits_needed = 0;
   TRY(carve_budget(ix, b, mem_dev, (size_t)mem_bytes, nq, (int)fmt, b->ext_pairs, true));
   set_targets(b, 0, nullptr, nullptr, nullptr);
   return submit(ix, b, 1, q_dev, nq, b->rho_in.data(), (int)fmt, (hipStream_t)stream);
@@ -1877,6 +1878,13 @@ gt_status gt_batch_info(const gt_batch* b, int64_t* max_level_entries, int64_t* 
   if (max_level_entries) *max_level_entries = b->last_max_entries;
   if (results) *results = b->last_results;
   if (continued_tiles) *continued_tiles = b->continued_tiles;
+  return GT_OK;
+}
+
+gt_status gt_batch_needed_pairs(const gt_batch* b, int64_t* pairs) {
+  g_err.clear();
+  if (!b || !pairs) return fail(GT_ERR_INVALID_ARG, "NULL argument");
+  *pairs = b->hits_needed;
   return GT_OK;
 }
 

@@ -29,7 +29,7 @@ GT_MAX_LEVELS = 40
 
 EXPORTS = ["gt_build_tree", "gt_insert", "gt_query_batch", "gt_query_batch_noalloc",
            "gt_exhaustive", "gt_call_bytes", "gt_batch_create_external",
-           "gt_batch_submit_external", "gt_batch_info", "gt_batch_create",
+           "gt_batch_submit_external", "gt_batch_info", "gt_batch_needed_pairs", "gt_batch_create",
            "gt_batch_submit", "gt_batch_poll", "gt_batch_finish", "gt_batch_destroy",
            "gt_get_stats", "gt_read_pools", "gt_set_option", "gt_destroy", "gt_last_error"]
 
@@ -38,6 +38,7 @@ class GTError(RuntimeError):
     def __init__(self, status: int, msg: str):
         super().__init__(f"{STATUS_NAMES.get(status, status)}: {msg}")
         self.status = status
+        self.needed_pairs = 0  # candidates that an external workspace's call had no room for
 
 
 class GTStats(ctypes.Structure):
@@ -92,6 +93,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.gt_batch_info.restype = st
     lib.gt_batch_info.argtypes = [vp, ctypes.POINTER(i64), ctypes.POINTER(i64),
                                   ctypes.POINTER(i32)]
+    lib.gt_batch_needed_pairs.restype = st
+    lib.gt_batch_needed_pairs.argtypes = [vp, ctypes.POINTER(i64)]
     lib.gt_batch_create.restype = st
     lib.gt_batch_create.argtypes = [vp, i32, ctypes.POINTER(vp)]
     lib.gt_batch_submit.restype = st
@@ -384,6 +387,19 @@ class ExternalWorkspace(Workspace):
                                               ctypes.c_void_p(mem_ptr), int(mem_bytes), int(pairs),
                                               ctypes.c_void_p(self.stream.cuda_stream)))
         self._nq = nq
+
+    def finish(self, max_results=None) -> Results:
+        """As Workspace.finish.  A call that ends with GT_ERR_CAPACITY because one
+        query's candidates do not fit its memory says how many there are
+        (GTError.needed_pairs): submit it again with at least that many pairs."""
+        try:
+            return super().finish(max_results)
+        except GTError as e:
+            if e.status == GT_ERR_CAPACITY:
+                p = ctypes.c_int64(0)
+                _check(lib().gt_batch_needed_pairs(self._h, ctypes.byref(p)))
+                e.needed_pairs = p.value
+            raise
 
     def info(self) -> dict:
         """Of the last finished call: largest frontier level, results, tiles

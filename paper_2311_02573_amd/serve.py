@@ -12,7 +12,11 @@ not, the packed group is cut back (later requests stay queued), and if not
 even its first request fits, the requests wait until running calls return
 their memory.  A call whose frontier outgrows its estimate still completes
 (the library then runs it one query tile at a time), only later, and raises
-the estimate for the calls after it.  Running calls overlap on the device.
+the estimate for the calls after it.  A call with a query whose candidates
+alone outgrow its memory ends with their number (an error's needed_pairs);
+its requests go back to the head of the queue, one to a call, and the one that
+holds the query is admitted with that room.  A request that the whole arena has
+no room for then ends as failed.  Running calls overlap on the device.
 
 Inserts (the paper's streaming setting, Sec. 4) are applied between steps; a
 request sees the vectors indexed when it was admitted.  Latency = completion
@@ -49,7 +53,10 @@ class Request:
     epoch_n: int | None = None  # vectors visible to the request
     results: list | None = None  # per query: (ids int64, sims float32)
     timeout_s: float | None = None  # longest wait for admission (None: no limit)
-    status: str = "waiting"      # waiting, running, done, cancelled, timeout
+    status: str = "waiting"      # waiting, running, done, cancelled, timeout, failed
+    alone: bool = False          # shares no call: it was in one that had no room for its candidates
+    pairs_min: int = 0           # candidates its own call had no room for, with a margin
+    error: str | None = None     # why it failed
 
     @property
     def nq(self) -> int:
@@ -142,6 +149,7 @@ class _Call:
     sizes: list
     offset: int
     nbytes: int
+    pairs: int
 
 
 class Server:
@@ -158,12 +166,13 @@ class Server:
         self.busy: list[_Call] = []
         self.waiting: collections.deque[Request] = collections.deque()
         self.finished: list[Request] = []
-        self.dropped: list[Request] = []   # cancelled or timed out
+        self.dropped: list[Request] = []   # cancelled, timed out or failed
         self.est = estimator or Estimator()
         self.clock = clock
         self.t0 = clock()
         self.memory_waits = 0        # admission passes that found no memory for the next request
         self.continued_calls = 0     # calls whose frontier outgrew their memory
+        self.retried_calls = 0       # calls whose requests ran again for lack of candidate room
         self.calls = 0
 
     def now(self) -> float:
@@ -198,13 +207,14 @@ class Server:
             self.finished.append(req)
 
     def _expire(self):
-        """Requests that waited past their admission timeout end unserved."""
+        """Requests that waited past their admission timeout end unserved (one
+        that was admitted and has to run again no longer waits for it)."""
         if not self.waiting:
             return
         now = self.now()
         keep = collections.deque()
         for r in self.waiting:
-            if r.timeout_s is not None and now - r.arrival > r.timeout_s:
+            if r.timeout_s is not None and r.admitted is None and now - r.arrival > r.timeout_s:
                 self._end(r, "timeout")
             else:
                 keep.append(r)
@@ -221,11 +231,12 @@ class Server:
         self._admit()
         return done
 
-    def _memory_for(self, nq: int, least_ok: bool = False):
-        """(offset, bytes, pairs) reserved in the arena for a call of nq
-        queries at its estimated memory (or at the least memory the call
+    def _memory_for(self, group, least_ok: bool = False):
+        """(offset, bytes, pairs) reserved in the arena for a call of the group's
+        requests at its estimated memory (or at the least memory the call
         accepts, with least_ok), or None."""
-        pairs = self.est.pairs(nq)
+        nq = sum(r.nq for r in group)
+        pairs = max(self.est.pairs(nq), group[0].pairs_min)  # (a request with a minimum is alone)
         need, least = self.backend.call_bytes(nq, self.est.frontier(nq), pairs)
         nbytes = least if least_ok else need
         off = self.arena.alloc(nbytes)
@@ -234,13 +245,13 @@ class Server:
     def _admit(self):
         while self.free and self.waiting:
             k, total = 0, 0
-            while k < len(self.waiting) and total + self.waiting[k].nq <= self.max_queries:
+            while (k < len(self.waiting) and total + self.waiting[k].nq <= self.max_queries
+                   and not (k > 0 and (self.waiting[0].alone or self.waiting[k].alone))):
                 total += self.waiting[k].nq
                 k += 1
             got = None
             while k > 0:
-                nq = sum(self.waiting[i].nq for i in range(k))
-                got = self._memory_for(nq)
+                got = self._memory_for([self.waiting[i] for i in range(k)])
                 if got is not None:
                     break
                 k -= 1          # later requests stay queued
@@ -249,10 +260,16 @@ class Server:
                 # with the least memory it accepts (its frontier may then run
                 # tile by tile)
                 k = 1
-                got = self._memory_for(self.waiting[0].nq, least_ok=True)
+                first = self.waiting[0]
+                got = self._memory_for([first], least_ok=True)
                 if got is None:
-                    raise MemoryError(f"a request of {self.waiting[0].nq} queries does not fit "
-                                      f"the serving memory budget of {self.arena.size} bytes")
+                    msg = (f"a request of {first.nq} queries does not fit "
+                           f"the serving memory budget of {self.arena.size} bytes")
+                    if not first.pairs_min:
+                        raise MemoryError(msg)
+                    first.error = f"{msg} with its {first.pairs_min} candidates"
+                    self._end(self.waiting.popleft(), "failed")
+                    continue
             if got is None:
                 self.memory_waits += 1
                 return
@@ -268,7 +285,7 @@ class Server:
             q = self.backend.concat([r.queries for r in group])
             rho = np.concatenate([r.rho for r in group])
             self.backend.submit(ws, q, rho, self.pool, off, nbytes, pairs)
-            self.busy.append(_Call(ws, group, [r.nq for r in group], off, nbytes))
+            self.busy.append(_Call(ws, group, [r.nq for r in group], off, nbytes, pairs))
             self.calls += 1
 
     def _complete(self) -> int:
@@ -278,7 +295,14 @@ class Server:
             if not call.ws.poll():
                 still.append(call)
                 continue
-            lists = call.ws.finish().to_lists()
+            try:
+                lists = call.ws.finish().to_lists()
+            except Exception as e:
+                if getattr(e, "needed_pairs", 0) <= call.pairs:
+                    raise
+                self._again(call, e.needed_pairs)
+                done += sum(r.status == "cancelled" for r in call.requests)
+                continue
             info = call.ws.info()
             self.arena.release(call.offset, call.nbytes)
             nq = sum(call.sizes)
@@ -300,6 +324,23 @@ class Server:
         self.busy = still
         return done
 
+    def _again(self, call: _Call, needed_pairs: int):
+        """Queues the requests of a call that had no room for needed_pairs
+        candidates again, at the head: each by itself, or its only one with that
+        room (and a margin for rows inserted by then)."""
+        self.arena.release(call.offset, call.nbytes)
+        self.free.append(call.ws)
+        self.retried_calls += 1
+        for r in reversed(call.requests):
+            if r.status == "cancelling":
+                self._end(r, "cancelled")
+                continue
+            r.status = "waiting"
+            r.alone = True
+            if len(call.requests) == 1:
+                r.pairs_min = max(r.pairs_min, needed_pairs + needed_pairs // 4 + 1024)
+            self.waiting.appendleft(r)
+
     def drain(self, timeout_s: float = 60.0):
         t_end = self.now() + timeout_s
         while not self.idle:
@@ -311,14 +352,14 @@ class Server:
     def summary(self) -> dict:
         return {"memory_budget_bytes": self.arena.size, "memory_peak_bytes": self.arena.peak,
                 "calls": self.calls, "memory_waits": self.memory_waits,
-                "continued_calls": self.continued_calls,
+                "continued_calls": self.continued_calls, "retried_calls": self.retried_calls,
                 "estimate_entries_per_tile": round(self.est.entries, 1),
                 "estimate_pairs_per_query": round(self.est.pairs_q, 1)}
 
 
 def latency_summary(reqs) -> dict:
-    """Latency percentiles over the requests served (cancelled and timed-out
-    requests are counted apart)."""
+    """Latency percentiles over the requests served (cancelled, timed-out and
+    failed requests are counted apart)."""
     served = [r for r in reqs if r.status == "done" and r.latency is not None]
     lat = np.array([r.latency for r in served]) * 1e3
     nq = sum(r.nq for r in served)
@@ -327,6 +368,7 @@ def latency_summary(reqs) -> dict:
     return {"requests": int(len(lat)), "queries": int(nq),
             "cancelled": sum(r.status == "cancelled" for r in reqs),
             "timed_out": sum(r.status == "timeout" for r in reqs),
+            "failed": sum(r.status == "failed" for r in reqs),
             "p50_ms": round(float(np.percentile(lat, 50)), 3),
             "p99_ms": round(float(np.percentile(lat, 99)), 3),
             "mean_ms": round(float(lat.mean()), 3)}
