@@ -17,6 +17,7 @@ import json
 import os
 import sys
 import time
+import traceback
 
 import numpy as np
 
@@ -165,6 +166,21 @@ def measure_roofline(idx, q, rho, pool, nq, walk_subtract, d, side_steps):
     return roofline, su, first_sparse
 
 
+def side_leg(name, leg):
+    """A leg beside the headline: its failure is reported in its place and does
+    not take the line with it."""
+    try:
+        return leg()
+    except Exception as e:
+        log(f"{name} leg failed:\n{traceback.format_exc()}")
+        return {"error": f"{type(e).__name__}: {e}"}
+
+
+def serving_legs(seconds, torch, gt, synth, dev):
+    return {name: side_leg(name, lambda: leg(seconds, torch, gt, synth, dev))
+            for name, leg in (("serving", serving_leg), ("serving_stress", stress_serving_leg))}
+
+
 def cpu_info():
     """CPU model (from /proc/cpuinfo) and the cores this process may use."""
     model = None
@@ -232,9 +248,7 @@ def main():
         sys.exit(1)
     dev = torch.device("cuda:0")
     if args.leg == "serve":
-        out = {"serving": serving_leg(args.serve_seconds, torch, gt, synth, dev),
-               "serving_stress": stress_serving_leg(args.serve_seconds, torch, gt, synth, dev)}
-        print(json.dumps(out), flush=True)
+        print(json.dumps(serving_legs(args.serve_seconds, torch, gt, synth, dev)), flush=True)
         return
 
     t0 = time.time()
@@ -586,11 +600,10 @@ def main():
     del idx, q
     torch.cuda.empty_cache()
     if args.signed_n > 0 and not args.no_side:
-        out["signed"] = signed_leg(args, torch, gt, synth, dev)
+        out["signed"] = side_leg("signed", lambda: signed_leg(args, torch, gt, synth, dev))
         torch.cuda.empty_cache()
     if args.serve_seconds > 0:
-        out["serving"] = serving_leg(args.serve_seconds, torch, gt, synth, dev)
-        out["serving_stress"] = stress_serving_leg(args.serve_seconds, torch, gt, synth, dev)
+        out.update(serving_legs(args.serve_seconds, torch, gt, synth, dev))
     print(json.dumps(out), flush=True)
     if args.copy_calib:
         src = torch.ones(1 << 28, dtype=torch.float32, device=dev)
