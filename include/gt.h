@@ -308,15 +308,17 @@ gt_status gt_get_stats(const gt_index* index, gt_stats* out);
 gt_status gt_read_pools(const gt_index* index, int32_t level, int64_t first, int64_t count,
                         gt_pool fmt, void* host_out);
 
-/* Runtime knobs (benchmarking and tests; results never depend on them):
+/* Runtime knobs (benchmarking and tests; results never depend on them).  Calls of
+ * few query tiles or on small trees walk all levels in one launch; a
+ * "head_level", "grid", "dense_last" or "walk_subtract" other than its default,
+ * which asks for steps of the level-by-level walk, has every call take those.
  *   "profile"     0/1: time kernel groups with HIP events (gt_stats.ms_*)
  *   "head_level"  level whose pools are all taken as live, 0..depth-1; tests
  *                 start at level head_level + 1 (-1 = automatic: with dense
  *                 steps only the last dense level is tested; float32 pools
  *                 start where pools hold about 32 rows and follow the calls'
  *                 frontiers, unless dense_last is given)
- *   "grid"        workgroups of the persistent walk kernels (0 = one per CU; any
- *                 other value also has every call walked level by level)
+ *   "grid"        workgroups of the persistent walk kernels (0 = one per CU)
  *   "dense_last"  last level tested with dense steps, every pool against every
  *                 query (-2 = automatic, -1 = none; bf16 and fp8 pools only).
  *                 Automatic: the level whose pools hold about 16 populated

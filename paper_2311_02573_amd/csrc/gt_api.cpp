@@ -288,13 +288,14 @@ int bucket_bits_of(int sparse_from, int nt) {
 //     641; 2^14 x 1000 (512), 2048 267 / 858; few pools of few columns: 2^16 x
 //     300 (2,048), 2048 440 / 646, 2^18 x 128 (8,192), 1024 722 / 764
 // and 88 against 201 - 327 us for one query.  Calls with options that ask for
-// the level kernels (an explicit head or grid, row counting) take those.
+// the level kernels (an explicit head, grid, dense level or subtraction step,
+// row counting) take those.
 constexpr int kSubtreeTiles = 128;
 
 void choose_subtree(const Index* ix, Batch* b, int width) {
   b->sub_top = -1;
   if (b->kind != 1 || b->nt < 1 || b->nt > kSubtreeTiles || b->n_epoch < 1 || b->counted ||
-      ix->grid > 0 || ix->head_level >= 0)
+      ix->grid > 0 || ix->head_level >= 0 || ix->dense_last != -2 || ix->walk_subtract >= 0)
     return;
   const bool f32 = b->fmt == GT_POOL_F32;
   int first = b->dense_last >= 0 ? b->dense_last : f32 ? f32_first_of(ix, b, 0) : b->head + 1;
