@@ -125,7 +125,8 @@ def measure_roofline(idx, q, rho, pool, nq, walk_subtract, d, side_steps):
         raw_sparse += ((1 << h) * su["last_tiles"] - entries[h]) * 2 * dp * esz
     raw_leaf = entries[D - 1] * 2 * dp * 4
     n_sub = len(sub_levels)
-    walk_name = (f"k_walk_level<{pool}>" if n_sub == 0 else
+    walk_name = (f"k_walk_subtree<{pool}>" if n_dense == 0 and n_sparse == 1 < D - 1 - h else
+                 f"k_walk_level<{pool}>" if n_sub == 0 else
                  "k_walk_sub<bf16>" if n_sub == n_sparse else "k_walk_sub+k_walk_level<bf16>")
     groups = {
         f"k_dense_level<{pool}>": (dense_bytes, ms_dense, n_dense),

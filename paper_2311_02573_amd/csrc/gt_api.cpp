@@ -288,13 +288,13 @@ int bucket_bits_of(int sparse_from, int nt) {
 //     641; 2^14 x 1000 (512), 2048 267 / 858; few pools of few columns: 2^16 x
 //     300 (2,048), 2048 440 / 646, 2^18 x 128 (8,192), 1024 722 / 764
 // and 88 against 201 - 327 us for one query.  Calls with options that ask for
-// the level kernels (an explicit head, grid, dense level or subtraction step,
-// row counting) take those.
+// the level kernels (an explicit head, grid, dense level or subtraction step)
+// take those.
 constexpr int kSubtreeTiles = 128;
 
 void choose_subtree(const Index* ix, Batch* b, int width) {
   b->sub_top = -1;
-  if (b->kind != 1 || b->nt < 1 || b->nt > kSubtreeTiles || b->n_epoch < 1 || b->counted ||
+  if (b->kind != 1 || b->nt < 1 || b->nt > kSubtreeTiles || b->n_epoch < 1 ||
       ix->grid > 0 || ix->head_level >= 0 || ix->dense_last != -2 || ix->walk_subtract >= 0)
     return;
   const bool f32 = b->fmt == GT_POOL_F32;
@@ -337,7 +337,7 @@ void choose_levels(const Index* ix, Batch* b) {
   if (b->dense_last >= 0 && ix->head_level < 0) b->head = b->dense_last - 1;
   b->counted = ix->count_unique && b->kind == 1 && !b->fixed;
   choose_subtree(ix, b, b->maxpool ? ix->pw : ix->dp);
-  if (b->kind == 1 && b->fmt == GT_POOL_F32 && b->sub_top < 0 && !b->counted)
+  if (b->kind == 1 && b->fmt == GT_POOL_F32 && b->sub_top < 0)
     b->head = f32_first_of(ix, b, 1) - 1;
   b->nb = bucket_bits_of(b->dense_last >= 0 ? b->dense_last : b->head, b->nt);
   if (b->sub_top >= 0) b->nb = std::min(b->nb, b->sub_top);  // a subtree's entries share a bucket
@@ -692,6 +692,7 @@ gt_status enqueue_walk(Index* ix, Batch* b) {
     a.out_mask = b->fr_mask[(D - 1) & 1];
     a.lvl_count = b->lvl_count;
     a.stat = gt::stat_levels(b->lvl_count);
+    a.bitmap = bitmap;
     a.over = &b->ctr->fr_over;
     ev_launch_begin(b);
     HIPCHK(gt::launch_walk_subtree(f, a, s));

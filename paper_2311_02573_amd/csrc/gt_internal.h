@@ -216,6 +216,7 @@ struct SubtreeArgs {
   uint64_t* out_mask;
   uint32_t* lvl_count;      // [levels x kMaxSlots]
   unsigned long long* stat; // stripe 0, level 0 of the test counters
+  uint32_t* bitmap;         // optional: one bit per tree row read
   unsigned int* over;
 };
 // The subtree walk's shape for a call whose first tested level is `first`

@@ -310,6 +310,10 @@ __global__ __launch_bounds__(kSubtreeThreads, 1) void k_walk_subtree(SubtreeArgs
         if ((lane & 3) == x) mine = part;
       }
       mine = lane < 16 ? (mine & g.pm) : 0ull;
+      if (a.bitmap && lane < 16 && g.pm) {
+        const uint64_t row = ((uint64_t)1 << l) - 1 + g.node;
+        atomicOr(&a.bitmap[row >> 5], 1u << (row & 31));
+      }
       if (lane < 16) pairs += (uint32_t)__popcll(g.pm);
       const uint64_t bal = __ballot(mine != 0ull);
       if (bal == 0ull) return;
