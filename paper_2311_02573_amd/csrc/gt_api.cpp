@@ -6,14 +6,12 @@
 
 #include <algorithm>
 #include <chrono>
-#include <list>
-#include <mutex>
 #include <string>
 #include <type_traits>
-#include <unordered_map>
 #include <vector>
 
 #include "gt.h"
+#include "gt_block_pool.h"
 #include "gt_internal.h"
 #include "gt_numerics.h"
 
@@ -46,103 +44,27 @@ gt_status fail(gt_status s, const std::string& msg) {
     if (s_ != GT_OK) return s_;    \
   } while (0)
 
-// Large device blocks between their uses.  Freeing gigabytes and allocating
-// them again makes the driver clear them, 28 ms per GB once its cleared pages
-// have run out (measured: 80 ms of the 83 ms of a repeated 200,000 x 1000
-// build; up to seconds in single calls), so freed blocks of kPoolMin bytes or
-// more are kept for the next allocation that fits them closely.  At most
-// kPoolMax bytes per device stay here, the oldest leave first, blocks idle for
-// kPoolIdle leave with the next allocation or free, and everything leaves
-// when an allocation fails.  A block is only kept once the device has finished
-// all work (what hipFree waits for too), so it carries no stream.
-class BlockPool {
- public:
-  static constexpr size_t kPoolMin = size_t(32) << 20;
-  static constexpr size_t kPoolMax = size_t(4) << 30;
-  static constexpr std::chrono::seconds kPoolIdle{2};
-
-  hipError_t alloc(void** p, size_t bytes) {
-    int dev = -1;
-    if (bytes < kPoolMin || hipGetDevice(&dev) != hipSuccess) return hipMalloc(p, bytes);
-    std::lock_guard<std::mutex> lock(mu_);
-    drop_idle();
-    auto best = idle_.end();
-    for (auto it = idle_.begin(); it != idle_.end(); ++it)
-      if (it->dev == dev && it->bytes >= bytes && it->bytes <= bytes + bytes / 8 &&
-          (best == idle_.end() || it->bytes < best->bytes))
-        best = it;
-    if (best != idle_.end()) {
-      *p = best->p;
-      live_[best->p] = {dev, best->bytes};
-      idle_.erase(best);
-      return hipSuccess;
-    }
-    hipError_t e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory && !idle_.empty()) {
-      (void)hipGetLastError();
-      while (!idle_.empty()) drop(idle_.begin());
-      e = hipMalloc(p, bytes);
-    }
-    if (e == hipSuccess) live_[*p] = {dev, bytes};
+struct HipMemory {
+  using Error = hipError_t;
+  using Time = std::chrono::steady_clock::time_point;
+  static constexpr Error kOk = hipSuccess, kNoMemory = hipErrorOutOfMemory;
+  static Error alloc(void** p, size_t bytes) {
+    const Error e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
     return e;
   }
-
-  void free(void* p) {
+  static void free(void* p) { (void)hipFree(p); }
+  static int current() {
     int dev = -1;
-    std::lock_guard<std::mutex> lock(mu_);
-    drop_idle();
-    const auto it = live_.find(p);
-    if (it == live_.end()) {
-      (void)hipFree(p);
-      return;
-    }
-    const Live b = it->second;
-    live_.erase(it);
-    if (b.bytes > kPoolMax || hipGetDevice(&dev) != hipSuccess || dev != b.dev ||
-        hipDeviceSynchronize() != hipSuccess) {
-      (void)hipFree(p);
-      return;
-    }
-    size_t held = b.bytes;
-    for (const Idle& x : idle_) held += x.dev == dev ? x.bytes : 0;
-    for (auto x = idle_.begin(); x != idle_.end() && held > kPoolMax;) {  // oldest first
-      if (x->dev == dev) {
-        held -= x->bytes;
-        x = drop(x);
-      } else {
-        ++x;
-      }
-    }
-    idle_.push_back({p, dev, b.bytes, std::chrono::steady_clock::now()});
+    return hipGetDevice(&dev) == hipSuccess ? dev : -1;
   }
-
- private:
-  struct Live {
-    int dev;
-    size_t bytes;
-  };
-  struct Idle {
-    void* p;
-    int dev;
-    size_t bytes;
-    std::chrono::steady_clock::time_point since;
-  };
-  std::list<Idle>::iterator drop(std::list<Idle>::iterator it) {
-    (void)hipFree(it->p);
-    return idle_.erase(it);
-  }
-  void drop_idle() {
-    const auto now = std::chrono::steady_clock::now();
-    while (!idle_.empty() && now - idle_.front().since > kPoolIdle) drop(idle_.begin());
-  }
-  std::mutex mu_;
-  std::unordered_map<void*, Live> live_;
-  std::list<Idle> idle_;  // in the order of their freeing
+  static bool synchronize() { return hipDeviceSynchronize() == hipSuccess; }
+  static Time now() { return std::chrono::steady_clock::now(); }
 };
 
 // (never destroyed: an index may outlive the library's static objects)
-BlockPool& pool() {
-  static BlockPool* p = new BlockPool;
+gt::BlockPool<HipMemory>& pool() {
+  static auto* p = new gt::BlockPool<HipMemory>;
   return *p;
 }
 
@@ -152,7 +74,6 @@ gt_status dalloc(Index* ix, T** p, size_t count) {
   void* q = nullptr;
   hipError_t e = pool().alloc(&q, count * sizeof(T));
   if (e != hipSuccess) {
-    (void)hipGetLastError();
     return fail(GT_ERR_OUT_OF_MEMORY, "hipMalloc of " + std::to_string(count * sizeof(T)) +
                                           " bytes failed: " + hipGetErrorString(e));
   }
@@ -164,10 +85,7 @@ gt_status dalloc(Index* ix, T** p, size_t count) {
 template <class T>
 void dfree(Index* ix, T** p, size_t count) {
   if (*p) {
-    if (std::max<size_t>(count, 1) * sizeof(T) < BlockPool::kPoolMin)
-      (void)hipFree(*p);
-    else
-      pool().free(*p);
+    pool().free(*p);
     ix->bytes -= (int64_t)(std::max<size_t>(count, 1) * sizeof(T));
   }
   *p = nullptr;

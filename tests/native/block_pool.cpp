@@ -1,0 +1,123 @@
+// The pool of freed device blocks over a made-up device of a few GiB, with a
+// clock of its own.  Prints the name of each check that held.
+#include "gt_block_pool.h"
+
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <map>
+
+namespace {
+
+constexpr size_t MB = size_t(1) << 20;
+
+struct FakeMemory {
+  using Error = int;
+  using Time = std::chrono::steady_clock::time_point;
+  static constexpr Error kOk = 0, kNoMemory = 2;
+  static std::map<char*, size_t> blocks;
+  static size_t limit, used;
+  static int dev, syncs;
+  static Time clock;
+  static char* next;
+
+  static Error alloc(void** p, size_t bytes) {
+    if (used + bytes > limit) return kNoMemory;
+    blocks[next] = bytes;
+    used += bytes;
+    *p = next;
+    next += bytes;
+    return kOk;
+  }
+  static void free(void* p) {
+    const auto it = blocks.find(static_cast<char*>(p));
+    if (it == blocks.end()) abort();  // freed twice, or never allocated
+    used -= it->second;
+    blocks.erase(it);
+  }
+  static int current() { return dev; }
+  static bool synchronize() {
+    ++syncs;
+    return true;
+  }
+  static Time now() { return clock; }
+};
+std::map<char*, size_t> FakeMemory::blocks;
+size_t FakeMemory::limit = 0, FakeMemory::used = 0;
+int FakeMemory::dev = 0, FakeMemory::syncs = 0;
+FakeMemory::Time FakeMemory::clock{};
+char* FakeMemory::next = reinterpret_cast<char*>(uintptr_t(1) << 40);
+
+using Mem = FakeMemory;
+using Pool = gt::BlockPool<Mem>;
+
+void reset(size_t limit) {
+  if (Mem::used != 0) abort();
+  Mem::limit = limit;
+  Mem::dev = Mem::syncs = 0;
+}
+void* take(Pool& p, size_t bytes) {
+  void* q = nullptr;
+  if (p.alloc(&q, bytes) != Mem::kOk) return nullptr;
+  return q;
+}
+void check(bool ok, const char* what) {
+  if (!ok) {
+    printf("FAILED %s\n", what);
+    exit(1);
+  }
+  printf("%s\n", what);
+}
+void pass(double s) {
+  Mem::clock += std::chrono::duration_cast<Mem::Time::duration>(std::chrono::duration<double>(s));
+}
+
+}  // namespace
+
+int main() {
+  {
+    reset(1000 * MB);
+    Pool p;
+    void* a = take(p, 400 * MB);
+    p.free(a);
+    check(Mem::used == 400 * MB && take(p, 400 * MB) == a, "a freed block serves the next allocation");
+    p.free(a);
+    void* b = take(p, 700 * MB);
+    check(b && Mem::used == 700 * MB, "a large allocation without memory has the idle blocks back");
+    p.free(b);
+    void* c = take(p, 290 * MB);
+    void* d = take(p, 20 * MB);
+    check(d && Mem::used == 310 * MB, "so has a small one");
+    p.free(c);
+    p.free(d);
+    check(Mem::used == 290 * MB, "small blocks are freed");
+    pass(3.0);
+    d = take(p, MB);
+    check(Mem::used == MB, "idle blocks leave with a small allocation");
+    c = take(p, 100 * MB);
+    p.free(c);
+    pass(3.0);
+    p.free(d);
+    check(Mem::used == 0, "and with a small free");
+  }
+  {
+    reset(20000 * MB);
+    Pool p;
+    void* b[6];
+    for (auto& x : b) x = take(p, 1000 * MB);
+    for (auto& x : b) p.free(x);
+    check(Mem::used == 4000 * MB, "at most 4 GiB stay");
+    check(take(p, 1000 * MB) >= b[2], "the oldest left");
+    Mem::dev = 1;
+    void* o = take(p, 1000 * MB);
+    check(Mem::used == 5000 * MB, "another device has blocks of its own");
+    Mem::dev = 0;
+    p.free(o);
+    check(Mem::used == 4000 * MB, "a block freed with another device current is not kept");
+    Mem::blocks.clear();
+    Mem::used = 0;
+  }
+  printf("done\n");
+  return 0;
+}
