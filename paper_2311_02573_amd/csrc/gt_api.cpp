@@ -58,6 +58,16 @@ struct HipMemory {
     int dev = -1;
     return hipGetDevice(&dev) == hipSuccess ? dev : -1;
   }
+  // p is an allocation of that size on device dev
+  static bool is_block(void* p, size_t bytes, int dev) {
+    hipPointerAttribute_t a;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, p) == hipSuccess && hipMemGetAddressRange(&base, &size, p) == hipSuccess)
+      return a.device == dev && base == p && size >= bytes;
+    (void)hipGetLastError();
+    return false;
+  }
   static bool synchronize() { return hipDeviceSynchronize() == hipSuccess; }
   static Time now() { return std::chrono::steady_clock::now(); }
 };
@@ -85,8 +95,9 @@ gt_status dalloc(Index* ix, T** p, size_t count) {
 template <class T>
 void dfree(Index* ix, T** p, size_t count) {
   if (*p) {
-    pool().free(*p);
-    ix->bytes -= (int64_t)(std::max<size_t>(count, 1) * sizeof(T));
+    const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
+    pool().free(*p, bytes);
+    ix->bytes -= (int64_t)bytes;
   }
   *p = nullptr;
 }

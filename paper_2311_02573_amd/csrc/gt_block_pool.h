@@ -4,9 +4,7 @@
 #include <stddef.h>
 
 #include <chrono>
-#include <list>
 #include <mutex>
-#include <unordered_map>
 
 namespace gt {
 
@@ -14,11 +12,12 @@ namespace gt {
 // them again makes the driver clear them, 28 ms per GB once its cleared pages
 // have run out (measured: 80 ms of the 83 ms of a repeated 200,000 x 1000
 // build; up to seconds in single calls), so freed blocks of kPoolMin bytes or
-// more are kept for the next allocation that fits them closely.  At most
-// kPoolMax bytes per device stay here, the oldest leave first, blocks idle for
-// kPoolIdle leave with the next allocation or free of any size, and everything
-// leaves when one fails.  A block is only kept once the device has finished
-// all work (what hipFree waits for too), so it carries no stream.
+// more are kept for the next allocation of their size.  At most kPoolMax bytes
+// per device stay here, the oldest leave first, blocks idle for kPoolIdle
+// leave with the next allocation or free of any size, and everything leaves
+// when one fails.  A block is only kept once the device has finished all work
+// (what hipFree waits for too), so it carries no stream.  Nothing here throws:
+// the pool's entries are an array.
 template <class Dev>
 class BlockPool {
  public:
@@ -30,82 +29,67 @@ class BlockPool {
     std::lock_guard<std::mutex> lock(mu_);
     drop_idle();
     const int dev = Dev::current();
-    if (bytes < kPoolMin || dev < 0) return take(p, bytes);
-    auto best = idle_.end();
-    for (auto it = idle_.begin(); it != idle_.end(); ++it)
-      if (it->dev == dev && it->bytes >= bytes && it->bytes <= bytes + bytes / 8 &&
-          (best == idle_.end() || it->bytes < best->bytes))
-        best = it;
-    if (best != idle_.end()) {
-      *p = best->p;
-      live_[best->p] = {dev, best->bytes};
-      idle_.erase(best);
-      return Dev::kOk;
+    for (int k = 0; k < count_; ++k)
+      if (idle_[k].dev == dev && idle_[k].bytes == bytes) {
+        *p = idle_[k].p;
+        erase(k);
+        return Dev::kOk;
+      }
+    typename Dev::Error e = Dev::alloc(p, bytes);
+    if (e == Dev::kNoMemory && count_ > 0) {
+      while (count_ > 0) drop(0);
+      e = Dev::alloc(p, bytes);
     }
-    const typename Dev::Error e = take(p, bytes);
-    if (e == Dev::kOk) live_[*p] = {dev, bytes};
     return e;
   }
 
-  void free(void* p) {
+  // bytes: as it was allocated with
+  void free(void* p, size_t bytes) {
     std::lock_guard<std::mutex> lock(mu_);
     drop_idle();
     const int dev = Dev::current();
-    const auto it = live_.find(p);
-    if (it == live_.end()) {
+    if (bytes < kPoolMin || bytes > kPoolMax || dev < 0 || !Dev::is_block(p, bytes, dev) ||
+        !Dev::synchronize()) {
       Dev::free(p);
       return;
     }
-    const Live b = it->second;
-    live_.erase(it);
-    if (b.bytes > kPoolMax || dev != b.dev || !Dev::synchronize()) {
-      Dev::free(p);
-      return;
-    }
-    size_t held = b.bytes;
-    for (const Idle& x : idle_) held += x.dev == dev ? x.bytes : 0;
-    for (auto x = idle_.begin(); x != idle_.end() && held > kPoolMax;) {  // oldest first
-      if (x->dev == dev) {
-        held -= x->bytes;
-        x = drop(x);
+    size_t held = bytes;
+    for (int k = 0; k < count_; ++k) held += idle_[k].dev == dev ? idle_[k].bytes : 0;
+    for (int k = 0; k < count_ && held > kPoolMax;) {  // oldest first
+      if (idle_[k].dev == dev) {
+        held -= idle_[k].bytes;
+        drop(k);
       } else {
-        ++x;
+        ++k;
       }
     }
-    idle_.push_back({p, dev, b.bytes, Dev::now()});
+    if (count_ == kEntries) drop(0);
+    idle_[count_++] = {p, dev, bytes, Dev::now()};
   }
 
  private:
-  struct Live {
-    int dev;
-    size_t bytes;
-  };
+  static constexpr int kEntries = 2 * (int)(kPoolMax / kPoolMin);  // (of all devices)
   struct Idle {
     void* p;
     int dev;
     size_t bytes;
     typename Dev::Time since;
   };
-  // A device allocation; without memory for it, again after everything left.
-  typename Dev::Error take(void** p, size_t bytes) {
-    typename Dev::Error e = Dev::alloc(p, bytes);
-    if (e == Dev::kNoMemory && !idle_.empty()) {
-      while (!idle_.empty()) drop(idle_.begin());
-      e = Dev::alloc(p, bytes);
-    }
-    return e;
+  void erase(int k) {
+    for (--count_; k < count_; ++k) idle_[k] = idle_[k + 1];
   }
-  typename std::list<Idle>::iterator drop(typename std::list<Idle>::iterator it) {
-    Dev::free(it->p);
-    return idle_.erase(it);
+  void drop(int k) {
+    void* p = idle_[k].p;
+    erase(k);
+    Dev::free(p);
   }
   void drop_idle() {
     const auto now = Dev::now();
-    while (!idle_.empty() && now - idle_.front().since > kPoolIdle) drop(idle_.begin());
+    while (count_ > 0 && now - idle_[0].since > kPoolIdle) drop(0);
   }
   std::mutex mu_;
-  std::unordered_map<void*, Live> live_;
-  std::list<Idle> idle_;  // in the order of their freeing
+  Idle idle_[kEntries];  // in the order of their freeing
+  int count_ = 0;
 };
 
 }  // namespace gt

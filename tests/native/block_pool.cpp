@@ -17,6 +17,7 @@ struct FakeMemory {
   using Time = std::chrono::steady_clock::time_point;
   static constexpr Error kOk = 0, kNoMemory = 2;
   static std::map<char*, size_t> blocks;
+  static std::map<char*, int> home;
   static size_t limit, used;
   static int dev, syncs;
   static Time clock;
@@ -25,6 +26,7 @@ struct FakeMemory {
   static Error alloc(void** p, size_t bytes) {
     if (used + bytes > limit) return kNoMemory;
     blocks[next] = bytes;
+    home[next] = dev;
     used += bytes;
     *p = next;
     next += bytes;
@@ -37,6 +39,10 @@ struct FakeMemory {
     blocks.erase(it);
   }
   static int current() { return dev; }
+  static bool is_block(void* p, size_t bytes, int d) {
+    char* c = static_cast<char*>(p);
+    return home.at(c) == d && blocks.at(c) >= bytes;
+  }
   static bool synchronize() {
     ++syncs;
     return true;
@@ -44,6 +50,7 @@ struct FakeMemory {
   static Time now() { return clock; }
 };
 std::map<char*, size_t> FakeMemory::blocks;
+std::map<char*, int> FakeMemory::home;
 size_t FakeMemory::limit = 0, FakeMemory::used = 0;
 int FakeMemory::dev = 0, FakeMemory::syncs = 0;
 FakeMemory::Time FakeMemory::clock{};
@@ -80,25 +87,28 @@ int main() {
     reset(1000 * MB);
     Pool p;
     void* a = take(p, 400 * MB);
-    p.free(a);
+    p.free(a, 400 * MB);
     check(Mem::used == 400 * MB && take(p, 400 * MB) == a, "a freed block serves the next allocation");
-    p.free(a);
+    p.free(a, 400 * MB);
+    a = take(p, 390 * MB);
+    check(Mem::used == 790 * MB, "a block serves its own size only: what is counted is what is held");
+    Mem::free(a);
     void* b = take(p, 700 * MB);
     check(b && Mem::used == 700 * MB, "a large allocation without memory has the idle blocks back");
-    p.free(b);
+    p.free(b, 700 * MB);
     void* c = take(p, 290 * MB);
     void* d = take(p, 20 * MB);
     check(d && Mem::used == 310 * MB, "so has a small one");
-    p.free(c);
-    p.free(d);
+    p.free(c, 290 * MB);
+    p.free(d, 20 * MB);
     check(Mem::used == 290 * MB, "small blocks are freed");
     pass(3.0);
     d = take(p, MB);
     check(Mem::used == MB, "idle blocks leave with a small allocation");
     c = take(p, 100 * MB);
-    p.free(c);
+    p.free(c, 100 * MB);
     pass(3.0);
-    p.free(d);
+    p.free(d, MB);
     check(Mem::used == 0, "and with a small free");
   }
   {
@@ -106,14 +116,14 @@ int main() {
     Pool p;
     void* b[6];
     for (auto& x : b) x = take(p, 1000 * MB);
-    for (auto& x : b) p.free(x);
+    for (auto& x : b) p.free(x, 1000 * MB);
     check(Mem::used == 4000 * MB, "at most 4 GiB stay");
     check(take(p, 1000 * MB) >= b[2], "the oldest left");
     Mem::dev = 1;
     void* o = take(p, 1000 * MB);
     check(Mem::used == 5000 * MB, "another device has blocks of its own");
     Mem::dev = 0;
-    p.free(o);
+    p.free(o, 1000 * MB);
     check(Mem::used == 4000 * MB, "a block freed with another device current is not kept");
     Mem::blocks.clear();
     Mem::used = 0;
