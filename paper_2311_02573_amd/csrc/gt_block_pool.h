@@ -26,45 +26,49 @@ class BlockPool {
   static constexpr std::chrono::seconds kPoolIdle{2};
 
   typename Dev::Error alloc(void** p, size_t bytes) {
-    std::lock_guard<std::mutex> lock(mu_);
-    drop_idle();
+    give_expired();
     const int dev = Dev::current();
-    for (int k = 0; k < count_; ++k)
-      if (idle_[k].dev == dev && idle_[k].bytes == bytes) {
-        *p = idle_[k].p;
-        erase(k);
-        return Dev::kOk;
-      }
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      for (int k = 0; k < count_; ++k)
+        if (idle_[k].dev == dev && idle_[k].bytes == bytes) {
+          *p = idle_[k].p;
+          erase(k);
+          return Dev::kOk;
+        }
+    }
     typename Dev::Error e = Dev::alloc(p, bytes);
-    if (e == Dev::kNoMemory && count_ > 0) {
-      while (count_ > 0) drop(0);
+    if (e == Dev::kNoMemory) {
+      // again after every idle block, and those that other threads are giving
+      // back, have left; until then none is kept
+      change_short(1);
+      give_back([](const Idle&) { return true; });
       e = Dev::alloc(p, bytes);
+      change_short(-1);
     }
     return e;
   }
 
   // bytes: as it was allocated with
   void free(void* p, size_t bytes) {
-    std::lock_guard<std::mutex> lock(mu_);
-    drop_idle();
+    give_expired();
     const int dev = Dev::current();
     if (bytes < kPoolMin || bytes > kPoolMax || dev < 0 || !Dev::is_block(p, bytes, dev) ||
         !Dev::synchronize()) {
       Dev::free(p);
       return;
     }
-    size_t held = bytes;
-    for (int k = 0; k < count_; ++k) held += idle_[k].dev == dev ? idle_[k].bytes : 0;
-    for (int k = 0; k < count_ && held > kPoolMax;) {  // oldest first
-      if (idle_[k].dev == dev) {
-        held -= idle_[k].bytes;
-        drop(k);
-      } else {
-        ++k;
+    const Idle x = {p, dev, bytes, Dev::now()};
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (fits(x)) {
+        idle_[count_++] = x;
+        return;
       }
     }
-    if (count_ == kEntries) drop(0);
-    idle_[count_++] = {p, dev, bytes, Dev::now()};
+    give_back([&](const Idle& o) {  // the oldest
+      return short_ == 0 && ((o.dev == dev && held(dev) + bytes > kPoolMax) || count_ == kEntries);
+    }, &x);
   }
 
  private:
@@ -75,21 +79,62 @@ class BlockPool {
     size_t bytes;
     typename Dev::Time since;
   };
+  // (mu_ is held)
+  size_t held(int dev) const {
+    size_t n = 0;
+    for (int k = 0; k < count_; ++k) n += idle_[k].dev == dev ? idle_[k].bytes : 0;
+    return n;
+  }
+  bool fits(const Idle& x) const {
+    return short_ == 0 && count_ < kEntries && held(x.dev) + x.bytes <= kPoolMax;
+  }
+  void change_short(int by) {
+    std::lock_guard<std::mutex> lock(mu_);
+    short_ += by;
+  }
   void erase(int k) {
     for (--count_; k < count_; ++k) idle_[k] = idle_[k + 1];
   }
-  void drop(int k) {
-    void* p = idle_[k].p;
-    erase(k);
-    Dev::free(p);
+  // Frees the blocks of which `leaves` is true, then keeps `add`.  The entries
+  // are locked while the blocks are picked, not while the device frees them;
+  // giving back is one thread's at a time, so that who waits for its turn finds
+  // the memory of the others' blocks.
+  template <class F>
+  void give_back(F leaves, const Idle* add = nullptr) {
+    std::lock_guard<std::mutex> turn(turn_);
+    void* out[kEntries];
+    int n = 0;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      for (int k = 0; k < count_;) {
+        if (leaves(idle_[k])) {
+          out[n++] = idle_[k].p;
+          erase(k);
+        } else {
+          ++k;
+        }
+      }
+      if (add && fits(*add))
+        idle_[count_++] = *add;
+      else if (add)
+        out[n++] = add->p;
+    }
+    for (int k = 0; k < n; ++k) Dev::free(out[k]);
   }
-  void drop_idle() {
+  void give_expired() {
     const auto now = Dev::now();
-    while (count_ > 0 && now - idle_[0].since > kPoolIdle) drop(0);
+    auto expired = [&](const Idle& x) { return now - x.since > kPoolIdle; };
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (count_ == 0 || !expired(idle_[0])) return;
+    }
+    give_back(expired);
   }
-  std::mutex mu_;
+  std::mutex turn_;  // taken before mu_
+  std::mutex mu_;    // of the entries; no device call is made under it
   Idle idle_[kEntries];  // in the order of their freeing
   int count_ = 0;
+  int short_ = 0;        // threads that found no memory
 };
 
 }  // namespace gt

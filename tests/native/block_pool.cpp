@@ -6,7 +6,10 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <atomic>
+#include <future>
 #include <map>
+#include <thread>
 
 namespace {
 
@@ -19,11 +22,16 @@ struct FakeMemory {
   static std::map<char*, size_t> blocks;
   static std::map<char*, int> home;
   static size_t limit, used;
-  static int dev, syncs;
+  static int dev;
+  static std::atomic<int> syncs;
   static Time clock;
   static char* next;
 
+  static std::mutex mu;
+  static std::atomic<bool> busy, waiting;  // the device has work: synchronize() waits
+
   static Error alloc(void** p, size_t bytes) {
+    std::lock_guard<std::mutex> lock(mu);
     if (used + bytes > limit) return kNoMemory;
     blocks[next] = bytes;
     home[next] = dev;
@@ -33,6 +41,7 @@ struct FakeMemory {
     return kOk;
   }
   static void free(void* p) {
+    std::lock_guard<std::mutex> lock(mu);
     const auto it = blocks.find(static_cast<char*>(p));
     if (it == blocks.end()) abort();  // freed twice, or never allocated
     used -= it->second;
@@ -40,11 +49,16 @@ struct FakeMemory {
   }
   static int current() { return dev; }
   static bool is_block(void* p, size_t bytes, int d) {
+    std::lock_guard<std::mutex> lock(mu);
     char* c = static_cast<char*>(p);
     return home.at(c) == d && blocks.at(c) >= bytes;
   }
   static bool synchronize() {
     ++syncs;
+    while (busy) {
+      waiting = true;
+      std::this_thread::yield();
+    }
     return true;
   }
   static Time now() { return clock; }
@@ -52,7 +66,10 @@ struct FakeMemory {
 std::map<char*, size_t> FakeMemory::blocks;
 std::map<char*, int> FakeMemory::home;
 size_t FakeMemory::limit = 0, FakeMemory::used = 0;
-int FakeMemory::dev = 0, FakeMemory::syncs = 0;
+int FakeMemory::dev = 0;
+std::atomic<int> FakeMemory::syncs{0};
+std::mutex FakeMemory::mu;
+std::atomic<bool> FakeMemory::busy{false}, FakeMemory::waiting{false};
 FakeMemory::Time FakeMemory::clock{};
 char* FakeMemory::next = reinterpret_cast<char*>(uintptr_t(1) << 40);
 
@@ -62,7 +79,8 @@ using Pool = gt::BlockPool<Mem>;
 void reset(size_t limit) {
   if (Mem::used != 0) abort();
   Mem::limit = limit;
-  Mem::dev = Mem::syncs = 0;
+  Mem::dev = 0;
+  Mem::syncs = 0;
 }
 void* take(Pool& p, size_t bytes) {
   void* q = nullptr;
@@ -127,6 +145,50 @@ int main() {
     check(Mem::used == 4000 * MB, "a block freed with another device current is not kept");
     Mem::blocks.clear();
     Mem::used = 0;
+  }
+  {
+    reset(2000 * MB);
+    Pool p;
+    void* a = take(p, 400 * MB);
+    void* b = take(p, 100 * MB);
+    p.free(b, 100 * MB);
+    Mem::busy = true;  // one thread's free waits for the device
+    std::thread t([&] { p.free(a, 400 * MB); });
+    while (!Mem::waiting) std::this_thread::yield();
+    auto other = std::async(std::launch::async, [&] {
+      void* c = take(p, 100 * MB);
+      void* d = take(p, 50 * MB);
+      Mem::free(c);
+      Mem::free(d);
+      return c == b && d;
+    });
+    const bool ended = other.wait_for(std::chrono::seconds(20)) == std::future_status::ready;
+    Mem::busy = false;
+    t.join();
+    check(ended && other.get(), "another thread allocates while one waits for the device");
+    check(Mem::used == 400 * MB && take(p, 400 * MB) == a, "whose block is kept when it is done");
+    Mem::free(a);
+  }
+  {
+    // four threads on blocks of three sizes, memory for less than they keep
+    reset(1200 * MB);
+    Pool p;
+    std::atomic<int> failed{0};
+    std::thread t[4];
+    for (int k = 0; k < 4; ++k)
+      t[k] = std::thread([&, k] {
+        for (int i = 0; i < 3000; ++i) {
+          const size_t n = (60 + 70 * ((k + i) % 3)) * MB;
+          void* x = take(p, n);
+          if (!x) ++failed;
+          if (x) p.free(x, n);
+        }
+      });
+    for (auto& x : t) x.join();
+    check(failed == 0, "no allocation fails for memory that others are giving back");
+    pass(3.0);
+    p.free(take(p, MB), MB);
+    check(Mem::used == 0, "and all of it comes back");
   }
   printf("done\n");
   return 0;
