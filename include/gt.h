@@ -342,9 +342,9 @@ gt_status gt_read_pools(const gt_index* index, int32_t level, int64_t first, int
 gt_status gt_set_option(gt_index* index, const char* key, int64_t value);
 
 /* Frees every device allocation of the index.  NULL is ignored.  Freed blocks
- * of 32 MiB or more may stay with the library for its next allocations: at
- * most 4 GiB per device, until they have been idle for two seconds at its
- * next allocation or free, or an allocation of it fails. */
+ * of 32 MiB or more stay with the library for its next allocations of their
+ * sizes: at most 4 GiB per device, for two seconds, or until an allocation of
+ * the library fails. */
 void gt_destroy(gt_index* index);
 
 /* Message for the last error on the calling thread ("" if none).  The string

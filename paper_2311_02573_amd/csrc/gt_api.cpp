@@ -2,6 +2,8 @@
 // device workspaces, and the launch sequence of each call.
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <signal.h>
+#include <stdlib.h>
 #include <string.h>
 
 #include <algorithm>
@@ -70,11 +72,29 @@ struct HipMemory {
   }
   static bool synchronize() { return hipDeviceSynchronize() == hipSuccess; }
   static Time now() { return std::chrono::steady_clock::now(); }
+  // The pool's own thread: no signals, and its frees disturb no other thread's
+  // stream capture.
+  static void thread_starts() {
+    sigset_t all;
+    sigfillset(&all);
+    (void)pthread_sigmask(SIG_BLOCK, &all, nullptr);
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  static void wait(std::condition_variable& wake, std::unique_lock<std::mutex>& lock, Time until) {
+    wake.wait_until(lock, until);
+  }
 };
 
-// (never destroyed: an index may outlive the library's static objects)
+// (Never destroyed: an index may outlive the library's static objects.  Its
+// thread ends before the runtime does: handlers run in reverse order, and the
+// runtime was there when this one was registered.)
 gt::BlockPool<HipMemory>& pool() {
-  static auto* p = new gt::BlockPool<HipMemory>;
+  static gt::BlockPool<HipMemory>* const p = [] {
+    static auto* q = new gt::BlockPool<HipMemory>;
+    std::atexit([] { q->stop(); });
+    return q;
+  }();
   return *p;
 }
 

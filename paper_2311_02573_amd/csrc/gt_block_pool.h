@@ -2,9 +2,12 @@
 // their uses.
 #pragma once
 #include <stddef.h>
+#include <unistd.h>
 
 #include <chrono>
+#include <condition_variable>
 #include <mutex>
+#include <thread>
 
 namespace gt {
 
@@ -14,16 +17,23 @@ namespace gt {
 // build; up to seconds in single calls), so freed blocks of kPoolMin bytes or
 // more are kept for the next allocation of their size.  At most kPoolMax bytes
 // per device stay here, the oldest leave first, blocks idle for kPoolIdle
-// leave with the next allocation or free of any size, and everything leaves
-// when one fails.  A block is only kept once the device has finished all work
-// (what hipFree waits for too), so it carries no stream.  Nothing here throws:
-// the pool's entries are an array.
+// leave by themselves (a thread that lives while blocks are idle frees them:
+// a program that has closed its indexes makes no call that could), and
+// everything leaves when an allocation fails.  A block is only kept once the
+// device has finished all work (what hipFree waits for too), so it carries no
+// stream.  Nothing here throws: the pool's entries are an array, and without a
+// thread nothing is kept.
 template <class Dev>
 class BlockPool {
  public:
   static constexpr size_t kPoolMin = size_t(32) << 20;
   static constexpr size_t kPoolMax = size_t(4) << 30;
   static constexpr std::chrono::seconds kPoolIdle{2};
+
+  ~BlockPool() {
+    stop();
+    give_back([](const Idle&) { return true; });
+  }
 
   typename Dev::Error alloc(void** p, size_t bytes) {
     give_expired();
@@ -54,14 +64,14 @@ class BlockPool {
     give_expired();
     const int dev = Dev::current();
     if (bytes < kPoolMin || bytes > kPoolMax || dev < 0 || !Dev::is_block(p, bytes, dev) ||
-        !Dev::synchronize()) {
+        getpid() != pid_ || !Dev::synchronize()) {
       Dev::free(p);
       return;
     }
     const Idle x = {p, dev, bytes, Dev::now()};
     {
       std::lock_guard<std::mutex> lock(mu_);
-      if (fits(x)) {
+      if (fits(x) && start()) {
         idle_[count_++] = x;
         return;
       }
@@ -69,6 +79,20 @@ class BlockPool {
     give_back([&](const Idle& o) {  // the oldest
       return short_ == 0 && ((o.dev == dev && held(dev) + bytes > kPoolMax) || count_ == kEntries);
     }, &x);
+  }
+
+  // Ends the thread; nothing is kept from then on.  For the process's exit (a
+  // forked child has no such thread to end).
+  void stop() {
+    if (getpid() != pid_) return;
+    std::thread t;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      stopped_ = true;
+      t.swap(thread_);
+    }
+    wake_.notify_all();
+    if (t.joinable()) t.join();
   }
 
  private:
@@ -86,7 +110,7 @@ class BlockPool {
     return n;
   }
   bool fits(const Idle& x) const {
-    return short_ == 0 && count_ < kEntries && held(x.dev) + x.bytes <= kPoolMax;
+    return !stopped_ && short_ == 0 && count_ < kEntries && held(x.dev) + x.bytes <= kPoolMax;
   }
   void change_short(int by) {
     std::lock_guard<std::mutex> lock(mu_);
@@ -114,7 +138,7 @@ class BlockPool {
           ++k;
         }
       }
-      if (add && fits(*add))
+      if (add && fits(*add) && start())
         idle_[count_++] = *add;
       else if (add)
         out[n++] = add->p;
@@ -130,11 +154,42 @@ class BlockPool {
     }
     give_back(expired);
   }
+  // Starts the thread that frees expired blocks, where none runs (it ends when it
+  // finds no block idle); the caller holds mu_ until it has added one.
+  bool start() {
+    if (running_) return true;
+    try {
+      if (thread_.joinable()) thread_.join();  // (it has ended: it let go of mu_ with running_ cleared)
+      thread_ = std::thread([this] { expire(); });
+    } catch (...) {
+      return false;
+    }
+    return running_ = true;
+  }
+  void expire() {
+    Dev::thread_starts();
+    for (;;) {
+      {
+        std::unique_lock<std::mutex> lock(mu_);
+        if (stopped_ || count_ == 0) {
+          running_ = false;
+          return;
+        }
+        const auto until = idle_[0].since + kPoolIdle;
+        if (Dev::now() <= until) Dev::wait(wake_, lock, until);
+      }
+      give_expired();
+    }
+  }
   std::mutex turn_;  // taken before mu_
   std::mutex mu_;    // of the entries; no device call is made under it
   Idle idle_[kEntries];  // in the order of their freeing
   int count_ = 0;
   int short_ = 0;        // threads that found no memory
+  std::condition_variable wake_;
+  std::thread thread_;
+  bool running_ = false, stopped_ = false;
+  const pid_t pid_ = getpid();
 };
 
 }  // namespace gt

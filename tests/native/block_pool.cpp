@@ -24,7 +24,7 @@ struct FakeMemory {
   static size_t limit, used;
   static int dev;
   static std::atomic<int> syncs;
-  static Time clock;
+  static std::atomic<double> clock;  // seconds
   static char* next;
 
   static std::mutex mu;
@@ -61,16 +61,23 @@ struct FakeMemory {
     }
     return true;
   }
-  static Time now() { return clock; }
+  static Time now() {
+    return Time(std::chrono::duration_cast<Time::duration>(std::chrono::duration<double>(clock.load())));
+  }
+  static void thread_starts() { ++threads; }
+  static void wait(std::condition_variable& wake, std::unique_lock<std::mutex>& lock, Time) {
+    wake.wait_for(lock, std::chrono::milliseconds(1));
+  }
+  static std::atomic<int> threads;
 };
 std::map<char*, size_t> FakeMemory::blocks;
 std::map<char*, int> FakeMemory::home;
 size_t FakeMemory::limit = 0, FakeMemory::used = 0;
 int FakeMemory::dev = 0;
-std::atomic<int> FakeMemory::syncs{0};
+std::atomic<int> FakeMemory::syncs{0}, FakeMemory::threads{0};
 std::mutex FakeMemory::mu;
 std::atomic<bool> FakeMemory::busy{false}, FakeMemory::waiting{false};
-FakeMemory::Time FakeMemory::clock{};
+std::atomic<double> FakeMemory::clock{0.0};
 char* FakeMemory::next = reinterpret_cast<char*>(uintptr_t(1) << 40);
 
 using Mem = FakeMemory;
@@ -93,9 +100,21 @@ void check(bool ok, const char* what) {
     exit(1);
   }
   printf("%s\n", what);
+  fflush(stdout);
+}
+// Waits until nothing is allocated, with no further call of the pool.
+bool gone() {
+  for (int k = 0; k < 20000; ++k) {
+    {
+      std::lock_guard<std::mutex> lock(Mem::mu);
+      if (Mem::used == 0) return true;
+    }
+    std::this_thread::sleep_for(std::chrono::milliseconds(1));
+  }
+  return false;
 }
 void pass(double s) {
-  Mem::clock += std::chrono::duration_cast<Mem::Time::duration>(std::chrono::duration<double>(s));
+  Mem::clock = Mem::clock + s;
 }
 
 }  // namespace
@@ -136,15 +155,15 @@ int main() {
     for (auto& x : b) x = take(p, 1000 * MB);
     for (auto& x : b) p.free(x, 1000 * MB);
     check(Mem::used == 4000 * MB, "at most 4 GiB stay");
-    check(take(p, 1000 * MB) >= b[2], "the oldest left");
+    void* r = take(p, 1000 * MB);
+    check(r >= b[2], "the oldest left");
     Mem::dev = 1;
     void* o = take(p, 1000 * MB);
     check(Mem::used == 5000 * MB, "another device has blocks of its own");
     Mem::dev = 0;
     p.free(o, 1000 * MB);
     check(Mem::used == 4000 * MB, "a block freed with another device current is not kept");
-    Mem::blocks.clear();
-    Mem::used = 0;
+    p.free(r, 1000 * MB);
   }
   {
     reset(2000 * MB);
@@ -189,6 +208,39 @@ int main() {
     pass(3.0);
     p.free(take(p, MB), MB);
     check(Mem::used == 0, "and all of it comes back");
+  }
+  {
+    reset(2000 * MB);
+    Pool p;
+    for (int round = 0; round < 3; ++round) {
+      void* a = take(p, 300 * MB);
+      void* b = take(p, 100 * MB);
+      p.free(a, 300 * MB);
+      pass(1.0);
+      p.free(b, 100 * MB);
+      pass(1.5);
+      pass(1.0);
+      check(gone(), "idle blocks leave by themselves");
+    }
+    void* a = take(p, 300 * MB);
+    p.free(a, 300 * MB);
+    p.stop();
+    pass(3.0);
+    a = take(p, 300 * MB);
+    p.free(a, 300 * MB);
+    check(Mem::used == 0, "after the end nothing is kept");
+  }
+  for (int k = 0; k < 200; ++k) {
+    // a thread that ends as the next block comes
+    static Pool p;
+    void* a = take(p, 300 * MB);
+    p.free(a, 300 * MB);
+    pass(2.5);
+    if (k % 3) std::this_thread::sleep_for(std::chrono::microseconds(300 * (k % 7)));
+    if (k == 199) {
+      check(gone(), "the last block leaves too");
+      p.stop();
+    }
   }
   printf("done\n");
   return 0;
