@@ -7,8 +7,8 @@ paper).  The timed steps run back to back on one stream through two
 workspaces (the next batch is enqueued before the host waits for the previous
 one); per-call latency comes from a second run that waits for every call.  Workload: N = 2^20 softmax feature vectors, d = 1000, 1024
 queries per batch, rho = 0.9, bfloat16 pool sums.  Beside it: the plain float32
-walk, the float8 walk and the exhaustive float32 GEMM on the same batch, and
-the CPU float64 oracle on a bounded sample of the same queries.
+walk, the float8 walk and the exhaustive GEMM (float32 rows, multiplied as split
+float16 operands) on the same batch, and the CPU float64 oracle on a bounded sample of the same queries.
 
 Prints one JSON line.  Only one GPU is used; --gpus > 1 exits.
 """
@@ -36,7 +36,7 @@ def counter_summary(pool, nq):
     return os.path.join(ROOT, "profiles", f"counters_walk_{pool}_n1m_d1000_b{nq}_rho0.9.md")
 
 
-KERNEL_SOURCES = ["k_walk.hip", "gt_numerics.h", "gt_device.h", "gt_internal.h", "gt_api.cpp"]
+KERNEL_SOURCES = ["k_walk.hip", "gt_mma.h", "gt_numerics.h", "gt_device.h", "gt_internal.h", "gt_api.cpp"]
 
 
 def kernel_source_hash():

@@ -236,7 +236,10 @@ int bucket_bits_of(int sparse_from, int nt) {
 //     1000 (4,096), 512 344 / 397; 300,007 x 777 (9,376), 257 457 / 500, 512 704 /
 //     641; 2^14 x 1000 (512), 2048 267 / 858; few pools of few columns: 2^16 x
 //     300 (2,048), 2048 440 / 646, 2^18 x 128 (8,192), 1024 722 / 764
-// and 88 against 201 - 327 us for one query.  Calls with options that ask for
+// and 88 against 201 - 327 us for one query.  (Around the lines the sides differ
+// by shape: in windows at 262 - 268 MB the subtree walk took 648 / 709 and 619 /
+// 630, but 460 / 427; in float8 at 262,144 pools 341 / 347, but 336 / 325.)
+// Calls with options that ask for
 // the level kernels (an explicit head, grid, dense level or subtraction step)
 // take those.
 constexpr int kSubtreeTiles = 128;

@@ -149,8 +149,9 @@ __device__ __forceinline__ void load_steps(uint4 (&x)[C], const unsigned char* r
 // of the one before it, across windows too, and the next window is on its way
 // while one is multiplied: without either, a level of 2048 bfloat16 columns
 // took 21 us, 12 of them for copying 256 KB.  Walk of 2^17 x 2048, 256 queries:
-// 82 us, 152 before.  (Blocks are what the registers hold: a larger one spills,
-// 98 us.)
+// 82 us, 152 before.  (Blocks are what the registers hold of bfloat16 and float32
+// rows: a larger one spills, 98 us.  Float8, whose operands are read two steps at
+// a time, spills 7 to 29 registers at these sizes.)
 template <int FMT, int NQB, int G>
 __device__ __forceinline__ void windowed_products(const unsigned char* const (&row)[G], bool any,
                                                   unsigned char* lds, const unsigned char* qsrc,
