@@ -175,7 +175,8 @@ gt_status gt_query_batch(gt_index* index, const float* q_dev, int32_t nq, const 
                          float* sims_dev, int64_t* total_out, void* stream);
 
 /* Exhaustive baseline (the paper's Exh, Sec. 4): every (query, vector) dot
- * product by a float32 matrix-core GEMM with a threshold epilogue, followed by
+ * product of the float32 rows by a matrix-core GEMM (split float16 operands, or
+ * float32 ones where a threshold lies between 0 and 2^-16) with a threshold epilogue, followed by
  * the same exact test as gt_query_batch, so results are identical to it.
  * Arguments, synchronisation and errors as gt_query_batch. */
 gt_status gt_exhaustive(gt_index* index, const float* q_dev, int32_t nq, const double* rho_host,

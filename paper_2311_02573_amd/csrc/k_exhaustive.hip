@@ -87,6 +87,29 @@ __global__ __launch_bounds__(256) void k_split_queries(const float* __restrict__
   if (t == 0) thr_out[b] = b < nq ? ldexpf(thr[b], e) : INFINITY;
 }
 
+// Room for each lane's candidates: a workgroup of four waves reserves with one add.
+// False if none has any.
+__device__ __forceinline__ bool reserve(uint32_t count, int lane, int wave, DevCounters* ctr,
+                                        unsigned long long& pos) {
+  __shared__ uint32_t wcount[4];
+  __shared__ unsigned long long wbase;
+  uint32_t incl = count;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t c = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += c;
+  }
+  if (lane == 63) wcount[wave] = incl;
+  __syncthreads();
+  const uint32_t all = wcount[0] + wcount[1] + wcount[2] + wcount[3];
+  if (all == 0u) return false;
+  if (threadIdx.x == 0) wbase = atomicAdd(&ctr->ncand, (unsigned long long)all);
+  __syncthreads();
+  pos = wbase + incl - count;
+  for (int k = 0; k < wave; ++k) pos += wcount[k];
+  return true;
+}
+
 // Operands of one 16-dimension step of a wave.
 struct SplitOps {
   f16x8 ah[4], al[4], bh[4], bl[4];
@@ -112,8 +135,6 @@ __global__ __launch_bounds__(kEThreads, 1) void k_gemm_threshold(
   __shared__ __attribute__((aligned(1024))) unsigned char lds0[kEStage];
   __shared__ __attribute__((aligned(1024))) unsigned char lds1[kEStage];
   __shared__ float thr_lds[kET];
-  __shared__ uint32_t wcount[4];
-  __shared__ unsigned long long wbase;
   const int64_t rblocks = (n + kET - 1) / kET;
   const int64_t total = rblocks * qblocks;
   const int64_t per_xcd = (total + 7) / 8;
@@ -305,20 +326,8 @@ __global__ __launch_bounds__(kEThreads, 1) void k_gemm_threshold(
     }
     count += (uint32_t)(__popc(kept[i][0]) + __popc(kept[i][1]));
   }
-  uint32_t incl = count;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t c = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += c;
-  }
-  if (lane == 63) wcount[wave] = incl;
-  __syncthreads();
-  const uint32_t all = wcount[0] + wcount[1] + wcount[2] + wcount[3];
-  if (all == 0u) return;
-  if (tid == 0) wbase = atomicAdd(&ctr->ncand, (unsigned long long)all);
-  __syncthreads();
-  unsigned long long pos = wbase + incl - count;
-  for (int k = 0; k < wave; ++k) pos += wcount[k];
+  unsigned long long pos;
+  if (!reserve(count, lane, wave, ctr, pos)) return;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -435,34 +444,39 @@ __global__ __launch_bounds__(256) void k_gemm_small_rho(const float* __restrict_
     }
   }
 
-  // epilogue: keep (query, vector) if the score may reach rho * |q| * |f|
+  // Epilogue as above: keep (query, vector) if the score may reach rho * |q| * |f|,
+  // counted first (with one add per wave and accumulator register, the add's one
+  // address set the time of a call with many candidates: 9.6 M of them 88 ms, now
+  // 16.6).
   float nfv[2];
-  int64_t rid[2];
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
-    rid[b] = r0 + wr + 32 * b + c;
-    nfv[b] = rid[b] < n ? nf[rid[b]] : 0.0f;
+    const int64_t row = r0 + wr + 32 * b + c;
+    nfv[b] = row < n ? nf[row] : 0.0f;
   }
+  uint32_t kept[2], count = 0;  // bit 16 b + i of word a
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < 2; ++a) {
+    kept[a] = 0u;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int qi = qt * kFT + wq + 32 * a + 8 * (i >> 2) + 4 * half + (i & 3);
       const float th = qi < nq ? thr[qi] : INFINITY;
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const bool keep = nfv[b] > 0.0f && acc[a][b][i] >= th * nfv[b] * (1.0f - 0x1p-20f);
-        const uint64_t bal = __ballot(keep);
-        if (bal) {
-          unsigned long long base = 0;
-          if (lane == 0) base = atomicAdd(&ctr->ncand, (unsigned long long)__popcll(bal));
-          base = __shfl(base, 0, 64);
-          if (keep) {
-            const unsigned long long pos = base + __popcll(bal & ((1ull << lane) - 1ull));
-            if (pos < cap) cand[pos] = make_uint2((uint32_t)qi, (uint32_t)rid[b]);
-          }
-        }
-      }
+      for (int b = 0; b < 2; ++b)
+        if (nfv[b] > 0.0f && acc[a][b][i] >= th * nfv[b] * (1.0f - 0x1p-20f)) kept[a] |= 1u << (16 * b + i);
+    }
+    count += (uint32_t)__popc(kept[a]);
+  }
+  unsigned long long pos;
+  if (!reserve(count, lane, wave, ctr, pos)) return;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+    for (uint32_t m = kept[a]; m; m &= m - 1u) {
+      const int bit = __ffs((int)m) - 1, i = bit & 15;
+      const int qi = qt * kFT + wq + 32 * a + 8 * (i >> 2) + 4 * half + (i & 3);
+      if (pos < cap) cand[pos] = make_uint2((uint32_t)qi, (uint32_t)(r0 + wr + 32 * (bit >> 4) + c));
+      ++pos;
     }
 }
 
